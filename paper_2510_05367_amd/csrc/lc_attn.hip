@@ -1,7 +1,7 @@
 // Attention cores on gfx950.
 //
-// Spatial attention (tokens = the H*W positions of one frame) is a flash-style kernel: one
-// workgroup owns a block of queries of one (frame, head), walks the keys in tiles of 64 staged in
+// Spatial attention (tokens = the H*W positions of one frame) is a flash-style kernel (one for fp32 stages, one for
+// bf16 stages): one workgroup owns a block of queries of one (frame, head), walks the keys in tiles of 64 staged in
 // LDS and keeps a running max / sum per query, so the T x T score matrix never exists and the
 // kernel needs no workspace. Scores are produced transposed, S^T[key][query] = K Q^T, with
 // 32x32 MFMA tiles: one lane then holds 16 keys of ONE query, so the softmax statistics are
@@ -87,21 +87,10 @@ __global__ __launch_bounds__(256, 2) void spatial_attn_kernel(const T* __restric
   // rows 40..63 are padding), row D is set to ones, so O^T[D][q] accumulates the sum over keys of
   // exactly the (rounded) probabilities that multiply V, and is rescaled with the rest of O^T.
   constexpr bool ROWSUM = D % 32 != 0;
-  // Softmax exponents for free as well: when the padded contraction of K Q^T has a spare slot (d = 40
-  // contracts 48) and the queries come multiplied by scale * log2(e), slot D of every key is 1 and
-  // slot D of a query holds minus its running maximum (in the operand type, in log2 units). The
-  // MFMA then delivers  s * scale * log2(e) - m  directly and the probability is exp2 of that: no
-  // per-score multiply-add. Any rounding of m cancels, since the same m enters the probabilities,
-  // the denominator (ones row above) and the rescaling of O^T.
-  constexpr bool FOLD = PRE && sizeof(T) == 2 && DP > D && ROWSUM;
-  constexpr int KX = D / M::K, HX = (D % M::K) / M::LK, EX = (D % M::K) % M::LK;  // where slot D lives
   if (ROWSUM) {
     __syncthreads();
     for (int i = tid; i < 2 * kKeys; i += 256)
       reinterpret_cast<T*>(&v_lds[i / kKeys][D * VROW])[i % kKeys] = from_f32<T>(1.f);
-    if (FOLD)
-      for (int i = tid; i < 2 * kKeys; i += 256)
-        reinterpret_cast<T*>(&k_lds[i / kKeys][(i % kKeys) * KROW])[D] = from_f32<T>(1.f);
   }
 
   // ---- staging: K packet i = tid + 256 j of a stage is (key i / PK, packet i % PK); V^T packet i is
@@ -157,18 +146,13 @@ __global__ __launch_bounds__(256, 2) void spatial_attn_kernel(const T* __restric
     for (int kk = 0; kk < KSTEPS; ++kk) {
       const int e = kk * M::K + hh * M::LK;
       qf[t][kk] = (qi < nq && e < D) ? M::load(base + (int64_t)q * ld + e) : M::zero();
-      if constexpr (FOLD) {  // slots >= D must be zero: slot D will carry the running maximum
-#pragma unroll
-        for (int j = 0; j < M::LK; ++j)
-          if (e + j >= D) qf[t][kk][j] = (bf16_t)0.f;
-      }
     }
   }
   f32x16 o[NQT][DM];
   float m_run[NQT], l_run[NQT];  // running max (raw score units) and per-lane partial sum
 #pragma unroll
   for (int t = 0; t < NQT; ++t) {
-    m_run[t] = FOLD ? 0.f : -INFINITY;  // FOLD: log2 units, as held in slot D of the query
+    m_run[t] = -INFINITY;
     l_run[t] = 0.f;
 #pragma unroll
     for (int mt = 0; mt < DM; ++mt)
@@ -232,29 +216,7 @@ __global__ __launch_bounds__(256, 2) void spatial_attn_kernel(const T* __restric
       // took the rescaling branch for some lane; with the margin hardly any after the first. (A lane whose own
       // score stays inside the margin keeps its m when the branch is taken for another: exp2(0) = 1 exactly.)
       constexpr float kLazy = 8.f;
-      if constexpr (FOLD) {
-        // sc already is s * scale * log2(e) - m_run: a score above the offset shows as a positive one
-        const bool first = st_i == 0;  // the first stage sets the offset, which may be negative
-        if (first || __builtin_amdgcn_ballot_w64(mx > kLazy) != 0) {
-          mx = fmaxf(mx, __shfl_xor(mx, 32, 64));  // a stage always holds at least one valid key: finite
-          // (each query decides for itself: what the other lanes of the wavefront do must not show in its bits,
-          // or the result would depend on which queries share a wavefront, i.e. on the query window)
-          float m_new = m_run[t] + ((first || mx > kLazy) ? mx : 0.f);
-          m_new = static_cast<float>(static_cast<bf16_t>(m_new));  // as slot D will hold it
-          const float delta = m_new - m_run[t];
-          const float alpha = __builtin_amdgcn_exp2f(-delta);
-          m_run[t] = m_new;
-#pragma unroll
-          for (int mt = 0; mt < DM; ++mt)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) o[t][mt][r] *= alpha;
-#pragma unroll
-          for (int kt = 0; kt < KT; ++kt)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) sc[t][kt][r] -= delta;
-          if (hh == HX) qf[t][KX][EX] = static_cast<bf16_t>(-m_new);
-        }
-      } else if (st_i == 0 || __builtin_amdgcn_ballot_w64((mx - m_run[t]) * scale_log2e > kLazy) != 0) {
+      if (st_i == 0 || __builtin_amdgcn_ballot_w64((mx - m_run[t]) * scale_log2e > kLazy) != 0) {
         mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
         const bool up = st_i == 0 || (mx - m_run[t]) * scale_log2e > kLazy;
         const float m_new = up ? fmaxf(m_run[t], mx) : m_run[t];
@@ -274,7 +236,7 @@ __global__ __launch_bounds__(256, 2) void spatial_attn_kernel(const T* __restric
         float p[16];
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-          p[r] = FOLD ? __builtin_amdgcn_exp2f(sc[t][kt][r]) : __builtin_amdgcn_exp2f(fmaf(sc[t][kt][r], scale_log2e, -mc));
+          p[r] = __builtin_amdgcn_exp2f(fmaf(sc[t][kt][r], scale_log2e, -mc));
           if (!ROWSUM) ps += p[r];
         }
         if constexpr (sizeof(T) == 2) {
@@ -338,6 +300,406 @@ __global__ __launch_bounds__(256, 2) void spatial_attn_kernel(const T* __restric
   }
 }
 
+// f(0), f(1), .. f(N - 1) with compile-time indexes (the bodies below index register arrays)
+template <int I, int N, class F> __device__ __forceinline__ void static_for(F&& f) {
+  if constexpr (I < N) {
+    f(std::integral_constant<int, I>{});
+    static_for<I + 1, N>(static_cast<F&&>(f));
+  }
+}
+
+// Spatial attention of the bf16 stages. What bounds it: the matrix pipe (d = 64: 512 cycles of MFMAs per 32 keys x 64
+// queries and wavefront) and, beside it, the vector port (32 exponentials at about 10 cycles, 16 packs, 32 additions).
+// Here the two overlap inside a wavefront. A substep is 32 keys, and
+// three independent pieces of work are issued interleaved, a few vector instructions behind every MFMA:
+//   scores of substep j + 1 (K Q^T)  |  probabilities of substep j  |  O^T += V^T P^T of substep j - 1
+// Fragments are requested from LDS half a substep ahead of their use. K and V^T go from global memory straight into
+// LDS (16 bytes per lane) into a ring of four 64-key stages: stage s + 2 is requested at the start of stage s, one
+// barrier per stage. (Four, because the scores run into stage s + 1 and the lagging V fragments are read until late in
+// stage s.) 16-byte slots are XOR-swizzled where a row is 128 bytes.
+// No running maximum: softmax does not depend on the offset it subtracts, and with scores in log2 units between -90
+// and 100 exp2 needs none in fp32 (bf16 has the same exponent range and rounds relatively). The denominator and O^T
+// tell afterwards: a query whose denominator left [2^-90, 2^110] or whose O^T is not finite is flagged and, in a rare
+// second sweep, done again with its exact maximum (found in a sweep over the keys of its own). The decision is each
+// query's own, and so is every bit of its result, whoever shares its wavefront.
+// Measured (us per launch, with a kernel that ran the two phases in turn / this one): d = 64, 5 x 9216 tokens, 2304
+// queries, 5 heads 204 / 170 alone and 157 / 132 with two launches in flight (1.02 PFLOP/s); d = 40, 4 x 4096, 8 heads
+// 123 / 104; d = 40, 8 x 9216 1110 / 960; cross-attention to 77 keys, 16 x 4096, 8 heads 48 / 45. The matrix pipe is busy
+// 80 % of the cycles and the clock falls from 2.4 to 1.6 - 1.9 GHz (with zeros as input it stays at 2.3): what bounds it
+// now is power.
+// NQT: 32-query tiles per wavefront. Two share every fragment read; one is for launches that would otherwise leave
+// compute units without a workgroup.
+template <int D, int NQT, bool PRE, bool XA>
+__global__ __launch_bounds__(256, 2) void spatial_attn_ring_kernel(const bf16_t* __restrict__ qk, int ldq,
+                                                                   const bf16_t* __restrict__ vt, int Tp,
+                                                                   bf16_t* __restrict__ out, int T_tok, int C, int q0, int nq,
+                                                                   int qw, int qstride, float scale_log2e,
+                                                                   const bf16_t* __restrict__ kx, int ldk, int Tk, int kv_div) {
+  typedef Mma32<bf16_t> M;
+  typedef M::Frag Frag;
+  constexpr int KSTEPS = (D + 15) / 16;     // MFMAs along d
+  constexpr int DM = (D + 31) / 32;         // 32-row tiles of O^T
+  constexpr int KP = 2 * KSTEPS;            // 16-byte slots of a K row in LDS (those beyond d meet zeros of q)
+  constexpr int KSLOT = kKeys * KP * 16, VSLOT = DM * 32 * 128, SLOT = KSLOT + VSLOT;
+  constexpr int NB = 4;                     // stages in LDS
+  constexpr bool ROWSUM = D % 32 != 0;      // a spare row of V^T holds ones: O^T[D] is the denominator
+  constexpr bool KSWZ = KP == 8;            // 128-byte K rows
+  constexpr int NKI = KP, NVI = D / 8;      // wavefront instructions that move one stage of K, of V^T
+  constexpr int KJ = (NKI + 3) / 4, VJ = (NVI + 3) / 4;
+  constexpr int NQK = NQT * KSTEPS, NPV = NQT * 2 * DM, NM = NQK + NPV;  // MFMAs of a substep
+  constexpr int NE = NQT * 16;              // exponentials of a substep
+  constexpr int NF = KSTEPS + 2 * DM;       // LDS fragments of a substep, NQT MFMAs each
+  constexpr int kAhead = 2 * DM < 6 / NQT ? 2 * DM : 6 / NQT;
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  auto kl = [&](int b) { return smem + b * SLOT; };
+  auto vl = [&](int b) { return smem + b * SLOT + KSLOT; };
+  int* redo_flag = reinterpret_cast<int*>(smem + NB * SLOT);
+
+  const int tid = threadIdx.x, lane = tid & 63, wid = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lq = lane & 31, hh = lane >> 5;
+  int qb = blockIdx.x, head = blockIdx.y, frame = blockIdx.z;
+  {  // all query blocks of one (frame, head) on one XCD, as above
+    const int nqb = gridDim.x, heads = gridDim.y, nprob = gridDim.y * gridDim.z;
+    if (nprob % 8 == 0) {
+      const int lin = blockIdx.x + nqb * (blockIdx.y + heads * blockIdx.z);
+      const int xcd = lin & 7, slot = lin >> 3;
+      const int prob = xcd + 8 * (slot / nqb);
+      qb = slot % nqb;
+      head = prob % heads;
+      frame = prob / heads;
+    }
+  }
+  const bf16_t* __restrict__ base = qk + (int64_t)frame * T_tok * ldq + head * D;
+  const int kvf = XA ? frame / kv_div : frame, TK = XA ? Tk : T_tok, ldkk = XA ? ldk : ldq;
+  const bf16_t* __restrict__ kb = XA ? kx + (int64_t)kvf * Tk * ldk + head * D : base + C;
+  const bf16_t* __restrict__ vbase = vt + ((int64_t)kvf * C + head * D) * Tp;
+  const int qblk = qb * (4 * NQT * 32) + wid * (NQT * 32);
+  auto token_of = [&](int qi) { const int r = qi / qw; return q0 + r * qstride + (qi - r * qw); };
+
+  // rows of V^T beyond d: ones in row D (ROWSUM), zeros below; the loads never touch them
+  if constexpr (ROWSUM) {
+    constexpr int per = (DM * 32 - D) * 8;  // 16-byte packets of a stage
+    for (int i = tid; i < NB * per; i += 256) {
+      const int b = i / per, p = i - b * per;
+      const uint32_t v = p < 8 ? 0x3f803f80u : 0u;
+      *reinterpret_cast<uint4*>(vl(b) + D * 128 + p * 16) = uint4{v, v, v, v};
+    }
+  }
+  if (tid == 0) *redo_flag = 0;
+
+  // ---- global -> LDS. K: packet p of a stage is (key p / KP, slot p % KP); V^T: (row p / 8, slot p % 8)
+  uint32_t koff[KJ], voff[VJ];
+#pragma unroll
+  for (int j = 0; j < KJ; ++j) {
+    const int p = min(wid + 4 * j, NKI - 1) * 64 + lane, key = p / KP, sl = p % KP;
+    const int c = KSWZ ? (sl ^ ((key >> 1) & 7)) : min(sl, D / 8 - 1);  // (slots beyond d: a copy of the last packet)
+    koff[j] = (uint32_t)(key * ldkk + c * 8) * 2;
+  }
+#pragma unroll
+  for (int j = 0; j < VJ; ++j) {
+    const int p = min(wid + 4 * j, NVI - 1) * 64 + lane, dim = p / 8, sl = p % 8;
+    voff[j] = (uint32_t)(dim * Tp + (sl ^ ((dim >> 1) & 7)) * 8) * 2;
+  }
+  auto issue = [&](int st) {
+    unsigned char* b = kl(st & (NB - 1));
+    const char* kg = (const char*)kb + (int64_t)st * kKeys * ldkk * 2;
+    const char* vg = (const char*)vbase + (int64_t)st * kKeys * 2;
+#ifdef __HIP_DEVICE_COMPILE__  // the host pass only needs the kernel's stub; it does not know this builtin
+    if (st * kKeys + kKeys <= TK) {
+#pragma unroll
+      for (int j = 0; j < KJ; ++j)
+        __builtin_amdgcn_global_load_lds((const void*)(kg + koff[j]), b + min(wid + 4 * j, NKI - 1) * 1024, 16, 0, 0);
+    } else {  // keys beyond the sequence: the last one again (masked below)
+#pragma unroll
+      for (int j = 0; j < KJ; ++j) {
+        const int n = min(wid + 4 * j, NKI - 1), key = (n * 64 + lane) / KP;
+        const int back = max(key - (TK - 1 - st * kKeys), 0);
+        __builtin_amdgcn_global_load_lds((const void*)(kg + koff[j] - (int64_t)back * ldkk * 2), b + n * 1024, 16, 0, 0);
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < VJ; ++j)
+      __builtin_amdgcn_global_load_lds((const void*)(vg + voff[j]), b + KSLOT + min(wid + 4 * j, NVI - 1) * 1024, 16, 0, 0);
+#else
+    (void)b; (void)kg; (void)vg;
+#endif
+  };
+  // every load has landed (for every wavefront, behind the barrier); LDS reads in flight are left alone: the stage they
+  // read is written again two barriers later at the earliest
+  auto stage_barrier = [&]() {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(7 << 4 | 15 << 8);  // vmcnt(0)
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+  };
+
+  // ---- Q fragments (B operand of S^T = K Q^T); slots beyond d are zeros
+  Frag qf[NQT][KSTEPS];
+#pragma unroll
+  for (int t = 0; t < NQT; ++t) {
+    const int qi = qblk + t * 32 + lq;
+    const int q = token_of(min(qi, nq - 1));
+#pragma unroll
+    for (int kk = 0; kk < KSTEPS; ++kk) {
+      const int e = kk * 16 + hh * 8;
+      qf[t][kk] = (qi < nq && e < D) ? M::load(base + (int64_t)q * ldq + e) : M::zero();
+    }
+  }
+  const int krow = lq * (KP * 16), kkey = KSWZ ? ((lq >> 1) & 7) : 0;
+  const int vrow = lq * 128, vkey = (lq >> 1) & 7;
+  auto kfrag = [&](const unsigned char* k, int u, int kk) {
+    return M::load((const bf16_t*)(k + u * 32 * KP * 16 + krow + (((kk * 2 + hh) ^ kkey) << 4)));
+  };
+  // the 8 keys a lane contracts in step st of substep u: V^T columns 32 u + 16 st + 8 hh ..+7
+  auto vfrag = [&](const unsigned char* v, int u, int st, int mt) {
+    return M::load((const bf16_t*)(v + mt * 32 * 128 + vrow + (((4 * u + 2 * st + hh) ^ vkey) << 4)));
+  };
+  auto beyond = [&](int key0, int r) { return key0 + 4 * hh + 8 * (r >> 2) + (r & 3) >= TK; };  // accumulator r's key
+
+  const int nstage = (TK + kKeys - 1) / kKeys;
+  f32x16 o[NQT][DM];
+  float lsum[NQT][2];
+  float m[NQT];  // second sweep only: the exact maxima, in the units of the exponent
+#pragma unroll
+  for (int t = 0; t < NQT; ++t) m[t] = 0.f;
+
+  auto sweep = [&](auto safe_c) __attribute__((always_inline)) {
+    constexpr bool SAFE = decltype(safe_c)::value;
+    f32x16 sA[NQT], sB[NQT];     // scores: of this substep, of the next
+    Frag pA[NQT][2], pB[NQT][2]; // probabilities as operands: of this substep, of the one before
+    Frag kf[KSTEPS], vf[2][DM];
+    const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int t = 0; t < NQT; ++t) {
+      lsum[t][0] = lsum[t][1] = 0.f;
+      pB[t][0] = pB[t][1] = M::zero();
+#pragma unroll
+      for (int mt = 0; mt < DM; ++mt) o[t][mt] = zero16;
+    }
+    // O^T += (V^T of the 32 keys (vp, up)) pp; sn = K Q^T of the keys (ks, us); pc = probabilities of sc (first key key0).
+    // The fragment of group g (NQT MFMAs each: V fragments, then K fragments) is requested kAhead groups before its use,
+    // the first V fragments of the next substep, (vn, un), in the last groups of this one.
+    auto substep = [&](f32x16 (&sn)[NQT], f32x16 (&sc)[NQT], Frag (&pc)[NQT][2], Frag (&pp)[NQT][2], const unsigned char* vp, int up,
+                       const unsigned char* ks, int us, const unsigned char* vn, int un, int key0)
+                       __attribute__((always_inline)) {
+      if (key0 + 32 > TK) {  // uniform: some keys lie beyond the sequence
+        int kb0 = key0 + 4 * hh;
+        asm volatile("" : "+v"(kb0));  // (left alone the compiler computes the sixteen indexes outside the branch)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const bool gone = kb0 + 8 * (r >> 2) + (r & 3) >= TK;
+#pragma unroll
+          for (int t = 0; t < NQT; ++t)
+            if (gone) sc[t][r] = -INFINITY;
+        }
+      }
+      static_for<0, NM>([&](auto m_c) __attribute__((always_inline)) {
+        constexpr int i = decltype(m_c)::value;
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (i % NQT == 0) {
+          constexpr int g = i / NQT + kAhead;
+          if constexpr (g < 2 * DM) vf[g / DM][g % DM] = vfrag(vp, up, g / DM, g % DM);
+          else if constexpr (g < NF) kf[g - 2 * DM] = kfrag(ks, us, g - 2 * DM);
+          else vf[(g - NF) / DM][(g - NF) % DM] = vfrag(vn, un, (g - NF) / DM, (g - NF) % DM);
+          __builtin_amdgcn_sched_barrier(0);
+          // the group's own fragment has arrived, the kAhead younger ones may be on their way (left alone the compiler
+          // waits for all of them at every fourth group)
+          __builtin_amdgcn_s_waitcnt(15 | 7 << 4 | kAhead << 8 | 3 << 14);
+        }
+        if constexpr (i < NPV) {
+          constexpr int st = i / (DM * NQT), mt = i / NQT % DM, t = i % NQT;
+          M::mma(vf[st][mt], pp[t][st], o[t][mt]);
+        } else {
+          constexpr int kk = (i - NPV) / NQT, t = i % NQT;
+          sn[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[kk], qf[t][kk], kk ? sn[t] : zero16, 0, 0, 0);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        constexpr int e0 = (i * NE / NM) & ~1, e1 = i == NM - 1 ? NE : (((i + 1) * NE / NM) & ~1);
+        static_for<0, (e1 - e0) / 2>([&](auto e_c) __attribute__((always_inline)) {
+          constexpr int e = e0 + 2 * decltype(e_c)::value, t = e / 16, r = e % 16;
+          float p[2];
+#pragma unroll
+          for (int k = 0; k < 2; ++k) {
+            float x = sc[t][r + k];
+            if (SAFE) x = PRE ? x - m[t] : fmaf(x, scale_log2e, -m[t]);
+            else if (!PRE) x *= scale_log2e;
+            p[k] = __builtin_amdgcn_exp2f(x);
+            pc[t][r / 8][r % 8 + k] = static_cast<bf16_t>(p[k]);
+          }
+          // the denominator sums the probabilities as rounded, like the ones row does: what one key contributes to
+          // numerator and denominator then cancels, however peaked the softmax is
+          if constexpr (!ROWSUM) {
+            bf16x2 p2, one2;
+            p2[0] = pc[t][r / 8][r % 8];
+            p2[1] = pc[t][r / 8][r % 8 + 1];
+            one2[0] = one2[1] = (bf16_t)1.f;
+            lsum[t][e / 2 % 2] = __builtin_amdgcn_fdot2_f32_bf16(p2, one2, lsum[t][e / 2 % 2], false);
+          }
+        });
+      });
+      // (computed here: left alone the compiler moves them behind the branch of the next substep, which uses them)
+#pragma unroll
+      for (int t = 0; t < NQT; ++t) asm volatile("" : "+v"(pc[t][0]), "+v"(pc[t][1]));
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    issue(0);
+    if (nstage > 1) issue(1);
+    stage_barrier();
+    static_for<0, KSTEPS>([&](auto kk) __attribute__((always_inline)) { kf[decltype(kk)::value] = kfrag(kl(0), 0, decltype(kk)::value); });
+    static_for<0, NQK>([&](auto i) __attribute__((always_inline)) {
+      constexpr int kk = decltype(i)::value / NQT, t = decltype(i)::value % NQT;
+      sA[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[kk], qf[t][kk], kk ? sA[t] : zero16, 0, 0, 0);
+    });
+    static_for<0, kAhead>([&](auto g) __attribute__((always_inline)) {
+      vf[decltype(g)::value / DM][decltype(g)::value % DM] = vfrag(vl(0), 0, decltype(g)::value / DM, decltype(g)::value % DM);
+    });
+    // (in the first substep the probabilities of "the substep before" are zeros: any finite V does, its own is at hand.
+    // Behind the last stage the K requests and scores are of no stage: in bounds, never used.)
+    for (int s = 0; s < nstage; ++s) {
+      if (s) stage_barrier();
+      if (s + 2 < nstage) issue(s + 2);
+      const int b = s & (NB - 1), bn = (s + 1) & (NB - 1), bp = s ? (s - 1) & (NB - 1) : 0;
+      if (s * kKeys + kKeys > TK) {
+        // columns of V^T beyond the sequence hold anything: zeros, so that they meet zero probabilities safely
+        for (int i = tid; i < D * kKeys; i += 256) {
+          const int dim = i / kKeys, col = i % kKeys;
+          if (s * kKeys + vcol_inv<bf16_t>(col) >= TK)
+            *reinterpret_cast<bf16_t*>(vl(b) + dim * 128 + (((col >> 3) ^ ((dim >> 1) & 7)) << 4) + (col & 7) * 2) = (bf16_t)0.f;
+        }
+        __syncthreads();
+      }
+      substep(sB, sA, pA, pB, vl(bp), s ? 1 : 0, kl(b), 1, vl(b), 0, s * kKeys);
+      substep(sA, sB, pB, pA, vl(b), 0, kl(bn), 0, vl(b), 1, s * kKeys + 32);
+    }
+    const unsigned char* vlast = vl((nstage - 1) & (NB - 1));
+    static_for<0, 2 * DM>([&](auto i) __attribute__((always_inline)) {
+      constexpr int st = decltype(i)::value / DM, mt = decltype(i)::value % DM;
+      const Frag v = decltype(i)::value < kAhead ? vf[st][mt] : vfrag(vlast, 1, st, mt);
+#pragma unroll
+      for (int t = 0; t < NQT; ++t) M::mma(v, pB[t][st], o[t][mt]);
+    });
+  };
+
+  // ---- normalise and store the queries of tile t: lane holds O^T[dim = 32 mt + 8 (r / 4) + 4 hh + r % 4][query lq]
+  auto denominator = [&](int t) {
+    if constexpr (ROWSUM) {  // O^T[D][q] sits in register r of the lanes of half hsel
+      constexpr int rem = D % 32, hsel = (rem % 8) / 4, r = (rem / 8) * 4 + rem % 4;
+      return __shfl(o[t][D / 32][r], lq + 32 * hsel, 64);
+    } else {
+      const float l = lsum[t][0] + lsum[t][1];
+      return l + __shfl_xor(l, 32, 64);
+    }
+  };
+  auto store = [&](int t, float inv) {
+    const int qi = qblk + t * 32 + lq;
+    if (qi >= nq) return;
+    bf16_t* orow = out + ((int64_t)frame * T_tok + token_of(qi)) * C + head * D;
+#pragma unroll
+    for (int mt = 0; mt < DM; ++mt)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const int dim = mt * 32 + 8 * g + 4 * hh;
+        if (dim < D) {
+          bf16x4 ov;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) ov[e] = static_cast<bf16_t>(o[t][mt][4 * g + e] * inv);
+          *reinterpret_cast<bf16x4*>(orow + dim) = ov;
+        }
+      }
+  };
+
+  sweep(std::false_type{});
+  bool redo[NQT], any = false;
+#pragma unroll
+  for (int t = 0; t < NQT; ++t) {
+    const float l = denominator(t);
+    float worst = 0.f;  // NaN or infinite if any element is
+#pragma unroll
+    for (int mt = 0; mt < DM; ++mt)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) worst = fmaf(o[t][mt][r], 0.f, worst);
+    int bad = !(l >= 0x1p-90f && l <= 0x1p110f) || worst != 0.f;
+    bad |= __shfl_xor(bad, 32, 64);
+    redo[t] = bad && qblk + t * 32 + lq < nq;
+    any |= redo[t];
+    if (!bad) store(t, 1.f / l);
+  }
+  if (__builtin_amdgcn_ballot_w64(any) != 0 && lane == 0) *redo_flag = 1;
+  __syncthreads();
+  if (*redo_flag) {
+    // exact maxima of every query, then the sweep again with them
+    float mx[NQT];
+#pragma unroll
+    for (int t = 0; t < NQT; ++t) mx[t] = -INFINITY;
+    for (int s = 0; s < nstage; ++s) {
+      __syncthreads();
+      issue(s);
+      stage_barrier();
+#pragma unroll
+      for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int t = 0; t < NQT; ++t) {
+          f32x16 sc;
+#pragma unroll
+          for (int r = 0; r < 16; ++r) sc[r] = 0.f;
+#pragma unroll
+          for (int kk = 0; kk < KSTEPS; ++kk) M::mma(kfrag(kl(s & (NB - 1)), u, kk), qf[t][kk], sc);
+#pragma unroll
+          for (int r = 0; r < 16; ++r)
+            if (!beyond(s * kKeys + 32 * u, r)) mx[t] = fmaxf(mx[t], sc[r]);
+        }
+    }
+#pragma unroll
+    for (int t = 0; t < NQT; ++t) m[t] = fmaxf(mx[t], __shfl_xor(mx[t], 32, 64)) * (PRE ? 1.f : scale_log2e);
+    __syncthreads();
+    sweep(std::true_type{});
+#pragma unroll
+    for (int t = 0; t < NQT; ++t) {
+      const float l = denominator(t);
+      if (redo[t]) store(t, 1.f / l);
+    }
+  }
+}
+
+template <int D, int NQT, bool PRE, bool XA>
+static hipError_t run_ring(hipStream_t s, const bf16_t* qk, int ldq, const bf16_t* vt, int Tp, bf16_t* out, int frames, int T_tok, int heads,
+                           int q0, int nq, int qw, int qstride, const bf16_t* kx, int ldk, int Tk, int kv_div) {
+  constexpr int lds = 4 * (kKeys * ((D + 15) / 16) * 32 + (D + 31) / 32 * 32 * 128) + 16;
+  static_assert(2 * lds <= 160 * 1024, "two workgroups per compute unit");
+  auto kern = spatial_attn_ring_kernel<D, NQT, PRE, XA>;
+  static bool attr_done = false;  // per instantiation
+  if (!attr_done) {
+    const hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    if (e != hipSuccess) return e;
+    attr_done = true;
+  }
+  const float sl = PRE ? 1.f : 1.4426950408889634f / sqrtf((float)D);
+  dim3 grid((nq + 128 * NQT - 1) / (128 * NQT), heads, frames);
+  kern<<<grid, 256, lds, s>>>(qk, ldq, vt, Tp, out, T_tok, heads * D, q0, nq, qw, qstride, sl, kx, ldk, Tk, kv_div);
+  return hipGetLastError();
+}
+template <bool PRE, bool XA>
+static hipError_t ring_dispatch(hipStream_t s, const bf16_t* qk, int ldq, const bf16_t* vt, int Tp, bf16_t* out, int frames, int T_tok, int heads,
+                                int d, int q0, int nq, int qw, int qstride, const bf16_t* kx = nullptr, int ldk = 0, int Tk = 0,
+                                int kv_div = 1) {
+  // One query tile per wavefront while two would leave a quarter of the 256 compute units without a workgroup: the extra
+  // fragment reads cost less than idle units (d = 40, one frame of 4096 tokens, 8 heads: 128 workgroups 57 us, 256
+  // workgroups 43 us; d = 64, 225 against 450 workgroups: 164 and 159 us alone, 133 and 145 us with two launches in flight).
+  const bool narrow = (int64_t)((nq + 255) / 256) * heads * frames < 192;
+#define LC_GO(D)                                                                                                                        \
+  return narrow ? run_ring<D, 1, PRE, XA>(s, qk, ldq, vt, Tp, out, frames, T_tok, heads, q0, nq, qw, qstride, kx, ldk, Tk, kv_div)      \
+                : run_ring<D, 2, PRE, XA>(s, qk, ldq, vt, Tp, out, frames, T_tok, heads, q0, nq, qw, qstride, kx, ldk, Tk, kv_div)
+  switch (d) {
+    case 8: LC_GO(8);
+    case 16: LC_GO(16);
+    case 32: LC_GO(32);
+    case 40: LC_GO(40);
+    case 64: LC_GO(64);
+    default: return hipErrorInvalidValue;
+  }
+#undef LC_GO
+}
+
 template <class T, int NQT, bool PRE>
 static hipError_t spatial_dispatch(hipStream_t s, const T* qk, int ldq, const T* vt, int Tp, T* out, int frames,
                                    int T_tok, int heads, int d, int q0, int nq, int qw, int qstride) {
@@ -374,8 +736,7 @@ hipError_t launch_spatial_attention_window(hipStream_t s, int dt, const void* qk
     if ((int64_t)q0 + (int64_t)r * qstride + (nq - 1 - r * qw) >= T) return hipErrorInvalidValue;
   }
 #define LC_ARGS(TT) s, (const TT*)qk, ldq, (const TT*)vt, Tp, (TT*)out, frames, T, heads, d, q0, nq, qw, qstride
-  if (dt == kBF16)
-    return q_prescaled ? spatial_dispatch<bf16_t, 2, true>(LC_ARGS(bf16_t)) : spatial_dispatch<bf16_t, 2, false>(LC_ARGS(bf16_t));
+  if (dt == kBF16) return q_prescaled ? ring_dispatch<true, false>(LC_ARGS(bf16_t)) : ring_dispatch<false, false>(LC_ARGS(bf16_t));
   return q_prescaled ? spatial_dispatch<float, 1, true>(LC_ARGS(float)) : spatial_dispatch<float, 1, false>(LC_ARGS(float));
 #undef LC_ARGS
 }
@@ -387,9 +748,9 @@ static hipError_t cross_dispatch(hipStream_t s, const T* q, int ldq, const T* k,
                                  int Tq, int Tk, int kv_div, int heads, int d) {
   constexpr int NQT = sizeof(T) == 2 ? 2 : 1;
   const int C = heads * d;
-  const float sl = 1.4426950408889634f / sqrtf((float)d);
+  const float sl = 1.f;  // the queries carry the scale
   dim3 grid((Tq + 4 * NQT * 32 - 1) / (4 * NQT * 32), heads, frames);
-#define LC_GO(D) spatial_attn_kernel<T, D, NQT, false, true><<<grid, 256, 0, s>>>(q, ldq, vt, Tp, out, Tq, C, 0, Tq, Tq, 0, sl, k, ldk, Tk, kv_div)
+#define LC_GO(D) spatial_attn_kernel<T, D, NQT, true, true><<<grid, 256, 0, s>>>(q, ldq, vt, Tp, out, Tq, C, 0, Tq, Tq, 0, sl, k, ldk, Tk, kv_div)
   switch (d) {
     case 8: LC_GO(8); break;
     case 16: LC_GO(16); break;
@@ -406,8 +767,8 @@ hipError_t launch_cross_attention(hipStream_t s, int dt, const void* q, int ldq,
   if (frames <= 0 || Tq <= 0) return hipSuccess;
   if (Tk <= 0 || kv_div <= 0 || frames % kv_div || Tp % kKeys != 0 || Tp < Tk) return hipErrorInvalidValue;
   if (dt == kBF16)
-    return cross_dispatch<bf16_t>(s, (const bf16_t*)q, ldq, (const bf16_t*)k, ldk, (const bf16_t*)vt, Tp, (bf16_t*)out, frames, Tq, Tk,
-                                  kv_div, heads, d);
+    return ring_dispatch<true, true>(s, (const bf16_t*)q, ldq, (const bf16_t*)vt, Tp, (bf16_t*)out, frames, Tq, heads, d, 0, Tq, Tq, 0,
+                                      (const bf16_t*)k, ldk, Tk, kv_div);
   return cross_dispatch<float>(s, (const float*)q, ldq, (const float*)k, ldk, (const float*)vt, Tp, (float*)out, frames, Tq, Tk, kv_div,
                                heads, d);
 }

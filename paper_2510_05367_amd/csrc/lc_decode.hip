@@ -173,9 +173,10 @@ lc_status attn_block(lc_decoder* d, const DPlan& p, int n, float* h) {
   f.dt = g.dtype; f.y_f32 = 0; f.taps = 1; f.src = 1; f.Cin = C; f.Cout = 3 * C; f.Cout_store = 3 * C; f.w = d->at_wqkv;
   f.rows = (int64_t)n * T; f.in_map = RowMap{0, T, T}; f.out_map = RowMap{0, 0, 1 << 30}; f.x = h; f.y = qkv;
   f.scale = (const float*)(d->arena + p.off_scale); f.shift = (const float*)(d->arena + p.off_shift);
+  f.q_cols = C; f.q_scale = attn_q_scale(g.head_dim);
   LCD_HIP(d, launch_fused(d->s, f));
   LCD_HIP(d, launch_make_vt(d->s, g.dtype, qkv + (size_t)2 * C * es, 3 * C, vt, n, T, Tp, C));
-  LCD_HIP(d, launch_spatial_attention(d->s, g.dtype, qkv, 3 * C, vt, Tp, ao, n, T, g.heads, g.head_dim, 0, T, 0));
+  LCD_HIP(d, launch_spatial_attention(d->s, g.dtype, qkv, 3 * C, vt, Tp, ao, n, T, g.heads, g.head_dim, 0, T, 1));
   memset(&f, 0, sizeof f);
   f.dt = g.dtype; f.y_f32 = 1; f.taps = 1; f.src = 0; f.Cin = C; f.Cout = C; f.Cout_store = C; f.w = d->at_wo; f.bias = d->at_bo;
   f.rows = (int64_t)n * T; f.in_map = f.out_map = RowMap{0, 0, 1 << 30}; f.x = ao; f.res = h; f.y = h;

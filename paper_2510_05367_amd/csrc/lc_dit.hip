@@ -216,12 +216,14 @@ inline char* slot_ptr(lc_dit* c, int s) { return c->arena + c->plan.off_slots + 
 inline const float* mod_blk(const lc_dit* c, const float* mod, int blk) { return mod + (int64_t)blk * c->cfg.B * 6 * c->cfg.D; }
 
 // y[rows][Cout] = x[rows][Cin] W^T + bias; x of the operand type, y fp32 (y32) or of the operand type
+// q_cols: the first channels, multiplied by the softmax scale before they are rounded (the form attention takes)
 lc_status linear(lc_dit* c, const void* w, const float* bias, int Cin, int Cout, int64_t rows, const void* x, void* y, int y32,
-                 int act = 0) {
+                 int act = 0, int q_cols = 0) {
   FusedDesc f;
   memset(&f, 0, sizeof f);
   f.dt = c->cfg.dtype; f.y_f32 = y32; f.taps = 1; f.src = 0; f.Cin = Cin; f.Cout = Cout; f.Cout_store = Cout; f.w = w; f.bias = bias;
   f.rows = rows; f.in_map = f.out_map = RowMap{0, 0, 1 << 30}; f.x = x; f.y = y; f.act = act;
+  if (q_cols) { f.q_cols = q_cols; f.q_scale = attn_q_scale(c->cfg.head_dim); }
   LCT_HIP(c, launch_fused(c->cs, f));
   return LC_OK;
 }
@@ -269,11 +271,11 @@ lc_status run_block(lc_dit* c, int i, const float* mod, float* x, const float* d
   for (int64_t r0 = 0; r0 < R; r0 += p.tc) {
     const int n = (int)std::min<int64_t>(p.tc, R - r0);
     if ((s = ln_mod(c, x + r0 * D, delta ? delta + r0 * D : nullptr, m, 0, 1, xn, n, r0)) != LC_OK) return s;
-    if ((s = linear(c, w.wqkv, w.bqkv, D, 3 * D, n, xn, qkv + r0 * 3 * D * es, 0)) != LC_OK) return s;
+    if ((s = linear(c, w.wqkv, w.bqkv, D, 3 * D, n, xn, qkv + r0 * 3 * D * es, 0, 0, D)) != LC_OK) return s;
   }
   LCT_HIP(c, launch_make_vt(c->cs, g.dtype, qkv + (size_t)2 * D * es, 3 * D, vt, g.B, T, Tp, D));
   for (int q0 = 0; q0 < T; q0 += p.qc)  // a chunk of queries of every batch element against all keys
-    LCT_HIP(c, launch_spatial_attention(c->cs, g.dtype, qkv, 3 * D, vt, Tp, ao, g.B, T, g.heads, g.head_dim, q0, std::min(q0 + p.qc, T), 0));
+    LCT_HIP(c, launch_spatial_attention(c->cs, g.dtype, qkv, 3 * D, vt, Tp, ao, g.B, T, g.heads, g.head_dim, q0, std::min(q0 + p.qc, T), 1));
   for (int64_t r0 = 0; r0 < R; r0 += p.tc) {
     const int n = (int)std::min<int64_t>(p.tc, R - r0);
     if ((s = linear(c, w.wo, w.bo, D, D, n, ao + r0 * D * es, t, 1)) != LC_OK) return s;

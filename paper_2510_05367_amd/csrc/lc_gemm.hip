@@ -700,7 +700,7 @@ hipError_t launch_fused(hipStream_t s, const FusedDesc& d) {
     return hipErrorInvalidValue;
   if (d.taps == 1 && d.win_w) return hipErrorInvalidValue;  // the streaming linear kernel has no spatial window
   const int esz = (int)dtype_size(d.dt);
-  if (d.q_cols && (d.taps != 1 || d.q_cols % 4 || d.q_cols > d.Cout || d.bias || d.res)) return hipErrorInvalidValue;
+  if (d.q_cols && (d.taps != 1 || d.q_cols % 4 || d.q_cols > d.Cout || d.res)) return hipErrorInvalidValue;
   if (d.stat && (d.taps != 9 || d.planar_out || !(d.y_f32 || esz == 4) || d.stat_splits != conv_stat_splits(d.H, d.W)))
     return hipErrorInvalidValue;
   if (d.Cin % (kRow / esz) != 0) return hipErrorInvalidValue;

@@ -309,7 +309,7 @@ hipError_t launch_lin2(hipStream_t s, const FusedDesc& d) {
   if (d.Cin % 64 || d.Cin <= 0 || (d.Cout % 160 && d.Cout % 128) || d.Cout_store != d.Cout) return hipErrorNotSupported;
   if (d.in_map.rows_per_seg <= 0 || d.out_map.rows_per_seg <= 0) return hipErrorInvalidValue;
   if (d.res && !d.y_f32) return hipErrorNotSupported;
-  if (d.q_cols && (d.bias || d.res)) return hipErrorInvalidValue;
+  if (d.q_cols && d.res) return hipErrorInvalidValue;
   if (d.y2 && !d.y_f32) return hipErrorInvalidValue;
   if (d.act && (d.y_f32 || d.res || d.q_cols || d.act > 2)) return hipErrorInvalidValue;
   if (d.act == 2 && d.Cout % 128) return hipErrorNotSupported;

@@ -623,7 +623,9 @@ lc_status tf_rows(lc_unet* c, const TfP& w, float* x, RowMap m, const float* sca
   LCU_TRY(linear(c, w.wo1, C, C, rows, ao, z, 1, onto_z));
   if (w.cross) {  // queries from the tokens, keys and values from the conditioning tokens of the batch element
     LCU_TRY(ln(c, z, w.ln2, nullptr, a, rows, C, rpf));
-    LCU_TRY(linear(c, w.q2, C, C, rows, a, qkv, 0));
+    LinOpt scaled;
+    scaled.q_cols = C;
+    LCU_TRY(linear(c, w.q2, C, C, rows, a, qkv, 0, scaled));
     LCU_TRY(cross());
     LCU_TRY(linear(c, w.wo2, C, C, rows, ao, z, 1, onto_z));
   }

@@ -207,6 +207,37 @@ def test_spatial_attention_every_head_size(heads, head_dim, dtype):
         stage.close()
 
 
+@pytest.mark.parametrize("heads,head_dim,F,H,W", [(8, 40, 2, 8, 8), (1, 64, 2, 10, 14), (2, 32, 3, 12, 16), (8, 40, 16, 18, 30), (5, 64, 18, 18, 30)])
+def test_spatial_attention_out_of_range_scores(heads, head_dim, F, H, W):
+    """The bf16 kernel subtracts no maximum and does a query again with its exact one when exp2 left its range. Every
+    third query here has logits of several hundred, the others ordinary ones, so that wavefronts hold both kinds; few
+    tokens (one query tile per wavefront) and many (two), key counts of one stage, of whole stages and a remainder.
+    A window of queries must give the bits of the whole launch."""
+    C = heads * head_dim
+    cfg = synth.StageConfig(f"sr_{heads}x{head_dim}", B=1, F=F, H=H, W=W, C_lat=4, C=C, C_deep=64, groups=8 if C == 64 else 32, n_res=1,
+                            heads=heads, head_dim=head_dim, dtype="bf16")
+    stage, _ = make_stage(cfg, seed=6)
+    try:
+        N, T = cfg.N, cfg.T
+        qkv = act(cfg, (N * T, 3 * C), 252)
+        qkv[::3, :C] *= np.float32(120.0)
+        qkv = synth.round_to_bf16(qkv)
+        qd = dev(stage, qkv)
+        out = stage.empty(N * T, C)
+        lcb.lc_op_spatial_attention(stage.ctx, qd.data_ptr(), out.data_ptr(), N, 0, T, 0)
+        part = stage.empty(N * T, C)
+        part.copy_(out)
+        part.view(N, T, C)[:, 7:61].fill_(3.0)
+        lcb.lc_op_spatial_attention(stage.ctx, qd.data_ptr(), part.data_ptr(), N, 7, 61, 0)
+        stage.sync()
+        a = qkv.astype(np.float64).reshape(N, T, 3 * C)
+        ref = lo.attention_core(a[..., :C], a[..., C:2 * C], a[..., 2 * C:], heads).reshape(N * T, C)
+        check(f"spatial core out of range {heads}x{head_dim} T={T}", host(out), ref, "bf16")
+        assert torch.equal(out, part)
+    finally:
+        stage.close()
+
+
 def test_temporal_attention_core(st):
     stage, cfg, w = st
     B, F, C = cfg.B, cfg.F, cfg.C
