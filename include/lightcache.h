@@ -154,9 +154,10 @@ lc_status lc_set_workspace(lc_ctx* ctx, void* arena, size_t bytes);
 /* ---- the method ------------------------------------------------------------------------ */
 
 /* Feature chunk ([CHK]). frame_chunk = frames of the flattened B*F axis processed per pass by
- * the per-frame operators; token_chunk = spatial positions per pass of temporal attention and
- * query tokens per pass of spatial attention. 0 = unchunked; values above the axis length clamp;
- * a chunk that does not divide the axis gives a short last pass. If token_chunk == 0 and
+ * the per-frame operators; token_chunk = spatial positions per pass of temporal attention (the
+ * queries of spatial attention need no workspace of their own and go in one pass). 0 = unchunked; values
+ * above the axis length clamp; a chunk that does not divide the axis gives passes of about the same size,
+ * none larger than the chunk. If token_chunk == 0 and
  * frame_chunk > 0, temporal attention uses ceil(frame_chunk * H*W / (B*F)) positions per pass
  * (as many rows as a frame chunk). Chunking never changes results (each output is reduced in the
  * same order). LC_ERR_NOMEM if a workspace is set and is too small for the new setting. */
@@ -288,7 +289,7 @@ lc_status lc_op_res_block(lc_ctx* ctx, int layer, const void* x, void* y, int fr
 lc_status lc_op_qkv(lc_ctx* ctx, int layer, const void* x, void* qkv, int frames);
 /* Whole attention blocks, in place on the float rows h (the sequence of launches a step issues, on the chunk
  * scratch): h += proj(Attn(qkv(GroupNorm(h)))). Spatial: `frames` frames [frames*H*W, C], at most the frame
- * chunk (LC_ERR_NOMEM beyond), queries in token chunks; the V third of q,k,v goes from the projection's
+ * chunk (LC_ERR_NOMEM beyond); the V third of q,k,v goes from the projection's
  * epilogue straight into the transposed layout the attention kernel stages. Temporal: all B*F frames
  * [B*F*H*W, C], in position chunks. */
 lc_status lc_op_spatial_block(lc_ctx* ctx, void* h, int frames);
@@ -377,8 +378,8 @@ lc_status lc_decoder_sync(lc_decoder* dec);
  * + shift_mlp; x += gate_mlp * (W2 gelu_tanh(W1 h + b1) + b2). LN: per token, biased variance, no affine; q,k,v
  * projections with bias; `heads` heads of `head_dim`, scale 1/sqrt(head_dim). The modulation vectors are inputs.
  * Feature chunk ([CHK]): token_chunk of the B*T tokens of a step per pass of LayerNorm / projections / MLP (a pass may
- * run across batch elements: every row looks up its own modulation) and min(token_chunk, T) queries of every batch
- * element per pass of the attention (against all keys); it never changes results. Hidden states and modulation are float at the boundary;
+ * run across batch elements: every row looks up its own modulation); the queries of the attention go in one pass. It
+ * never changes results. Hidden states and modulation are float at the boundary;
  * weights have cfg dtype (bf16: MFMA operands bf16, accumulation and the residual stream fp32).
  * Requirements (else LC_ERR_SHAPE): sizes > 0; D a multiple of 64, <= 2048; heads * head_dim == D; head_dim in
  * {8, 16, 32, 40, 64}; L <= LC_DIT_MAX_BLOCKS; 0 <= cache_a <= cache_b <= L; mlp_ratio <= 8; 1 <= dev_slots <= 8;

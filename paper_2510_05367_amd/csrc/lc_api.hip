@@ -41,7 +41,8 @@ constexpr size_t kAlign = 256;
 inline size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 
 struct Plan {
-  int fc, tc, qc;  // effective frame chunk, temporal position chunk, spatial query chunk
+  int fc, tc;      // effective frame chunk, temporal position chunk: the largest a pass may take
+  int fs, ts;      // what a pass takes (see make_plan)
   int blocks;      // spatial blocks per frame (1: no spatial chunk)
   size_t off_h, off_slots, slot_bytes, off_partH, off_partT, off_partU, off_partD, partD_bytes, off_scale, off_shift, off_scale_cat,
       off_shift_cat, off_ws,
@@ -174,9 +175,14 @@ Plan make_plan(const lc_config& g, int frame_chunk, int token_chunk, int eta, in
   // position chunks of the temporal block in whole 32-row tiles where the frame allows it (the
   // weight-stationary linear kernel works on such tiles)
   if (T % 32 == 0) p.tc = (int)std::min<int64_t>(T, ((int64_t)p.tc + 31) / 32 * 32);
-  p.qc = token_chunk > 0 ? (int)std::min<int64_t>(token_chunk, T) : (int)T;
-  // with a spatial chunk the position chunks of the temporal block and the query chunks are its blocks
-  if (eta * omega > 1) p.tc = p.qc = (g.H / eta) * (g.W / omega);
+  // with a spatial chunk the position chunks of the temporal block are its blocks
+  if (eta * omega > 1) p.tc = (g.H / eta) * (g.W / omega);
+  // What a pass really takes: as many passes as chunks of fc frames (tc positions) need, all of about the same size. A
+  // short last chunk costs nearly as much as a full one (9 frames by four: 4 + 4 + 1 took a 3x3 convolution 36, 36 and
+  // 32 us), and two lanes share equal chunks better.
+  p.fs = (int)((N + (N + p.fc - 1) / p.fc - 1) / ((N + p.fc - 1) / p.fc));
+  p.ts = (int)((T + (T + p.tc - 1) / p.tc - 1) / ((T + p.tc - 1) / p.tc));
+  if (T % 32 == 0 && p.tc % 32 == 0) p.ts = (p.ts + 31) / 32 * 32;
   p.blocks = eta * omega;
   size_t off = 0;
   p.off_h = off; off += align_up((size_t)(N * T * g.C) * 4);  // the skip / residual stream is fp32
@@ -191,6 +197,7 @@ Plan make_plan(const lc_config& g, int frame_chunk, int token_chunk, int eta, in
   // does not change) plus one for the single-operator entry points.
   size_t sp = std::max((size_t)stat_splits((int)T), (size_t)conv_stat_splits(g.H, g.W));
   if (T % 32 == 0) sp = std::max(sp, (size_t)(T / 32));
+  if (g.dtype == kBF16) sp = std::max(sp, (size_t)conv_in_splits(g.H, g.W));
   const size_t ph = std::max(sp * g.C, (size_t)stat_splits((int)(T / 4)) * g.C_deep);
   p.off_partT = off; off += align_up((size_t)N * sp * g.C * 2 * sizeof(float));
   p.off_partU = off; off += align_up((size_t)N * sp * g.C * 2 * sizeof(float));
@@ -348,7 +355,10 @@ lc_status gn_scale_shift(lc_ctx* c, const void* x, int frames, int rows_per_fram
 // The choice between the two must not depend on how the stage is chunked (a chunked step reproduces
 // the unchunked one bit for bit, and the two kernels round differently): `tiled` says that the stage's
 // geometry suits the weight-stationary kernel for every chunking (frames of a multiple of 32 positions).
-lc_status linear(lc_ctx* c, int kind, FusedDesc d, bool* wrote_stats, bool tiled) {
+// Stages that are not tiled apply GroupNorm in a pass of its own into `rows16` (bf16 rows of d.Cin channels, as many as
+// the launch has), whose dense rows the streamed kernel contracts, where it covers the widths: 4 frames of 2160
+// positions, 320 -> 960 channels, took the kernel that normalises in its loader 73 us, the two together take 20 us.
+lc_status linear(lc_ctx* c, int kind, FusedDesc d, bool* wrote_stats, bool tiled, void* rows16 = nullptr) {
   hipError_t e = hipErrorNotSupported;
   if (tiled) {
     Prof pr_(c, kind);
@@ -359,6 +369,11 @@ lc_status linear(lc_ctx* c, int kind, FusedDesc d, bool* wrote_stats, bool tiled
   if (e == hipErrorNotSupported) {
     d.stat = nullptr;
     Prof pr_(c, kind);
+    if (rows16 && d.dt == kBF16 && d.src == 1 && !d.y_f32 && lin2_covers(d.Cin, d.Cout)) {
+      e = launch_gn_apply(c->cs, (const float*)d.x, d.scale, d.shift, rows16, d.rows, d.Cin, d.in_map.rows_per_seg, d.in_map);
+      if (e != hipSuccess) return fail(c, LC_ERR_HIP, "GroupNorm apply: %s", hipGetErrorString(e));
+      d.src = 0; d.x = rows16; d.in_map = dense_map();
+    }
     e = launch_fused(c->cs, d);
   }
   if (e != hipSuccess) return fail(c, LC_ERR_HIP, "linear layer: %s", hipGetErrorString(e));
@@ -396,21 +411,20 @@ FusedDesc flinear_desc(lc_ctx* c, const void* w, const void* w_frag, const float
 }
 
 // h = conv3x3(x): x planar [frames][C_lat][H][W] of the operand type, h fp32 rows. With `stat` the
-// partial sums of h are written too ([frame][T/32][C][2]; T must be a multiple of 32); *wrote tells
-// whether the kernel that ran could do that.
-lc_status conv_in_block(lc_ctx* c, const void* x, void* h, int frames, float* stat, bool* wrote_stats, Win win);
-lc_status conv_in_run(lc_ctx* c, const void* x, void* h, int frames, float* stat, bool* wrote_stats) {
+// partial sums of h are written there too where the kernel that runs can do that: *wrote tells.
+lc_status conv_in_block(lc_ctx* c, const void* x, void* h, int frames, float* stat, StatRef* wrote, Win win);
+lc_status conv_in_run(lc_ctx* c, const void* x, void* h, int frames, float* stat, StatRef* wrote) {
   const Blocks bl = blocks_of(c, c->cfg.H, c->cfg.W);
-  for (int i = 0; i < bl.n; ++i) {  // (every block runs the same kernel: *wrote_stats is that of any of them)
-    const lc_status s = conv_in_block(c, x, h, frames, stat, wrote_stats, bl.w[i]);
+  for (int i = 0; i < bl.n; ++i) {  // (every block runs the same kernel: *wrote is that of any of them)
+    const lc_status s = conv_in_block(c, x, h, frames, stat, wrote, bl.w[i]);
     if (s != LC_OK) return s;
   }
   return LC_OK;
 }
-lc_status conv_in_block(lc_ctx* c, const void* x, void* h, int frames, float* stat, bool* wrote_stats, Win win) {
+lc_status conv_in_block(lc_ctx* c, const void* x, void* h, int frames, float* stat, StatRef* wrote, Win win) {
   const lc_config& g = c->cfg;
   const int T = g.H * g.W;
-  if (wrote_stats) *wrote_stats = false;
+  if (wrote) *wrote = StatRef{nullptr, 0};
   if (c->pw.cin_wp) {  // (a property of the stage's geometry: the same kernel for every chunking)
     hipError_t e;
     {
@@ -419,7 +433,7 @@ lc_status conv_in_block(lc_ctx* c, const void* x, void* h, int frames, float* st
       if (e == hipErrorNotSupported) pr_.cancel();
     }
     if (e == hipSuccess) {
-      if (wrote_stats) *wrote_stats = stat != nullptr;
+      if (wrote) *wrote = StatRef{stat, conv_in_splits(g.H, g.W)};
       return LC_OK;
     }
     if (e != hipErrorNotSupported) return fail(c, LC_ERR_HIP, "conv_in: %s", hipGetErrorString(e));
@@ -439,7 +453,7 @@ lc_status conv_in_block(lc_ctx* c, const void* x, void* h, int frames, float* st
       if (e == hipErrorNotSupported) pr_.cancel();
     }
     if (e == hipSuccess) {
-      if (wrote_stats) *wrote_stats = d.stat != nullptr;
+      if (wrote) *wrote = StatRef{d.stat, d.stat_splits};
       return LC_OK;
     }
     if (e != hipErrorNotSupported) return fail(c, LC_ERR_HIP, "conv_in: %s", hipGetErrorString(e));
@@ -550,7 +564,7 @@ lc_status conv_out(lc_ctx* c, const void* u, void* eps, int frames, StatRef u_st
 }
 
 // Spatial attention block of `nf` frames, in place on the fp32 rows hc [nf*T][C]:
-// hc += proj(Attn_spatial(qkv(GroupNorm(hc)))), queries in chunks of plan.qc tokens. `scr`: scratch for q,k rows,
+// hc += proj(Attn_spatial(qkv(GroupNorm(hc)))). `scr`: scratch for q,k rows,
 // V^T and the attention output of these frames. `st`: partial sums of hc if its producer wrote them. `stat_out`:
 // where the partial sums of the result go ([frame][T/32][C][2]) or nullptr; *wrote tells whether they were written.
 lc_status spatial_block(lc_ctx* c, char* hc, char* scr, int nf, StatRef st, float* stat_out, bool* wrote) {
@@ -578,7 +592,7 @@ lc_status spatial_block(lc_ctx* c, char* hc, char* scr, int nf, StatRef st, floa
     d.yt = vt; d.yt_from = 2 * C; d.yt_T = T; d.yt_Tp = Tp;
     d.q_scale = attn_q_scale(g.head_dim); d.q_cols = C;  // the softmax scale rides on q, applied before rounding
     if (bl.w[i].w) set_row_win(d, bl.w[i], g.H, g.W, 1, 1);
-    s = linear(c, LC_K_QKV, d, nullptr, tiled);
+    s = linear(c, LC_K_QKV, d, nullptr, tiled, ao);
     if (s != LC_OK) return s;
   }
   for (int i = 0; i < bl.n; ++i) {
@@ -587,9 +601,8 @@ lc_status spatial_block(lc_ctx* c, char* hc, char* scr, int nf, StatRef st, floa
       LC_LAUNCH(c, LC_K_SATTN, launch_spatial_attention_window(c->cs, g.dtype, qk, 2 * C, vt, Tp, ao, nf, T, g.heads, g.head_dim,
                                                                w.y0 * g.W + w.x0, w.w * w.h, w.w, g.W, 1));
     } else {
-      for (int q0 = 0; q0 < T; q0 += c->plan.qc)
-        LC_LAUNCH(c, LC_K_SATTN, launch_spatial_attention(c->cs, g.dtype, qk, 2 * C, vt, Tp, ao, nf, T, g.heads,
-                                                          g.head_dim, q0, std::min(q0 + c->plan.qc, T), 1));
+      // (all queries at once whatever the token chunk: the kernel keeps nothing per query in memory)
+      LC_LAUNCH(c, LC_K_SATTN, launch_spatial_attention(c->cs, g.dtype, qk, 2 * C, vt, Tp, ao, nf, T, g.heads, g.head_dim, 0, T, 1));
     }
   }
   // the output projection closes the block; its partial sums are those of the next GroupNorm's input
@@ -607,7 +620,7 @@ lc_status spatial_block(lc_ctx* c, char* hc, char* scr, int nf, StatRef st, floa
   return LC_OK;
 }
 
-// Temporal attention block over all N frames, in place on h [N*T][C] (fp32), per position chunk of plan.tc
+// Temporal attention block over all N frames, in place on h [N*T][C] (fp32), per position chunk of plan.ts
 // positions on the lanes: h += proj(Attn_temporal(qkv(GroupNorm(h)))), statistics per whole frame. `tst`: partial
 // sums of h if its producers wrote them. *ustat: in, whether the partial sums of the result may go to partU;
 // out, whether they were written.
@@ -623,14 +636,14 @@ lc_status temporal_block(lc_ctx* c, char* h, StatRef tst, bool* ustat) {
   const float *sc0 = scale_p(c), *sh0 = shift_p(c);  // of all frames: every position chunk reads them, on either lane
   const Blocks bl = blocks_of(c, g.H, g.W);
   const bool spatial = bl.w[0].w != 0;  // position chunks = the blocks of the spatial chunk
-  const int nchunks = spatial ? bl.n : (T + p.tc - 1) / p.tc;
+  const int nchunks = spatial ? bl.n : (T + p.ts - 1) / p.ts;
   const int pos_lanes = loop_lanes(c, nchunks);
   if (pos_lanes > 1 && (s = fork_lanes(c)) != LC_OK) return s;
   for (int ci = 0; ci < nchunks; ++ci) {
     use_lane(c, ci % pos_lanes);
     char* ws = ws_ptr(c);
-    const int p0 = spatial ? 0 : ci * p.tc;
-    const int np = spatial ? bl.w[ci].w * bl.w[ci].h : std::min(p.tc, T - p0);
+    const int p0 = spatial ? 0 : ci * p.ts;
+    const int np = spatial ? bl.w[ci].w * bl.w[ci].h : std::min(p.ts, T - p0);
     const int64_t rows = (int64_t)N * np;
     // dense row r of a pass = (frame r / np, the r % np-th position of the chunk)
     RowMap m{p0, T, np};
@@ -641,7 +654,7 @@ lc_status temporal_block(lc_ctx* c, char* h, StatRef tst, bool* ustat) {
                                 dense_map(), h, nullptr, qkv, 0);
     dq.scale = sc0; dq.shift = sh0;
     if (spatial) set_row_win(dq, bl.w[ci], g.H, g.W, 1, 0);
-    s = linear(c, LC_K_QKV, dq, nullptr, tiled);
+    s = linear(c, LC_K_QKV, dq, nullptr, tiled, ao);
     if (s != LC_OK) return s;
     LC_LAUNCH(c, LC_K_TATTN, launch_temporal_attention(c->cs, g.dtype, qkv, ao, g.B, g.F, np, g.heads, g.head_dim));
     // this projection finishes the skip feature: its partial sums, for the up block, go to partU
@@ -667,16 +680,16 @@ lc_status run_step_lanes(lc_ctx* c, const void* x, void* eps, int slot, bool ful
   const size_t es = dtype_size(g.dtype);
   char* h = h_ptr(c);
   const Packed& w = c->pw;
-  const int frame_lanes = loop_lanes(c, (N + p.fc - 1) / p.fc);
+  const int frame_lanes = loop_lanes(c, (N + p.fs - 1) / p.fs);
 
   // ---- shallow down branch D_m, per frame chunk
   const bool tiled = T % 32 == 0;  // whole 32-row tiles in every frame and position chunk: see linear()
   bool tstat = tiled;              // the 32-row tiles of the projection kernels stay inside a frame
   if (frame_lanes > 1) { lc_status s = fork_lanes(c); if (s != LC_OK) return s; }
-  for (int n0 = 0, ci = 0; n0 < N; n0 += p.fc, ++ci) {
+  for (int n0 = 0, ci = 0; n0 < N; n0 += p.fs, ++ci) {
     use_lane(c, ci % frame_lanes);
     char* ws = ws_ptr(c);
-    const int nf = std::min(p.fc, N - n0);
+    const int nf = std::min(p.fs, N - n0);
     const int64_t pc = (int64_t)nf * T;
     char* hc = h + (size_t)n0 * T * C * 4;
     char* hb = ws;                                           // fp32 ping-pong partner of hc
@@ -687,10 +700,8 @@ lc_status run_step_lanes(lc_ctx* c, const void* x, void* eps, int slot, bool ful
     // for the GroupNorm that reads it next (where its tiles fit the frame; else they are computed apart)
     StatRef st{nullptr, 0};
     {
-      bool wrote = false;
-      lc_status s = conv_in_run(c, (const char*)x + (size_t)n0 * g.C_lat * T * es, cur, nf, partH(c), &wrote);
+      lc_status s = conv_in_run(c, (const char*)x + (size_t)n0 * g.C_lat * T * es, cur, nf, partH(c), &st);
       if (s != LC_OK) return s;
-      if (wrote) st = StatRef{partH(c), T / 32};
     }
     for (int i = 0; i < g.n_res; ++i) {
       char* nxt = cur == hc ? hb : hc;
@@ -712,7 +723,7 @@ lc_status run_step_lanes(lc_ctx* c, const void* x, void* eps, int slot, bool ful
   }
 
   // ---- temporal block: per-frame statistics over whole frames, then per position chunk
-  bool ustat = T % 32 == 0 && p.tc % 32 == 0;  // the 32-row tiles of a position chunk stay inside a frame and a split
+  bool ustat = T % 32 == 0 && p.ts % 32 == 0;  // the 32-row tiles of a position chunk stay inside a frame and a split
   {
     lc_status s = temporal_block(c, h, tstat ? StatRef{partT(c), T / 32} : StatRef{nullptr, 0}, &ustat);
     if (s != LC_OK) return s;
@@ -725,9 +736,9 @@ lc_status run_step_lanes(lc_ctx* c, const void* x, void* eps, int slot, bool ful
     LC_HIP(c, hipStreamWaitEvent(c->cs, c->ev_in_done[slot], 0));
     c->in_pending[slot] = 0;
     if (frame_lanes > 1) { lc_status s = fork_lanes(c); if (s != LC_OK) return s; }
-    for (int n0 = 0, ci = 0; n0 < N; n0 += p.fc, ++ci) {
+    for (int n0 = 0, ci = 0; n0 < N; n0 += p.fs, ++ci) {
       use_lane(c, ci % frame_lanes);
-      const int nf = std::min(p.fc, N - n0);
+      const int nf = std::min(p.fs, N - n0);
       char* hc = h + (size_t)n0 * T * C * 4;
       char* d0 = ws_ptr(c);  // fp32
       char* dc = deep + (size_t)n0 * (T / 4) * Cd * es;
@@ -765,9 +776,9 @@ lc_status run_step_lanes(lc_ctx* c, const void* x, void* eps, int slot, bool ful
                                  w.up_gn.gamma, w.up_gn.beta, g.groups, g.gn_eps, sc_cat, sh_cat, N));
   }
   if (frame_lanes > 1) { lc_status s = fork_lanes(c); if (s != LC_OK) return s; }
-  for (int n0 = 0, ci = 0; n0 < N; n0 += p.fc, ++ci) {
+  for (int n0 = 0, ci = 0; n0 < N; n0 += p.fs, ++ci) {
     use_lane(c, ci % frame_lanes);
-    const int nf = std::min(p.fc, N - n0);
+    const int nf = std::min(p.fs, N - n0);
     char* hc = h + (size_t)n0 * T * C * 4;
     char* dc = deep + (size_t)n0 * (T / 4) * Cd * es;
     char* u = ws_ptr(c);  // fp32

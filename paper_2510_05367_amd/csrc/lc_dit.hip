@@ -125,7 +125,6 @@ inline size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 struct BlkW { void *wqkv, *wo, *w1, *w2; float *bqkv, *bo, *b1, *b2; };
 struct TPlan {
   int tc;  // rows per chunk of the per-row layers (LayerNorm, projections, MLP): tokens of the B*T of a step
-  int qc;  // queries per batch element and attention launch
   size_t off_x, off_slots, slot_bytes, off_qkv, off_vt, off_ao, off_xn, off_hid, off_t, total;
 };
 
@@ -192,9 +191,8 @@ TPlan make_tplan(const lc_dit_config& g, int token_chunk) {
   const size_t es = dtype_size(g.dtype);
   const int64_t R = (int64_t)g.B * g.T;
   // the per-row layers walk the B*T rows of a step in chunks that may run across batch elements (all rows at once
-  // without a chunk); attention takes the same number of queries of every batch element, at most all T
+  // without a chunk)
   p.tc = (token_chunk <= 0 || token_chunk > R) ? (int)R : token_chunk;
-  p.qc = std::min(p.tc, g.T);
   size_t off = 0;
   auto take = [&](size_t bytes) { size_t o = off; off += align_up(bytes); return o; };
   p.off_x = take((size_t)R * g.D * 4);
@@ -274,8 +272,8 @@ lc_status run_block(lc_dit* c, int i, const float* mod, float* x, const float* d
     if ((s = linear(c, w.wqkv, w.bqkv, D, 3 * D, n, xn, qkv + r0 * 3 * D * es, 0, 0, D)) != LC_OK) return s;
   }
   LCT_HIP(c, launch_make_vt(c->cs, g.dtype, qkv + (size_t)2 * D * es, 3 * D, vt, g.B, T, Tp, D));
-  for (int q0 = 0; q0 < T; q0 += p.qc)  // a chunk of queries of every batch element against all keys
-    LCT_HIP(c, launch_spatial_attention(c->cs, g.dtype, qkv, 3 * D, vt, Tp, ao, g.B, T, g.heads, g.head_dim, q0, std::min(q0 + p.qc, T), 1));
+  // (all queries at once whatever the token chunk: the kernel keeps nothing per query in memory)
+  LCT_HIP(c, launch_spatial_attention(c->cs, g.dtype, qkv, 3 * D, vt, Tp, ao, g.B, T, g.heads, g.head_dim, 0, T, 1));
   for (int64_t r0 = 0; r0 < R; r0 += p.tc) {
     const int n = (int)std::min<int64_t>(p.tc, R - r0);
     if ((s = linear(c, w.wo, w.bo, D, D, n, ao + r0 * D * es, t, 1)) != LC_OK) return s;

@@ -27,6 +27,10 @@ hipError_t launch_gn_finalize(hipStream_t s, const float* partA, int CA, int spl
                               const float* partB, int CB, int splitsB, int rowsB, float wB,
                               const float* gamma, const float* beta, int groups, float eps,
                               float* scale, float* shift, int frames);
+// y[r][:] = bf16(x[m(r)][:] * scale[f][:] + shift[f][:]), f = r / rows_per_frame: GroupNorm applied to fp32 rows [..][C]
+// (C % 8 == 0), gathered through m; y dense bf16 rows.
+hipError_t launch_gn_apply(hipStream_t s, const float* x, const float* scale, const float* shift, void* y, int64_t rows, int C,
+                           int rows_per_frame, RowMap m);
 // A spatial window of a frame, in pixels: the spatial block of a feature chunk. w == 0: the whole frame.
 struct Win { int x0, y0, w, h; };
 
@@ -54,9 +58,9 @@ struct ConvDesc {
 };
 hipError_t launch_conv(hipStream_t s, const ConvDesc& d);
 // eps = conv3x3_{C -> C_lat}(SiLU(u * scale + shift)) + bias: u fp32 rows [frames][H*W][C], scale / shift
-// [frames][C], w [32][9][C] (rows beyond C_lat zero), eps planar [frames][C_lat][H][W]. bf16 stages with
-// C = 320, W % 16 == 0, H % 4 == 0 only: otherwise hipErrorNotSupported (use the general kernel).
-// win: the pixels to compute (win.w == 0: the whole frame); x0, w multiples of 16 and y0, h of 4.
+// [frames][C], w [32][9][C] (rows beyond C_lat zero), eps planar [frames][C_lat][H][W]. bf16 stages with C = 64, 128, 192
+// or 320 and C_lat <= 16 only: otherwise hipErrorNotSupported (use the general kernel).
+// win: the pixels to compute (win.w == 0: the whole frame); it starts on a 16 x 4 tile and ends on one or at the frame's edge.
 hipError_t launch_conv_out_tile(hipStream_t s, int dt, const void* u, const float* scale, const float* shift, const void* w,
                                 const float* bias, void* out, int frames, int H, int W, int C, int C_lat, Win win);
 
@@ -124,6 +128,8 @@ struct FusedDesc {
   int q_cols;
 };
 inline float attn_q_scale(int head_dim) { return 1.4426950408889634f / sqrtf((float)head_dim); }
+// splits per frame of the statistics the first convolution's tile kernel writes (32-pixel segments of the image rows)
+inline int conv_in_splits(int H, int W) { return H * ((W + 31) / 32); }
 // splits per frame of the statistics a 3x3 launch writes
 inline int conv_stat_splits(int H, int W) { return 4 * ((W + 15) / 16) * ((H + 7) / 8); }
 // The tiles (16 x 8 pixels) of a 3x3 launch's window: false if the window does not start on a tile boundary, or
@@ -145,6 +151,7 @@ hipError_t launch_conv_ws(hipStream_t s, const FusedDesc& d);
 // taps == 1, src == 0 of a bf16 stage (lc_lin2.hip: 256 x 160 tiles, operands streamed through a ring of LDS stages);
 // hipErrorNotSupported for widths it does not cover, never because of the rows. launch_fused tries it first.
 hipError_t launch_lin2(hipStream_t s, const FusedDesc& d);
+inline bool lin2_covers(int Cin, int Cout) { return Cin > 0 && Cin % 64 == 0 && (Cout % 160 == 0 || Cout % 128 == 0); }
 // taps == 1 with the weights resident in registers (needs w_frag); hipErrorNotSupported for shapes it does not cover
 hipError_t launch_linear(hipStream_t s, const FusedDesc& d);
 inline hipError_t launch_linear_any(hipStream_t s, const FusedDesc& d) {
@@ -179,9 +186,9 @@ hipError_t launch_temporal_attention(hipStream_t s, int dt, const void* qkv, voi
 
 // ---- small kernels -------------------------------------------------------------------------
 // h[frames*H*W][C] (fp32) = conv3x3(x[frames][Cl][H][W] of type dt); w_packed float [Cl*9][C], bias float [C].
-// conv_in for bf16 stages whose image rows are whole 32-pixel segments, with the GroupNorm partial sums of its
-// output (lc_conv.hip); hipErrorNotSupported otherwise
-// win: the pixels to compute (win.w == 0: the whole frame); x0 and w multiples of 32.
+// conv_in for bf16 stages, a 32-pixel segment of an image row per workgroup, with the GroupNorm partial sums of its
+// output, [frame][conv_in_splits(H, W)][C][2] (lc_conv.hip); hipErrorNotSupported for widths it does not cover
+// win: the pixels to compute (win.w == 0: the whole frame); x0 a multiple of 32, w too or up to the frame's edge.
 hipError_t launch_conv_in_tile(hipStream_t s, int dt, const void* x, const void* wp, const float* bias, float* y, float* stat,
                                int frames, int H, int W, int Cl, int C, Win win);
 hipError_t launch_conv_in(hipStream_t s, int dt, const void* x, void* h, int frames, int H, int W, int Cl, int C,

@@ -306,7 +306,7 @@ static hipError_t run_lin2(hipStream_t s, Lin2Args a) {
 
 hipError_t launch_lin2(hipStream_t s, const FusedDesc& d) {
   if (d.dt != kBF16 || d.taps != 1 || d.src != 0 || d.stat || d.win_w || d.planar_out) return hipErrorNotSupported;
-  if (d.Cin % 64 || d.Cin <= 0 || (d.Cout % 160 && d.Cout % 128) || d.Cout_store != d.Cout) return hipErrorNotSupported;
+  if (!lin2_covers(d.Cin, d.Cout) || d.Cout_store != d.Cout) return hipErrorNotSupported;
   if (d.in_map.rows_per_seg <= 0 || d.out_map.rows_per_seg <= 0) return hipErrorInvalidValue;
   if (d.res && !d.y_f32) return hipErrorNotSupported;
   if (d.q_cols && d.res) return hipErrorInvalidValue;

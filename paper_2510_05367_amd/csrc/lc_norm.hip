@@ -160,4 +160,39 @@ hipError_t launch_gn_finalize(hipStream_t s, const float* partA, int CA, int spl
   return hipGetLastError();
 }
 
+// y[r][:] = bf16(x[m(r)][:] * scale[f][:] + shift[f][:]), f = r / rows_per_frame: GroupNorm applied to fp32 rows and
+// rounded once, the operand of the projection into a transformer block. Thread = 8 channels of one row.
+// MAPPED: the dense rows are gathered through the row map (a chunk of positions out of every frame).
+template <bool MAPPED>
+__global__ __launch_bounds__(256) void gn_apply_kernel(const float* __restrict__ x, const float* __restrict__ scale,
+                                                       const float* __restrict__ shift, bf16_t* __restrict__ y, int64_t rows,
+                                                       int C8, int rows_per_frame, RowMap m) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i >= rows * C8) return;
+  const int64_t r = i / C8;
+  const int c = (int)(i - r * C8) * 8;
+  const int64_t f = r / rows_per_frame;
+  const int64_t sr = MAPPED ? m(r) : r;
+  float v[8], sc[8], sh[8];
+  load_f<float, 8>(x + sr * C8 * 8 + c, v);
+  load_f<float, 8>(scale + f * C8 * 8 + c, sc);
+  load_f<float, 8>(shift + f * C8 * 8 + c, sh);
+  Vec16<bf16_t> o;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) o.set(e, fmaf(v[e], sc[e], sh[e]));
+  store16(y + r * C8 * 8 + c, o);
+}
+
+hipError_t launch_gn_apply(hipStream_t s, const float* x, const float* scale, const float* shift, void* y, int64_t rows, int C,
+                           int rows_per_frame, RowMap m) {
+  if (rows <= 0) return hipSuccess;
+  if (C % 8 || rows_per_frame <= 0 || m.rows_per_seg <= 0) return hipErrorInvalidValue;
+  const unsigned blocks = (unsigned)((rows * (C / 8) + 255) / 256);
+  if (m.rows_per_seg >= rows || m.seg_stride == m.rows_per_seg)  // consecutive rows from m.base on
+    gn_apply_kernel<false><<<blocks, 256, 0, s>>>(x + m.base * C, scale, shift, (bf16_t*)y, rows, C / 8, rows_per_frame, m);
+  else
+    gn_apply_kernel<true><<<blocks, 256, 0, s>>>(x, scale, shift, (bf16_t*)y, rows, C / 8, rows_per_frame, m);
+  return hipGetLastError();
+}
+
 }  // namespace lc

@@ -120,29 +120,6 @@ __global__ __launch_bounds__(256) void temb_bias_kernel(const T* __restrict__ te
   if (lane == 0) out[item] = acc + bt[o] + bias[o];
 }
 
-// y[r][:] = bf16(x[m(r)][:] * scale[f][:] + shift[f][:]), f = r / rows_per_frame: GroupNorm applied to fp32 rows and
-// rounded once, the operand of the projection into a transformer block. Thread = 8 channels of one row.
-// MAPPED: the dense rows are gathered through the row map (a chunk of positions out of every frame).
-template <bool MAPPED>
-__global__ __launch_bounds__(256) void gn_apply_kernel(const float* __restrict__ x, const float* __restrict__ scale,
-                                                       const float* __restrict__ shift, bf16_t* __restrict__ y, int64_t rows,
-                                                       int C8, int rows_per_frame, RowMap m) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= rows * C8) return;
-  const int64_t r = i / C8;
-  const int c = (int)(i - r * C8) * 8;
-  const int64_t f = r / rows_per_frame;
-  const int64_t sr = MAPPED ? m(r) : r;
-  float v[8], sc[8], sh[8];
-  load_f<float, 8>(x + sr * C8 * 8 + c, v);
-  load_f<float, 8>(scale + f * C8 * 8 + c, sc);
-  load_f<float, 8>(shift + f * C8 * 8 + c, sh);
-  Vec16<bf16_t> o;
-#pragma unroll
-  for (int e = 0; e < 8; ++e) o.set(e, fmaf(v[e], sc[e], sh[e]));
-  store16(y + r * C8 * 8 + c, o);
-}
-
 // dst[r][0:Ca] = a[r][:], dst[r][Ca:Ca+Cb] = b[r][:] (fp32, Ca and Cb multiples of 4), fused with what the residual
 // block needs of the concatenated rows next: their GroupNorm partial sums (partial[frame][split][Ca + Cb][2], 64-row splits as the statistics kernel writes them, folded in
 // the same fixed order) and, when yb != nullptr, a copy rounded to bf16 (the operand of the 1x1 shortcut). One
@@ -333,7 +310,7 @@ UPlan make_uplan(const lc_unet_config& g, int frame_chunk) {
   // that the convolutions write beside their output, times the widest tensor of the level
   auto splits_of = [&](int lvl) {
     const int H = g.H >> lvl, W = g.W >> lvl;
-    return (int64_t)std::max({stat_splits(H * W), conv_stat_splits(H, W), (H * W + 31) / 32});
+    return (int64_t)std::max({stat_splits(H * W), conv_stat_splits(H, W), (H * W + 31) / 32, lvl ? 0 : conv_in_splits(H, W)});
   };
   const int64_t splits_c = std::max({splits_of(0) * (g.C + g.C1), splits_of(1) * std::max(g.C1 + g.C2, g.C), splits_of(2) * std::max(g.C1, g.C2)});
   // the same for what one block hands to the next: a block's output of all frames
@@ -468,13 +445,7 @@ lc_status linear(lc_unet* c, const LinP& w, int Cin, int Cout, int64_t rows, con
 // y (bf16, dense rows) = x[m(r)] * scale[r / rows_per_frame] + shift[...]
 lc_status gn_apply(lc_unet* c, const float* x, const float* scale, const float* shift, void* y, int64_t rows, int C, int rows_per_frame,
                    RowMap m) {
-  const int64_t n = rows * (C / 8);
-  const unsigned blocks = (unsigned)((n + 255) / 256);
-  if (m.rows_per_seg >= rows || m.seg_stride == m.rows_per_seg)  // consecutive rows from m.base on
-    gn_apply_kernel<false><<<blocks, 256, 0, c->cs>>>(x + m.base * C, scale, shift, (bf16_t*)y, rows, C / 8, rows_per_frame, m);
-  else
-    gn_apply_kernel<true><<<blocks, 256, 0, c->cs>>>(x, scale, shift, (bf16_t*)y, rows, C / 8, rows_per_frame, m);
-  LCU_HIP(c, hipGetLastError());
+  LCU_HIP(c, launch_gn_apply(c->cs, x, scale, shift, y, rows, C, rows_per_frame, m));
   return LC_OK;
 }
 
@@ -742,10 +713,10 @@ lc_status run_step(lc_unet* c, const void* x, const void* temb, const void* cond
     const char* xc = (const char*)x + (size_t)n0 * g.C_lat * P * es;
     float* y = m0 + (size_t)n0 * P * g.C;
     // the tiled kernel where the shape allows it (a property of the configuration, never of the chunk)
-    hipError_t e = c->cin_wp ? launch_conv_in_tile(c->cs, g.dtype, xc, c->cin_wp, c->cin_b, y, pa + (size_t)n0 * (P / 32) * g.C * 2, nc, H, W,
+    hipError_t e = c->cin_wp ? launch_conv_in_tile(c->cs, g.dtype, xc, c->cin_wp, c->cin_b, y, pa + (size_t)n0 * conv_in_splits(H, W) * g.C * 2, nc, H, W,
                                                    g.C_lat, g.C, Win{0, 0, 0, 0})
                              : hipErrorNotSupported;
-    if (e == hipSuccess) { cin_st = Stats{pa, P / 32}; return LC_OK; }
+    if (e == hipSuccess) { cin_st = Stats{pa, conv_in_splits(H, W)}; return LC_OK; }
     if (e != hipErrorNotSupported) LCU_HIP(c, e);
     LCU_HIP(c, launch_conv_in(c->cs, g.dtype, xc, y, nc, H, W, g.C_lat, g.C, c->cin_w, c->cin_b));
     return LC_OK;

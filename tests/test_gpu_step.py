@@ -342,3 +342,32 @@ def test_profiling_brackets_count_launches():
         lcb.lc_set_profiling(stage.ctx, 0)
     finally:
         stage.close()
+
+
+@pytest.mark.parametrize("F,H,W,C,heads,head_dim", [(5, 10, 14, 320, 8, 40), (9, 6, 34, 320, 5, 64), (5, 10, 18, 64, 1, 64), (3, 16, 18, 64, 2, 32)])
+def test_ragged_frames_in_bf16(F, H, W, C, heads, head_dim):
+    """Frames that are no whole 32-row tiles, image rows that are no whole 32-pixel or 16-pixel segments: GroupNorm
+    applied in a pass of its own and the streamed linear kernel with V^T in its epilogue (C = 320), short segments of
+    the first convolution, partial tiles of the last one. Against the oracle, and bit for bit for chunks that divide
+    the frames evenly, with a remainder, and not at all."""
+    cfg = synth.StageConfig(f"ragged_{C}_{H}x{W}", B=1, F=F, H=H, W=W, C_lat=4, C=C, C_deep=2 * C, groups=32, n_res=1, heads=heads,
+                            head_dim=head_dim, dtype="bf16")
+    stage, w = make_stage(cfg, seed=3)
+    try:
+        x, deep = synth.make_latents(cfg, 4), synth.make_deep(cfg, 5)
+        orc = lo.Oracle(cfg, {k: v.astype(np.float64) for k, v in w.items()})
+        orc.cache_write(0, deep)
+        ref = orc.cached_step(x, 0)
+        xd, dd = dev(stage, x), dev(stage, deep)
+        outs = []
+        for chunk in (0, 2, 4, 1):
+            stage.set_chunk(chunk, 0)
+            stage.cache_write(0, dd)
+            eps = stage.empty(*x.shape)
+            stage.cached_step(xd, eps, 0)
+            stage.sync()
+            outs.append(eps)
+        check(cfg.name, host(outs[0]), ref, "bf16")
+        assert all(torch.equal(outs[0], o) for o in outs[1:])
+    finally:
+        stage.close()
