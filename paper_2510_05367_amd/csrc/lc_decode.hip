@@ -28,18 +28,24 @@ struct ConvP { void* w; float* b; };
 
 struct DPlan {
   size_t off_a, off_b, off_part, off_scale, off_shift, off_one, off_zero, off_qkv, off_vt, off_ao, total;
+  size_t lane_off, lane_stride;  // [lane_off, lane_off + lane_stride): what one lane works in
+  int lanes;
 };
 
 }  // namespace
 
 struct lc_decoder {
   lc_decoder_config cfg;
-  hipStream_t s;
+  hipStream_t s;          // the stream kernels are issued on right now
+  hipStream_t s_main, s_aux;  // the caller's stream; the library's own second one
+  hipEvent_t ev_fork, ev_join;
+  char* lane;             // where the lane's scratch offsets count from
   void* wblob;
   size_t wblob_bytes;
   bool have_weights;
   // packed weights
   float *cin_w, *cin_b;
+  void* cin_wp;  // conv_in weights as rows [C][64] of the operand type (k = plane * 9 + tap, zero padded), or nullptr
   GnP res_gn[2 + LC_DEC_MAX_LEVELS]; ConvP res[2 + LC_DEC_MAX_LEVELS];  // mid.res0, mid.res1, up0.res, ...
   GnP at_gn; void *at_wqkv, *at_wo; float* at_bo;
   ConvP upc[LC_DEC_MAX_LEVELS];
@@ -90,37 +96,47 @@ lc_status check_dcfg(lc_decoder* d, const lc_decoder_config* g) {
   return LC_OK;
 }
 
-// Workspace of a pass over `n` frames: two ping-pong fp32 maps that hold the largest map of any stage (the
-// upsampled input of the last level's convolution), GroupNorm partial sums and scale / shift, a unit scale and a
-// zero shift (the convolution after the upsampling takes its input as it is), and the attention block's q,k,v,
-// V^T and output at the latent resolution.
+// Workspace of a pass over `n` frames. The maps alternate between two fp32 buffers: `a` takes the output of the first
+// convolution and of every level's upsampling convolution, `b` the residual blocks', so `b` need not hold the last and
+// largest map (the upsampled input of a convolution exists nowhere). Then GroupNorm partial sums and scale / shift, a
+// unit scale and a zero shift (the convolution after the upsampling takes its input as it is), and the attention
+// block's q,k rows, V^T and normalised rows / output at the latent resolution. The footprint is that of two maps of the
+// largest stage with its input upsampled (what a pass with a separate upsampling would hold); where the scratch of two
+// passes fits into it, as for widths that fall from level to level, alternate slices run on two streams.
 DPlan make_dplan(const lc_decoder_config& g, int n) {
   DPlan p;
   const size_t es = dtype_size(g.dtype);
   const int64_t P0 = (int64_t)g.H * g.W;
-  int64_t max_elems = P0 * g.widths[0], max_splits_c = (int64_t)stat_splits((int)P0) * g.widths[0];
+  int64_t elems_a = P0 * g.widths[0], elems_b = elems_a, elems_up = elems_a, splits_c = 0;
   int maxC = g.widths[0];
-  int64_t P = P0;
-  for (int l = 0; l < g.levels; ++l) {
-    P *= 4;
-    max_elems = std::max(max_elems, P * std::max(g.widths[l], g.widths[l + 1]));
-    max_splits_c = std::max(max_splits_c, (int64_t)stat_splits((int)P) * g.widths[l + 1]);
-    maxC = std::max(maxC, g.widths[l + 1]);
+  for (int l = 0; l <= g.levels; ++l) {
+    const int H = g.H << l, W = g.W << l;
+    const int64_t e = P0 * ((int64_t)1 << 2 * l) * g.widths[l];
+    elems_a = std::max(elems_a, e);
+    if (l < g.levels) elems_b = std::max(elems_b, e);
+    elems_up = std::max({elems_up, e, l ? P0 * ((int64_t)1 << 2 * l) * g.widths[l - 1] : (int64_t)0});
+    const int splits = std::max({stat_splits(H * W), conv_stat_splits(H, W), l ? 0 : conv_in_splits(H, W)});
+    splits_c = std::max(splits_c, (int64_t)splits * g.widths[l]);
+    maxC = std::max(maxC, g.widths[l]);
   }
   size_t off = 0;
   auto take = [&](size_t bytes) { size_t o = off; off += align_up(bytes); return o; };
-  p.off_a = take((size_t)n * max_elems * 4);
-  p.off_b = take((size_t)n * max_elems * 4);
-  p.off_part = take((size_t)n * max_splits_c * 2 * 4);
-  p.off_scale = take((size_t)n * maxC * 4);
-  p.off_shift = take((size_t)n * maxC * 4);
   p.off_one = take((size_t)n * maxC * 4);
   p.off_zero = take((size_t)n * maxC * 4);
+  p.lane_off = off;
+  p.off_a = take((size_t)n * elems_a * 4);
+  p.off_b = take((size_t)n * elems_b * 4);
+  p.off_part = take((size_t)n * splits_c * 2 * 4);
+  p.off_scale = take((size_t)n * maxC * 4);
+  p.off_shift = take((size_t)n * maxC * 4);
   const int C0 = g.widths[0];
-  p.off_qkv = take((size_t)n * P0 * 3 * C0 * es);
+  p.off_qkv = take((size_t)n * P0 * 2 * C0 * es);
   p.off_vt = take((size_t)n * C0 * attn_tp((int)P0) * es);
   p.off_ao = take((size_t)n * P0 * C0 * es);
-  p.total = off;
+  p.lane_stride = off - p.lane_off;
+  const size_t maps = (size_t)n * (2 * elems_up - elems_a - elems_b) * 4;  // beyond what one pass holds
+  p.lanes = maps >= p.lane_stride ? 2 : 1;
+  p.total = off + maps;
   return p;
 }
 
@@ -128,58 +144,75 @@ inline int eff_slice(const lc_decoder_config& g, int slice_frames) {
   return (slice_frames <= 0 || slice_frames > g.N) ? g.N : slice_frames;
 }
 
-// scale / shift of GroupNorm(x) for n frames of fp32 rows [rows][C]
-lc_status gn(lc_decoder* d, const DPlan& p, const float* x, int n, int rows, int C, const GnP& w) {
+// Partial sums [frame][splits][C][2] of a tensor, written by the kernel that produced it (part == nullptr: none)
+struct Stats { const float* part; int splits; };
+
+// scale / shift of GroupNorm(x) for n frames of fp32 rows [rows][C]; st: the partial sums of x if its producer wrote them
+lc_status gn(lc_decoder* d, const DPlan& p, const float* x, Stats st, int n, int rows, int C, const GnP& w) {
   const lc_decoder_config& g = d->cfg;
-  float* part = (float*)(d->arena + p.off_part);
-  LCD_HIP(d, launch_gn_stats(d->s, kF32, x, part, n, rows, C));
-  LCD_HIP(d, launch_gn_finalize(d->s, part, C, stat_splits(rows), rows, 1.f, nullptr, 0, 0, 0, 0.f, w.g, w.b, g.groups, g.gn_eps,
-                                (float*)(d->arena + p.off_scale), (float*)(d->arena + p.off_shift), n));
+  if (!st.part) {
+    float* part = (float*)(d->lane + p.off_part);
+    LCD_HIP(d, launch_gn_stats(d->s, kF32, x, part, n, rows, C));
+    st = Stats{part, stat_splits(rows)};
+  }
+  LCD_HIP(d, launch_gn_finalize(d->s, st.part, C, st.splits, rows, 1.f, nullptr, 0, 0, 0, 0.f, w.g, w.b, g.groups, g.gn_eps,
+                                (float*)(d->lane + p.off_scale), (float*)(d->lane + p.off_shift), n));
   return LC_OK;
 }
 
-// y = [res +] conv3x3(act(x)): src 2 = SiLU(GroupNorm(x)) with the scale / shift at hand, src 1 = x as it is
+// y = [res +] conv3x3(act(x)) at H x W, y fp32 rows with its partial sums. src 2: act = SiLU(GroupNorm(x)) with the scale /
+// shift at hand; src 1: x, at half the resolution, nearest 2x upsampled on the way in.
 lc_status conv(lc_decoder* d, const DPlan& p, const ConvP& w, int src, int Cin, int Cout, int n, int H, int W, const float* x,
-               const float* res, void* y, int planar, int Cout_store) {
+               const float* res, float* y, Stats* st) {
   FusedDesc f;
   memset(&f, 0, sizeof f);
-  f.dt = d->cfg.dtype; f.y_f32 = planar ? 0 : 1; f.taps = 9; f.src = src; f.Cin = Cin; f.Cout = Cout; f.Cout_store = Cout_store;
-  f.w = w.w; f.bias = w.b; f.frames = n; f.H = H; f.W = W; f.x = x; f.res = res; f.y = y; f.planar_out = planar;
-  f.scale = (const float*)(d->arena + (src == 2 ? p.off_scale : p.off_one));
-  f.shift = (const float*)(d->arena + (src == 2 ? p.off_shift : p.off_zero));
+  f.dt = d->cfg.dtype; f.y_f32 = 1; f.taps = 9; f.src = src; f.Cin = Cin; f.Cout = Cout; f.Cout_store = Cout;
+  f.w = w.w; f.bias = w.b; f.frames = n; f.H = H; f.W = W; f.x = x; f.res = res; f.y = y; f.up2 = src == 1;
+  f.scale = (const float*)(src == 2 ? d->lane + p.off_scale : d->arena + p.off_one);
+  f.shift = (const float*)(src == 2 ? d->lane + p.off_shift : d->arena + p.off_zero);
   f.in_map = f.out_map = RowMap{0, 0, 1 << 30};
+  f.stat = (float*)(d->lane + p.off_part); f.stat_splits = conv_stat_splits(H, W);  // (those of x are folded by now)
   LCD_HIP(d, launch_fused(d->s, f));
+  *st = Stats{f.stat, f.stat_splits};
   return LC_OK;
 }
 
-lc_status res_block(lc_decoder* d, const DPlan& p, int idx, int C, int n, int H, int W, const float* x, float* y) {
-  lc_status s = gn(d, p, x, n, H * W, C, d->res_gn[idx]);
+lc_status res_block(lc_decoder* d, const DPlan& p, int idx, int C, int n, int H, int W, const float* x, float* y, Stats* st) {
+  lc_status s = gn(d, p, x, *st, n, H * W, C, d->res_gn[idx]);
   if (s != LC_OK) return s;
-  return conv(d, p, d->res[idx], 2, C, C, n, H, W, x, x, y, 0, C);
+  return conv(d, p, d->res[idx], 2, C, C, n, H, W, x, x, y, st);
 }
 
 // h += proj(Attn(qkv(GroupNorm(h)))) over the H*W positions of each frame, in place on fp32 rows
-lc_status attn_block(lc_decoder* d, const DPlan& p, int n, float* h) {
+lc_status attn_block(lc_decoder* d, const DPlan& p, int n, float* h, Stats* st) {
   const lc_decoder_config& g = d->cfg;
   const int T = g.H * g.W, C = g.widths[0], Tp = attn_tp(T);
-  const size_t es = dtype_size(g.dtype);
-  lc_status s = gn(d, p, h, n, T, C, d->at_gn);
+  const int64_t rows = (int64_t)n * T;
+  lc_status s = gn(d, p, h, *st, n, T, C, d->at_gn);
   if (s != LC_OK) return s;
-  char* qkv = d->arena + p.off_qkv;
-  char* vt = d->arena + p.off_vt;
-  char* ao = d->arena + p.off_ao;
+  *st = Stats{nullptr, 0};
+  const float* scale = (const float*)(d->lane + p.off_scale);
+  const float* shift = (const float*)(d->lane + p.off_shift);
+  char* qk = d->lane + p.off_qkv;
+  char* vt = d->lane + p.off_vt;
+  char* ao = d->lane + p.off_ao;
+  // q (with the softmax scale) and k as rows, V transposed from the projection's epilogue. The streamed linear kernel
+  // takes normalised bf16 rows (in the buffer of the attention output, free until then); other widths and types are
+  // normalised in the loader.
+  const bool dense = g.dtype == kBF16 && lin2_covers(C, 3 * C) && lin2_covers(C, C) && T % 4 == 0;
+  if (dense) LCD_HIP(d, launch_gn_apply(d->s, h, scale, shift, ao, rows, C, T, RowMap{0, T, T}));
   FusedDesc f;
   memset(&f, 0, sizeof f);
-  f.dt = g.dtype; f.y_f32 = 0; f.taps = 1; f.src = 1; f.Cin = C; f.Cout = 3 * C; f.Cout_store = 3 * C; f.w = d->at_wqkv;
-  f.rows = (int64_t)n * T; f.in_map = RowMap{0, T, T}; f.out_map = RowMap{0, 0, 1 << 30}; f.x = h; f.y = qkv;
-  f.scale = (const float*)(d->arena + p.off_scale); f.shift = (const float*)(d->arena + p.off_shift);
+  f.dt = g.dtype; f.y_f32 = 0; f.taps = 1; f.src = dense ? 0 : 1; f.Cin = C; f.Cout = 3 * C; f.Cout_store = 3 * C; f.w = d->at_wqkv;
+  f.rows = rows; f.in_map = RowMap{0, T, T}; f.out_map = RowMap{0, 0, 1 << 30}; f.x = dense ? (void*)ao : (void*)h; f.y = qk;
+  f.scale = scale; f.shift = shift;
   f.q_cols = C; f.q_scale = attn_q_scale(g.head_dim);
+  f.yt = vt; f.yt_from = 2 * C; f.yt_T = T; f.yt_Tp = Tp;
   LCD_HIP(d, launch_fused(d->s, f));
-  LCD_HIP(d, launch_make_vt(d->s, g.dtype, qkv + (size_t)2 * C * es, 3 * C, vt, n, T, Tp, C));
-  LCD_HIP(d, launch_spatial_attention(d->s, g.dtype, qkv, 3 * C, vt, Tp, ao, n, T, g.heads, g.head_dim, 0, T, 1));
+  LCD_HIP(d, launch_spatial_attention(d->s, g.dtype, qk, 2 * C, vt, Tp, ao, n, T, g.heads, g.head_dim, 0, T, 1));
   memset(&f, 0, sizeof f);
   f.dt = g.dtype; f.y_f32 = 1; f.taps = 1; f.src = 0; f.Cin = C; f.Cout = C; f.Cout_store = C; f.w = d->at_wo; f.bias = d->at_bo;
-  f.rows = (int64_t)n * T; f.in_map = f.out_map = RowMap{0, 0, 1 << 30}; f.x = ao; f.res = h; f.y = h;
+  f.rows = rows; f.in_map = f.out_map = RowMap{0, 0, 1 << 30}; f.x = ao; f.res = h; f.y = h;
   LCD_HIP(d, launch_fused(d->s, f));
   return LC_OK;
 }
@@ -187,26 +220,43 @@ lc_status attn_block(lc_decoder* d, const DPlan& p, int n, float* h) {
 // one pass: n frames of latents z -> n decoded images
 lc_status decode_pass(lc_decoder* d, const DPlan& p, const void* z, void* img, int n) {
   const lc_decoder_config& g = d->cfg;
-  float* a = (float*)(d->arena + p.off_a);
-  float* b = (float*)(d->arena + p.off_b);
+  float* a = (float*)(d->lane + p.off_a);
+  float* b = (float*)(d->lane + p.off_b);
   int H = g.H, W = g.W;
   const int C0 = g.widths[0];
-  LCD_HIP(d, launch_conv_in(d->s, g.dtype, z, a, n, H, W, g.C_lat, C0, d->cin_w, d->cin_b));
-  lc_status s = res_block(d, p, 0, C0, n, H, W, a, b);
+  Stats st{nullptr, 0};
+  {
+    float* part = (float*)(d->lane + p.off_part);
+    const hipError_t e = d->cin_wp ? launch_conv_in_tile(d->s, g.dtype, z, d->cin_wp, d->cin_b, a, part, n, H, W, g.C_lat, C0, Win{0, 0, 0, 0})
+                                   : hipErrorNotSupported;
+    if (e == hipSuccess) st = Stats{part, conv_in_splits(H, W)};
+    else if (e != hipErrorNotSupported) LCD_HIP(d, e);
+    else LCD_HIP(d, launch_conv_in(d->s, g.dtype, z, a, n, H, W, g.C_lat, C0, d->cin_w, d->cin_b));
+  }
+  lc_status s = res_block(d, p, 0, C0, n, H, W, a, b, &st);
   if (s != LC_OK) return s;
-  if ((s = attn_block(d, p, n, b)) != LC_OK) return s;
-  if ((s = res_block(d, p, 1, C0, n, H, W, b, a)) != LC_OK) return s;
-  for (int l = 0; l < g.levels; ++l) {  // the map at hand is in `a`
+  if ((s = attn_block(d, p, n, b, &st)) != LC_OK) return s;
+  if ((s = res_block(d, p, 1, C0, n, H, W, b, a, &st)) != LC_OK) return s;
+  for (int l = 0; l < g.levels; ++l) {
     const int Cl = g.widths[l], Cn = g.widths[l + 1];
-    if ((s = res_block(d, p, 2 + l, Cl, n, H, W, a, b)) != LC_OK) return s;
-    LCD_HIP(d, launch_up2_rows(d->s, b, a, n, H, W, Cl));
+    if ((s = res_block(d, p, 2 + l, Cl, n, H, W, a, b, &st)) != LC_OK) return s;
     H *= 2; W *= 2;
-    if ((s = conv(d, p, d->upc[l], 1, Cl, Cn, n, H, W, a, nullptr, b, 0, Cn)) != LC_OK) return s;
-    std::swap(a, b);
+    if ((s = conv(d, p, d->upc[l], 1, Cl, Cn, n, H, W, b, nullptr, a, &st)) != LC_OK) return s;
   }
   const int CL = g.widths[g.levels];
-  if ((s = gn(d, p, a, n, H * W, CL, d->out_gn)) != LC_OK) return s;
-  return conv(d, p, d->out, 2, CL, 32, n, H, W, a, nullptr, img, 1, g.C_img);
+  if ((s = gn(d, p, a, st, n, H * W, CL, d->out_gn)) != LC_OK) return s;
+  const float* scale = (const float*)(d->lane + p.off_scale);
+  const float* shift = (const float*)(d->lane + p.off_shift);
+  const hipError_t e = launch_conv_out_tile(d->s, g.dtype, a, scale, shift, d->out.w, d->out.b, img, n, H, W, CL, g.C_img, Win{0, 0, 0, 0});
+  if (e == hipSuccess) return LC_OK;
+  if (e != hipErrorNotSupported) LCD_HIP(d, e);
+  FusedDesc f;
+  memset(&f, 0, sizeof f);
+  f.dt = g.dtype; f.taps = 9; f.src = 2; f.Cin = CL; f.Cout = 32; f.Cout_store = g.C_img; f.w = d->out.w; f.bias = d->out.b;
+  f.frames = n; f.H = H; f.W = W; f.x = a; f.y = img; f.planar_out = 1; f.scale = scale; f.shift = shift;
+  f.in_map = f.out_map = RowMap{0, 0, 1 << 30};
+  LCD_HIP(d, launch_fused(d->s, f));
+  return LC_OK;
 }
 
 }  // namespace
@@ -231,7 +281,15 @@ lc_status lc_decoder_create(const lc_decoder_config* cfg, void* stream, lc_decod
   lc_decoder* d = new (std::nothrow) lc_decoder();
   if (!d) return dfail(nullptr, LC_ERR_NOMEM, "out of host memory");
   d->cfg = *cfg;
-  d->s = (hipStream_t)stream;
+  d->s = d->s_main = (hipStream_t)stream;
+  d->s_aux = nullptr; d->ev_fork = d->ev_join = nullptr; d->lane = nullptr;
+  if (hipStreamCreateWithFlags(&d->s_aux, hipStreamNonBlocking) != hipSuccess ||
+      hipEventCreateWithFlags(&d->ev_fork, hipEventDisableTiming) != hipSuccess ||
+      hipEventCreateWithFlags(&d->ev_join, hipEventDisableTiming) != hipSuccess) {
+    d->wblob = nullptr;
+    lc_decoder_destroy(d);
+    return dfail(nullptr, LC_ERR_HIP, "creating the second stream failed");
+  }
   d->wblob = nullptr; d->wblob_bytes = 0; d->have_weights = false;
   d->arena = nullptr; d->arena_bytes = 0;
   *out = d;
@@ -240,7 +298,10 @@ lc_status lc_decoder_create(const lc_decoder_config* cfg, void* stream, lc_decod
 
 lc_status lc_decoder_destroy(lc_decoder* d) {
   if (!d) return LC_OK;
-  (void)hipStreamSynchronize(d->s);
+  (void)hipStreamSynchronize(d->s_main);
+  if (d->s_aux) (void)hipStreamDestroy(d->s_aux);
+  if (d->ev_fork) (void)hipEventDestroy(d->ev_fork);
+  if (d->ev_join) (void)hipEventDestroy(d->ev_join);
   if (d->wblob) (void)hipFree(d->wblob);
   delete d;
   return LC_OK;
@@ -260,7 +321,7 @@ lc_status lc_decoder_load_weights(lc_decoder* d, const lc_decoder_weights* w) {
   if (!ok) return dfail(d, LC_ERR_ARG, "a weight pointer is NULL");
   size_t off = 0;
   auto take = [&](size_t bytes) { size_t o = off; off += align_up(bytes); return o; };
-  const size_t o_cin_w = take((size_t)g.C_lat * 9 * C0 * 4), o_cin_b = take((size_t)C0 * 4);
+  const size_t o_cin_w = take((size_t)g.C_lat * 9 * C0 * 4), o_cin_b = take((size_t)C0 * 4), o_cin_wp = take((size_t)C0 * 64 * es);
   size_t o_rg[2 + LC_DEC_MAX_LEVELS], o_rb[2 + LC_DEC_MAX_LEVELS], o_rw[2 + LC_DEC_MAX_LEVELS], o_rbias[2 + LC_DEC_MAX_LEVELS];
   for (int i = 0; i < 2 + L; ++i) {
     const int C = i < 2 ? C0 : g.widths[i - 2];
@@ -283,7 +344,11 @@ lc_status lc_decoder_load_weights(lc_decoder* d, const lc_decoder_weights* w) {
 #define CW(src, dst_off, co, ci, copad) LCD_HIP(d, launch_pack_conv_w(s, dt, src, b + dst_off, co, ci, 9, copad))
   LCD_HIP(d, launch_pack_conv_in_w(s, dt, w->conv_in_w, (float*)(b + o_cin_w), C0, g.C_lat));
   F32(w->conv_in_b, o_cin_b, C0, C0);
-  d->cin_w = (float*)(b + o_cin_w); d->cin_b = (float*)(b + o_cin_b);
+  d->cin_w = (float*)(b + o_cin_w); d->cin_b = (float*)(b + o_cin_b); d->cin_wp = nullptr;
+  if (dt == kBF16 && g.C_lat * 9 <= 64) {
+    LCD_HIP(d, launch_pad_rows(s, dt, w->conv_in_w, b + o_cin_wp, C0, g.C_lat * 9, 64));
+    d->cin_wp = b + o_cin_wp;
+  }
   for (int i = 0; i < 2 + L; ++i) {
     const int C = i < 2 ? C0 : g.widths[i - 2];
     const lc_gnconv_w& r = i < 2 ? w->mid_res[i] : w->up_res[i - 2];
@@ -343,11 +408,26 @@ lc_status lc_decode(lc_decoder* d, const void* z, void* img, int slice_frames) {
   LCD_HIP(d, launch_fill_f32(d->s, (float*)(d->arena + p.off_zero), (int64_t)n * maxC, 0.f));
   const size_t zf = (size_t)g.C_lat * g.H * g.W * es;
   const size_t imf = (size_t)g.C_img * ((size_t)g.H << g.levels) * ((size_t)g.W << g.levels) * es;
-  for (int n0 = 0; n0 < g.N; n0 += n) {
-    const lc_status s = decode_pass(d, p, (const char*)z + n0 * zf, (char*)img + n0 * imf, std::min(n, g.N - n0));
-    if (s != LC_OK) return s;
+  // Slices depend on nothing but the weights: alternate ones go to the caller's stream and to one of the library's own,
+  // forked from and joined into it here, each with its own scratch. The launches of one frame leave most of the device
+  // idle at the latent resolution (64 workgroups), and one slice's fill the other's gaps.
+  const int lanes = std::min(p.lanes, (g.N + n - 1) / n);
+  if (lanes > 1) {
+    LCD_HIP(d, hipEventRecord(d->ev_fork, d->s_main));
+    LCD_HIP(d, hipStreamWaitEvent(d->s_aux, d->ev_fork, 0));
   }
-  return LC_OK;
+  lc_status s = LC_OK;
+  for (int n0 = 0, i = 0; n0 < g.N && s == LC_OK; n0 += n, ++i) {
+    d->s = i % lanes ? d->s_aux : d->s_main;
+    d->lane = d->arena + (i % lanes) * p.lane_stride;
+    s = decode_pass(d, p, (const char*)z + n0 * zf, (char*)img + n0 * imf, std::min(n, g.N - n0));
+  }
+  d->s = d->s_main;
+  if (lanes > 1) {  // whatever happened: joined
+    LCD_HIP(d, hipEventRecord(d->ev_join, d->s_aux));
+    LCD_HIP(d, hipStreamWaitEvent(d->s_main, d->ev_join, 0));
+  }
+  return s;
 }
 
 lc_status lc_decoder_sync(lc_decoder* d) {

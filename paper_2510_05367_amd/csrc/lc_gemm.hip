@@ -47,6 +47,7 @@ struct GemmArgs {
   void* yt;             // linear only: channels >= yt_from go, transposed, to the V^T layout of spatial attention
   int yt_from, yt_T, yt_Tp;
   int frames, H, W, tiles_x, tiles_y;
+  int up_shift;         // conv, SRC 1: x is [frames][H >> up_shift][W >> up_shift][Cin]
   int win_tx0, win_ty0, win_tx, win_ty;  // conv: the tiles a launch covers, origin and extent in tiles
   int64_t rows;
   RowMap in_map, out_map;
@@ -190,7 +191,10 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmArgs a) {
         o.q[0] = *reinterpret_cast<const f32x4*>((const T*)a.x2 + dr * (a.Cin - a.Cs) + (c0 - a.Cs));
       } else if (NORM) {
         const int ldx = SRC == 3 ? a.Cs : a.Cin;
-        load_raw((const float*)a.x + (((int64_t)frame * a.H + cy) * a.W + cx) * ldx + c0, o);
+        if constexpr (SRC == 1)  // up_shift == 1: x has half the resolution (nearest 2x upsampling)
+          load_raw((const float*)a.x + (((int64_t)frame * (a.H >> a.up_shift) + (cy >> a.up_shift)) * (a.W >> a.up_shift) + (cx >> a.up_shift)) * ldx + c0, o);
+        else
+          load_raw((const float*)a.x + (((int64_t)frame * a.H + cy) * a.W + cx) * ldx + c0, o);
       } else {
         o.q[0] = *reinterpret_cast<const f32x4*>((const T*)a.x + (((int64_t)frame * a.H + cy) * a.W + cx) * a.Cin + c0);
       }
@@ -644,7 +648,7 @@ static hipError_t run_gemm(hipStream_t s, const FusedDesc& d) {
   a.res = (const float*)d.res; a.y = d.y;
   a.Cin = d.Cin; a.Cs = d.Cs; a.Cout = d.Cout; a.Cout_store = d.yt ? d.yt_from : d.Cout_store; a.ldw = d.taps * d.Cin;
   a.yt = d.yt; a.yt_from = d.yt_from; a.yt_T = d.yt_T; a.yt_Tp = d.yt_Tp;
-  a.frames = d.frames; a.H = d.H; a.W = d.W;
+  a.frames = d.frames; a.H = d.H; a.W = d.W; a.up_shift = d.up2 ? 1 : 0;
   a.tiles_x = (d.W + 15) / 16; a.tiles_y = (d.H + 7) / 8;
   a.rows = d.rows; a.in_map = d.in_map; a.out_map = d.out_map;
   a.stat = d.stat; a.stat_splits = d.stat_splits;
@@ -704,6 +708,7 @@ hipError_t launch_fused(hipStream_t s, const FusedDesc& d) {
   if (d.stat && (d.taps != 9 || d.planar_out || !(d.y_f32 || esz == 4) || d.stat_splits != conv_stat_splits(d.H, d.W)))
     return hipErrorInvalidValue;
   if (d.Cin % (kRow / esz) != 0) return hipErrorInvalidValue;
+  if (d.up2 && (d.taps != 9 || d.src != 1 || ((d.H | d.W) & 1))) return hipErrorInvalidValue;
   if (d.src == 3 && (d.Cs % (kRow / esz) != 0 || d.Cs <= 0 || d.Cs >= d.Cin || (d.H | d.W) & 1)) return hipErrorInvalidValue;
   if (d.taps == 9) {  // the kernel with specialised wavefronts where the stage's widths suit it
     const hipError_t e = launch_conv_ws(s, d);

@@ -83,6 +83,7 @@ struct FusedDesc {
   const void* w_frag;  // taps == 1: the same matrix in MFMA fragment order (launch_pack_lin_w), or nullptr
   const float* bias;   // [Cout] or nullptr
   int frames, H, W;    // taps == 9
+  int up2;             // taps == 9, src == 1: x is [frames][H / 2][W / 2][Cin] and is upsampled 2x (nearest) on the way in
   // Spatial window (the spatial block of a feature chunk): only the pixels [win_y0, win_y0 + win_h) x
   // [win_x0, win_x0 + win_w) of every frame are computed, by the tiles they belong to in the whole frame (a
   // window starts on a tile boundary and ends on one or at the frame's edge), with the halo read from the
@@ -207,8 +208,6 @@ hipError_t launch_pack_lin_w(hipStream_t s, int dt, const void* w, void* out, in
 // w[Cout][Cin] -> out[Cout][Cin_padded] with zero columns appended
 hipError_t launch_pad_rows(hipStream_t s, int dt, const void* w, void* out, int Cout, int Cin, int Cin_padded);
 hipError_t launch_to_f32(hipStream_t s, int dt, const void* src, float* dst, int n, int n_padded);
-// nearest 2x upsampling of fp32 rows [frames][H][W][C] -> [frames][2H][2W][C] (C % 4 == 0)
-hipError_t launch_up2_rows(hipStream_t s, const float* src, float* dst, int frames, int H, int W, int C);
 hipError_t launch_fill_f32(hipStream_t s, float* dst, int64_t n, float v);
 hipError_t launch_copy_rows(hipStream_t s, int dt, const void* src, void* dst, int64_t elems);
 

@@ -204,7 +204,7 @@ struct UPlan {
   size_t map_bytes;  // one map of all frames: the largest tensor that passes between two blocks
   size_t off_map[3], off_s, off_d1, off_slots, slot_bytes;
   size_t off_part, off_parta, off_partb, off_scale, off_shift, off_one, off_zero, off_tb, off_kv, off_vtx;
-  size_t off_xc, off_h, off_sc, off_xb, off_up;                   // one chunk inside a residual block or a resampling
+  size_t off_xc, off_h, off_sc, off_xb;                           // one chunk inside a residual block
   size_t off_z, off_a, off_qkv, off_vt, off_ao, off_u, off_g;     // one chunk inside a transformer block (same memory)
   size_t total;
 };
@@ -295,7 +295,7 @@ inline int level_chunk(int frame_chunk, int level, int N) {
 // Arena. Of all frames: three maps for the tensors that pass between blocks, the two skips kept across the deep
 // branch, the device slots, the GroupNorm scale / shift. Of one chunk (nc frames in the per-frame blocks, as many
 // rows of all frames in the temporal ones): the inside of a residual block (concatenated input, hidden map,
-// shortcut) or of a resampling (upsampled map), and, in the same memory, the token buffers of a transformer block.
+// shortcut) and, in the same memory, the token buffers of a transformer block.
 UPlan make_uplan(const lc_unet_config& g, int frame_chunk) {
   UPlan p;
   const size_t es = dtype_size(g.dtype);
@@ -341,7 +341,6 @@ UPlan make_uplan(const lc_unet_config& g, int frame_chunk) {
   p.off_h = take((size_t)hid * 4);
   p.off_sc = take((size_t)hid * 4);
   p.off_xb = take(g.dtype == kBF16 ? (size_t)cat * es : 0);
-  p.off_up = take((size_t)std::max(nc1 * P1 * g.C2, nc0 * P * g.C1) * 4);
   const size_t end_rb = off;
   // ---- one chunk, transformer blocks
   off = chunk0;
@@ -398,7 +397,7 @@ lc_status gn(lc_unet* c, const float* x, int n, int rows, int C, const NormP& w)
 }
 
 // y = [res +] conv3x3(act(x)) over n frames; src 2: SiLU(GroupNorm(x)) with the scale / shift at hand (those of frame
-// `f0` on), src 1: x as it is. planar: y is [n][Cout_store][H][W] of the stage's dtype (the last convolution).
+// `f0` on), src 1: x, at half the resolution, nearest 2x upsampled. planar: y is [n][Cout_store][H][W] of the stage's dtype (the last convolution).
 // stat: where the partial sums of y go ([frame of the launch][conv_stat_splits(H, W)][Cout][2]), or nullptr.
 lc_status conv(lc_unet* c, const ConvP& w, const float* bias, int src, int Cin, int Cout, int n, int f0, int H, int W, const float* x,
                const float* res, void* y, int planar, int Cout_store, float* stat = nullptr) {
@@ -407,6 +406,7 @@ lc_status conv(lc_unet* c, const ConvP& w, const float* bias, int src, int Cin, 
   memset(&f, 0, sizeof f);
   f.dt = c->cfg.dtype; f.y_f32 = planar ? 0 : 1; f.taps = 9; f.src = src; f.Cin = Cin; f.Cout = Cout; f.Cout_store = Cout_store;
   f.w = w.w; f.w_tiles = w.wt; f.bias = bias; f.frames = n; f.H = H; f.W = W; f.x = x; f.res = res; f.y = y; f.planar_out = planar;
+  f.up2 = src == 1;
   f.scale = (const float*)(c->arena + (src == 2 ? p.off_scale : p.off_one)) + (size_t)f0 * Cin;
   f.shift = (const float*)(c->arena + (src == 2 ? p.off_shift : p.off_zero)) + (size_t)f0 * Cin;
   f.in_map = f.out_map = dense_map();
@@ -680,14 +680,12 @@ lc_status down_conv(lc_unet* c, const ConvP& w, int C, int level, const float* x
   });
 }
 
-// y [N][2H][2W][C] (level `level`) = conv3x3(nearest2x(x [N][H][W][C])) (the level below); the upsampled map exists
-// for one chunk of frames at a time
+// y [N][2H][2W][C] (level `level`) = conv3x3(nearest2x(x [N][H][W][C])) (the level below); upsampled on the way into the
+// convolution
 lc_status up_conv(lc_unet* c, const ConvP& w, int C, int level, const float* x, float* y) {
   const int H = c->cfg.H >> (level + 1), W = c->cfg.W >> (level + 1);
-  float* up = (float*)(c->arena + c->plan.off_up);
   return frame_chunks(c, level, [&](int n0, int nc) -> lc_status {
-    LCU_HIP(c, launch_up2_rows(c->cs, x + (size_t)n0 * H * W * C, up, nc, H, W, C));
-    return conv(c, w, w.b, 1, C, C, nc, 0, 2 * H, 2 * W, up, nullptr, y + (size_t)n0 * 4 * H * W * C, 0, C);
+    return conv(c, w, w.b, 1, C, C, nc, 0, 2 * H, 2 * W, x + (size_t)n0 * H * W * C, nullptr, y + (size_t)n0 * 4 * H * W * C, 0, C);
   });
 }
 
@@ -758,6 +756,10 @@ lc_status run_step(lc_unet* c, const void* x, const void* temb, const void* cond
   LCU_TRY(tt_block(c, c->tt[3], 0, m1));
   return frame_chunks(c, 0, [&](int n0, int nc) -> lc_status {
     LCU_TRY(gn(c, m1 + (size_t)n0 * P * g.C, nc, P, g.C, c->out_gn));
+    const hipError_t e = launch_conv_out_tile(c->cs, g.dtype, m1 + (size_t)n0 * P * g.C, (const float*)(c->arena + p.off_scale),
+                                              (const float*)(c->arena + p.off_shift), c->out.w, c->out.b,
+                                              (char*)eps + (size_t)n0 * g.C_lat * P * es, nc, H, W, g.C, g.C_lat, Win{0, 0, 0, 0});
+    if (e != hipErrorNotSupported) { LCU_HIP(c, e); return LC_OK; }
     return conv(c, c->out, c->out.b, 2, g.C, 32, nc, 0, H, W, m1 + (size_t)n0 * P * g.C, nullptr, (char*)eps + (size_t)n0 * g.C_lat * P * es, 1,
                 g.C_lat);
   });

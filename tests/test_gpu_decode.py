@@ -107,3 +107,23 @@ def test_decode_full_size_frame_by_frame():
             check(f"decoded frame {f}", host(one[f:f + 1]), orc.decode(z[f:f + 1], 1), cfg.dtype)
     finally:
         dec.close()
+
+
+@pytest.mark.parametrize("widths,heads,head_dim,H,W", [((64, 128, 192), 1, 64, 6, 10), ((320, 192, 64), 8, 40, 5, 7), ((128, 320), 2, 64, 9, 4)])
+def test_decode_odd_sizes_in_bf16(widths, heads, head_dim, H, W):
+    """Widths and sizes that take every kernel of a bf16 pass: the last convolution at 64, 192 and 320 channels, frames
+    of no whole tiles at each level, odd latents (positions per frame not a multiple of four: V^T goes the general
+    way), upsampling on the way into a convolution, slices on two streams. Slices of every kind agree bit for bit."""
+    cfg = synth.DecoderConfig(f"odd_{widths[0]}_{H}x{W}", N=5, H=H, W=W, C_lat=4, C_img=3, widths=widths, groups=32, heads=heads,
+                              head_dim=head_dim, dtype="bf16")
+    w = synth.make_decoder_weights(cfg, 0)
+    dec = lcb.Decoder(cfg, w, max_slice=cfg.N)
+    try:
+        z = synth.make_decoder_latents(cfg, 1)
+        zd = dec.to_device(z)
+        outs = [dec.decode(zd, n) for n in (1, 2, 3, 0)]
+        dec.sync()
+        check(cfg.name, host(outs[0]), do.DecoderOracle(cfg, w64_of(w)).decode(z, 1), cfg.dtype)
+        assert all(torch.equal(outs[0], o) for o in outs[1:])
+    finally:
+        dec.close()
