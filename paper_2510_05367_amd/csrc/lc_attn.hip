@@ -542,9 +542,19 @@ __global__ __launch_bounds__(256, 2) void spatial_attn_ring_kernel(const bf16_t*
       for (int t = 0; t < NQT; ++t) asm volatile("" : "+v"(pc[t][0]), "+v"(pc[t][1]));
       __builtin_amdgcn_sched_barrier(0);
     };
+    // columns of V^T beyond the sequence hold anything: zeros, so that they meet zero probabilities safely
+    auto clear_beyond = [&](int s, int b) {
+      for (int i = tid; i < D * kKeys; i += 256) {
+        const int dim = i / kKeys, col = i % kKeys;
+        if (s * kKeys + vcol_inv<bf16_t>(col) >= TK)
+          *reinterpret_cast<bf16_t*>(vl(b) + dim * 128 + (((col >> 3) ^ ((dim >> 1) & 7)) << 4) + (col & 7) * 2) = (bf16_t)0.f;
+      }
+      __syncthreads();
+    };
     issue(0);
     if (nstage > 1) issue(1);
     stage_barrier();
+    if (kKeys > TK) clear_beyond(0, 0);  // (before the first fragments of V are requested, below)
     static_for<0, KSTEPS>([&](auto kk) __attribute__((always_inline)) { kf[decltype(kk)::value] = kfrag(kl(0), 0, decltype(kk)::value); });
     static_for<0, NQK>([&](auto i) __attribute__((always_inline)) {
       constexpr int kk = decltype(i)::value / NQT, t = decltype(i)::value % NQT;
@@ -559,15 +569,7 @@ __global__ __launch_bounds__(256, 2) void spatial_attn_ring_kernel(const bf16_t*
       if (s) stage_barrier();
       if (s + 2 < nstage) issue(s + 2);
       const int b = s & (NB - 1), bn = (s + 1) & (NB - 1), bp = s ? (s - 1) & (NB - 1) : 0;
-      if (s * kKeys + kKeys > TK) {
-        // columns of V^T beyond the sequence hold anything: zeros, so that they meet zero probabilities safely
-        for (int i = tid; i < D * kKeys; i += 256) {
-          const int dim = i / kKeys, col = i % kKeys;
-          if (s * kKeys + vcol_inv<bf16_t>(col) >= TK)
-            *reinterpret_cast<bf16_t*>(vl(b) + dim * 128 + (((col >> 3) ^ ((dim >> 1) & 7)) << 4) + (col & 7) * 2) = (bf16_t)0.f;
-        }
-        __syncthreads();
-      }
+      if (s && s * kKeys + kKeys > TK) clear_beyond(s, b);
       substep(sB, sA, pA, pB, vl(bp), s ? 1 : 0, kl(b), 1, vl(b), 0, s * kKeys);
       substep(sA, sB, pB, pA, vl(b), 0, kl(bn), 0, vl(b), 1, s * kKeys + 32);
     }
