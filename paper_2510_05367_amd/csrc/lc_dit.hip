@@ -215,13 +215,29 @@ inline const float* mod_blk(const lc_dit* c, const float* mod, int blk) { return
 
 // y[rows][Cout] = x[rows][Cin] W^T + bias; x of the operand type, y fp32 (y32) or of the operand type
 // q_cols: the first channels, multiplied by the softmax scale before they are rounded (the form attention takes)
+// vt: the channels from 2 Cin on go there transposed instead (rows of y have 2 Cin channels); r0: the rows' place in the step
 lc_status linear(lc_dit* c, const void* w, const float* bias, int Cin, int Cout, int64_t rows, const void* x, void* y, int y32,
-                 int act = 0, int q_cols = 0) {
+                 int act = 0, int q_cols = 0, void* vt = nullptr, int64_t r0 = 0) {
   FusedDesc f;
   memset(&f, 0, sizeof f);
   f.dt = c->cfg.dtype; f.y_f32 = y32; f.taps = 1; f.src = 0; f.Cin = Cin; f.Cout = Cout; f.Cout_store = Cout; f.w = w; f.bias = bias;
   f.rows = rows; f.in_map = f.out_map = RowMap{0, 0, 1 << 30}; f.x = x; f.y = y; f.act = act;
   if (q_cols) { f.q_cols = q_cols; f.q_scale = attn_q_scale(c->cfg.head_dim); }
+  if (vt) { f.yt = vt; f.yt_from = 2 * Cin; f.yt_T = c->cfg.T; f.yt_Tp = attn_tp(c->cfg.T); f.row0 = r0; }
+  LCT_HIP(c, launch_fused(c->cs, f));
+  return LC_OK;
+}
+
+// dst += gate * (x W^T + bias) in the projection's own epilogue (dst is then read and written once, and the branch output
+// never): gate_add's arithmetic on the same values. Widths of lin_gate_covers, T >= 32.
+lc_status linear_gated(lc_dit* c, const void* w, const float* bias, int Cin, int64_t rows, const void* x, float* dst, const float* mod,
+                       int which, int64_t r0) {
+  const int D = c->cfg.D;
+  FusedDesc f;
+  memset(&f, 0, sizeof f);
+  f.dt = c->cfg.dtype; f.y_f32 = 1; f.taps = 1; f.src = 0; f.Cin = Cin; f.Cout = D; f.Cout_store = D; f.w = w; f.bias = bias;
+  f.rows = rows; f.in_map = f.out_map = RowMap{0, 0, 1 << 30}; f.x = x; f.y = dst; f.res = dst;
+  f.gate = mod + (int64_t)which * D; f.gate_ld = (int64_t)6 * D; f.gate_T = c->cfg.T; f.gate_n = c->cfg.B; f.row0 = r0;
   LCT_HIP(c, launch_fused(c->cs, f));
   return LC_OK;
 }
@@ -265,17 +281,27 @@ lc_status run_block(lc_dit* c, int i, const float* mod, float* x, const float* d
   char* hid = c->arena + p.off_hid;
   float* t = (float*)(c->arena + p.off_t);
   lc_status s;
+  // (bf16, widths of the streamed kernels: the gated sum in the projections' epilogues, and V^T from q,k,v's where rows come
+  // in fours; the separate passes cost 16 + 16 + 14 us a block at 8192 rows x 1024, 13 % of it)
+  const bool gated = g.dtype == kBF16 && lin_gate_covers(D, D) && T >= 32;
+  const bool vt_fused = g.dtype == kBF16 && lin2_covers(D, 3 * D) && 2 * D % (3 * D % 160 == 0 ? 160 : 128) == 0 && T % 4 == 0 &&
+                        (p.tc % 4 == 0 || p.tc >= R);
+  const int ldq = vt_fused ? 2 * D : 3 * D;
   // ---- attention branch: q,k,v of every token first
   for (int64_t r0 = 0; r0 < R; r0 += p.tc) {
     const int n = (int)std::min<int64_t>(p.tc, R - r0);
     if ((s = ln_mod(c, x + r0 * D, delta ? delta + r0 * D : nullptr, m, 0, 1, xn, n, r0)) != LC_OK) return s;
-    if ((s = linear(c, w.wqkv, w.bqkv, D, 3 * D, n, xn, qkv + r0 * 3 * D * es, 0, 0, D)) != LC_OK) return s;
+    if ((s = linear(c, w.wqkv, w.bqkv, D, 3 * D, n, xn, qkv + r0 * ldq * es, 0, 0, D, vt_fused ? vt : nullptr, r0)) != LC_OK) return s;
   }
-  LCT_HIP(c, launch_make_vt(c->cs, g.dtype, qkv + (size_t)2 * D * es, 3 * D, vt, g.B, T, Tp, D));
+  if (!vt_fused) LCT_HIP(c, launch_make_vt(c->cs, g.dtype, qkv + (size_t)2 * D * es, 3 * D, vt, g.B, T, Tp, D));
   // (all queries at once whatever the token chunk: the kernel keeps nothing per query in memory)
-  LCT_HIP(c, launch_spatial_attention(c->cs, g.dtype, qkv, 3 * D, vt, Tp, ao, g.B, T, g.heads, g.head_dim, 0, T, 1));
+  LCT_HIP(c, launch_spatial_attention(c->cs, g.dtype, qkv, ldq, vt, Tp, ao, g.B, T, g.heads, g.head_dim, 0, T, 1));
   for (int64_t r0 = 0; r0 < R; r0 += p.tc) {
     const int n = (int)std::min<int64_t>(p.tc, R - r0);
+    if (gated) {
+      if ((s = linear_gated(c, w.wo, w.bo, D, n, ao + r0 * D * es, dst + r0 * D, m, 2, r0)) != LC_OK) return s;
+      continue;
+    }
     if ((s = linear(c, w.wo, w.bo, D, D, n, ao + r0 * D * es, t, 1)) != LC_OK) return s;
     if ((s = gate_add(c, dst + r0 * D, t, m, 2, n, r0)) != LC_OK) return s;
   }
@@ -291,6 +317,10 @@ lc_status run_block(lc_dit* c, int i, const float* mod, float* x, const float* d
       if (g.dtype == kBF16) gelu_kernel<bf16_t><<<(unsigned)((n16 + 255) / 256), 256, 0, c->cs>>>((bf16_t*)hid, n16);
       else gelu_kernel<float><<<(unsigned)((n16 + 255) / 256), 256, 0, c->cs>>>((float*)hid, n16);
       LCT_HIP(c, hipGetLastError());
+    }
+    if (gated) {
+      if ((s = linear_gated(c, w.w2, w.b2, H, n, hid, dst + r0 * D, m, 5, r0)) != LC_OK) return s;
+      continue;
     }
     if ((s = linear(c, w.w2, w.b2, H, D, n, hid, t, 1)) != LC_OK) return s;
     if ((s = gate_add(c, dst + r0 * D, t, m, 5, n, r0)) != LC_OK) return s;

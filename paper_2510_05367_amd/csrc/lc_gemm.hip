@@ -718,7 +718,7 @@ hipError_t launch_fused(hipStream_t s, const FusedDesc& d) {
     const hipError_t e = launch_lin2(s, d);
     if (e != hipErrorNotSupported) return e;
   }
-  if (d.y2 || d.act) return hipErrorInvalidValue;  // only that kernel writes the rounded copy / applies an activation
+  if (d.y2 || d.act || d.gate || d.row0) return hipErrorInvalidValue;  // only those kernels write the rounded copy, activate, gate
   return d.dt == kBF16 ? by_kind<bf16_t>(s, d) : by_kind<float>(s, d);
 }
 

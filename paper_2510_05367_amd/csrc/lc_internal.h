@@ -115,6 +115,12 @@ struct FusedDesc {
   // frame = r / yt_T, t = r % yt_T (the V^T layout of the spatial attention kernel). yt == nullptr: off.
   void* yt;
   int yt_from, yt_T, yt_Tp;
+  // taps == 1, src == 0, fp32 y with `res` of a bf16 stage over dense rows, widths of lin_gate_covers only, optional:
+  // y = res + gate[(row0 + r) / gate_T][:] * (x W^T + bias), gate_n vectors gate_ld floats apart, gate_T >= 32.
+  // row0 (a multiple of 4) also counts in yt's frames: frame = (row0 + r) / yt_T.
+  const float* gate;
+  int gate_T, gate_n;
+  int64_t gate_ld, row0;
   // Optional (fp32 output only): per-channel sum and sum of squares of the stored output, for the
   // GroupNorm that reads it next, so that no separate pass over the tensor is needed.
   // stat[frame][split][Cout][2]; nullptr = off. taps == 9: `frame` counts from the first frame of the
@@ -149,10 +155,11 @@ hipError_t launch_fused(hipStream_t s, const FusedDesc& d);
 // taps == 9 of a bf16 stage with specialised wavefronts (lc_convws.hip): the same results as the general
 // kernel bit for bit; hipErrorNotSupported for shapes it does not cover. launch_fused tries it first.
 hipError_t launch_conv_ws(hipStream_t s, const FusedDesc& d);
-// taps == 1, src == 0 of a bf16 stage (lc_lin2.hip: 256 x 160 tiles, operands streamed through a ring of LDS stages);
+// taps == 1, src == 0 of a bf16 stage (lc_lin2.hip, lc_lin3.hip: operands streamed through a ring of LDS stages);
 // hipErrorNotSupported for widths it does not cover, never because of the rows. launch_fused tries it first.
 hipError_t launch_lin2(hipStream_t s, const FusedDesc& d);
 inline bool lin2_covers(int Cin, int Cout) { return Cin > 0 && Cin % 64 == 0 && (Cout % 160 == 0 || Cout % 128 == 0); }
+inline bool lin_gate_covers(int Cin, int Cout) { return lin2_covers(Cin, Cout) && Cout % 128 == 0; }
 // taps == 1 with the weights resident in registers (needs w_frag); hipErrorNotSupported for shapes it does not cover
 hipError_t launch_linear(hipStream_t s, const FusedDesc& d);
 inline hipError_t launch_linear_any(hipStream_t s, const FusedDesc& d) {

@@ -1,0 +1,219 @@
+// Linear layers over dense bf16 rows on gfx950: the tiles beside lc_lin2.hip's 128 x 160, wide ones for launches that fill
+// the chip several times and small ones for launches that would leave most of it idle.
+//
+// What bounds these kernels is the LDS: a compute unit reads 64 bytes a clock from it with 16-byte reads (measured with
+// nothing else running), while its four matrix pipes finish a 32x32x16 MFMA each in 32 clocks. A wavefront that holds
+// MT x NT accumulator tiles reads (MT + NT) / (MT NT) KB per MFMA: 1.2 with lin2's one row tile, 1 at 2 x 2, 0.75 at 2 x 4.
+// Measured, us (lin2's tile -> this file's; rows x N x K): 8192 x 4096 x 1024 with GELU 95 -> 78 and 8192 x 3840 x 1280
+// 97 -> 81 (256 x 256), 8192 x 3072 x 1024 64 -> 56 (256 x 192), 8192 x 1024 x 4096 fp32 75 -> 67 (128 x 128),
+// 3000 x 768 x 3072 fp32 36 -> 27 (64 x 128), 1024 x 1024 x 4096 fp32 43 -> 23, 2048 x 320 x 1280 fp32 18 -> 9 (64 x 64).
+//
+// The K loop: a ring of S stages of 64 K elements (global -> LDS directly, packet c of row r in slot c ^ ((r >> 1) & 7)).
+// The one barrier of a step stands before its last group of MFMAs, whose operands are in registers by then: behind it the
+// stage is free (every wavefront has read it), its next load is issued, and the first fragments of the next stage are
+// requested, so that the barrier and the LDS round trip hide behind that group. K is walked in order by one wavefront per
+// output element, as lin2_kernel does: the same bits whatever the tile, so the launch may choose the tile by its rows.
+#include "lc_lin_epi.h"
+
+namespace lc {
+
+namespace {
+constexpr int kKB3 = 128;  // K bytes per step
+constexpr int kRawBuffer = 0x00020000;  // resource word 3: raw 32-bit data
+typedef __attribute__((address_space(3))) unsigned char* lds_ptr;
+}  // namespace
+
+// WM x WN wavefronts of MT x NT accumulator tiles (32 x 32): a tile of 32 WM MT rows x 32 WN NT channels
+template <class OT, int WM, int WN, int MT, int NT, int S>
+__global__ __launch_bounds__(WM * WN * 64, 2) void lin3_kernel(Lin2Args a) {
+  typedef Mma32<bf16_t> M;
+  constexpr int NW = WM * WN, kM = 32 * WM * MT, kN = 32 * WN * NT, kStage = (kM + kN) * kKB3;
+  constexpr int kXI = kM / 8 / NW, kWI = kN / 8 / NW, kPer = kXI + kWI;  // global->LDS instructions per wavefront per stage
+  static_assert(kM % (8 * NW) == 0 && kN % (8 * NW) == 0, "whole wavefront instructions");
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wid / WN, wn = wid % WN;
+  const int lp = lane & 31, hh = lane >> 5;
+  // (row tile, channel tile) of this workgroup: all channel tiles of a row tile on one XCD, where there are row tiles for
+  // all eight of them
+  const int lin = blockIdx.x;
+  int mt, nt;
+  if (a.ntm >= 8) {
+    const int xcd = lin & 7, slot = lin >> 3;
+    mt = xcd + 8 * (slot / a.ntn); nt = slot - (slot / a.ntn) * a.ntn;
+    if (mt >= a.ntm) return;  // the grid is padded to whole rounds of eight row tiles
+  } else {
+    nt = lin / a.ntm; mt = lin - nt * a.ntm;
+  }
+  const int64_t m0 = (int64_t)mt * kM;
+  const int n0 = nt * kN;
+
+  // ---- global -> LDS: instruction i of a tile moves rows 8 i .. 8 i + 7; this lane moves the packet that lands
+  //      in slot (lane & 7) of row 8 i + (lane >> 3), i.e. global packet (lane & 7) ^ ((row >> 1) & 7)
+  // Buffer loads: the compiler counts a FLAT-encoded load to LDS as one of LDS too, whose order is unknown, and then
+  // waits for every fragment in flight where it needs the oldest; and their bounds check reads rows beyond the end as 0.
+  const int lrow = lane >> 3;
+  int xofs[kXI], wofs[kWI];  // bytes from the tile's first row
+#pragma unroll
+  for (int j = 0; j < kXI; ++j) {
+    const int r = (wid + NW * j) * 8 + lrow;
+    xofs[j] = r * a.K * 2 + (((lane & 7) ^ ((r >> 1) & 7)) << 4);
+  }
+#pragma unroll
+  for (int j = 0; j < kWI; ++j) {
+    const int r = (wid + NW * j) * 8 + lrow;
+    wofs[j] = r * a.K * 2 + (((lane & 7) ^ ((r >> 1) & 7)) << 4);
+  }
+#ifdef __HIP_DEVICE_COMPILE__  // the host pass only needs the kernel's stub; it does not know these builtins
+  const int xrows = (int)min((int64_t)kM, a.rows - m0);
+  const __amdgpu_buffer_rsrc_t xr = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(a.x + m0 * a.K), 0, xrows * a.K * 2, kRawBuffer);
+  const __amdgpu_buffer_rsrc_t wr = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(a.w + (int64_t)n0 * a.K), 0, kN * a.K * 2, kRawBuffer);
+#endif
+  auto issue = [&](int step, int buf) {
+#ifdef __HIP_DEVICE_COMPILE__
+    lds_ptr xb = (lds_ptr)(smem + buf * kStage), wb = xb + kM * kKB3;
+    const int kofs = step * kKB3;
+#pragma unroll
+    for (int j = 0; j < kXI; ++j) __builtin_amdgcn_raw_ptr_buffer_load_lds(xr, xb + (wid + NW * j) * 1024, 16, xofs[j], kofs, 0, 0);
+#pragma unroll
+    for (int j = 0; j < kWI; ++j) __builtin_amdgcn_raw_ptr_buffer_load_lds(wr, wb + (wid + NW * j) * 1024, 16, wofs[j], kofs, 0, 0);
+#else
+    (void)step; (void)buf; (void)xofs; (void)wofs;
+#endif
+  };
+
+  f32x16 acc[MT][NT];
+#pragma unroll
+  for (int j = 0; j < MT; ++j)
+#pragma unroll
+    for (int i = 0; i < NT; ++i)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[j][i][r] = 0.f;
+
+  // fragment addresses inside a stage: row * 128 + ((slot ^ key) << 4), slot = hh + 2 kk (rows + 32 do not change the key)
+  const int key = (lp >> 1) & 7;
+  const int xrow0 = wm * (32 * MT) + lp, wrow0 = kM + wn * (32 * NT) + lp;
+  typename M::Frag xf[2][MT], wf[2][NT];
+  auto frags = [&](const unsigned char* st, int kk, int b) {
+    const int so = ((hh + 2 * kk) ^ key) << 4;
+#pragma unroll
+    for (int j = 0; j < MT; ++j) xf[b][j] = M::load((const bf16_t*)(st + (xrow0 + 32 * j) * kKB3 + so));
+#pragma unroll
+    for (int i = 0; i < NT; ++i) wf[b][i] = M::load((const bf16_t*)(st + (wrow0 + 32 * i) * kKB3 + so));
+  };
+  auto mma = [&](int b) {
+#pragma unroll
+    for (int i = 0; i < NT; ++i)
+#pragma unroll
+      for (int j = 0; j < MT; ++j) M::mma(xf[b][j], wf[b][i], acc[j][i]);
+  };
+
+  const int nsteps = a.K / 64;
+#pragma unroll
+  for (int j = 0; j < S; ++j)
+    if (j < nsteps) issue(j, j);
+  if (nsteps >= S) barrier_keep<(S - 1) * kPer>();
+  else barrier_keep<0>();
+  frags(smem, 0, 0);
+  int buf = 0;
+  for (int s = 0; s < nsteps; ++s) {
+    const unsigned char* st = smem + buf * kStage;
+    const int bnext = buf + 1 == S ? 0 : buf + 1;
+#pragma unroll
+    for (int kk = 0; kk < 3; ++kk) {  // the fragments of the next k-step are requested before this one's MFMAs
+      frags(st, kk + 1, (kk + 1) & 1);
+      __builtin_amdgcn_sched_barrier(0);
+      mma(kk & 1);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    if (s + 1 < nsteps) {
+      // this wavefront has read its last fragments of this stage, and its loads of the next one have landed (those of
+      // the S - 2 stages behind it may be on their way; at the end of K there are fewer)
+      if (s + S - 1 < nsteps) barrier_keep<(S - 2) * kPer>();
+      else barrier_keep<0>();
+      if (s + S < nsteps) issue(s + S, buf);
+      frags(smem + bnext * kStage, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    mma(1);  // (left in one place: a copy behind the loop costs the compiler a second set of accumulators)
+    buf = bnext;
+  }
+
+  // out, two column tiles at a time (their 64 channels of a row are a whole line, and the registers beside the accumulators
+  // hold no more); one at a time where the wavefront's channels do not start on a multiple of 64, so that a slice lies on
+  // one side of yt_from
+  constexpr int SL = NT % 2 ? 1 : 2;
+  const int c0 = n0 + wn * (32 * NT);
+#pragma unroll
+  for (int i = 0; i < NT; i += SL) {
+    const int ci = c0 + 32 * i;
+    float bias_l[SL], mul_l[SL];
+#pragma unroll
+    for (int e = 0; e < SL; ++e) {
+      const int co = ci + 32 * e + lp;
+      bias_l[e] = a.bias ? a.bias[co] : 0.f;
+      mul_l[e] = co < a.q_cols ? a.q_scale : 1.f;
+    }
+#pragma unroll
+    for (int j = 0; j < MT; ++j) {
+      f32x16 part[SL];
+#pragma unroll
+      for (int e = 0; e < SL; ++e) part[e] = acc[j][i + e];
+      lin_epilogue<OT, SL, false, true>(a, part, m0 + wm * (32 * MT) + 32 * j + 4 * hh, ci, lane, bias_l, mul_l);
+    }
+  }
+}
+
+template <class OT, int WM, int WN, int MT, int NT, int S>
+static hipError_t run_lin3_k(hipStream_t s, Lin2Args a) {
+  constexpr int kM = 32 * WM * MT, kN = 32 * WN * NT, lds = S * (kM + kN) * kKB3;
+  static_assert(lds <= 160 * 1024, "one workgroup's ring fits the LDS");
+  auto kern = lin3_kernel<OT, WM, WN, MT, NT, S>;
+  static bool done = false;  // per instantiation
+  if (!done) {
+    hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    if (e != hipSuccess) return e;
+    done = true;
+  }
+  if (a.N % kN || (int64_t)(kM > kN ? kM : kN) * a.K * 2 > 0x7fffffff) return hipErrorInvalidValue;  // (32-bit offsets in a tile)
+  a.ntn = a.N / kN;
+  a.ntm = (int)((a.rows + kM - 1) / kM);
+  const int rounds = a.ntm >= 8 ? (a.ntm + 7) / 8 * 8 : a.ntm;
+  kern<<<(unsigned)(rounds * a.ntn), WM * WN * 64, lds, s>>>(a);
+  return hipGetLastError();
+}
+
+// The tile of a dense launch; hipErrorNotSupported where lin2's 128 x 160 is the better one. 256 compute units: a launch
+// wants at least about that many workgroups, and the large tiles pay only where their last round is nearly full.
+hipError_t launch_lin3(hipStream_t s, const Lin2Args& a, bool y_f32) {
+  auto tiles = [&](int m, int n) { return (a.rows + m - 1) / m * (a.N / n); };
+  auto fills = [&](int64_t t) { return t >= 256 && t * 10 >= (t + 255) / 256 * 256 * 9; };
+  if (a.N % 160 == 0 && a.act != 2 && !a.gate) {
+    // 320 channels, K = 320 / 1280: 4096 rows 8.4 -> 5.9, 2048 rows 18 -> 9, but 16384 rows (256 tiles of 160) 12.6 against
+    // 15.8 and 26 against 30
+    if (a.N % 64 == 0 && tiles(128, 160) < 128)
+      return y_f32 ? run_lin3_k<float, 2, 2, 1, 1, 4>(s, a) : run_lin3_k<bf16_t, 2, 2, 1, 1, 4>(s, a);
+    // (fp32 outputs stay: 32768 x 640 x 640 47 against 51 with 128 x 128, 32768 x 640 x 2560 150 against 162)
+    if (y_f32) return hipErrorNotSupported;
+    // 8192 x 3840 x 1280 97 -> 81
+    if (a.N % 256 == 0 && fills(tiles(256, 256))) return run_lin3_k<bf16_t, 4, 2, 2, 4, 2>(s, a);
+    // 32768 x 1920 x 640 110 -> 103, but 131072 x 960 x 320 166 against 183: the larger tile's epilogue is not covered
+    if (a.N % 192 == 0 && a.K >= 640 && fills(tiles(256, 192))) return run_lin3_k<bf16_t, 4, 2, 2, 3, 2>(s, a);
+    return hipErrorNotSupported;
+  }
+  if (!y_f32) {
+    // 8192 x 4096 x 1024 88 with 128 x 128, 78 with 256 x 256; 8192 x 3072 x 1024 (384 tiles, the second round half empty)
+    // 59 against 64, and 56 with 256 x 192
+    if (a.N % 256 == 0 && fills(tiles(256, 256))) return run_lin3_k<bf16_t, 4, 2, 2, 4, 2>(s, a);
+    if (a.N % 192 == 0 && a.K >= 640 && a.act != 2 && fills(tiles(256, 192))) return run_lin3_k<bf16_t, 4, 2, 2, 3, 2>(s, a);
+  }
+  // 1024 x 4096 x 1024 (256 tiles of 128 x 128) 17.8, with 64 x 128 17.9; 1024 x 3072 x 1024 (192) 15.8 against 14.4
+  if (tiles(128, 128) >= 256 || a.act == 2)
+    return y_f32 ? run_lin3_k<float, 2, 2, 2, 2, 2>(s, a) : run_lin3_k<bf16_t, 2, 2, 2, 2, 2>(s, a);
+  // 512 x 3072 x 1024 (192 tiles of 64 x 128) 11.0 against 11.7 with 64 x 64; 1024 x 1024 x 1024 (128) 10.0 against 8.5
+  if (tiles(64, 128) >= 192) return y_f32 ? run_lin3_k<float, 2, 2, 1, 2, 3>(s, a) : run_lin3_k<bf16_t, 2, 2, 1, 2, 3>(s, a);
+  return y_f32 ? run_lin3_k<float, 2, 2, 1, 1, 4>(s, a) : run_lin3_k<bf16_t, 2, 2, 1, 1, 4>(s, a);
+}
+
+}  // namespace lc

@@ -1,0 +1,177 @@
+// What the linear kernels over dense bf16 rows (lc_lin2.hip, lc_lin3.hip) share: their arguments and the way a finished
+// accumulator tile leaves a wavefront.
+#pragma once
+#include <type_traits>
+
+#include "lc_internal.h"
+
+namespace lc {
+
+struct Lin2Args {
+  const bf16_t* x;     // [rows][K]
+  const bf16_t* w;     // [N][K]
+  const float* bias;   // [N] or nullptr
+  const float* res;    // fp32 [rows][N] or nullptr (may alias y)
+  void* y;             // [rows][N], bf16 or fp32
+  bf16_t* y2;          // fp32 output only: a copy of y rounded to bf16 (the next layer's operand), or nullptr
+  int64_t rows;
+  int K, N, ntm, ntn;
+  float q_scale;       // channels below q_cols are multiplied by this before they are rounded
+  int q_cols;
+  int act;             // 0 none, 1 GELU, 2 GEGLU over alternating 32-channel blocks (y is then N / 2 wide)
+  RowMap in_map, out_map;  // dense row r is row in_map(r) of x and row out_map(r) of y / res / y2
+  // bf16 output over dense rows only: channels >= yt_from are not stored in y (whose rows then have yt_from channels)
+  // but transposed into yt[g / yt_T][N - yt_from][yt_Tp] at column (t & ~63) + vcol(t & 63), g = row0 + r, t = g % yt_T:
+  // the V^T layout of the spatial attention kernel. nullptr: off. yt_from a multiple of a wavefront's channels, yt_T of 4.
+  bf16_t* yt;
+  int yt_from, yt_T, yt_Tp;
+  // fp32 output over dense rows, with `res` only: y = res + gate[(row0 + r) / gate_T][co] * (x W^T + bias), the gate vectors
+  // gate_ld floats apart, gate_n of them, gate_T >= 32 (a 32-row tile meets two at most). nullptr: off.
+  const float* gate;
+  int gate_T, gate_n;
+  int64_t gate_ld;
+  int64_t row0;  // gate, yt: the launch's first row within the whole matrix
+  int ldy;  // channels per row of y (yt_from with yt, else N; N / 2 after a GEGLU)
+};
+
+// A dense launch (N % 128 == 0 or % 160 == 0; yt_from % 64 == 0) on one of lc_lin3.hip's tiles; hipErrorNotSupported where
+// lin2_kernel's 128 x 160 is the better one (never with a gate).
+hipError_t launch_lin3(hipStream_t s, const Lin2Args& a, bool y_f32);
+
+// bf16 stores of a 32-row half tile, two channels per lane: lanes l and l ^ 1 hold channels c, c + 1 of the same rows;
+// they trade halves so that the even lane holds both channels of the even row of a pair and the odd lane both of the
+// odd row, and each stores 4 bytes: a wavefront instruction then writes 64 consecutive bytes of two rows instead of
+// 64 bytes of one with 2-byte stores. NV: column tiles (32 channels each) in val's second index.
+template <int NV, int NTV, bool MAPPED>
+__device__ __forceinline__ void store_pairs(const float (&val)[16][NTV], bf16_t* __restrict__ Y, int ldy, int c0, int64_t rbase,
+                                            int64_t rows, const RowMap& out_map, int lane, std::integral_constant<bool, MAPPED>) {
+  const int lp = lane & 31;
+  const bool odd = lane & 1;
+  // v_perm_b32 selectors (bytes 0-3: own pair, 4-7: the neighbour's): even (own lo, neighbour's lo), odd (neighbour's hi, own hi)
+  const uint32_t sel = odd ? 0x03020706u : 0x05040100u;
+#pragma unroll
+  for (int rp = 0; rp < 16; rp += 2) {
+    uint32_t out[NV];
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+      bf16x2 p2;
+      p2[0] = static_cast<bf16_t>(val[rp][i]);
+      p2[1] = static_cast<bf16_t>(val[rp + 1][i]);
+      const uint32_t own = __builtin_bit_cast(uint32_t, p2);
+      const uint32_t nb = (uint32_t)__builtin_amdgcn_mov_dpp((int)own, 0xB1 /* quad_perm [1,0,3,2] */, 0xF, 0xF, true);
+      out[i] = __builtin_amdgcn_perm(nb, own, sel);
+    }
+    const int64_t dr = rbase + 8 * (rp >> 2) + (rp & 3) + (odd ? 1 : 0);
+    if (dr >= rows) continue;
+    const int64_t row = MAPPED ? out_map(dr) : dr;
+#pragma unroll
+    for (int i = 0; i < NV; ++i) *reinterpret_cast<uint32_t*>(Y + row * ldy + c0 + 32 * i + (lp & ~1)) = out[i];
+  }
+}
+
+// The epilogue of one 32-row half tile of NT column tiles (32 channels each): the lane holds channel c0 + 32 i + lp of rows
+// rbase + 8 (r / 4) + r % 4, rbase already including 4 hh.
+// GATE: Lin2Args::gate may be set (its own registers: the kernels that never take one stay without them).
+template <class OT, int NT, bool MAPPED, bool GATE>
+__device__ __forceinline__ void lin_epilogue(const Lin2Args& a, const f32x16 (&acc)[NT], int64_t rbase, int c0, int lane,
+                                             const float (&bias_l)[NT], const float (&mul_l)[NT]) {
+  const int lp = lane & 31;
+  OT* Y = (OT*)a.y;
+  const float* R = a.res;
+  // The residual (which may be y itself: every element is read and written by the same lane) is fetched for a whole
+  // 32-row half at once, before the first store of that half: a load placed after a store that may alias it cannot
+  // be moved up by the compiler, and one round trip per element would cost more than the whole contraction.
+  float rv[16][NT];
+  if (R) {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      int64_t row = min(rbase + 8 * (r >> 2) + (r & 3), a.rows - 1);
+      if (MAPPED) row = a.out_map(row);
+#pragma unroll
+      for (int i = 0; i < NT; ++i) rv[r][i] = R[row * a.N + c0 + 32 * i + lp];
+    }
+  }
+  // all arithmetic of the half first, so that the stores below depend on no load: a store under a condition
+  // (the ragged last tile) would otherwise be preceded by a wait for everything in flight
+  float val[16][NT];
+  bool gated = false;
+  if constexpr (GATE && sizeof(OT) == 4 && !MAPPED) {
+    if (a.gate) {
+      gated = true;
+      const int b0 = (int)((a.row0 + rbase) / a.gate_T);
+      const int64_t next = (int64_t)(b0 + 1) * a.gate_T - a.row0;  // the first row of the next vector
+      const float* g0 = a.gate + min(b0, a.gate_n - 1) * a.gate_ld + c0 + lp;
+      const float* g1 = a.gate + min(b0 + 1, a.gate_n - 1) * a.gate_ld + c0 + lp;
+#pragma unroll
+      for (int i = 0; i < NT; ++i) {
+        const float ga = g0[32 * i], gb = g1[32 * i];
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const float g = rbase + 8 * (r >> 2) + (r & 3) >= next ? gb : ga;
+          val[r][i] = fmaf(g, acc[i][r] + bias_l[i], rv[r][i]);
+          asm volatile("" : "+v"(val[r][i]));
+        }
+      }
+    }
+  }
+  if (!gated) {
+#pragma unroll
+    for (int r = 0; r < 16; ++r)
+#pragma unroll
+      for (int i = 0; i < NT; ++i) {
+        val[r][i] = (acc[i][r] + bias_l[i]) * mul_l[i];
+        if (R) val[r][i] += rv[r][i];
+        if (sizeof(OT) == 2 && a.act == 1) val[r][i] = gelu_tanh_fast(val[r][i]);
+        asm volatile("" : "+v"(val[r][i]));  // computed here: left alone, the compiler sinks it into the store's branch
+      }
+  }
+  if constexpr (sizeof(OT) == 2) {
+    if (a.yt && c0 >= a.yt_from) {  // (uniform over the wavefront) a lane holds 4 consecutive rows of a channel: 8 bytes of V^T
+      const int Cv = a.N - a.yt_from;
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const int64_t dr = rbase + 8 * g;
+        if (dr >= a.rows) continue;  // (rows come in fours)
+        const int64_t f = (a.row0 + dr) / a.yt_T;
+        const int t = (int)(a.row0 + dr - f * a.yt_T);
+        bf16_t* dst = a.yt + (f * Cv + (c0 - a.yt_from) + lp) * a.yt_Tp + (t & ~63) + vcol<bf16_t>(t & 63);
+#pragma unroll
+        for (int i = 0; i < NT; ++i) {
+          bf16x4 o;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) o[e] = static_cast<bf16_t>(val[4 * g + e][i]);
+          *reinterpret_cast<bf16x4*>(dst + (int64_t)32 * i * a.yt_Tp) = o;
+        }
+      }
+      return;
+    }
+  }
+  if constexpr (sizeof(OT) == 2 && NT % 2 == 0) {
+    if (a.act == 2) {  // GEGLU: column tile 2 q holds 32 values, tile 2 q + 1 their gates; N / 2 channels leave
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+#pragma unroll
+        for (int q = 0; q < NT / 2; ++q) {
+          val[r][q] = val[r][2 * q] * gelu_tanh_fast(val[r][2 * q + 1]);
+          asm volatile("" : "+v"(val[r][q]));
+        }
+      store_pairs<NT / 2>(val, (bf16_t*)a.y, a.N / 2, c0 / 2, rbase, a.rows, a.out_map, lane, std::integral_constant<bool, MAPPED>{});
+      return;
+    }
+  }
+  if constexpr (sizeof(OT) == 2) {
+    store_pairs<NT>(val, (bf16_t*)a.y, a.ldy, c0, rbase, a.rows, a.out_map, lane, std::integral_constant<bool, MAPPED>{});
+  } else {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int64_t dr = rbase + 8 * (r >> 2) + (r & 3);
+      if (dr >= a.rows) continue;
+      const int64_t row = MAPPED ? a.out_map(dr) : dr;
+#pragma unroll
+      for (int i = 0; i < NT; ++i) Y[row * a.N + c0 + 32 * i + lp] = from_f32<OT>(val[r][i]);
+    }
+    if (a.y2) store_pairs<NT>(val, a.y2, a.N, c0, rbase, a.rows, a.out_map, lane, std::integral_constant<bool, MAPPED>{});
+  }
+}
+
+}  // namespace lc
