@@ -26,34 +26,41 @@ using namespace lc;
 
 namespace lc {
 
-// y[r][:] = LN(x[r][:]) * gamma + beta (+ pe[(r / rows_per_frame) % F][:]), one wavefront per row; biased variance.
-// x fp32, y of type T. D % 4 == 0, D <= 64 * 4 * LNA_MAXV.
+// y[r][:] = LN(x[r][:]) * gamma + beta (+ pe[(r / rows_per_frame) % F][:]); biased variance. x fp32, y of type T. D % 4 == 0,
+// D <= 4 LPR MAXV. Bound by memory: LPR lanes per row, so that every lane has several 16-byte loads in flight and none is
+// idle (at D = 320 a wavefront per row leaves 48 of 64 lanes idle in its second round).
 constexpr int LNA_MAXV = 8;
-template <class T>
+template <int LPR>
+__device__ __forceinline__ float row_sum(float v) {
+#pragma unroll
+  for (int o = LPR / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+  return v;
+}
+template <class T, int LPR, int MAXV>
 __global__ __launch_bounds__(256) void ln_affine_kernel(const float* __restrict__ x, const float* __restrict__ gamma,
                                                         const float* __restrict__ beta, const float* __restrict__ pe,
                                                         T* __restrict__ y, int64_t rows, int D, int rows_per_frame, int F, float eps) {
-  const int lane = threadIdx.x & 63;
-  const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (row >= rows) return;
+  const int lane = threadIdx.x & (LPR - 1);
+  const int64_t r_own = (int64_t)blockIdx.x * (256 / LPR) + threadIdx.x / LPR;
+  const int64_t row = min(r_own, rows - 1);  // (lanes beyond the end stay for the shuffles; they store nothing)
   const int nv = D / 4;
   const f32x4* xr = reinterpret_cast<const f32x4*>(x + row * D);
   const f32x4* pr = pe ? reinterpret_cast<const f32x4*>(pe + (int64_t)((row / rows_per_frame) % F) * D) : nullptr;
-  f32x4 v[LNA_MAXV];
+  f32x4 v[MAXV];
   float s = 0.f;
 #pragma unroll
-  for (int j = 0; j < LNA_MAXV; ++j) {
-    const int p = lane + 64 * j;
+  for (int j = 0; j < MAXV; ++j) {
+    const int p = lane + LPR * j;
     if (p < nv) {
       v[j] = xr[p];
       s += (v[j][0] + v[j][1]) + (v[j][2] + v[j][3]);
     }
   }
-  const float mu = wave_sum(s) / (float)D;
+  const float mu = row_sum<LPR>(s) / (float)D;
   float q = 0.f;
 #pragma unroll
-  for (int j = 0; j < LNA_MAXV; ++j) {
-    if (lane + 64 * j < nv) {
+  for (int j = 0; j < MAXV; ++j) {
+    if (lane + LPR * j < nv) {
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const float d = v[j][e] - mu;
@@ -61,10 +68,11 @@ __global__ __launch_bounds__(256) void ln_affine_kernel(const float* __restrict_
       }
     }
   }
-  const float rstd = 1.f / sqrtf(wave_sum(q) / (float)D + eps);
+  const float rstd = 1.f / sqrtf(row_sum<LPR>(q) / (float)D + eps);
+  if (r_own >= rows) return;
 #pragma unroll
-  for (int j = 0; j < LNA_MAXV; ++j) {
-    const int p = lane + 64 * j;
+  for (int j = 0; j < MAXV; ++j) {
+    const int p = lane + LPR * j;
     if (p < nv) {
       const f32x4 g = reinterpret_cast<const f32x4*>(gamma)[p], b = reinterpret_cast<const f32x4*>(beta)[p];
       float o[4];
@@ -449,13 +457,19 @@ lc_status gn_apply(lc_unet* c, const float* x, const float* scale, const float* 
   return LC_OK;
 }
 
+template <class T>
+void launch_ln(hipStream_t s, const float* z, const NormP& w, const float* pe, T* y, int64_t rows, int D, int rows_per_frame, int F, float eps) {
+  auto grid = [&](int lpr) { return (unsigned)((rows + 256 / lpr - 1) / (256 / lpr)); };
+  // five packets of 16 bytes a lane where the width allows; a property of the width, never of the rows
+  if (D <= 320) ln_affine_kernel<T, 16, 5><<<grid(16), 256, 0, s>>>(z, w.g, w.b, pe, y, rows, D, rows_per_frame, F, eps);
+  else if (D <= 640) ln_affine_kernel<T, 32, 5><<<grid(32), 256, 0, s>>>(z, w.g, w.b, pe, y, rows, D, rows_per_frame, F, eps);
+  else ln_affine_kernel<T, 64, LNA_MAXV><<<grid(64), 256, 0, s>>>(z, w.g, w.b, pe, y, rows, D, rows_per_frame, F, eps);
+}
+
 lc_status ln(lc_unet* c, const float* z, const NormP& w, const float* pe, void* y, int64_t rows, int D, int rows_per_frame) {
-  const unsigned blocks = (unsigned)((rows + 3) / 4);
   const lc_unet_config& g = c->cfg;
-  if (g.dtype == kBF16)
-    ln_affine_kernel<bf16_t><<<blocks, 256, 0, c->cs>>>(z, w.g, w.b, pe, (bf16_t*)y, rows, D, rows_per_frame, g.F, g.ln_eps);
-  else
-    ln_affine_kernel<float><<<blocks, 256, 0, c->cs>>>(z, w.g, w.b, pe, (float*)y, rows, D, rows_per_frame, g.F, g.ln_eps);
+  if (g.dtype == kBF16) launch_ln<bf16_t>(c->cs, z, w, pe, (bf16_t*)y, rows, D, rows_per_frame, g.F, g.ln_eps);
+  else launch_ln<float>(c->cs, z, w, pe, (float*)y, rows, D, rows_per_frame, g.F, g.ln_eps);
   LCU_HIP(c, hipGetLastError());
   return LC_OK;
 }
