@@ -553,7 +553,12 @@ __global__ __launch_bounds__(256, 2) void spatial_attn_ring_kernel(const bf16_t*
     };
     issue(0);
     if (nstage > 1) issue(1);
-    stage_barrier();
+    // this barrier also stands between what the prologue wrote to LDS (the rows of V^T beyond d) and the other wavefronts'
+    // first fragments: it waits for LDS too
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(7 << 4);  // vmcnt(0) lgkmcnt(0)
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
     if (kKeys > TK) clear_beyond(0, 0);  // (before the first fragments of V are requested, below)
     static_for<0, KSTEPS>([&](auto kk) __attribute__((always_inline)) { kf[decltype(kk)::value] = kfrag(kl(0), 0, decltype(kk)::value); });
     static_for<0, NQK>([&](auto i) __attribute__((always_inline)) {
