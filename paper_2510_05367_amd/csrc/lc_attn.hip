@@ -19,6 +19,11 @@ namespace lc {
 
 constexpr int kKeys = 64;  // keys per LDS stage
 
+namespace {
+constexpr int kRawBuffer = 0x00020000;  // resource word 3: raw 32-bit data
+typedef __attribute__((address_space(3))) unsigned char* lds_ptr;
+}  // namespace
+
 // qk: rows [frame*T + token] of stride ldq holding q at column 0 and k at column C (per head: + head*D).
 // vt: V transposed and block-permuted, [frame][C][Tp] with token t of a row at column vcol(t), Tp a
 // multiple of 64 (columns beyond T are never trusted: they are zeroed while staging).
@@ -339,7 +344,7 @@ __global__ __launch_bounds__(256, 2) void spatial_attn_ring_kernel(const bf16_t*
   typedef M::Frag Frag;
   constexpr int KSTEPS = (D + 15) / 16;     // MFMAs along d
   constexpr int DM = (D + 31) / 32;         // 32-row tiles of O^T
-  constexpr int KP = 2 * KSTEPS;            // 16-byte slots of a K row in LDS (those beyond d meet zeros of q)
+  constexpr int KP = 2 * KSTEPS;            // 16-byte slots of a K row in LDS (those beyond d are zeros)
   constexpr int KSLOT = kKeys * KP * 16, VSLOT = DM * 32 * 128, SLOT = KSLOT + VSLOT;
   constexpr int NB = 4;                     // stages in LDS
   constexpr bool ROWSUM = D % 32 != 0;      // a spare row of V^T holds ones: O^T[D] is the denominator
@@ -387,13 +392,15 @@ __global__ __launch_bounds__(256, 2) void spatial_attn_ring_kernel(const bf16_t*
   }
   if (tid == 0) *redo_flag = 0;
 
-  // ---- global -> LDS. K: packet p of a stage is (key p / KP, slot p % KP); V^T: (row p / 8, slot p % 8)
+  // ---- global -> LDS. K: packet p of a stage is (key p / KP, slot p % KP); V^T: (row p / 8, slot p % 8). Buffer loads,
+  // whose bounds check delivers zeros for the slots of K beyond d (a copy of anything there could meet the zeros of q with
+  // an infinity) and for keys beyond the sequence (masked below); the resource moves on by a stage.
   uint32_t koff[KJ], voff[VJ];
 #pragma unroll
   for (int j = 0; j < KJ; ++j) {
     const int p = min(wid + 4 * j, NKI - 1) * 64 + lane, key = p / KP, sl = p % KP;
-    const int c = KSWZ ? (sl ^ ((key >> 1) & 7)) : min(sl, D / 8 - 1);  // (slots beyond d: a copy of the last packet)
-    koff[j] = (uint32_t)(key * ldkk + c * 8) * 2;
+    const int c = KSWZ ? (sl ^ ((key >> 1) & 7)) : sl;
+    koff[j] = c < D / 8 ? (uint32_t)(key * ldkk + c * 8) * 2 : 0x7fffff00u;
   }
 #pragma unroll
   for (int j = 0; j < VJ; ++j) {
@@ -401,27 +408,21 @@ __global__ __launch_bounds__(256, 2) void spatial_attn_ring_kernel(const bf16_t*
     voff[j] = (uint32_t)(dim * Tp + (sl ^ ((dim >> 1) & 7)) * 8) * 2;
   }
   auto issue = [&](int st) {
-    unsigned char* b = kl(st & (NB - 1));
-    const char* kg = (const char*)kb + (int64_t)st * kKeys * ldkk * 2;
-    const char* vg = (const char*)vbase + (int64_t)st * kKeys * 2;
-#ifdef __HIP_DEVICE_COMPILE__  // the host pass only needs the kernel's stub; it does not know this builtin
-    if (st * kKeys + kKeys <= TK) {
+#ifdef __HIP_DEVICE_COMPILE__  // the host pass only needs the kernel's stub; it does not know these builtins
+    lds_ptr b = (lds_ptr)kl(st & (NB - 1));
+    const int keys = min(kKeys, TK - st * kKeys);
+    const __amdgpu_buffer_rsrc_t kr = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(kb + (int64_t)st * kKeys * ldkk), 0,
+                                                                        ((keys - 1) * ldkk + D) * 2, kRawBuffer);
+    const __amdgpu_buffer_rsrc_t vr = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(vbase + (int64_t)st * kKeys), 0,
+                                                                        (int)((uint32_t)((D - 1) * Tp + kKeys) * 2), kRawBuffer);
 #pragma unroll
-      for (int j = 0; j < KJ; ++j)
-        __builtin_amdgcn_global_load_lds((const void*)(kg + koff[j]), b + min(wid + 4 * j, NKI - 1) * 1024, 16, 0, 0);
-    } else {  // keys beyond the sequence: the last one again (masked below)
-#pragma unroll
-      for (int j = 0; j < KJ; ++j) {
-        const int n = min(wid + 4 * j, NKI - 1), key = (n * 64 + lane) / KP;
-        const int back = max(key - (TK - 1 - st * kKeys), 0);
-        __builtin_amdgcn_global_load_lds((const void*)(kg + koff[j] - (int64_t)back * ldkk * 2), b + n * 1024, 16, 0, 0);
-      }
-    }
+    for (int j = 0; j < KJ; ++j)
+      if (wid + 4 * j < NKI) __builtin_amdgcn_raw_ptr_buffer_load_lds(kr, b + (wid + 4 * j) * 1024, 16, koff[j], 0, 0, 0);
 #pragma unroll
     for (int j = 0; j < VJ; ++j)
-      __builtin_amdgcn_global_load_lds((const void*)(vg + voff[j]), b + KSLOT + min(wid + 4 * j, NVI - 1) * 1024, 16, 0, 0);
+      if (wid + 4 * j < NVI) __builtin_amdgcn_raw_ptr_buffer_load_lds(vr, b + KSLOT + (wid + 4 * j) * 1024, 16, voff[j], 0, 0, 0);
 #else
-    (void)b; (void)kg; (void)vg;
+    (void)st; (void)koff; (void)voff;
 #endif
   };
   // every load has landed (for every wavefront, behind the barrier); LDS reads in flight are left alone: the stage they
@@ -551,9 +552,11 @@ __global__ __launch_bounds__(256, 2) void spatial_attn_ring_kernel(const bf16_t*
       }
       __syncthreads();
     };
+    // V of "the stage before" the first one: zeros, which meet the zero probabilities of the first substep (stage 3 lands there)
+    for (int i = tid; i < D * 8; i += 256) *reinterpret_cast<uint4*>(vl(NB - 1) + i * 16) = uint4{0u, 0u, 0u, 0u};
     issue(0);
     if (nstage > 1) issue(1);
-    // this barrier also stands between what the prologue wrote to LDS (the rows of V^T beyond d) and the other wavefronts'
+    // this barrier also stands between what the prologue wrote to LDS (the rows of V^T beyond d, the zeros above) and the other wavefronts'
     // first fragments: it waits for LDS too
     asm volatile("" ::: "memory");
     __builtin_amdgcn_s_waitcnt(7 << 4);  // vmcnt(0) lgkmcnt(0)
@@ -566,16 +569,15 @@ __global__ __launch_bounds__(256, 2) void spatial_attn_ring_kernel(const bf16_t*
       sA[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[kk], qf[t][kk], kk ? sA[t] : zero16, 0, 0, 0);
     });
     static_for<0, kAhead>([&](auto g) __attribute__((always_inline)) {
-      vf[decltype(g)::value / DM][decltype(g)::value % DM] = vfrag(vl(0), 0, decltype(g)::value / DM, decltype(g)::value % DM);
+      vf[decltype(g)::value / DM][decltype(g)::value % DM] = vfrag(vl(NB - 1), 1, decltype(g)::value / DM, decltype(g)::value % DM);
     });
-    // (in the first substep the probabilities of "the substep before" are zeros: any finite V does, its own is at hand.
-    // Behind the last stage the K requests and scores are of no stage: in bounds, never used.)
+    // (Behind the last stage the K requests and scores are of no stage: in bounds, never used.)
     for (int s = 0; s < nstage; ++s) {
       if (s) stage_barrier();
       if (s + 2 < nstage) issue(s + 2);
-      const int b = s & (NB - 1), bn = (s + 1) & (NB - 1), bp = s ? (s - 1) & (NB - 1) : 0;
+      const int b = s & (NB - 1), bn = (s + 1) & (NB - 1), bp = (s - 1) & (NB - 1);
       if (s && s * kKeys + kKeys > TK) clear_beyond(s, b);
-      substep(sB, sA, pA, pB, vl(bp), s ? 1 : 0, kl(b), 1, vl(b), 0, s * kKeys);
+      substep(sB, sA, pA, pB, vl(bp), 1, kl(b), 1, vl(b), 0, s * kKeys);
       substep(sA, sB, pB, pA, vl(b), 0, kl(bn), 0, vl(b), 1, s * kKeys + 32);
     }
     const unsigned char* vlast = vl((nstage - 1) & (NB - 1));

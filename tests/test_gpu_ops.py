@@ -238,6 +238,44 @@ def test_spatial_attention_out_of_range_scores(heads, head_dim, F, H, W):
         stage.close()
 
 
+@pytest.mark.parametrize("heads,head_dim", [(8, 8), (4, 16), (2, 32), (8, 40), (5, 64)])
+@pytest.mark.parametrize("prescaled", [0, 1])
+def test_spatial_attention_infinities(heads, head_dim, prescaled):
+    """bf16 rows with infinities where softmax still has an answer. A key with an element of minus infinity that every
+    query meets with a positive one has probability zero and must leave the others' results alone (the padding of a key
+    row in LDS must not be a copy of it: zero times infinity). A value of plus infinity gives plus infinity in its channel
+    and nothing else (no probability of zero may meet it: each key has a positive one here). 140 tokens = two stages of
+    keys and a remainder; the infinities lie in the first substep of 32 keys, in the middle and in the remainder."""
+    C = heads * head_dim
+    cfg = synth.StageConfig(f"si_{heads}x{head_dim}", B=1, F=2, H=10, W=14, C_lat=4, C=C, C_deep=64, groups=8 if C % 32 else 32, n_res=1,
+                            heads=heads, head_dim=head_dim, dtype="bf16")
+    stage, _ = make_stage(cfg, seed=7)
+    try:
+        N, T = cfg.N, cfg.T
+        qkv = act(cfg, (N, T, 3, heads, head_dim), 253)
+        qkv[:, :, 0, :, -1] = np.abs(qkv[:, :, 0, :, -1]) + np.float32(0.25)  # (the last channel of a head: beside the padding)
+        gone, high = (3, 70, 139), (5, 90, 137)
+        qkv[:, gone, 1, :, -1] = -np.inf
+        for i, t in enumerate(high):
+            qkv[:, t, 2, :, 2 + i] = np.inf
+        qkv = synth.round_to_bf16(qkv)
+        a = qkv.astype(np.float64)
+        if prescaled:  # the definition's 1 / sqrt(d) and e as the factors the kernel leaves out
+            a[:, :, 0] *= np.sqrt(head_dim) / np.log2(np.e)
+        q, k, v = (np.ascontiguousarray(a[:, :, i].reshape(N, T, C)) for i in range(3))
+        keep = [t for t in range(T) if t not in gone]
+        ref = lo.attention_core(q, k[:, keep], v[:, keep], heads).reshape(N * T, C)
+        out = stage.empty(N * T, C)
+        lcb.lc_op_spatial_attention(stage.ctx, dev(stage, qkv.reshape(N * T, 3 * C)).data_ptr(), out.data_ptr(), N, 0, T, prescaled)
+        stage.sync()
+        got = host(out)
+        assert np.array_equal(np.isposinf(got), np.isposinf(ref))
+        finite = np.isfinite(ref)
+        check(f"spatial core with infinities {heads}x{head_dim}", got[finite], ref[finite], "bf16")
+    finally:
+        stage.close()
+
+
 def test_temporal_attention_core(st):
     stage, cfg, w = st
     B, F, C = cfg.B, cfg.F, cfg.C
