@@ -322,16 +322,28 @@ template <int I, int N, class F> __device__ __forceinline__ void static_for(F&& 
 // LDS (16 bytes per lane) into a ring of four 64-key stages: stage s + 2 is requested at the start of stage s, one
 // barrier per stage. (Four, because the scores run into stage s + 1 and the lagging V fragments are read until late in
 // stage s.) 16-byte slots are XOR-swizzled where a row is 128 bytes.
-// No running maximum: softmax does not depend on the offset it subtracts, and with scores in log2 units between -90
-// and 100 exp2 needs none in fp32 (bf16 has the same exponent range and rounds relatively). The denominator and O^T
-// tell afterwards: a query whose denominator left [2^-90, 2^110] or whose O^T is not finite is flagged and, in a rare
-// second sweep, done again with its exact maximum (found in a sweep over the keys of its own). The decision is each
-// query's own, and so is every bit of its result, whoever shares its wavefront.
+// What the exponents subtract: softmax does not depend on it, and with scores in log2 units of ordinary size exp2 needs
+// nothing subtracted in fp32 (bf16 has the same exponent range and rounds relatively). So a query's offset m is zero if the
+// largest of its first 32 scores lies within kNear of zero, else that score, rounded; a wavefront whose offsets are all zero
+// runs the plain form of a substep, which subtracts nothing, others the safe form, which does and raises an offset (scaling
+// what it has summed up) before a score passes it by kRaise. The plain form looks at the denominators after every stage: one
+// past kHigh sends its wavefront on in the safe form, and one past kBroken says that a score came that the safe form would
+// have raised m for; the workgroup is then done again, safely. Should an output not be finite after all (values near the end
+// of their own range), its query is done once more with its exact maximum, found in a sweep over the keys. Every decision
+// that shows in a query's bits is its own (x - 0 is x), whoever shares its wavefront.
 // Measured (us per launch, with a kernel that ran the two phases in turn / this one): d = 64, 5 x 9216 tokens, 2304
 // queries, 5 heads 204 / 170 alone and 157 / 132 with two launches in flight (1.02 PFLOP/s); d = 40, 4 x 4096, 8 heads
 // 123 / 104; d = 40, 8 x 9216 1110 / 960; cross-attention to 77 keys, 16 x 4096, 8 heads 48 / 45. The matrix pipe is busy
 // 80 % of the cycles and the clock falls from 2.4 to 1.6 - 1.9 GHz (with zeros as input it stays at 2.3): what bounds it
 // now is power.
+// Scores out of range (us; this kernel / the plain form alone, every workgroup with such a score done again with exact maxima /
+// a kernel with a running maximum throughout; d = 64, 5 x 9216 tokens, 5 heads | d = 40, 4 x 4096, 8 heads, both with the
+// pass that transposes V): deviation 1.4 in log2 units 562, 556, 663 | 128, 129, 150; 15: 606, 551, 684 | 141, 118, 150; 40:
+// 612, 1542, 673 | 138, 320, 147; 150: 638, 1501, 647 | 157, 303, 142; 500: 688, 1476, 643 | 173, 298, 143; all near -240:
+// 594, 1467, 660 | 131, 294, 131; one late key at +150: 1096, 1520, 653 | 224, 304, 132.
+// The limits: kNear + a few deviations of ordinary scores stay below kHigh, and kRaise leaves exp2's range (2^128) room for
+// values and sums. With kNear = 40 and kHigh = 2^40 scores of deviation 15 took 619, with 60 and 2^80, where more wavefronts
+// meet a score beyond kRaise in the plain form, 717.
 // NQT: 32-query tiles per wavefront. Two share every fragment read; one is for launches that would otherwise leave
 // compute units without a workgroup.
 template <int D, int NQT, bool PRE, bool XA>
@@ -355,10 +367,13 @@ __global__ __launch_bounds__(256, 2) void spatial_attn_ring_kernel(const bf16_t*
   constexpr int NE = NQT * 16;              // exponentials of a substep
   constexpr int NF = KSTEPS + 2 * DM;       // LDS fragments of a substep, NQT MFMAs each
   constexpr int kAhead = 2 * DM < 6 / NQT ? 2 * DM : 6 / NQT;
+  constexpr float kNear = 52.f, kRaise = 100.f, kAbove = 16.f;  // (see above)
+  constexpr float kHigh = 0x1p60f, kBroken = 0x1p99f;
+  enum Sweep { kPlain, kSafe, kExact };
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   auto kl = [&](int b) { return smem + b * SLOT; };
   auto vl = [&](int b) { return smem + b * SLOT + KSLOT; };
-  int* redo_flag = reinterpret_cast<int*>(smem + NB * SLOT);
+  int* flags = reinterpret_cast<int*>(smem + NB * SLOT);  // sweep again: every query safely; some with their exact maxima
 
   const int tid = threadIdx.x, lane = tid & 63, wid = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lq = lane & 31, hh = lane >> 5;
@@ -390,7 +405,7 @@ __global__ __launch_bounds__(256, 2) void spatial_attn_ring_kernel(const bf16_t*
       *reinterpret_cast<uint4*>(vl(b) + D * 128 + p * 16) = uint4{v, v, v, v};
     }
   }
-  if (tid == 0) *redo_flag = 0;
+  if (tid < 2) flags[tid] = 0;
 
   // ---- global -> LDS. K: packet p of a stage is (key p / KP, slot p % KP); V^T: (row p / 8, slot p % 8). Buffer loads,
   // whose bounds check delivers zeros for the slots of K beyond d (a copy of anything there could meet the zeros of q with
@@ -460,12 +475,15 @@ __global__ __launch_bounds__(256, 2) void spatial_attn_ring_kernel(const bf16_t*
   const int nstage = (TK + kKeys - 1) / kKeys;
   f32x16 o[NQT][DM];
   float lsum[NQT][2];
-  float m[NQT];  // second sweep only: the exact maxima, in the units of the exponent
-#pragma unroll
-  for (int t = 0; t < NQT; ++t) m[t] = 0.f;
+  float m[NQT];      // what the exponents subtract, in their own units (log2)
+  bool safe, broken;  // this wavefront subtracts it; a score passed kRaise while it did not
 
-  auto sweep = [&](auto safe_c) __attribute__((always_inline)) {
-    constexpr bool SAFE = decltype(safe_c)::value;
+  // the denominator, as far as this lane holds it
+  auto so_far = [&](int t) {
+    if constexpr (ROWSUM) return o[t][D / 32][(D % 32 / 8) * 4 + D % 4];  // (the other half of the lanes: a row of zeros)
+    else return fmaxf(lsum[t][0], lsum[t][1]);
+  };
+  auto sweep = [&](Sweep kind) __attribute__((always_inline)) {
     f32x16 sA[NQT], sB[NQT];     // scores: of this substep, of the next
     Frag pA[NQT][2], pB[NQT][2]; // probabilities as operands: of this substep, of the one before
     Frag kf[KSTEPS], vf[2][DM];
@@ -477,12 +495,14 @@ __global__ __launch_bounds__(256, 2) void spatial_attn_ring_kernel(const bf16_t*
 #pragma unroll
       for (int mt = 0; mt < DM; ++mt) o[t][mt] = zero16;
     }
+    auto exponent = [&](float x, int t) { return PRE ? x - m[t] : fmaf(x, scale_log2e, -m[t]); };
     // O^T += (V^T of the 32 keys (vp, up)) pp; sn = K Q^T of the keys (ks, us); pc = probabilities of sc (first key key0).
     // The fragment of group g (NQT MFMAs each: V fragments, then K fragments) is requested kAhead groups before its use,
     // the first V fragments of the next substep, (vn, un), in the last groups of this one.
-    auto substep = [&](f32x16 (&sn)[NQT], f32x16 (&sc)[NQT], Frag (&pc)[NQT][2], Frag (&pp)[NQT][2], const unsigned char* vp, int up,
+    auto substep = [&](auto safe_c, f32x16 (&sn)[NQT], f32x16 (&sc)[NQT], Frag (&pc)[NQT][2], Frag (&pp)[NQT][2], const unsigned char* vp, int up,
                        const unsigned char* ks, int us, const unsigned char* vn, int un, int key0)
                        __attribute__((always_inline)) {
+      constexpr bool SAFE = decltype(safe_c)::value;
       if (key0 + 32 > TK) {  // uniform: some keys lie beyond the sequence
         int kb0 = key0 + 4 * hh;
         asm volatile("" : "+v"(kb0));  // (left alone the compiler computes the sixteen indexes outside the branch)
@@ -492,6 +512,37 @@ __global__ __launch_bounds__(256, 2) void spatial_attn_ring_kernel(const bf16_t*
 #pragma unroll
           for (int t = 0; t < NQT; ++t)
             if (gone) sc[t][r] = -INFINITY;
+        }
+      }
+      if constexpr (SAFE) {
+        float hi[NQT];
+        bool any = false;
+#pragma unroll
+        for (int t = 0; t < NQT; ++t) {
+          hi[t] = sc[t][0];
+#pragma unroll
+          for (int r = 1; r < 16; ++r) hi[t] = fmaxf(hi[t], sc[t][r]);
+          hi[t] = exponent(hi[t], t);
+          any |= hi[t] > kRaise;
+        }
+        if (__builtin_amdgcn_ballot_w64(any) != 0) {  // some query's m is raised, and what it has summed up is scaled
+#pragma unroll
+          for (int t = 0; t < NQT; ++t) {
+            hi[t] = fmaxf(hi[t], __shfl_xor(hi[t], 32, 64));
+            const float k = hi[t] > kRaise ? rintf(hi[t]) + kAbove : 0.f;
+            const int by = -(int)fminf(k, 4096.f);  // (a factor 2^-k could be too small for a float where its products are not)
+            m[t] += k;
+            lsum[t][0] = ldexpf(lsum[t][0], by);
+            lsum[t][1] = ldexpf(lsum[t][1], by);
+#pragma unroll
+            for (int mt = 0; mt < DM; ++mt)
+#pragma unroll
+              for (int r = 0; r < 16; ++r) o[t][mt][r] = ldexpf(o[t][mt][r], by);
+#pragma unroll
+            for (int st = 0; st < 2; ++st)
+#pragma unroll
+              for (int e = 0; e < 8; ++e) pp[t][st][e] = static_cast<bf16_t>(ldexpf(static_cast<float>(pp[t][st][e]), by));
+          }
         }
       }
       static_for<0, NM>([&](auto m_c) __attribute__((always_inline)) {
@@ -521,10 +572,7 @@ __global__ __launch_bounds__(256, 2) void spatial_attn_ring_kernel(const bf16_t*
           float p[2];
 #pragma unroll
           for (int k = 0; k < 2; ++k) {
-            float x = sc[t][r + k];
-            if (SAFE) x = PRE ? x - m[t] : fmaf(x, scale_log2e, -m[t]);
-            else if (!PRE) x *= scale_log2e;
-            p[k] = __builtin_amdgcn_exp2f(x);
+            p[k] = __builtin_amdgcn_exp2f(SAFE ? exponent(sc[t][r + k], t) : PRE ? sc[t][r + k] : sc[t][r + k] * scale_log2e);
             pc[t][r / 8][r % 8 + k] = static_cast<bf16_t>(p[k]);
           }
           // the denominator sums the probabilities as rounded, like the ones row does: what one key contributes to
@@ -568,18 +616,58 @@ __global__ __launch_bounds__(256, 2) void spatial_attn_ring_kernel(const bf16_t*
       constexpr int kk = decltype(i)::value / NQT, t = decltype(i)::value % NQT;
       sA[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[kk], qf[t][kk], kk ? sA[t] : zero16, 0, 0, 0);
     });
+    if (kind != kExact) {
+      bool far = kind == kSafe;
+#pragma unroll
+      for (int t = 0; t < NQT; ++t) {
+        float hi = -INFINITY;
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+          if (!beyond(0, r)) hi = fmaxf(hi, sA[t][r]);
+        hi = fmaxf(hi, __shfl_xor(hi, 32, 64)) * (PRE ? 1.f : scale_log2e);
+        m[t] = fabsf(hi) > kNear && fabsf(hi) < INFINITY ? rintf(hi) : 0.f;
+        far |= m[t] != 0.f;
+      }
+      safe = __builtin_amdgcn_ballot_w64(far) != 0;
+    } else {
+      safe = true;
+    }
+    broken = false;
     static_for<0, kAhead>([&](auto g) __attribute__((always_inline)) {
       vf[decltype(g)::value / DM][decltype(g)::value % DM] = vfrag(vl(NB - 1), 1, decltype(g)::value / DM, decltype(g)::value % DM);
     });
     // (Behind the last stage the K requests and scores are of no stage: in bounds, never used.)
-    for (int s = 0; s < nstage; ++s) {
+    int s = 0;
+    auto stage = [&](auto safe_c) __attribute__((always_inline)) {
       if (s) stage_barrier();
       if (s + 2 < nstage) issue(s + 2);
       const int b = s & (NB - 1), bn = (s + 1) & (NB - 1), bp = (s - 1) & (NB - 1);
       if (s && s * kKeys + kKeys > TK) clear_beyond(s, b);
-      substep(sB, sA, pA, pB, vl(bp), 1, kl(b), 1, vl(b), 0, s * kKeys);
-      substep(sA, sB, pB, pA, vl(b), 0, kl(bn), 0, vl(b), 1, s * kKeys + 32);
+      substep(safe_c, sB, sA, pA, pB, vl(bp), 1, kl(b), 1, vl(b), 0, s * kKeys);
+      substep(safe_c, sA, sB, pB, pA, vl(b), 0, kl(bn), 0, vl(b), 1, s * kKeys + 32);
+    };
+    if (!safe) for (; s < nstage; ++s) {
+      stage(std::false_type{});
+      bool high = false;
+#pragma unroll
+      for (int t = 0; t < NQT; ++t) high |= so_far(t) > kHigh;
+      if (__builtin_expect(__builtin_amdgcn_ballot_w64(high) != 0, 0)) {
+        safe = true;  // (from the next stage on)
+        ++s;
+#pragma unroll
+        for (int t = 0; t < NQT; ++t) {
+          broken |= so_far(t) > kBroken;
+          if constexpr (ROWSUM) {  // (the last substep's are not in it yet)
+#pragma unroll
+            for (int st = 0; st < 2; ++st)
+#pragma unroll
+              for (int e = 0; e < 8; ++e) broken |= static_cast<float>(pB[t][st][e]) > kBroken;
+          }
+        }
+        break;
+      }
     }
+    for (; s < nstage; ++s) stage(std::true_type{});
     const unsigned char* vlast = vl((nstage - 1) & (NB - 1));
     static_for<0, 2 * DM>([&](auto i) __attribute__((always_inline)) {
       constexpr int st = decltype(i)::value / DM, mt = decltype(i)::value % DM;
@@ -617,29 +705,42 @@ __global__ __launch_bounds__(256, 2) void spatial_attn_ring_kernel(const bf16_t*
       }
   };
 
-  sweep(std::false_type{});
-  bool redo[NQT], any = false;
+  bool redo[NQT];
+  for (Sweep kind = kPlain;;) {  // (every decision here is the workgroup's)
+    sweep(kind);
+    if (kind == kPlain) {
 #pragma unroll
-  for (int t = 0; t < NQT; ++t) {
-    const float l = denominator(t);
-    float worst = 0.f;  // NaN or infinite if any element is
+      for (int t = 0; t < NQT; ++t) broken |= !safe && so_far(t) > kBroken;
+      if (__builtin_amdgcn_ballot_w64(broken) != 0 && lane == 0) flags[0] = 1;
+      __syncthreads();
+      if (flags[0]) {
+        kind = kSafe;
+        continue;
+      }
+    }
+    bool any = false;
 #pragma unroll
-    for (int mt = 0; mt < DM; ++mt)
+    for (int t = 0; t < NQT; ++t) {
+      const float l = denominator(t);
+      float worst = 0.f;  // NaN or infinite if any element is
 #pragma unroll
-      for (int r = 0; r < 16; ++r) worst = fmaf(o[t][mt][r], 0.f, worst);
-    int bad = !(l >= 0x1p-90f && l <= 0x1p110f) || worst != 0.f;
-    bad |= __shfl_xor(bad, 32, 64);
-    redo[t] = bad && qblk + t * 32 + lq < nq;
-    any |= redo[t];
-    if (!bad) store(t, 1.f / l);
-  }
-  if (__builtin_amdgcn_ballot_w64(any) != 0 && lane == 0) *redo_flag = 1;
-  __syncthreads();
-  if (*redo_flag) {
-    // exact maxima of every query, then the sweep again with them
-    float mx[NQT];
+      for (int mt = 0; mt < DM; ++mt)
 #pragma unroll
-    for (int t = 0; t < NQT; ++t) mx[t] = -INFINITY;
+        for (int r = 0; r < 16; ++r) worst = fmaf(o[t][mt][r], 0.f, worst);
+      int bad = !(l >= 0x1p-90f && l <= 0x1p125f) || worst != 0.f;
+      bad |= __shfl_xor(bad, 32, 64);
+      if (kind == kExact ? redo[t] : !bad) store(t, 1.f / l);
+      redo[t] = bad && qblk + t * 32 + lq < nq;
+      any |= redo[t];
+    }
+    if (kind == kExact) break;
+    if (__builtin_amdgcn_ballot_w64(any) != 0 && lane == 0) flags[1] = 1;
+    __syncthreads();
+    if (!flags[1]) break;
+    kind = kExact;
+    // the exact maxima of every query, for a sweep with them
+#pragma unroll
+    for (int t = 0; t < NQT; ++t) m[t] = -INFINITY;
     for (int s = 0; s < nstage; ++s) {
       __syncthreads();
       issue(s);
@@ -655,18 +756,12 @@ __global__ __launch_bounds__(256, 2) void spatial_attn_ring_kernel(const bf16_t*
           for (int kk = 0; kk < KSTEPS; ++kk) M::mma(kfrag(kl(s & (NB - 1)), u, kk), qf[t][kk], sc);
 #pragma unroll
           for (int r = 0; r < 16; ++r)
-            if (!beyond(s * kKeys + 32 * u, r)) mx[t] = fmaxf(mx[t], sc[r]);
+            if (!beyond(s * kKeys + 32 * u, r)) m[t] = fmaxf(m[t], sc[r]);
         }
     }
 #pragma unroll
-    for (int t = 0; t < NQT; ++t) m[t] = fmaxf(mx[t], __shfl_xor(mx[t], 32, 64)) * (PRE ? 1.f : scale_log2e);
+    for (int t = 0; t < NQT; ++t) m[t] = fmaxf(m[t], __shfl_xor(m[t], 32, 64)) * (PRE ? 1.f : scale_log2e);
     __syncthreads();
-    sweep(std::true_type{});
-#pragma unroll
-    for (int t = 0; t < NQT; ++t) {
-      const float l = denominator(t);
-      if (redo[t]) store(t, 1.f / l);
-    }
   }
 }
 
