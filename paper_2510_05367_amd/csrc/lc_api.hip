@@ -190,14 +190,13 @@ Plan make_plan(const lc_config& g, int frame_chunk, int token_chunk, int eta, in
   p.off_slots = off; off += p.slot_bytes * g.dev_slots;
   // GroupNorm partial sums [frame][split][channel][2]. The kernels that produce a normalised tensor
   // also write its partials, with their own split geometry (32-row tiles of the linear kernels,
-  // 32-pixel quarter tiles of the 3x3 kernels); the stand-alone statistics kernel uses 64-row splits.
+  // 32-pixel quarter tiles of the 3x3 kernels; those of the first convolution live in the chunk scratch); the stand-alone statistics kernel uses 64-row splits.
   // partH: the tensor at hand inside a frame chunk (also the half-resolution one of the deep stand-in);
   // partT / partU: input of the temporal block / skip input of the up block, written chunk by chunk
   // for all frames; partD: the cached deep feature, one region per device slot (kept while the slot
   // does not change) plus one for the single-operator entry points.
   size_t sp = std::max((size_t)stat_splits((int)T), (size_t)conv_stat_splits(g.H, g.W));
   if (T % 32 == 0) sp = std::max(sp, (size_t)(T / 32));
-  if (g.dtype == kBF16) sp = std::max(sp, (size_t)conv_in_splits(g.H, g.W));
   const size_t ph = std::max(sp * g.C, (size_t)stat_splits((int)(T / 4)) * g.C_deep);
   p.off_partT = off; off += align_up((size_t)N * sp * g.C * 2 * sizeof(float));
   p.off_partU = off; off += align_up((size_t)N * sp * g.C * 2 * sizeof(float));
@@ -700,7 +699,10 @@ lc_status run_step_lanes(lc_ctx* c, const void* x, void* eps, int slot, bool ful
     // for the GroupNorm that reads it next (where its tiles fit the frame; else they are computed apart)
     StatRef st{nullptr, 0};
     {
-      lc_status s = conv_in_run(c, (const char*)x + (size_t)n0 * g.C_lat * T * es, cur, nf, partH(c), &st);
+      // (the first convolution's own go where q,k,v will be: its splits follow the image rows, and of narrow frames there
+      // are more than partH holds - 8 bytes for every 2 columns at most, where q,k,v take 12 a pixel)
+      float* part = (float*)(ws + (size_t)pc * C * 4);
+      lc_status s = conv_in_run(c, (const char*)x + (size_t)n0 * g.C_lat * T * es, cur, nf, part, &st);
       if (s != LC_OK) return s;
     }
     for (int i = 0; i < g.n_res; ++i) {

@@ -112,6 +112,22 @@ def test_footprint_model_scales_with_chunk_not_with_frames():
     assert lcb.lc_workspace_bytes(s, 0, 0) < 4e9
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("H,W", [(64, 4), (64, 2), (36, 60), (40, 36), (32, 32)])
+def test_stage_footprint_of_ragged_and_narrow_frames(H, W, dtype):
+    """What the stage keeps, spelled out: a kernel with statistics of its own (the first convolution's, one split per row of
+    an image and 32 columns) must not make it more than that."""
+    cfg = synth.CONFIGS["animatediff"].with_(H=H, W=W, dtype=dtype)
+    c = lcb.make_config(cfg)
+    es, N, T, C, Cd = (2 if dtype == "bf16" else 4), cfg.N, cfg.T, cfg.C, cfg.C_deep
+    splits = max(-(-T // 64), 4 * -(-W // 16) * -(-H // 8), T // 32 if T % 32 == 0 else 0)
+    sums = 2 * N * splits * C * 8 + N * max(splits * C, -(-(T // 4) // 64) * Cd) * 8  # two tensors of all frames, one at hand
+    deep = c.dev_slots * lcb.lc_cache_entry_bytes(c) + (c.dev_slots + 1) * N * -(-(T // 4) // 64) * Cd * 8
+    scale_shift = 4 * N * (C + Cd) * 4
+    chunk = max(N * T * C * 4 + (3 * N * T * C + N * C * (-(-T // 64) * 64)) * es, 4 * C * N * T * es, N * (T // 4) * Cd * 4)
+    assert lcb.lc_workspace_bytes(c, 0, 0) <= N * T * C * 4 + sums + deep + scale_shift + chunk + (1 << 14)  # (256-byte rounding)
+
+
 def test_token_chunk_bounds_the_temporal_pass():
     cfg = synth.CONFIGS["svdxt"]
     c = lcb.make_config(cfg)

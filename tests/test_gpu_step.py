@@ -344,11 +344,13 @@ def test_profiling_brackets_count_launches():
         stage.close()
 
 
-@pytest.mark.parametrize("F,H,W,C,heads,head_dim", [(5, 10, 14, 320, 8, 40), (9, 6, 34, 320, 5, 64), (5, 10, 18, 64, 1, 64), (3, 16, 18, 64, 2, 32)])
+@pytest.mark.parametrize("F,H,W,C,heads,head_dim", [(5, 10, 14, 320, 8, 40), (9, 6, 34, 320, 5, 64), (5, 10, 18, 64, 1, 64), (3, 16, 18, 64, 2, 32),
+                                                    (7, 24, 4, 320, 8, 40), (5, 32, 2, 64, 1, 64)])
 def test_ragged_frames_in_bf16(F, H, W, C, heads, head_dim):
     """Frames that are no whole 32-row tiles, image rows that are no whole 32-pixel or 16-pixel segments: GroupNorm
     applied in a pass of its own and the streamed linear kernel with V^T in its epilogue (C = 320), short segments of
-    the first convolution, partial tiles of the last one. Against the oracle, and bit for bit for chunks that divide
+    the first convolution, partial tiles of the last one; frames so narrow that the first convolution has more splits of
+    statistics than rows in fours. Against the oracle, and bit for bit for chunks that divide
     the frames evenly, with a remainder, and not at all."""
     cfg = synth.StageConfig(f"ragged_{C}_{H}x{W}", B=1, F=F, H=H, W=W, C_lat=4, C=C, C_deep=2 * C, groups=32, n_res=1, heads=heads,
                             head_dim=head_dim, dtype="bf16")
