@@ -318,7 +318,7 @@ UPlan make_uplan(const lc_unet_config& g, int frame_chunk) {
   // that the convolutions write beside their output, times the widest tensor of the level
   auto splits_of = [&](int lvl) {
     const int H = g.H >> lvl, W = g.W >> lvl;
-    return (int64_t)std::max({stat_splits(H * W), conv_stat_splits(H, W), (H * W + 31) / 32, lvl ? 0 : conv_in_splits(H, W)});
+    return (int64_t)std::max({stat_splits(H * W), conv_stat_splits(H, W), (H * W + 31) / 32});
   };
   const int64_t splits_c = std::max({splits_of(0) * (g.C + g.C1), splits_of(1) * std::max(g.C1 + g.C2, g.C), splits_of(2) * std::max(g.C1, g.C2)});
   // the same for what one block hands to the next: a block's output of all frames
@@ -723,15 +723,18 @@ lc_status run_step(lc_unet* c, const void* x, const void* temb, const void* cond
   float *pa = (float*)(c->arena + p.off_parta), *pb = (float*)(c->arena + p.off_partb);
   const int cs0 = conv_stat_splits(H, W), cs1 = conv_stat_splits(H / 2, W / 2), cs2 = conv_stat_splits(H / 4, W / 4);
   // ---- shallow down: s = TT(ST(RB(conv_in(x))))
+  // (the first convolution's partial sums, one split per image row and 32 columns, are more than `pa` holds where frames are
+  // narrow: they go to a map that is free until its block is done)
   Stats cin_st{nullptr, 0};
+  float* pc = m1;
   LCU_TRY(frame_chunks(c, 0, [&](int n0, int nc) -> lc_status {
     const char* xc = (const char*)x + (size_t)n0 * g.C_lat * P * es;
     float* y = m0 + (size_t)n0 * P * g.C;
     // the tiled kernel where the shape allows it (a property of the configuration, never of the chunk)
-    hipError_t e = c->cin_wp ? launch_conv_in_tile(c->cs, g.dtype, xc, c->cin_wp, c->cin_b, y, pa + (size_t)n0 * conv_in_splits(H, W) * g.C * 2, nc, H, W,
+    hipError_t e = c->cin_wp ? launch_conv_in_tile(c->cs, g.dtype, xc, c->cin_wp, c->cin_b, y, pc + (size_t)n0 * conv_in_splits(H, W) * g.C * 2, nc, H, W,
                                                    g.C_lat, g.C, Win{0, 0, 0, 0})
                              : hipErrorNotSupported;
-    if (e == hipSuccess) { cin_st = Stats{pa, conv_in_splits(H, W)}; return LC_OK; }
+    if (e == hipSuccess) { cin_st = Stats{pc, conv_in_splits(H, W)}; return LC_OK; }
     if (e != hipErrorNotSupported) LCU_HIP(c, e);
     LCU_HIP(c, launch_conv_in(c->cs, g.dtype, xc, y, nc, H, W, g.C_lat, g.C, c->cin_w, c->cin_b));
     return LC_OK;

@@ -181,6 +181,11 @@ def test_unet_config_checks_and_footprint_without_a_gpu():
         assert abs(inside[fc] - (fc - 1) * inside[2]) <= 1 << 14, fc
     assert by_chunk[4] < 0.6 * ws
     assert lcb.lc_unet_chunk_workspace_bytes(c, -1) == 0
+    # narrow frames: no more per pixel than wide ones but for what is kept per frame or comes in whole tiles (the partial
+    # sums of 16 x 8 pixel tiles: here a quarter of a tile's columns are pixels)
+    wide, narrow = (lcb.lc_unet_workspace_bytes(lcb.make_unet_config(cfg.with_(H=h, W=w))) for h, w in ((16, 16), (64, 4)))
+    sums = 4 * 8 * (64 // 8) * cfg.N * (cfg.C + cfg.C1 + 2 * cfg.C)   # three buffers, the first of the concatenated width
+    assert narrow - wide <= sums
     for field, value in [("H", 6), ("C", 100), ("C1", 4096), ("groups", 7), ("head_dim", 24), ("C_lat", 17), ("ff_mult", 5), ("F", 0),
                          ("F", 64), ("ctx_dim", 100), ("dev_slots", 0), ("host_slots", 65), ("gn_eps", 0.0), ("ln_eps", -1.0)]:
         bad = lcb.make_unet_config(cfg)

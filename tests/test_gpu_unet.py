@@ -20,6 +20,7 @@ SMALL_BF16 = synth.UnetConfig("small_bf16", B=2, F=8, H=24, W=16, C_lat=4, C=64,
 # fp32 with 2 batch elements (per-element time embedding and conditioning) and head_dim 16
 SMALL_F32 = synth.UnetConfig("small_f32", B=2, F=3, H=8, W=12, C_lat=3, C=64, C1=64, C2=128, groups=16, head_dim=16,
                              ctx_len=5, ctx_dim=64, temb_dim=40, dtype="f32", ff_mult=2)
+NARROW_BF16 = SMALL_BF16.with_(name="narrow_bf16", H=32, W=4)     # more splits of the first convolution than other statistics have
 MID = synth.UNETS["mid"]
 
 
@@ -67,7 +68,7 @@ def run_case(cfg, odtype=np.float64, sharp=4.0, chain=False, frame_chunk=None):
         net.close()
 
 
-@pytest.mark.parametrize("cfg", [TINY, SMALL_F32, SMALL_BF16], ids=lambda c: c.name)
+@pytest.mark.parametrize("cfg", [TINY, SMALL_F32, SMALL_BF16, NARROW_BF16], ids=lambda c: c.name)
 def test_steps_match_oracle(cfg):
     run_case(cfg)
 
@@ -80,7 +81,7 @@ def test_chunked_steps_match_oracle(cfg, frame_chunk):
     run_case(cfg, frame_chunk=frame_chunk)
 
 
-@pytest.mark.parametrize("cfg", [SMALL_F32, SMALL_BF16], ids=lambda c: c.name)
+@pytest.mark.parametrize("cfg", [SMALL_F32, SMALL_BF16, NARROW_BF16], ids=lambda c: c.name)
 def test_chunked_equals_unchunked_bitwise(cfg):
     """Every chunk setting gives the normal step's eps, the cached feature and the cache step's eps of the run over all
     frames at once, bit for bit; the cached entries survive a change of the setting."""
