@@ -349,9 +349,6 @@ UPlan make_uplan(const lc_unet_config& g, int frame_chunk) {
   p.off_h = take((size_t)hid * 4);
   p.off_sc = take((size_t)hid * 4);
   p.off_xb = take(g.dtype == kBF16 ? (size_t)cat * es : 0);
-  // (room for one upsampled map, which no kernel needs any more: the footprint by chunk is part of the interface, and the
-  // share of it that scales with the chunk stays what callers have sized their chunks by)
-  take((size_t)std::max(nc1 * P1 * g.C2, nc0 * P * g.C1) * 4);
   const size_t end_rb = off;
   // ---- one chunk, transformer blocks
   off = chunk0;

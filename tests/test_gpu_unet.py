@@ -146,7 +146,10 @@ def test_benchmark_size_chunked_equals_unchunked():
     (f0, c0, d0, b0), (f1, c1, d1, b1) = results
     assert bool(torch.isfinite(f0).all())
     assert torch.equal(f1, f0) and torch.equal(c1, c0) and torch.equal(d1, d0)
-    assert b1 < 0.6 * b0
+    # the chunk's workspace lacks what 28 more frames take inside a residual block (concatenated input and its bf16 copy,
+    # hidden map, shortcut), give or take the rounding of each buffer
+    per_frame = cfg.H * cfg.W * ((cfg.C + cfg.C1) * (4 + 2) + 2 * cfg.C * 4)
+    assert abs((b0 - b1) - 28 * per_frame) < 1 << 14
 
 
 @pytest.mark.slow
