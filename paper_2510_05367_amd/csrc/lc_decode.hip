@@ -100,15 +100,18 @@ lc_status check_dcfg(lc_decoder* d, const lc_decoder_config* g) {
 // convolution and of every level's upsampling convolution, `b` the residual blocks', so `b` need not hold the last and
 // largest map (the upsampled input of a convolution exists nowhere). Then GroupNorm partial sums and scale / shift, a
 // unit scale and a zero shift (the convolution after the upsampling takes its input as it is), and the attention
-// block's q,k rows, V^T and normalised rows / output at the latent resolution. The footprint is that of two maps of the
-// largest stage with its input upsampled (what a pass with a separate upsampling would hold); where the scratch of two
-// passes fits into it, as for widths that fall from level to level, alternate slices run on two streams.
+// block's q,k rows, V^T and normalised rows / output at the latent resolution. The partial sums share their memory with
+// the latter: what the block normalises with is folded into scale / shift before q,k,v are written, and nothing behind it
+// reads them. Where the scratch of two passes takes no more than two maps of the largest stage with its input upsampled,
+// partial sums and attention rows apart (what a pass with a separate upsampling held, as for widths that fall from level to
+// level), there are two lanes and alternate slices run on two streams; else one, and no more memory than it needs.
 DPlan make_dplan(const lc_decoder_config& g, int n) {
   DPlan p;
   const size_t es = dtype_size(g.dtype);
   const int64_t P0 = (int64_t)g.H * g.W;
-  int64_t elems_a = P0 * g.widths[0], elems_b = elems_a, elems_up = elems_a, splits_c = 0;
-  int maxC = g.widths[0];
+  const int C0 = g.widths[0];
+  int64_t elems_a = P0 * C0, elems_b = elems_a, elems_up = elems_a, splits_c = 0, rows_c = 0;
+  int maxC = C0;
   for (int l = 0; l <= g.levels; ++l) {
     const int H = g.H << l, W = g.W << l;
     const int64_t e = P0 * ((int64_t)1 << 2 * l) * g.widths[l];
@@ -117,6 +120,7 @@ DPlan make_dplan(const lc_decoder_config& g, int n) {
     elems_up = std::max({elems_up, e, l ? P0 * ((int64_t)1 << 2 * l) * g.widths[l - 1] : (int64_t)0});
     const int splits = std::max({stat_splits(H * W), conv_stat_splits(H, W), l ? 0 : conv_in_splits(H, W)});
     splits_c = std::max(splits_c, (int64_t)splits * g.widths[l]);
+    rows_c = std::max(rows_c, (int64_t)stat_splits(H * W) * g.widths[l]);
     maxC = std::max(maxC, g.widths[l]);
   }
   size_t off = 0;
@@ -126,17 +130,22 @@ DPlan make_dplan(const lc_decoder_config& g, int n) {
   p.lane_off = off;
   p.off_a = take((size_t)n * elems_a * 4);
   p.off_b = take((size_t)n * elems_b * 4);
-  p.off_part = take((size_t)n * splits_c * 2 * 4);
   p.off_scale = take((size_t)n * maxC * 4);
   p.off_shift = take((size_t)n * maxC * 4);
-  const int C0 = g.widths[0];
-  p.off_qkv = take((size_t)n * P0 * 2 * C0 * es);
-  p.off_vt = take((size_t)n * C0 * attn_tp((int)P0) * es);
-  p.off_ao = take((size_t)n * P0 * C0 * es);
+  p.off_part = take((size_t)n * splits_c * 2 * 4);
+  const size_t end_part = off;
+  off = p.off_part;
+  const int64_t row_bytes = P0 * C0 * (int64_t)es, vt_bytes = (int64_t)C0 * attn_tp((int)P0) * (int64_t)es;
+  p.off_qkv = take((size_t)n * 2 * row_bytes);
+  p.off_vt = take((size_t)n * vt_bytes);
+  p.off_ao = take((size_t)n * row_bytes);
+  off = std::max(off, end_part);
   p.lane_stride = off - p.lane_off;
-  const size_t maps = (size_t)n * (2 * elems_up - elems_a - elems_b) * 4;  // beyond what one pass holds
-  p.lanes = maps >= p.lane_stride ? 2 : 1;
-  p.total = off + maps;
+  // (per frame: the number of lanes is a property of the configuration, never of the slice)
+  const int64_t lane = (elems_a + elems_b) * 4 + 2 * maxC * 4 + std::max(splits_c * 8, 3 * row_bytes + vt_bytes);
+  const int64_t apart = 2 * elems_up * 4 + rows_c * 8 + 2 * maxC * 4 + 4 * row_bytes + vt_bytes;
+  p.lanes = 2 * lane <= apart ? 2 : 1;
+  p.total = p.lane_off + p.lanes * p.lane_stride;
   return p;
 }
 

@@ -161,6 +161,31 @@ def test_decoder_config_checks_and_footprint_without_a_gpu():
         lcb.lc_decoder_check_config(lcb.make_decoder_config(synth.DECODERS[name]))
 
 
+@pytest.mark.parametrize("widths", [(64,), (512,), (64, 64), (64, 64, 64, 64), (64, 128, 256), (1024, 64), (64, 1024), (320, 320, 192, 64)])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_decoder_footprint_bounds(widths, dtype):
+    """No more than a pass with a separate upsampling holds (two maps of the largest stage with its upsampled input, 64-row
+    partial sums, q, k, v, V^T and the attention's output), whatever the kernels write beside their outputs; and where that
+    has no room for two slices side by side, no more than one takes."""
+    up = lambda v, m: -(-v // m) * m
+    for H, W in ((8, 8), (20, 36), (64, 12), (40, 56), (64, 64)):
+        cfg = synth.DECODERS["animatediff"].with_(N=7, H=H, W=W, widths=widths, heads=widths[0] // 64, head_dim=64, dtype=dtype)
+        es, P, L, C0 = (2 if dtype == "bf16" else 4), H * W, len(widths) - 1, widths[0]
+        maps = [P * 4 ** l * widths[l] for l in range(L + 1)]
+        ups = [P * 4 ** l * widths[l - 1] for l in range(1, L + 1)]
+        sums = max(-(-P * 4 ** l // 64) * widths[l] for l in range(L + 1)) * 8
+        tiles = max(4 * up(H << l, 8) // 8 * up(W << l, 16) // 16 * widths[l] for l in range(L + 1))
+        tiles = max(tiles, H * -(-W // 32) * C0) * 8
+        attn = (3 * P * C0 + C0 * up(P, 64)) * es
+        lane = (max(maps) + max(maps[:L] or maps)) * 4 + 2 * max(widths) * 4 + max(tiles, attn)
+        most = 2 * max(maps + ups) * 4 + sums + 4 * max(widths) * 4 + attn + P * C0 * es
+        for n in (1, 2, 7):
+            got = lcb.lc_decoder_workspace_bytes(lcb.make_decoder_config(cfg), n)
+            assert n * lane <= got <= n * most + (1 << 12), (H, W, n)
+            if 2 * lane > most:
+                assert got <= n * (lane + 2 * max(widths) * 4) + (1 << 12), (H, W, n)
+
+
 def test_unet_config_checks_and_footprint_without_a_gpu():
     cfg = synth.UNETS["sd15_video"]
     c = lcb.make_unet_config(cfg)

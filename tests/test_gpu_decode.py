@@ -52,8 +52,11 @@ def test_workspace_is_sized_by_the_slice():
     for n in (2, 4, 16):
         assert abs(lcb.lc_decoder_workspace_bytes(c, n) - n * one) <= 64 * 1024  # linear in the slice (alignment aside)
     assert lcb.lc_decoder_workspace_bytes(c, 0) == lcb.lc_decoder_workspace_bytes(c, 16) == lcb.lc_decoder_workspace_bytes(c, 99)
-    # one frame: two fp32 maps of the largest stage (the 512 x 512 x 192 upsampled input of the last convolution)
-    assert 2 * 512 * 512 * 192 * 4 <= one < 2 * 512 * 512 * 192 * 4 * 1.2
+    # one frame: no more than two fp32 maps of the largest stage with its upsampled input (512 x 512 x 192), which exists
+    # nowhere: instead the maps of two slices, decoded side by side, each with a map of the largest stage and one of the stage
+    # before it
+    big, before = 512 * 512 * AD.widths[-1] * 4, 256 * 256 * AD.widths[-2] * 4
+    assert 2 * (big + before) <= one <= 2 * 512 * 512 * 192 * 4
 
 
 def test_decoder_errors():
