@@ -2,8 +2,8 @@
 //
 // Spatial attention (tokens = the H*W positions of one frame) is a flash-style kernel (one for fp32 stages, one for
 // bf16 stages): one workgroup owns a block of queries of one (frame, head), walks the keys in tiles of 64 staged in
-// LDS and keeps a running max / sum per query, so the T x T score matrix never exists and the
-// kernel needs no workspace. Scores are produced transposed, S^T[key][query] = K Q^T, with
+// LDS and keeps per query what it has summed up and the offset its exponents subtract (fp32: a running maximum; bf16:
+// usually none), so the T x T score matrix never exists and the kernel needs no workspace. Scores are produced transposed, S^T[key][query] = K Q^T, with
 // 32x32 MFMA tiles: one lane then holds 16 keys of ONE query, so the softmax statistics are
 // in-lane plus a single cross-lane exchange, and the exponentials, packed to the storage type,
 // are directly the B operand of O^T[dim][query] += V^T[dim][key] P^T[key][query].
@@ -36,12 +36,13 @@ template <class T> __device__ __forceinline__ int vcol_inv(int c) { return vcol<
 // rounds them); `scale_log2e` is then 1.
 // XA (cross-attention): the keys are not the queries' own rows but rows [Tk] of stride ldk at kx, one set (with its
 // V^T) per group of kv_div consecutive frames; T_tok then counts the query tokens of a frame only.
-template <class T, int D, int NQT, bool PRE, bool XA = false>
-__global__ __launch_bounds__(256, 2) void spatial_attn_kernel(const T* __restrict__ qk, int ldq,
-                                                           const T* __restrict__ vt, int Tp, T* __restrict__ out,
+template <int D, bool PRE, bool XA = false>
+__global__ __launch_bounds__(256, 2) void spatial_attn_kernel(const float* __restrict__ qk, int ldq,
+                                                           const float* __restrict__ vt, int Tp, float* __restrict__ out,
                                                            int T_tok, int C, int q0, int nq, int qw, int qstride,
-                                                           float scale_log2e, const T* __restrict__ kx = nullptr,
+                                                           float scale_log2e, const float* __restrict__ kx = nullptr,
                                                            int ldk = 0, int Tk = 0, int kv_div = 1) {
+  typedef float T;
   typedef Mma32<T> M;
   constexpr int VEC = Vec16<T>::N;
   constexpr int DP = (D + M::K - 1) / M::K * M::K;  // contraction length of Q K^T, padded
@@ -82,7 +83,7 @@ __global__ __launch_bounds__(256, 2) void spatial_attn_kernel(const T* __restric
   const int ldkk = XA ? ldk : ld;
   const T* __restrict__ kb = XA ? kx + (int64_t)kvf * Tk * ldk + head * D : base + C;
   const T* __restrict__ vbase = vt + ((int64_t)kvf * C + head * D) * Tp;
-  const int qblk = qb * (4 * NQT * 32) + wid * (NQT * 32);  // first query number of this wavefront
+  const int qblk = qb * (4 * 32) + wid * 32;  // first query number of this wavefront
   auto token_of = [&](int qi) { const int r = qi / qw; return q0 + r * qstride + (qi - r * qw); };
 
   // zero both buffers once: K columns beyond D and V^T rows beyond D feed padded MFMA lanes
@@ -95,7 +96,7 @@ __global__ __launch_bounds__(256, 2) void spatial_attn_kernel(const T* __restric
   if (ROWSUM) {
     __syncthreads();
     for (int i = tid; i < 2 * kKeys; i += 256)
-      reinterpret_cast<T*>(&v_lds[i / kKeys][D * VROW])[i % kKeys] = from_f32<T>(1.f);
+      reinterpret_cast<T*>(&v_lds[i / kKeys][D * VROW])[i % kKeys] = 1.f;
   }
 
   // ---- staging: K packet i = tid + 256 j of a stage is (key i / PK, packet i % PK); V^T packet i is
@@ -142,28 +143,19 @@ __global__ __launch_bounds__(256, 2) void spatial_attn_kernel(const T* __restric
   };
 
   // ---- Q fragments (B operand of S^T = K Q^T): lane holds query lq, k-slots M::LK*hh + M::K*kk
-  typename M::Frag qf[NQT][KSTEPS];
+  const int qi = qblk + lq, q = token_of(qi);
+  typename M::Frag qf[KSTEPS];
 #pragma unroll
-  for (int t = 0; t < NQT; ++t) {
-    const int qi = qblk + t * 32 + lq;
-    const int q = token_of(qi);
-#pragma unroll
-    for (int kk = 0; kk < KSTEPS; ++kk) {
-      const int e = kk * M::K + hh * M::LK;
-      qf[t][kk] = (qi < nq && e < D) ? M::load(base + (int64_t)q * ld + e) : M::zero();
-    }
+  for (int kk = 0; kk < KSTEPS; ++kk) {
+    const int e = kk * M::K + hh * M::LK;
+    qf[kk] = (qi < nq && e < D) ? M::load(base + (int64_t)q * ld + e) : M::zero();
   }
-  f32x16 o[NQT][DM];
-  float m_run[NQT], l_run[NQT];  // running max (raw score units) and per-lane partial sum
+  f32x16 o[DM];
+  float m_run = -INFINITY, l_run = 0.f;  // running max (raw score units) and per-lane partial sum
 #pragma unroll
-  for (int t = 0; t < NQT; ++t) {
-    m_run[t] = -INFINITY;
-    l_run[t] = 0.f;
+  for (int mt = 0; mt < DM; ++mt)
 #pragma unroll
-    for (int mt = 0; mt < DM; ++mt)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) o[t][mt][r] = 0.f;
-  }
+    for (int r = 0; r < 16; ++r) o[mt][r] = 0.f;
   fetch_kv(0);
   __syncthreads();  // zero fill done
   stash_kv(0, 0);
@@ -176,7 +168,7 @@ __global__ __launch_bounds__(256, 2) void spatial_attn_kernel(const T* __restric
     if (st_i + 1 < nstage) fetch_kv(k0 + kKeys);
 
     // ---- S^T sub-tiles [32 keys][32 queries]
-    f32x16 sc[NQT][KT];
+    f32x16 sc[KT];
 #pragma unroll
     for (int kt = 0; kt < KT; ++kt) {
       typename M::Frag kf[KSTEPS];
@@ -184,125 +176,98 @@ __global__ __launch_bounds__(256, 2) void spatial_attn_kernel(const T* __restric
       for (int kk = 0; kk < KSTEPS; ++kk)
         kf[kk] = M::load(reinterpret_cast<const T*>(&k_lds[buf][(kt * 32 + lq) * KROW]) + kk * M::K + hh * M::LK);
 #pragma unroll
-      for (int t = 0; t < NQT; ++t) {
+      for (int r = 0; r < 16; ++r) sc[kt][r] = 0.f;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) sc[t][kt][r] = 0.f;
-#pragma unroll
-        for (int kk = 0; kk < KSTEPS; ++kk) M::mma(kf[kk], qf[t][kk], sc[t][kt]);
-      }
+      for (int kk = 0; kk < KSTEPS; ++kk) M::mma(kf[kk], qf[kk], sc[kt]);
     }
-#pragma unroll
-    for (int t = 0; t < NQT; ++t) {
-      // lane holds keys  k0 + kt*32 + 8*(r/4) + 4*hh + r%4  of query lq
-      if (tail) {
-        // (the key indices are built from a value the compiler cannot see through: left alone it hoists
-        // these 64 additions out of the branch and every stage pays for them)
-        int kbi = k0 + 4 * hh;
-        asm volatile("" : "+v"(kbi));
-#pragma unroll
-        for (int kt = 0; kt < KT; ++kt)
-#pragma unroll
-          for (int r = 0; r < 16; ++r)
-            if (kbi + kt * 32 + 8 * (r >> 2) + (r & 3) >= TK) sc[t][kt][r] = -INFINITY;
-      }
-      float mx = -INFINITY;
+    // lane holds keys  k0 + kt*32 + 8*(r/4) + 4*hh + r%4  of query lq
+    if (tail) {
+      // (the key indices are built from a value the compiler cannot see through: left alone it hoists
+      // these 64 additions out of the branch and every stage pays for them)
+      int kbi = k0 + 4 * hh;
+      asm volatile("" : "+v"(kbi));
 #pragma unroll
       for (int kt = 0; kt < KT; ++kt)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) mx = fmaxf(mx, sc[t][kt][r]);
-      // mx: over this lane's 16 keys of the query. The other half of the query's keys sits in lane l ^ 32; the
-      // exchange (a trip through LDS) is only made inside the rare branch below: whether ANY lane of the
-      // wavefront exceeds the margin is the same question asked of the per-lane and of the per-query maxima.
-      // The offset m subtracted in the exponent need not be the exact running maximum: any m gives the same
-      // softmax as long as exp2 stays in range, because the same m enters the probabilities, the denominator
-      // and the rescaling. So m is raised (and O^T, l rescaled) only when some query of the wavefront sees a
-      // score more than kLazy above its m (in log2 units: probabilities then reach at most 2^kLazy, harmless
-      // in fp32 and in bf16, which rounds relatively). With the exact maximum about 70 % of the 64-key stages
-      // took the rescaling branch for some lane; with the margin hardly any after the first. (A lane whose own
-      // score stays inside the margin keeps its m when the branch is taken for another: exp2(0) = 1 exactly.)
-      constexpr float kLazy = 8.f;
-      if (st_i == 0 || __builtin_amdgcn_ballot_w64((mx - m_run[t]) * scale_log2e > kLazy) != 0) {
-        mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-        const bool up = st_i == 0 || (mx - m_run[t]) * scale_log2e > kLazy;
-        const float m_new = up ? fmaxf(m_run[t], mx) : m_run[t];
-        const float alpha = __builtin_amdgcn_exp2f((m_run[t] - m_new) * scale_log2e);
-        m_run[t] = m_new;
-        if (!ROWSUM) l_run[t] *= alpha;
-#pragma unroll
-        for (int mt = 0; mt < DM; ++mt)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) o[t][mt][r] *= alpha;
-      }
-      const float mc = m_run[t] * scale_log2e;
-      typename M::Frag pf[KT][PSTEPS];
-      float ps = 0.f;
-#pragma unroll
-      for (int kt = 0; kt < KT; ++kt) {
-        float p[16];
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          p[r] = __builtin_amdgcn_exp2f(fmaf(sc[t][kt][r], scale_log2e, -mc));
-          if (!ROWSUM) ps += p[r];
-        }
-        if constexpr (sizeof(T) == 2) {
-#pragma unroll
-          for (int st = 0; st < PSTEPS; ++st)
-#pragma unroll
-            for (int e = 0; e < 8; ++e) pf[kt][st][e] = static_cast<bf16_t>(p[st * 8 + e]);
-        } else {
-#pragma unroll
-          for (int st = 0; st < PSTEPS; ++st) pf[kt][st] = p[st];
-        }
-      }
-      if (!ROWSUM) l_run[t] += ps;
-      // ---- O^T += V^T P^T. Step st of sub-tile kt contracts, in lane half hh, the keys of registers
-      //      [LK*st, LK*st + LK): bf16 -> keys 16*st + 4*hh + {0..3} and 16*st + 8 + 4*hh + {0..3}
-      //      (contiguous after the vcol permutation, at column 16*st + 8*hh); fp32 -> the single key
-      //      8*(st/4) + 4*hh + st%4.
-#pragma unroll
-      for (int kt = 0; kt < KT; ++kt)
-#pragma unroll
-        for (int st = 0; st < PSTEPS; ++st) {
-          int col;
-          if constexpr (sizeof(T) == 2) col = kt * 32 + 16 * st + 8 * hh;
-          else col = kt * 32 + 8 * (st >> 2) + 4 * hh + (st & 3);
-#pragma unroll
-          for (int mt = 0; mt < DM; ++mt) {
-            const typename M::Frag vf = M::load(reinterpret_cast<const T*>(&v_lds[buf][(mt * 32 + lq) * VROW]) + col);
-            M::mma(vf, pf[kt][st], o[t][mt]);
-          }
-        }
+        for (int r = 0; r < 16; ++r)
+          if (kbi + kt * 32 + 8 * (r >> 2) + (r & 3) >= TK) sc[kt][r] = -INFINITY;
     }
+    float mx = -INFINITY;
+#pragma unroll
+    for (int kt = 0; kt < KT; ++kt)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) mx = fmaxf(mx, sc[kt][r]);
+    // mx: over this lane's 16 keys of the query. The other half of the query's keys sits in lane l ^ 32; the
+    // exchange (a trip through LDS) is only made inside the rare branch below: whether ANY lane of the
+    // wavefront exceeds the margin is the same question asked of the per-lane and of the per-query maxima.
+    // The offset m subtracted in the exponent need not be the exact running maximum: any m gives the same
+    // softmax as long as exp2 stays in range, because the same m enters the probabilities, the denominator
+    // and the rescaling. So m is raised (and O^T, l rescaled) only when some query of the wavefront sees a
+    // score more than kLazy above its m (in log2 units: probabilities then reach at most 2^kLazy, harmless
+    // in fp32). With the exact maximum about 70 % of the 64-key stages
+    // took the rescaling branch for some lane; with the margin hardly any after the first. (A lane whose own
+    // score stays inside the margin keeps its m when the branch is taken for another: exp2(0) = 1 exactly.)
+    constexpr float kLazy = 8.f;
+    if (st_i == 0 || __builtin_amdgcn_ballot_w64((mx - m_run) * scale_log2e > kLazy) != 0) {
+      mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+      const bool up = st_i == 0 || (mx - m_run) * scale_log2e > kLazy;
+      const float m_new = up ? fmaxf(m_run, mx) : m_run;
+      const float alpha = __builtin_amdgcn_exp2f((m_run - m_new) * scale_log2e);
+      m_run = m_new;
+      if (!ROWSUM) l_run *= alpha;
+#pragma unroll
+      for (int mt = 0; mt < DM; ++mt)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) o[mt][r] *= alpha;
+    }
+    const float mc = m_run * scale_log2e;
+    typename M::Frag pf[KT][PSTEPS];
+    float ps = 0.f;
+#pragma unroll
+    for (int kt = 0; kt < KT; ++kt)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        pf[kt][r] = __builtin_amdgcn_exp2f(fmaf(sc[kt][r], scale_log2e, -mc));
+        if (!ROWSUM) ps += pf[kt][r];
+      }
+    if (!ROWSUM) l_run += ps;
+    // ---- O^T += V^T P^T. Step st of sub-tile kt contracts, in lane half hh, the single key 8*(st/4) + 4*hh + st%4.
+#pragma unroll
+    for (int kt = 0; kt < KT; ++kt)
+#pragma unroll
+      for (int st = 0; st < PSTEPS; ++st) {
+        const int col = kt * 32 + 8 * (st >> 2) + 4 * hh + (st & 3);
+#pragma unroll
+        for (int mt = 0; mt < DM; ++mt) {
+          const typename M::Frag vf = M::load(reinterpret_cast<const T*>(&v_lds[buf][(mt * 32 + lq) * VROW]) + col);
+          M::mma(vf, pf[kt][st], o[mt]);
+        }
+      }
     if (st_i + 1 < nstage) stash_kv(buf ^ 1, k0 + kKeys);
     __syncthreads();
   }
 
   // ---- normalise and store: lane holds O^T[dim = 32*mt + 8*(r/4) + 4*hh + r%4][query lq]
-#pragma unroll
-  for (int t = 0; t < NQT; ++t) {
-    const int qi = qblk + t * 32 + lq;
-    const int q = token_of(qi);
-    float l;
-    if (ROWSUM) {  // O^T[D][q] sits in register r of the lanes of half hsel
-      constexpr int rem = D % 32, hsel = (rem % 8) / 4, r = (rem / 8) * 4 + rem % 4;
-      l = __shfl(o[t][D / 32][r], lq + 32 * hsel, 64);
-    } else {
-      l = l_run[t] + __shfl_xor(l_run[t], 32, 64);
-    }
-    const float inv = 1.f / l;
-    if (qi >= nq) continue;
-    T* orow = out + ((int64_t)frame * T_tok + q) * C + head * D;
-#pragma unroll
-    for (int mt = 0; mt < DM; ++mt)
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const int dim = mt * 32 + 8 * g + 4 * hh;
-        if (dim < D) {
-#pragma unroll
-          for (int e = 0; e < 4; ++e) orow[dim + e] = from_f32<T>(o[t][mt][4 * g + e] * inv);
-        }
-      }
+  float l;
+  if (ROWSUM) {  // O^T[D][q] sits in register r of the lanes of half hsel
+    constexpr int rem = D % 32, hsel = (rem % 8) / 4, r = (rem / 8) * 4 + rem % 4;
+    l = __shfl(o[D / 32][r], lq + 32 * hsel, 64);
+  } else {
+    l = l_run + __shfl_xor(l_run, 32, 64);
   }
+  const float inv = 1.f / l;
+  if (qi >= nq) return;
+  T* orow = out + ((int64_t)frame * T_tok + q) * C + head * D;
+#pragma unroll
+  for (int mt = 0; mt < DM; ++mt)
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      const int dim = mt * 32 + 8 * g + 4 * hh;
+      if (dim < D) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) orow[dim + e] = o[mt][4 * g + e] * inv;
+      }
+    }
 }
 
 // f(0), f(1), .. f(N - 1) with compile-time indexes (the bodies below index register arrays)
@@ -804,13 +769,13 @@ static hipError_t ring_dispatch(hipStream_t s, const bf16_t* qk, int ldq, const 
 #undef LC_GO
 }
 
-template <class T, int NQT, bool PRE>
-static hipError_t spatial_dispatch(hipStream_t s, const T* qk, int ldq, const T* vt, int Tp, T* out, int frames,
+template <bool PRE>
+static hipError_t spatial_dispatch(hipStream_t s, const float* qk, int ldq, const float* vt, int Tp, float* out, int frames,
                                    int T_tok, int heads, int d, int q0, int nq, int qw, int qstride) {
   const int C = heads * d;
   const float sl = PRE ? 1.f : 1.4426950408889634f / sqrtf((float)d);
-  dim3 grid((nq + 4 * NQT * 32 - 1) / (4 * NQT * 32), heads, frames);
-#define LC_GO(D) spatial_attn_kernel<T, D, NQT, PRE><<<grid, 256, 0, s>>>(qk, ldq, vt, Tp, out, T_tok, C, q0, nq, qw, qstride, sl)
+  dim3 grid((nq + 127) / 128, heads, frames);
+#define LC_GO(D) spatial_attn_kernel<D, PRE><<<grid, 256, 0, s>>>(qk, ldq, vt, Tp, out, T_tok, C, q0, nq, qw, qstride, sl)
   switch (d) {
     case 8: LC_GO(8); break;
     case 16: LC_GO(16); break;
@@ -841,20 +806,18 @@ hipError_t launch_spatial_attention_window(hipStream_t s, int dt, const void* qk
   }
 #define LC_ARGS(TT) s, (const TT*)qk, ldq, (const TT*)vt, Tp, (TT*)out, frames, T, heads, d, q0, nq, qw, qstride
   if (dt == kBF16) return q_prescaled ? ring_dispatch<true, false>(LC_ARGS(bf16_t)) : ring_dispatch<false, false>(LC_ARGS(bf16_t));
-  return q_prescaled ? spatial_dispatch<float, 1, true>(LC_ARGS(float)) : spatial_dispatch<float, 1, false>(LC_ARGS(float));
+  return q_prescaled ? spatial_dispatch<true>(LC_ARGS(float)) : spatial_dispatch<false>(LC_ARGS(float));
 #undef LC_ARGS
 }
 
 // Cross-attention: queries q[frames*Tq] (stride ldq, head h at column h*d) against keys k[(frames/kv_div)*Tk] (stride
 // ldk) and their V^T [(frames/kv_div)][C][Tp]; out [frames*Tq][C]. Frame f uses the keys of group f / kv_div.
-template <class T>
-static hipError_t cross_dispatch(hipStream_t s, const T* q, int ldq, const T* k, int ldk, const T* vt, int Tp, T* out, int frames,
-                                 int Tq, int Tk, int kv_div, int heads, int d) {
-  constexpr int NQT = sizeof(T) == 2 ? 2 : 1;
+static hipError_t cross_dispatch(hipStream_t s, const float* q, int ldq, const float* k, int ldk, const float* vt, int Tp, float* out,
+                                 int frames, int Tq, int Tk, int kv_div, int heads, int d) {
   const int C = heads * d;
   const float sl = 1.f;  // the queries carry the scale
-  dim3 grid((Tq + 4 * NQT * 32 - 1) / (4 * NQT * 32), heads, frames);
-#define LC_GO(D) spatial_attn_kernel<T, D, NQT, true, true><<<grid, 256, 0, s>>>(q, ldq, vt, Tp, out, Tq, C, 0, Tq, Tq, 0, sl, k, ldk, Tk, kv_div)
+  dim3 grid((Tq + 127) / 128, heads, frames);
+#define LC_GO(D) spatial_attn_kernel<D, true, true><<<grid, 256, 0, s>>>(q, ldq, vt, Tp, out, Tq, C, 0, Tq, Tq, 0, sl, k, ldk, Tk, kv_div)
   switch (d) {
     case 8: LC_GO(8); break;
     case 16: LC_GO(16); break;
@@ -873,7 +836,7 @@ hipError_t launch_cross_attention(hipStream_t s, int dt, const void* q, int ldq,
   if (dt == kBF16)
     return ring_dispatch<true, true>(s, (const bf16_t*)q, ldq, (const bf16_t*)vt, Tp, (bf16_t*)out, frames, Tq, heads, d, 0, Tq, Tq, 0,
                                       (const bf16_t*)k, ldk, Tk, kv_div);
-  return cross_dispatch<float>(s, (const float*)q, ldq, (const float*)k, ldk, (const float*)vt, Tp, (float*)out, frames, Tq, Tk, kv_div,
+  return cross_dispatch(s, (const float*)q, ldq, (const float*)k, ldk, (const float*)vt, Tp, (float*)out, frames, Tq, Tk, kv_div,
                                heads, d);
 }
 

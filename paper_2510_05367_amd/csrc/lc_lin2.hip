@@ -173,11 +173,15 @@ static hipError_t run_lin2(hipStream_t s, Lin2Args a) {
   a.y = (OT*)a.y + a.out_map.base * nout;
   if (a.res) a.res += a.out_map.base * nout;
   if (a.y2) a.y2 += a.out_map.base * nout;
-  if (!a.yt || a.yt_from % 64 == 0) {
-    const hipError_t e = launch_lin3(s, a, sizeof(OT) == 4);
-    if (e != hipErrorNotSupported) return e;
+  if constexpr (NT == 4) {  // (yt_from is then a multiple of 128)
+    return launch_lin3(s, a, sizeof(OT) == 4);
+  } else {
+    if (!a.yt || a.yt_from % 64 == 0) {
+      const hipError_t e = launch_lin3(s, a, sizeof(OT) == 4);
+      if (e != hipErrorNotSupported) return e;
+    }
+    return a.gate ? hipErrorInvalidValue : run_lin2_k<OT, NT, false>(s, a);
   }
-  return a.gate ? hipErrorInvalidValue : run_lin2_k<OT, NT, false>(s, a);
 }
 
 hipError_t launch_lin2(hipStream_t s, const FusedDesc& d) {

@@ -25,8 +25,8 @@ def asm(tmp_path_factory):
 
 def kernels(asm):
     names = re.findall(r"^(_ZN2lc11lin2_kernelI(?:f|DF16b)Li(\d)ELb[01]EE[^:\n]*):", asm, flags=re.M)
-    # {fp32, bf16 output} x {160, 128 channels} x {dense, mapped rows}
-    assert len(names) == 8
+    # {fp32, bf16 output} x {160 channels, dense and mapped rows; 128 channels, mapped rows (dense ones have other tiles)}
+    assert len(names) == 6
     for name, nt in names:
         start = asm.index("\n" + name + ":")
         yield name, int(nt), asm[start:asm.index(".Lfunc_end", start)]
@@ -46,6 +46,6 @@ def test_ring_waits_match_emitted_loads(asm):
         assert dma % per_step == 0 and dma >= 2 * per_step, (name, dma, per_step)
     # two workgroups per compute unit: 256 registers per lane at most, and the LDS of both fits
     counts = re.findall(r"\.name:\s+(_ZN2lc11lin2_kernel\S*)\n(?:.*\n)*?\s+\.vgpr_count:\s+(\d+)", asm)
-    assert len(counts) == 8
+    assert len(counts) == 6
     for name, n in counts:
         assert int(n) <= 256, name
