@@ -43,3 +43,28 @@ def test_first_barrier_orders_the_prologues_lds_writes(kernels):
         assert "vmcnt(0)" in joined and "lgkmcnt(0)" in joined, (name, waits)
         writes = [i for i, l in enumerate(lines[:first]) if l.startswith("ds_write")]
         assert writes, name  # the flag at least
+
+
+def test_key_loops_barriers_wait_for_the_loads_and_nothing_spills(kernels):
+    """Behind the barrier of a stage every load to LDS that any wavefront issued has landed; and the two forms of the key loop
+    fit the registers of two wavefronts per SIMD (a spilled loop is slow and says nothing)."""
+    for name, body in kernels.items():
+        assert "scratch_" not in body, f"{name}: register spills"
+        assert max(int(r) for r in re.findall(r"\bv(\d+)\b", body)) < 256
+        lines = [l.split(";")[0].strip() for l in body.splitlines()]
+        lines = [l for l in lines if l]
+        loads = [i for i, l in enumerate(lines) if l.startswith("buffer_load_dwordx4") and l.endswith("lds")]
+        assert loads, name
+        # in front of a barrier: a wait for every load or (__syncthreads between writes and reads of LDS) for LDS, with no
+        # load to LDS and no write to it between the two; and in the stages, whose barriers follow loads, the former
+        full = 0
+        for i, l in enumerate(lines):
+            if l == "s_barrier":
+                for b in reversed(lines[:i]):
+                    assert not (b.startswith("ds_write") or b in ("s_barrier",) or b.endswith("lds")), (name, lines[max(i - 8, 0):i + 1])
+                    if b.startswith("s_waitcnt") and ("vmcnt(0)" in b or "lgkmcnt(0)" in b):
+                        full += "vmcnt(0)" in b
+                        break
+                    if b.endswith(":"):
+                        break
+        assert full >= 4, (name, full)  # first barrier of a sweep, plain loop, safe loop, the sweep for the maxima
