@@ -59,3 +59,19 @@ def test_gated_epilogue_matches_oracle(B, T, D):
         assert torch.equal(cached, full)
     finally:
         dit.close()
+
+
+# exactly 256 tiles of 128 x 128, and one row more (width 1024); widths of 160-channel tiles, exactly 128 of them and one row more
+@pytest.mark.parametrize("T,D,heads,chunk", [(4096, 1024, 16, 640), (4097, 1024, 16, 640), (4096, 640, 10, 1000), (4097, 640, 10, 1000)])
+def test_tiles_agree_bitwise_at_the_lines_between_them(T, D, heads, chunk):
+    cfg = BASE.with_(B=1, T=T, D=D, heads=heads, L=2, cache_a=1, cache_b=2, token_chunk=0)
+    dit = lcb.Dit(cfg, synth.make_dit_weights(cfg, 0), host_slots=0, dev_slots=1, token_chunk=0)
+    try:
+        xd, md = dit.to_device(synth.make_dit_hidden(cfg, 1)), dit.to_device(synth.make_dit_modulation(cfg, 2))
+        ref = steps(cfg, dit, xd, md)
+        assert bool(torch.isfinite(ref[0]).all()) and torch.equal(ref[0], ref[1])
+        dit.set_chunk(chunk)
+        for a, b in zip(steps(cfg, dit, xd, md), ref):
+            assert torch.equal(a, b)
+    finally:
+        dit.close()
