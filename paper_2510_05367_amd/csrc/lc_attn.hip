@@ -338,7 +338,8 @@ __global__ __launch_bounds__(256, 2) void spatial_attn_ring_kernel(const bf16_t*
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   auto kl = [&](int b) { return smem + b * SLOT; };
   auto vl = [&](int b) { return smem + b * SLOT + KSLOT; };
-  int* flags = reinterpret_cast<int*>(smem + NB * SLOT);  // sweep again: every query safely; some with their exact maxima
+  // sweep again: every query safely; some with their exact maxima, seen behind the first sweep, behind a safe one
+  int* flags = reinterpret_cast<int*>(smem + NB * SLOT);
 
   const int tid = threadIdx.x, lane = tid & 63, wid = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lq = lane & 31, hh = lane >> 5;
@@ -370,7 +371,7 @@ __global__ __launch_bounds__(256, 2) void spatial_attn_ring_kernel(const bf16_t*
       *reinterpret_cast<uint4*>(vl(b) + D * 128 + p * 16) = uint4{v, v, v, v};
     }
   }
-  if (tid < 2) flags[tid] = 0;
+  if (tid < 3) flags[tid] = 0;
 
   // ---- global -> LDS. K: packet p of a stage is (key p / KP, slot p % KP); V^T: (row p / 8, slot p % 8). Buffer loads,
   // whose bounds check delivers zeros for the slots of K beyond d (a copy of anything there could meet the zeros of q with
@@ -582,18 +583,32 @@ __global__ __launch_bounds__(256, 2) void spatial_attn_ring_kernel(const bf16_t*
       sA[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[kk], qf[t][kk], kk ? sA[t] : zero16, 0, 0, 0);
     });
     if (kind != kExact) {
-      bool far = kind == kSafe;
+      // (lane by lane first: the two halves of a query's scores are brought together only if some lane's are far)
+      float hi[NQT];
+      bool far = false;
 #pragma unroll
       for (int t = 0; t < NQT; ++t) {
-        float hi = -INFINITY;
+        hi[t] = -INFINITY;
 #pragma unroll
         for (int r = 0; r < 16; ++r)
-          if (!beyond(0, r)) hi = fmaxf(hi, sA[t][r]);
-        hi = fmaxf(hi, __shfl_xor(hi, 32, 64)) * (PRE ? 1.f : scale_log2e);
-        m[t] = fabsf(hi) > kNear && fabsf(hi) < INFINITY ? rintf(hi) : 0.f;
-        far |= m[t] != 0.f;
+          if (!beyond(0, r)) hi[t] = fmaxf(hi[t], sA[t][r]);
+        hi[t] *= PRE ? 1.f : scale_log2e;
+        m[t] = 0.f;
+        far |= !(fabsf(hi[t]) <= kNear);
       }
-      safe = __builtin_amdgcn_ballot_w64(far) != 0;
+      safe = kind == kSafe;
+      if (__builtin_amdgcn_ballot_w64(far) != 0) {
+        far = false;
+#pragma unroll
+        for (int t = 0; t < NQT; ++t) {
+          hi[t] = fmaxf(hi[t], __shfl_xor(hi[t], 32, 64));
+          if (fabsf(hi[t]) > kNear && fabsf(hi[t]) < INFINITY) {
+            m[t] = rintf(hi[t]);
+            far = true;
+          }
+        }
+        safe |= __builtin_amdgcn_ballot_w64(far) != 0;
+      }
     } else {
       safe = true;
     }
@@ -673,16 +688,6 @@ __global__ __launch_bounds__(256, 2) void spatial_attn_ring_kernel(const bf16_t*
   bool redo[NQT];
   for (Sweep kind = kPlain;;) {  // (every decision here is the workgroup's)
     sweep(kind);
-    if (kind == kPlain) {
-#pragma unroll
-      for (int t = 0; t < NQT; ++t) broken |= !safe && so_far(t) > kBroken;
-      if (__builtin_amdgcn_ballot_w64(broken) != 0 && lane == 0) flags[0] = 1;
-      __syncthreads();
-      if (flags[0]) {
-        kind = kSafe;
-        continue;
-      }
-    }
     bool any = false;
 #pragma unroll
     for (int t = 0; t < NQT; ++t) {
@@ -699,9 +704,18 @@ __global__ __launch_bounds__(256, 2) void spatial_attn_ring_kernel(const bf16_t*
       any |= redo[t];
     }
     if (kind == kExact) break;
-    if (__builtin_amdgcn_ballot_w64(any) != 0 && lane == 0) flags[1] = 1;
+    if (kind == kPlain) {
+#pragma unroll
+      for (int t = 0; t < NQT; ++t) broken |= !safe && so_far(t) > kBroken;
+      if (__builtin_amdgcn_ballot_w64(broken) != 0 && lane == 0) flags[0] = 1;
+    }
+    if (__builtin_amdgcn_ballot_w64(any) != 0 && lane == 0) flags[1 + kind] = 1;
     __syncthreads();
-    if (!flags[1]) break;
+    if (kind == kPlain && flags[0]) {  // (what was stored is stored again)
+      kind = kSafe;
+      continue;
+    }
+    if (!flags[1 + kind]) break;
     kind = kExact;
     // the exact maxima of every query, for a sweep with them
 #pragma unroll
