@@ -283,9 +283,14 @@ hipError_t launch_conv(hipStream_t s, const ConvDesc& d) {
 //     each covers the four image rows of the tile;
 //   - the wavefronts' partial sums meet in LDS and are added in a fixed order.
 // Frames that are no whole tiles: the halo is read from clamped places and the missing pixels are not stored.
-// NT threads: with 512 two wavefronts share a SIMD, and one's transcendentals overlap the other's loads.
+// NT threads: with 512 two wavefronts of a workgroup share a SIMD, and one's transcendentals overlap the other's loads. The
+// halo is requested in two batches and the sums meet where it was, so that at C = 320 two workgroups fit on a compute unit
+// (116 registers, 71 KB of LDS; with one, of 178 and 103, launches of more than 256 tiles waited for each other: us, C = 320,
+// one / two workgroups / the general kernel: 8 x 36 x 60 24.3 / 17.7 / 22.2, 32 x 36 x 60 57.2 / 41.3 / 46.7, 32 x 62 x 64 99.8
+// / 69.3 / 61.4, 16 x 72 x 100 96.2 / 66.0 / 60.2, 4 x 64 x 64 15.6 / 15.3 / -, 32 x 64 x 64 99.2 / 69.3 / -). The choice
+// between this kernel and the general one may not depend on the number of frames (they round differently).
 template <int C, int NT>
-__global__ __launch_bounds__(NT) void conv_out_tile_kernel(const float* __restrict__ u, const float* __restrict__ scale,
+__global__ __launch_bounds__(NT, 4) void conv_out_tile_kernel(const float* __restrict__ u, const float* __restrict__ scale,
                                                            const float* __restrict__ shift, const bf16_t* __restrict__ w,
                                                            const float* __restrict__ bias, bf16_t* __restrict__ out, int H,
                                                            int W, int C_lat, int wx0, int wy0) {
@@ -295,12 +300,13 @@ __global__ __launch_bounds__(NT) void conv_out_tile_kernel(const float* __restri
   constexpr int PPR = C / 8;                     // 16-byte bf16 packets per pixel
   constexpr int GRP = NT / PPR;                  // pixels staged per round
   constexpr int RND = (HP + GRP - 1) / GRP;      // rounds
+  constexpr int BAT = (RND + 1) / 2;             // rounds in flight
   constexpr int CB = C / 32;                     // k-steps per tap
   constexpr int NKS = 9 * CB;                    // k-steps
   constexpr int NW = NT / 64;                    // wavefronts
   constexpr int KSW = (NKS + NW - 1) / NW;       // k-steps per wavefront
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  float* const red = reinterpret_cast<float*>(smem + HP * XS);  // [wave][row 4][channel 16][x 16]
+  float* const red = reinterpret_cast<float*>(smem);  // [wave][row 4][channel 16][x 16], where the halo was
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -309,38 +315,41 @@ __global__ __launch_bounds__(NT) void conv_out_tile_kernel(const float* __restri
   // ---- staging: thread = (packet column, pixel group); its halo pixels are grp, grp + GRP, ...
   const int col = tid % PPR, grp = tid / PPR;
   const int c0 = col * 8;
-  f32x4 raw[RND][2];
   const float* uf = u + (int64_t)frame * H * W * C + c0;
-#pragma unroll
-  for (int j = 0; j < RND; ++j) {
-    const int hp = min(grp + GRP * j, HP - 1);
-    const int iy = min(max(y0 + hp / HW_ - 1, 0), H - 1), ix = min(max(x0 + hp % HW_ - 1, 0), W - 1);  // clamped: valid
-    const float* px = uf + ((int64_t)iy * W + ix) * C;
-    raw[j][0] = *reinterpret_cast<const f32x4*>(px);
-    raw[j][1] = *reinterpret_cast<const f32x4*>(px + 4);
-  }
   float sc[8], sh[8];
   load_f<float, 8>(scale + (int64_t)frame * C + c0, sc);
   load_f<float, 8>(shift + (int64_t)frame * C + c0, sh);
-  // ---- this wavefront's weights: k-step ks = wid + NW j is (tap ks / CB, channels 32 (ks % CB) ..)
   typename M::Frag af[KSW];
-  {
-    const int co = lane & 15, g = lane >> 4;
 #pragma unroll
-    for (int j = 0; j < KSW; ++j) {
-      const int ks = min(wid + NW * j, NKS - 1);  // beyond the end: a repeat, never used
-      af[j] = M::load(w + ((int64_t)co * 9 + ks / CB) * C + (ks % CB) * 32, g);
+  for (int j0 = 0; j0 < RND; j0 += BAT) {
+    f32x4 raw[BAT][2];
+#pragma unroll
+    for (int j = 0; j < BAT; ++j) {
+      const int hp = min(grp + GRP * (j0 + j), HP - 1);
+      const int iy = min(max(y0 + hp / HW_ - 1, 0), H - 1), ix = min(max(x0 + hp % HW_ - 1, 0), W - 1);  // clamped: valid
+      const float* px = uf + ((int64_t)iy * W + ix) * C;
+      raw[j][0] = *reinterpret_cast<const f32x4*>(px);
+      raw[j][1] = *reinterpret_cast<const f32x4*>(px + 4);
     }
-  }
+    // ---- this wavefront's weights, behind the last requests: k-step ks = wid + NW j is (tap ks / CB, channels 32 (ks % CB) ..)
+    if (j0 + BAT >= RND) {
+      const int co = lane & 15, g = lane >> 4;
 #pragma unroll
-  for (int j = 0; j < RND; ++j) {
-    const int hp = grp + GRP * j;
-    const int iy = y0 + hp / HW_ - 1, ix = x0 + hp % HW_ - 1;
-    const bool inside = iy >= 0 && iy < H && ix >= 0 && ix < W;  // the padding is zero after the activation
-    Vec16<bf16_t> o;
+      for (int j = 0; j < KSW; ++j) {
+        const int ks = min(wid + NW * j, NKS - 1);  // beyond the end: a repeat, never used
+        af[j] = M::load(w + ((int64_t)co * 9 + ks / CB) * C + (ks % CB) * 32, g);
+      }
+    }
 #pragma unroll
-    for (int e = 0; e < 8; ++e) o.set(e, inside ? silu_fast(fmaf(raw[j][e >> 2][e & 3], sc[e], sh[e])) : 0.f);
-    if (grp < GRP && hp < HP) *reinterpret_cast<Vec16<bf16_t>*>(smem + hp * XS + col * 16) = o;
+    for (int j = 0; j < BAT; ++j) {
+      const int hp = grp + GRP * (j0 + j);
+      const int iy = y0 + hp / HW_ - 1, ix = x0 + hp % HW_ - 1;
+      const bool inside = iy >= 0 && iy < H && ix >= 0 && ix < W;  // the padding is zero after the activation
+      Vec16<bf16_t> o;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) o.set(e, inside ? silu_fast(fmaf(raw[j][e >> 2][e & 3], sc[e], sh[e])) : 0.f);
+      if (grp < GRP && hp < HP) *reinterpret_cast<Vec16<bf16_t>*>(smem + hp * XS + col * 16) = o;
+    }
   }
   __syncthreads();
 
@@ -363,6 +372,7 @@ __global__ __launch_bounds__(NT) void conv_out_tile_kernel(const float* __restri
       }
     }
   }
+  __syncthreads();  // every wavefront has read its pixels
   // lane holds channels 4 (lane / 16) + r of pixel x = lane % 16
 #pragma unroll
   for (int n = 0; n < 4; ++n)
@@ -488,7 +498,7 @@ template <int C>
 static hipError_t run_conv_out(hipStream_t s, const float* u, const float* scale, const float* shift, const bf16_t* w, const float* bias,
                                bf16_t* out, int frames, int H, int W, int C_lat, Win win) {
   constexpr int NT = 512;
-  constexpr int lds = (6 * 18) * (C * 2 + 16) + (NT / 64) * 4 * 16 * 16 * 4;
+  constexpr int halo = 6 * 18 * (C * 2 + 16), sums = (NT / 64) * 4 * 16 * 16 * 4, lds = halo > sums ? halo : sums;
   auto kern = conv_out_tile_kernel<C, NT>;
   static bool attr_set = false;  // per instantiation
   if (!attr_set) {

@@ -54,6 +54,8 @@ def test_small_kernels_stay_small(tmp):
     conv = kernel_meta(tmp, "lc_conv.hip")
     for name, (vg, scratch) in pick(conv, "conv_in_tile_kernel").items():
         assert vg <= 128 and scratch == 0, (name, vg, scratch)  # four workgroups of four wavefronts per compute unit
+    for name, (vg, scratch) in pick(conv, "conv_out_tile_kernel").items():
+        assert vg <= 128 and scratch == 0, (name, vg, scratch)  # two workgroups of eight wavefronts
     attn = kernel_meta(tmp, "lc_attn.hip")
     for name, (vg, scratch) in pick(attn, "temporal_attn_mfma_kernel").items():
         assert vg <= 64 and scratch == 0, (name, vg, scratch)
