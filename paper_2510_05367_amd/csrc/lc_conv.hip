@@ -455,14 +455,25 @@ __global__ __launch_bounds__(256) void conv_in_tile_kernel(const bf16_t* __restr
       const int ch = t * 32 + l32;
       const float bv = bias[ch];
       float s1 = 0.f, s2 = 0.f;
+      if (npx == 32) {  // (uniform; a store under a condition costs a change of the execution mask each)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const float v = acc[r] + bv;
-        const int px = 8 * (r >> 2) + 4 * hh + (r & 3);
-        if (px < npx) {
+        for (int r = 0; r < 16; ++r) {
+          const float v = acc[r] + bv;
+          const int px = 8 * (r >> 2) + 4 * hh + (r & 3);
           yrow[(int64_t)px * C + ch] = v;
           s1 += v;
           s2 = fmaf(v, v, s2);
+        }
+      } else {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const float v = acc[r] + bv;
+          const int px = 8 * (r >> 2) + 4 * hh + (r & 3);
+          if (px < npx) {
+            yrow[(int64_t)px * C + ch] = v;
+            s1 += v;
+            s2 = fmaf(v, v, s2);
+          }
         }
       }
       s1 += __shfl_xor(s1, 32, 64);

@@ -50,6 +50,27 @@ def test_finalize_fits_beside_the_convolution(tmp):
         assert vg <= 240 and scratch == 0, (name, vg, scratch)
 
 
+def test_whole_segments_of_the_first_convolution_store_unconditionally(tmp):
+    """conv_in_tile_kernel is bound by its stores. A condition per store (pixels beyond the end of an image row) changes the
+    execution mask each time; segments of 32 existing pixels, all of them in frames of a multiple of 32 columns, must not
+    pay for that: each of a wavefront's three channel tiles has its 16 stores in a row."""
+    out = tmp / "lc_conv.s"
+    subprocess.run([lcbuild._hipcc(), *lcbuild.FLAGS, "-S", "--cuda-device-only", str(CSRC / "lc_conv.hip"), "-o", str(out)], check=True,
+                   capture_output=True)
+    asm = out.read_text()
+    name = re.search(r"^(_ZN2lc19conv_in_tile_kernel[^:\n]*):", asm, flags=re.M).group(1)
+    body = asm[asm.index("\n" + name + ":"):]
+    runs, n = [], 0
+    for l in body[:body.index(".Lfunc_end")].splitlines():
+        l = l.split(";")[0].strip()
+        if l.startswith("global_store_dword "):
+            n += 1
+        elif "saveexec" in l or l.startswith("s_cbranch") or l.startswith(".LBB"):
+            runs.append(n)
+            n = 0
+    assert sorted(runs)[-3:] == [16, 16, 16], runs
+
+
 def test_small_kernels_stay_small(tmp):
     conv = kernel_meta(tmp, "lc_conv.hip")
     for name, (vg, scratch) in pick(conv, "conv_in_tile_kernel").items():
