@@ -424,7 +424,11 @@ lc_status conv_in_block(lc_ctx* c, const void* x, void* h, int frames, float* st
   const lc_config& g = c->cfg;
   const int T = g.H * g.W;
   if (wrote) *wrote = StatRef{nullptr, 0};
-  if (c->pw.cin_wp) {  // (a property of the stage's geometry: the same kernel for every chunking)
+  // A property of the stage's geometry: the same kernel for every chunking. Frames of up to 8 columns fill too little of the
+  // tile kernel's 32-pixel segments (32 frames of 64 x 4, us: tile kernel 23.6, linear 16.4; 64 x 8 23.7 and 20.4; 64 x 16 27.5
+  // and 27.7; with 8 frames 11.7 and 13.0, 12.7 and 14.1)
+  const bool narrow = g.W <= 8 && T % 32 == 0;
+  if (c->pw.cin_wp && !narrow) {
     hipError_t e;
     {
       Prof pr_(c, LC_K_CONV_IN);

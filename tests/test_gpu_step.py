@@ -345,7 +345,7 @@ def test_profiling_brackets_count_launches():
 
 
 @pytest.mark.parametrize("F,H,W,C,heads,head_dim", [(5, 10, 14, 320, 8, 40), (9, 6, 34, 320, 5, 64), (5, 10, 18, 64, 1, 64), (3, 16, 18, 64, 2, 32),
-                                                    (7, 24, 4, 320, 8, 40), (5, 32, 2, 64, 1, 64)])
+                                                    (7, 24, 4, 320, 8, 40), (5, 32, 2, 64, 1, 64), (5, 22, 4, 320, 8, 40)])
 def test_ragged_frames_in_bf16(F, H, W, C, heads, head_dim):
     """Frames that are no whole 32-row tiles, image rows that are no whole 32-pixel or 16-pixel segments: GroupNorm
     applied in a pass of its own and the streamed linear kernel with V^T in its epilogue (C = 320), short segments of
@@ -373,3 +373,30 @@ def test_ragged_frames_in_bf16(F, H, W, C, heads, head_dim):
         assert all(torch.equal(outs[0], o) for o in outs[1:])
     finally:
         stage.close()
+
+
+def test_first_convolution_of_narrow_frames_keeps_its_kernel():
+    """Frames of 4 columns whose pixels come in 32s: the first convolution takes the gathering linear kernel, whose tiles run
+    across image rows, and not 32-pixel segments of which 28 are missing. Against 16 columns, whose segments are half full:
+    32 frames of 64 rows, 320 channels, 18.4 us in segments and 11.4 in the linear kernel against 23.0."""
+    us = {}
+    for W in (4, 16):
+        cfg = synth.StageConfig(f"narrow_{W}", B=1, F=32, H=64, W=W, C_lat=4, C=320, C_deep=640, groups=32, n_res=1, heads=8,
+                                head_dim=40, dtype="bf16")
+        stage, _ = make_stage(cfg, seed=3)
+        try:
+            xd, h = dev(stage, synth.make_latents(cfg, 4)), torch.empty(cfg.N * cfg.T, cfg.C, device="cuda")
+            best = float("inf")
+            for _ in range(6):
+                a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+                a.record()
+                for _ in range(20):
+                    lcb.lc_op_conv_in(stage.ctx, xd.data_ptr(), h.data_ptr(), cfg.N)
+                b.record()
+                torch.cuda.synchronize()
+                best = min(best, a.elapsed_time(b) * 50)
+            us[W] = best
+        finally:
+            stage.close()
+    print(us, flush=True)
+    assert us[4] < 0.65 * us[16], us
