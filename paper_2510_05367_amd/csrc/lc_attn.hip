@@ -279,9 +279,8 @@ template <int I, int N, class F> __device__ __forceinline__ void static_for(F&& 
 }
 
 // Spatial attention of the bf16 stages. What bounds it: the matrix pipe (d = 64: 512 cycles of MFMAs per 32 keys x 64
-// queries and wavefront) and, beside it, the vector port (32 exponentials at about 10 cycles, 16 packs, 32 additions).
-// Here the two overlap inside a wavefront. A substep is 32 keys, and
-// three independent pieces of work are issued interleaved, a few vector instructions behind every MFMA:
+// queries and wavefront) and, beside it, the vector port (32 exponentials, 16 packs, 16 dot products for the denominator).
+// Here the two overlap inside a wavefront. A substep is 32 keys, and three independent pieces of work are issued interleaved, a few vector instructions behind every MFMA:
 //   scores of substep j + 1 (K Q^T)  |  probabilities of substep j  |  O^T += V^T P^T of substep j - 1
 // Fragments are requested from LDS half a substep ahead of their use. K and V^T go from global memory straight into
 // LDS (16 bytes per lane) into a ring of four 64-key stages: stage s + 2 is requested at the start of stage s, one
@@ -298,9 +297,11 @@ template <int I, int N, class F> __device__ __forceinline__ void static_for(F&& 
 // that shows in a query's bits is its own (x - 0 is x), whoever shares its wavefront.
 // Measured (us per launch, with a kernel that ran the two phases in turn / this one): d = 64, 5 x 9216 tokens, 2304
 // queries, 5 heads 204 / 170 alone and 157 / 132 with two launches in flight (1.02 PFLOP/s); d = 40, 4 x 4096, 8 heads
-// 123 / 104; d = 40, 8 x 9216 1110 / 960; cross-attention to 77 keys, 16 x 4096, 8 heads 48 / 45. The matrix pipe is busy
-// 80 % of the cycles and the clock falls from 2.4 to 1.6 - 1.9 GHz (with zeros as input it stays at 2.3): what bounds it
-// now is power.
+// 121 / 101; d = 40, 8 x 9216 1110 / 960; cross-attention to 77 keys, 16 x 4096, 8 heads 48 / 43. Counters, shares of the
+// cycles: d = 40, 4 x 4096: matrix pipe 52 % (41 % in turn), exponentials 59 % (47 %), LDS 74 %, clock 2.2 GHz; 32 x 4096: 61 %,
+// 69 %, 88 %, 2.0 GHz; d = 64, 2 x 4096, 16 heads: 48 % each, 1.9 GHz. Nothing is full but the LDS of the larger d = 40 launches,
+// and the clock falls with the work done in a cycle (with zeros as input it stays at 2.3): the rest is what one wavefront's
+// instructions wait for each other.
 // Scores out of range (us; this kernel / the plain form alone, every workgroup with such a score done again with exact maxima /
 // a kernel with a running maximum throughout; d = 64, 5 x 9216 tokens, 5 heads | d = 40, 4 x 4096, 8 heads, both with the
 // pass that transposes V): deviation 1.4 in log2 units 562, 556, 663 | 128, 129, 150; 15: 606, 551, 684 | 141, 118, 150; 40:
