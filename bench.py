@@ -35,12 +35,12 @@ PEAK_HBM_GBS = 8000.0
 # WRITE_SIZE runs summarised under profiles/ (fetch x 2.0, the factor a plain copy of known size gave). Valid only
 # for the kernel sources the counters were taken with: `sha256_16` covers the listed files, else traffic is null.
 TRAFFIC = {
-    "conv_up": {"sources": ("lc_convws.hip", "lc_common.h", "lc_internal.h"), "sha256_16": "9f27ba249d998d07",
+    "conv_up": {"sources": ("lc_convws.hip", "lc_common.h", "lc_internal.h"), "sha256_16": "9dd072ac2f610b74",
                 "bytes_per_launch": 83.6e6 + 22.3e6},
-    "sattn": {"sources": ("lc_attn.hip", "lc_common.h", "lc_internal.h"), "sha256_16": "7aacbd5d82e993a6",
+    "sattn": {"sources": ("lc_attn.hip", "lc_common.h", "lc_internal.h"), "sha256_16": "0057d4a2151eab47",
               "bytes_per_launch": 61.0e6 + 12.6e6},
-    "conv_res": {"sources": ("lc_convws.hip", "lc_common.h", "lc_internal.h"), "sha256_16": "9f27ba249d998d07",
-                 "bytes_per_launch": 54.5e6 + 22.3e6},
+    "conv_res": {"sources": ("lc_convws.hip", "lc_common.h", "lc_internal.h"), "sha256_16": "9dd072ac2f610b74",
+                 "bytes_per_launch": 54.6e6 + 22.3e6},
 }
 TRAFFIC_WORKLOAD = ("animatediff", 4)
 
@@ -212,9 +212,9 @@ def roofline_of(lcb, torch, stage, cfg, fc, family, step, K, peak):
         padded = frames * cfg.heads * 2.0 * cfg.T * cfg.T * (pad_qk + pad_pv)
         r["context"] = {"exp_per_launch": exps, "exp_floor_ms": round(exps / 9.83e12 * 1e3, 5),
                         "executed_flops_per_launch": padded, "mfma_floor_ms": round(padded / (peak * 1e12) * 1e3, 5),
-                        "note": "the counter summary under profiles/ shows the matrix pipe and the transcendental unit "
-                                "taking turns (42 % and 48 % busy): the sum of the two floors is what the kernel's "
-                                "launch time compares with"}
+                        "note": "the counter summary under profiles/ shows the matrix pipe 52 %, the transcendental unit 59 % and "
+                                "the LDS 74 % busy: the two floors overlap, and the launch time compares with more than "
+                                "the larger and less than their sum"}
     r.update({"traffic": measured_traffic(family, cfg.name, fc), "traffic_unit": "bytes/launch",
               "avg_launch_ms": round(avg_ms, 5), "launches_per_step": d["launches"] // K,
               "total_ms_per_step": round(d["ms"] / K, 4)})

@@ -1,8 +1,9 @@
 // Linear layers over dense bf16 rows on gfx950: the tiles beside lc_lin2.hip's 128 x 160, wide ones for launches that fill
 // the chip several times and small ones for launches that would leave most of it idle.
 //
-// What bounds these kernels is the LDS: a compute unit reads 64 bytes a clock from it with 16-byte reads (measured with
-// nothing else running), while its four matrix pipes finish a 32x32x16 MFMA each in 32 clocks. A wavefront that holds
+// What loads these kernels most is the LDS: a compute unit reads 64 bytes a clock from it with 16-byte reads (measured with
+// nothing else running), while its four matrix pipes finish a 32x32x16 MFMA each in 32 clocks (counters at 8192 rows of
+// 1024: LDS 55 - 68 % of the cycles, matrix pipe 33 - 37 %). A wavefront that holds
 // MT x NT accumulator tiles reads (MT + NT) / (MT NT) KB per MFMA: 1.2 with lin2's one row tile, 1 at 2 x 2, 0.75 at 2 x 4.
 // Measured, us (lin2's tile -> this file's; rows x N x K): 8192 x 4096 x 1024 with GELU 95 -> 78 and 8192 x 3840 x 1280
 // 97 -> 81 (256 x 256), 8192 x 3072 x 1024 64 -> 56 (256 x 192), 8192 x 1024 x 4096 fp32 75 -> 67 (128 x 128),

@@ -342,7 +342,7 @@ UPlan make_uplan(const lc_unet_config& g, int frame_chunk) {
   p.off_kv = take((size_t)g.B * g.ctx_len * 2 * std::max(g.C, g.C1) * es);
   p.off_vtx = take((size_t)g.B * std::max(g.C, g.C1) * attn_tp(g.ctx_len) * es);
   const size_t chunk0 = off;
-  // ---- one chunk, residual blocks and resamplings
+  // ---- one chunk, residual blocks
   const int64_t cat = std::max(nc0 * P * (g.C + g.C1), nc1 * P1 * (g.C1 + g.C2));
   const int64_t hid = std::max({nc0 * P * g.C, nc1 * P1 * g.C1, nc2 * P2 * g.C2});
   p.off_xc = take((size_t)cat * 4);

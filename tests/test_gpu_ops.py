@@ -184,7 +184,7 @@ def test_attention_blocks_in_place(st):
 @pytest.mark.parametrize("heads,head_dim", [(8, 8), (4, 16), (2, 32), (8, 40), (1, 64)])
 def test_spatial_attention_every_head_size(heads, head_dim, dtype):
     """Every head size the library accepts takes a different path through the spatial kernel (rows of V^T that
-    deliver the softmax denominators or not, the running maximum folded into a spare contraction slot or not):
+    deliver the softmax denominators or not, padding in the contraction of K Q^T or not):
     each against the definition, unit and sharp logits, 140 tokens = two full key stages and a ragged third."""
     C = heads * head_dim
     cfg = synth.StageConfig(f"s_{heads}x{head_dim}_{dtype}", B=1, F=2, H=10, W=14, C_lat=4, C=C, C_deep=64, groups=8,
@@ -209,7 +209,8 @@ def test_spatial_attention_every_head_size(heads, head_dim, dtype):
 
 @pytest.mark.parametrize("heads,head_dim,F,H,W", [(8, 40, 2, 8, 8), (1, 64, 2, 10, 14), (2, 32, 3, 12, 16), (8, 40, 16, 18, 30), (5, 64, 18, 18, 30)])
 def test_spatial_attention_out_of_range_scores(heads, head_dim, F, H, W):
-    """The bf16 kernel subtracts no maximum and does a query again with its exact one when exp2 left its range. Every
+    """The bf16 kernel subtracts nothing in the exponent while a wavefront's scores are ordinary ones, and else an offset of each
+    query's own. Every
     third query here has logits of several hundred, the others ordinary ones, so that wavefronts hold both kinds; few
     tokens (one query tile per wavefront) and many (two), key counts of one stage, of whole stages and a remainder.
     A window of queries must give the bits of the whole launch."""
