@@ -352,7 +352,7 @@ typedef struct lc_decoder_weights {
 lc_status lc_decoder_check_config(const lc_decoder_config* cfg);                     /* host only */
 /* Workspace a pass over slice_frames frames needs (0 or > N: all N frames): per frame of the slice the maps of the largest
  * stage and of the stage before it, once, or twice where two slices side by side take no more than two maps of the largest
- * stage with its input upsampled. */
+ * stage with its input upsampled; with it statistics and the attention block's q,k,v. 0 if cfg is invalid. Host only. */
 size_t lc_decoder_workspace_bytes(const lc_decoder_config* cfg, int slice_frames);
 const char* lc_decoder_last_error(const lc_decoder* dec);
 /* stream: hipStream_t owned by the caller, must outlive the decoder. */
