@@ -51,7 +51,8 @@ struct Plan {
 };
 
 struct GnW { float *gamma, *beta; };
-struct ConvW { void* w; float* b; void* wt; };  // wt: tile order for the specialised conv kernel, or nullptr
+// wt: tile order for the specialised conv kernel, wf: fragment order for the one over activated rows, or nullptr
+struct ConvW { void* w; float* b; void *wt, *wf; };
 struct AttnW { GnW gn; void* wqkv; void* wo; float* bo; void* wqkv_f; void* wo_f; };  // *_f: fragment order
 struct Packed {
   float* cin_w; float* cin_b;
@@ -394,7 +395,7 @@ FusedDesc fconv_desc(lc_ctx* c, const ConvW& w, int Cin, int Cout, int frames, i
   FusedDesc d;
   memset(&d, 0, sizeof d);
   d.dt = c->cfg.dtype; d.y_f32 = y_f32; d.taps = 9; d.src = 2; d.Cin = Cin; d.Cout = Cout; d.Cout_store = Cout;
-  d.w = w.w; d.w_tiles = c->conv_general ? nullptr : w.wt; d.bias = w.b; d.frames = frames; d.H = H; d.W = W; d.x = x; d.scale = scale_p(c); d.shift = shift_p(c);
+  d.w = w.w; d.w_tiles = c->conv_general ? nullptr : w.wt; d.w_frags = c->conv_general ? nullptr : w.wf; d.bias = w.b; d.frames = frames; d.H = H; d.W = W; d.x = x; d.scale = scale_p(c); d.shift = shift_p(c);
   d.res = res; d.y = y; d.in_map = dense_map(); d.out_map = dense_map();
   return d;
 }
@@ -466,6 +467,14 @@ lc_status conv_in_block(lc_ctx* c, const void* x, void* h, int frames, float* st
   return LC_OK;
 }
 
+// The activated rows of a 3x3 convolution go into the chunk scratch behind its first `used` bytes (lc_internal.h: FusedDesc::xact)
+void set_conv_act(lc_ctx* c, FusedDesc& d, size_t used) {
+  used = align_up(used);
+  if (used >= c->plan.ws_bytes) return;
+  d.xact = ws_ptr(c) + used;
+  d.xact_bytes = c->plan.ws_bytes - used;
+}
+
 // residual block body: y = x + conv3x3(SiLU(GN(x))); x fp32 [frames][H*W][Cn]; y must not alias x.
 // `in`: partial sums of x if its producer wrote them. `out` (fp32 y only): receives the partial sums of y.
 lc_status res_block(lc_ctx* c, const GnW& gn, const ConvW& cw, int Cn, int frames, int H, int W, const void* x,
@@ -473,6 +482,7 @@ lc_status res_block(lc_ctx* c, const GnW& gn, const ConvW& cw, int Cn, int frame
   lc_status s = gn_scale_shift(c, x, frames, H * W, Cn, gn, in);
   if (s != LC_OK) return s;
   FusedDesc d = fconv_desc(c, cw, Cn, Cn, frames, H, W, x, x, y, y_f32);
+  set_conv_act(c, d, (size_t)frames * H * W * Cn * 4);  // (x or y may be an fp32 map at its start; its partial sums are folded)
   if (out && (y_f32 || c->cfg.dtype == kF32)) {
     d.stat = partH(c);  // the partials of x have been folded into scale/shift by now
     d.stat_splits = conv_stat_splits(H, W);
@@ -501,6 +511,7 @@ lc_status up_conv(lc_ctx* c, const void* skip, const void* deep, void* u, int fr
   if (sc && sh) {
     FusedDesc d = fconv_desc(c, c->pw.up, C + Cd, C, frames, g.H, g.W, skip, nullptr, u, 1);
     d.src = 3; d.x2 = deep; d.Cs = C; d.scale = sc; d.shift = sh;
+    set_conv_act(c, d, (size_t)frames * T * C * 4);
     if (out) {
       d.stat = partH(c);
       d.stat_splits = conv_stat_splits(g.H, g.W);
@@ -527,6 +538,7 @@ lc_status up_conv(lc_ctx* c, const void* skip, const void* deep, void* u, int fr
                                c->pw.up_gn.gamma, c->pw.up_gn.beta, g.groups, g.gn_eps, scale_p(c), shift_p(c), frames));
   FusedDesc d = fconv_desc(c, c->pw.up, C + Cd, C, frames, g.H, g.W, skip, nullptr, u, 1);
   d.src = 3; d.x2 = deep; d.Cs = C;
+  set_conv_act(c, d, (size_t)frames * T * C * 4);
   if (out) {
     d.stat = partH(c);
     d.stat_splits = conv_stat_splits(g.H, g.W);
@@ -1019,6 +1031,14 @@ lc_status lc_load_weights(lc_ctx* c, const lc_weights* w) {
     for (int i = 0; i < g.n_res; ++i) o_res_wt[i] = take((size_t)C * 9 * C * es);
     o_up_wt = take((size_t)C * 9 * (C + Cd) * es);
   }
+  // and one in the fragment order of the kernel that contracts activated rows (the deep stand-in's too)
+  const bool frags = dt == kBF16 && C % 64 == 0 && Cd % 64 == 0;
+  size_t o_res_wf[LC_MAX_RES] = {0}, o_up_wf = 0, o_dres_wf = 0;
+  if (frags) {
+    for (int i = 0; i < g.n_res; ++i) o_res_wf[i] = take((size_t)C * 9 * C * es);
+    o_up_wf = take((size_t)C * 9 * (C + Cd) * es);
+    o_dres_wf = take((size_t)Cd * 9 * Cd * es);
+  }
   size_t o_at[2][7];
   for (int k = 0; k < 2; ++k) {
     o_at[k][0] = take((size_t)C * 4); o_at[k][1] = take((size_t)C * 4);
@@ -1056,10 +1076,14 @@ lc_status lc_load_weights(lc_ctx* c, const lc_weights* w) {
     F32(w->res[i].gn_g, o_res_g[i], C, C); F32(w->res[i].gn_b, o_res_b[i], C, C);
     CW(w->res[i].w, o_res_w[i], C, C, 9, C); F32(w->res[i].b, o_res_bias[i], C, C);
     p.res_gn[i] = GnW{(float*)(b + o_res_g[i]), (float*)(b + o_res_b[i])};
-    p.res[i] = ConvW{b + o_res_w[i], (float*)(b + o_res_bias[i]), nullptr};
+    p.res[i] = ConvW{b + o_res_w[i], (float*)(b + o_res_bias[i]), nullptr, nullptr};
     if (tiles) {
       LC_HIP(c, launch_pack_conv_w_tiles(s, dt, b + o_res_w[i], b + o_res_wt[i], C, C));
       p.res[i].wt = b + o_res_wt[i];
+    }
+    if (frags) {
+      LC_HIP(c, launch_pack_conv_w_frags(s, dt, b + o_res_w[i], b + o_res_wf[i], C, C));
+      p.res[i].wf = b + o_res_wf[i];
     }
   }
   const lc_attn_w* aw[2] = {&w->sattn, &w->tattn};
@@ -1078,23 +1102,28 @@ lc_status lc_load_weights(lc_ctx* c, const lc_weights* w) {
                    (float*)(b + o_at[k][4]), b + o_at[k][5], b + o_at[k][6]};
   }
   CW(w->down_w, o_down_w, Cd, C, 9, Cd); F32(w->down_b, o_down_b, Cd, Cd);
-  p.down = ConvW{b + o_down_w, (float*)(b + o_down_b), nullptr};
+  p.down = ConvW{b + o_down_w, (float*)(b + o_down_b), nullptr, nullptr};
   F32(w->dres.gn_g, o_dres_g, Cd, Cd); F32(w->dres.gn_b, o_dres_b, Cd, Cd);
   CW(w->dres.w, o_dres_w, Cd, Cd, 9, Cd); F32(w->dres.b, o_dres_bias, Cd, Cd);
   p.dres_gn = GnW{(float*)(b + o_dres_g), (float*)(b + o_dres_b)};
-  p.dres = ConvW{b + o_dres_w, (float*)(b + o_dres_bias), nullptr};
+  p.dres = ConvW{b + o_dres_w, (float*)(b + o_dres_bias), nullptr, nullptr};
   F32(w->up.gn_g, o_up_g, C + Cd, C + Cd); F32(w->up.gn_b, o_up_b, C + Cd, C + Cd);
   CW(w->up.w, o_up_w, C, C + Cd, 9, C); F32(w->up.b, o_up_bias, C, C);
   p.up_gn = GnW{(float*)(b + o_up_g), (float*)(b + o_up_b)};
-  p.up = ConvW{b + o_up_w, (float*)(b + o_up_bias), nullptr};
+  p.up = ConvW{b + o_up_w, (float*)(b + o_up_bias), nullptr, nullptr};
   if (tiles) {
     LC_HIP(c, launch_pack_conv_w_tiles(s, dt, b + o_up_w, b + o_up_wt, C, C + Cd));
     p.up.wt = b + o_up_wt;
   }
+  if (frags) {
+    LC_HIP(c, launch_pack_conv_w_frags(s, dt, b + o_up_w, b + o_up_wf, C, C + Cd));
+    LC_HIP(c, launch_pack_conv_w_frags(s, dt, b + o_dres_w, b + o_dres_wf, Cd, Cd));
+    p.up.wf = b + o_up_wf; p.dres.wf = b + o_dres_wf;
+  }
   F32(w->out.gn_g, o_out_g, C, C); F32(w->out.gn_b, o_out_b, C, C);
   CW(w->out.w, o_out_w, Cl, C, 9, 32); F32(w->out.b, o_out_bias, Cl, 32);
   p.out_gn = GnW{(float*)(b + o_out_g), (float*)(b + o_out_b)};
-  p.out = ConvW{b + o_out_w, (float*)(b + o_out_bias), nullptr};
+  p.out = ConvW{b + o_out_w, (float*)(b + o_out_bias), nullptr, nullptr};
 #undef F32
 #undef CW
   LC_HIP(c, hipStreamSynchronize(s));

@@ -24,10 +24,11 @@ constexpr size_t kAlign = 256;
 inline size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 
 struct GnP { float *g, *b; };
-struct ConvP { void* w; float* b; };
+struct ConvP { void* w; float* b; void* wf; };  // wf: fragment order for the kernel over activated rows, or nullptr
 
 struct DPlan {
   size_t off_a, off_b, off_part, off_scale, off_shift, off_one, off_zero, off_qkv, off_vt, off_ao, total;
+  size_t frame_a;               // bytes of one frame in buffer `a`
   size_t lane_off, lane_stride;  // [lane_off, lane_off + lane_stride): what one lane works in
   int lanes;
 };
@@ -128,6 +129,7 @@ DPlan make_dplan(const lc_decoder_config& g, int n) {
   p.off_one = take((size_t)n * maxC * 4);
   p.off_zero = take((size_t)n * maxC * 4);
   p.lane_off = off;
+  p.frame_a = (size_t)elems_a * 4;
   p.off_a = take((size_t)n * elems_a * 4);
   p.off_b = take((size_t)n * elems_b * 4);
   p.off_scale = take((size_t)n * maxC * 4);
@@ -170,26 +172,50 @@ lc_status gn(lc_decoder* d, const DPlan& p, const float* x, Stats st, int n, int
 }
 
 // y = [res +] conv3x3(act(x)) at H x W, y fp32 rows with its partial sums. src 2: act = SiLU(GroupNorm(x)) with the scale /
-// shift at hand; src 1: x, at half the resolution, nearest 2x upsampled on the way in.
-lc_status conv(lc_decoder* d, const DPlan& p, const ConvP& w, int src, int Cin, int Cout, int n, int H, int W, const float* x,
-               const float* res, float* y, Stats* st) {
+// shift at hand; src 1: x, at half the resolution, nearest 2x upsampled on the way in; src 0: the same with x rounded already.
+// act: room for the activated rows, act_bytes of it, or nullptr. y16: y is rounded to bf16 rows instead, without partial sums
+// (*st is then what it was).
+lc_status conv(lc_decoder* d, const DPlan& p, const ConvP& w, int src, int Cin, int Cout, int n, int H, int W, const void* x,
+               const float* res, void* y, Stats* st, void* act = nullptr, size_t act_bytes = 0, bool y16 = false) {
   FusedDesc f;
   memset(&f, 0, sizeof f);
-  f.dt = d->cfg.dtype; f.y_f32 = 1; f.taps = 9; f.src = src; f.Cin = Cin; f.Cout = Cout; f.Cout_store = Cout;
-  f.w = w.w; f.bias = w.b; f.frames = n; f.H = H; f.W = W; f.x = x; f.res = res; f.y = y; f.up2 = src == 1;
+  f.w_frags = w.wf; f.xact = act; f.xact_bytes = act_bytes;
+  f.dt = d->cfg.dtype; f.y_f32 = y16 ? 0 : 1; f.taps = 9; f.src = src; f.Cin = Cin; f.Cout = Cout; f.Cout_store = Cout;
+  f.w = w.w; f.bias = w.b; f.frames = n; f.H = H; f.W = W; f.x = x; f.res = res; f.y = y; f.up2 = src < 2;
   f.scale = (const float*)(src == 2 ? d->lane + p.off_scale : d->arena + p.off_one);
   f.shift = (const float*)(src == 2 ? d->lane + p.off_shift : d->arena + p.off_zero);
   f.in_map = f.out_map = RowMap{0, 0, 1 << 30};
-  f.stat = (float*)(d->lane + p.off_part); f.stat_splits = conv_stat_splits(H, W);  // (those of x are folded by now)
+  if (!y16) { f.stat = (float*)(d->lane + p.off_part); f.stat_splits = conv_stat_splits(H, W); }  // (those of x are folded by now)
   LCD_HIP(d, launch_fused(d->s, f));
-  *st = Stats{f.stat, f.stat_splits};
+  if (!y16) *st = Stats{f.stat, f.stat_splits};
   return LC_OK;
 }
 
-lc_status res_block(lc_decoder* d, const DPlan& p, int idx, int C, int n, int H, int W, const float* x, float* y, Stats* st) {
+// whether launch_conv_dma takes a convolution of these widths over frames of this size
+bool conv_covered(lc_decoder* d, const ConvP& w, int Cin, int Cout, int H, int W, bool up2) {
+  FusedDesc f;
+  memset(&f, 0, sizeof f);
+  f.dt = d->cfg.dtype; f.taps = 9; f.Cin = Cin; f.Cout = Cout; f.Cout_store = Cout; f.w_frags = w.wf; f.H = H; f.W = W; f.up2 = up2;
+  return launch_conv_dma(d->s, f) == hipSuccess;  // (no frames: nothing is launched)
+}
+
+// Room for the activated rows of a residual block's convolution over n frames of H x W x C: behind the map of that size at the
+// start of buffer `a`, which holds the largest map of all. A property of the configuration, never of the slice.
+void* res_act(lc_decoder* d, const DPlan& p, int C, int n, int H, int W, size_t* bytes) {
+  const size_t e = (size_t)H * W * C;
+  *bytes = 0;
+  if (d->cfg.dtype != kBF16 || e * 6 > p.frame_a) return nullptr;
+  *bytes = (size_t)n * e * 2;
+  return d->lane + p.off_a + (size_t)n * e * 4;
+}
+
+// y16: y as bf16 rows (what a convolution reads that takes them as they are)
+lc_status res_block(lc_decoder* d, const DPlan& p, int idx, int C, int n, int H, int W, const float* x, float* y, Stats* st, bool y16 = false) {
   lc_status s = gn(d, p, x, *st, n, H * W, C, d->res_gn[idx]);
   if (s != LC_OK) return s;
-  return conv(d, p, d->res[idx], 2, C, C, n, H, W, x, x, y, st);
+  size_t bytes;
+  void* act = res_act(d, p, C, n, H, W, &bytes);
+  return conv(d, p, d->res[idx], 2, C, C, n, H, W, x, x, y, st, act, bytes, y16);
 }
 
 // h += proj(Attn(qkv(GroupNorm(h)))) over the H*W positions of each frame, in place on fp32 rows
@@ -248,9 +274,14 @@ lc_status decode_pass(lc_decoder* d, const DPlan& p, const void* z, void* img, i
   if ((s = res_block(d, p, 1, C0, n, H, W, b, a, &st)) != LC_OK) return s;
   for (int l = 0; l < g.levels; ++l) {
     const int Cl = g.widths[l], Cn = g.widths[l + 1];
-    if ((s = res_block(d, p, 2 + l, Cl, n, H, W, a, b, &st)) != LC_OK) return s;
+    // only the upsampling convolution reads the block's output, rounded to bf16 as it contracts it: where both take the
+    // kernel over activated rows, the block leaves it so
+    size_t bytes;
+    const bool y16 = res_act(d, p, Cl, n, H, W, &bytes) && conv_covered(d, d->res[2 + l], Cl, Cl, H, W, false) &&
+                     conv_covered(d, d->upc[l], Cl, Cn, 2 * H, 2 * W, true);
+    if ((s = res_block(d, p, 2 + l, Cl, n, H, W, a, b, &st, y16)) != LC_OK) return s;
     H *= 2; W *= 2;
-    if ((s = conv(d, p, d->upc[l], 1, Cl, Cn, n, H, W, b, nullptr, a, &st)) != LC_OK) return s;
+    if ((s = conv(d, p, d->upc[l], y16 ? 0 : 1, Cl, Cn, n, H, W, b, nullptr, a, &st)) != LC_OK) return s;
   }
   const int CL = g.widths[g.levels];
   if ((s = gn(d, p, a, st, n, H * W, CL, d->out_gn)) != LC_OK) return s;
@@ -336,6 +367,13 @@ lc_status lc_decoder_load_weights(lc_decoder* d, const lc_decoder_weights* w) {
     const int C = i < 2 ? C0 : g.widths[i - 2];
     o_rg[i] = take((size_t)C * 4); o_rb[i] = take((size_t)C * 4); o_rw[i] = take((size_t)C * 9 * C * es); o_rbias[i] = take((size_t)C * 4);
   }
+  // the 3x3 weights once more in the fragment order of the kernel that contracts activated rows
+  const bool frags = dt == kBF16;
+  size_t o_rf[2 + LC_DEC_MAX_LEVELS] = {0}, o_uf[LC_DEC_MAX_LEVELS] = {0};
+  if (frags) {
+    for (int i = 0; i < 2 + L; ++i) { const int C = i < 2 ? C0 : g.widths[i - 2]; o_rf[i] = take((size_t)C * 9 * C * es); }
+    for (int l = 0; l < L; ++l) o_uf[l] = take((size_t)g.widths[l + 1] * 9 * g.widths[l] * es);
+  }
   const size_t o_ag = take((size_t)C0 * 4), o_ab = take((size_t)C0 * 4), o_aqkv = take((size_t)3 * C0 * C0 * es),
                o_awo = take((size_t)C0 * C0 * es), o_abo = take((size_t)C0 * 4);
   size_t o_uw[LC_DEC_MAX_LEVELS], o_ub[LC_DEC_MAX_LEVELS];
@@ -363,7 +401,11 @@ lc_status lc_decoder_load_weights(lc_decoder* d, const lc_decoder_weights* w) {
     const lc_gnconv_w& r = i < 2 ? w->mid_res[i] : w->up_res[i - 2];
     F32(r.gn_g, o_rg[i], C, C); F32(r.gn_b, o_rb[i], C, C); CW(r.w, o_rw[i], C, C, C); F32(r.b, o_rbias[i], C, C);
     d->res_gn[i] = GnP{(float*)(b + o_rg[i]), (float*)(b + o_rb[i])};
-    d->res[i] = ConvP{b + o_rw[i], (float*)(b + o_rbias[i])};
+    d->res[i] = ConvP{b + o_rw[i], (float*)(b + o_rbias[i]), nullptr};
+    if (frags) {
+      LCD_HIP(d, launch_pack_conv_w_frags(s, dt, b + o_rw[i], b + o_rf[i], C, C));
+      d->res[i].wf = b + o_rf[i];
+    }
   }
   F32(w->mid_attn.gn_g, o_ag, C0, C0); F32(w->mid_attn.gn_b, o_ab, C0, C0);
   LCD_HIP(d, launch_copy_rows(s, dt, w->mid_attn.wq, b + o_aqkv, (int64_t)C0 * C0));
@@ -376,12 +418,16 @@ lc_status lc_decoder_load_weights(lc_decoder* d, const lc_decoder_weights* w) {
   for (int l = 0; l < L; ++l) {
     CW(w->up_conv_w[l], o_uw[l], g.widths[l + 1], g.widths[l], g.widths[l + 1]);
     F32(w->up_conv_b[l], o_ub[l], g.widths[l + 1], g.widths[l + 1]);
-    d->upc[l] = ConvP{b + o_uw[l], (float*)(b + o_ub[l])};
+    d->upc[l] = ConvP{b + o_uw[l], (float*)(b + o_ub[l]), nullptr};
+    if (frags) {
+      LCD_HIP(d, launch_pack_conv_w_frags(s, dt, b + o_uw[l], b + o_uf[l], g.widths[l + 1], g.widths[l]));
+      d->upc[l].wf = b + o_uf[l];
+    }
   }
   F32(w->out.gn_g, o_og, CL, CL); F32(w->out.gn_b, o_ob, CL, CL);
   CW(w->out.w, o_ow, g.C_img, CL, 32); F32(w->out.b, o_obias, g.C_img, 32);
   d->out_gn = GnP{(float*)(b + o_og), (float*)(b + o_ob)};
-  d->out = ConvP{b + o_ow, (float*)(b + o_obias)};
+  d->out = ConvP{b + o_ow, (float*)(b + o_obias), nullptr};
 #undef F32
 #undef CW
   LCD_HIP(d, hipStreamSynchronize(s));

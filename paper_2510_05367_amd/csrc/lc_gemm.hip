@@ -708,10 +708,16 @@ hipError_t launch_fused(hipStream_t s, const FusedDesc& d) {
   if (d.stat && (d.taps != 9 || d.planar_out || !(d.y_f32 || esz == 4) || d.stat_splits != conv_stat_splits(d.H, d.W)))
     return hipErrorInvalidValue;
   if (d.Cin % (kRow / esz) != 0) return hipErrorInvalidValue;
-  if (d.up2 && (d.taps != 9 || d.src != 1 || ((d.H | d.W) & 1))) return hipErrorInvalidValue;
+  if (d.up2 && (d.taps != 9 || d.src > 1 || ((d.H | d.W) & 1))) return hipErrorInvalidValue;
   if (d.src == 3 && (d.Cs % (kRow / esz) != 0 || d.Cs <= 0 || d.Cs >= d.Cin || (d.H | d.W) & 1)) return hipErrorInvalidValue;
-  if (d.taps == 9) {  // the kernel with specialised wavefronts where the stage's widths suit it
-    const hipError_t e = launch_conv_ws(s, d);
+  if (d.taps == 9) {
+    // an activation pass and the kernel without loaders where there is room for the activated rows; else the kernel with
+    // specialised wavefronts where the stage's widths suit it. All agree bit for bit. (at 32 frames of 64 x 64, 320 channels:
+    // residual convolution 343 us with specialised wavefronts, 37 + 225 here; up convolution 848 and 52 + 556)
+    hipError_t e = d.w_frags ? (d.src ? launch_conv_act_dma(s, d) : launch_conv_dma(s, d)) : hipErrorNotSupported;
+    if (e != hipErrorNotSupported) return e;
+    if (d.bias_div || d.src == 0) return hipErrorInvalidValue;  // only that kernel has a bias per frame and takes rows as they are
+    e = launch_conv_ws(s, d);
     if (e != hipErrorNotSupported) return e;
   }
   if (d.taps == 1 && d.src == 0) {  // dense bf16 rows: the kernel with a ring of LDS stages

@@ -31,6 +31,11 @@ hipError_t launch_gn_finalize(hipStream_t s, const float* partA, int CA, int spl
 // (C % 8 == 0), gathered through m; y dense bf16 rows.
 hipError_t launch_gn_apply(hipStream_t s, const float* x, const float* scale, const float* shift, void* y, int64_t rows, int C,
                            int rows_per_frame, RowMap m);
+// The rows a 3x3 convolution contracts, for launch_conv_dma: y (bf16 [frames][rows_per_frame][Ca + Cb]) = SiLU(x * scale[f] + shift[f]),
+// or x where scale is nullptr, with x the channel concatenation of xa [..][Ca] and xb [..][Cb] (Cb may be 0), both of type
+// x_dt; scale / shift rows of a frame are ld floats apart. Ca, Cb multiples of 8. hipErrorNotSupported for shapes it does not cover.
+hipError_t launch_conv_act(hipStream_t s, int x_dt, const void* xa, int Ca, const void* xb, int Cb, const float* scale, const float* shift,
+                           int ld, void* y, int frames, int rows_per_frame);
 // A spatial window of a frame, in pixels: the spatial block of a feature chunk. w == 0: the whole frame.
 struct Win { int x0, y0, w, h; };
 
@@ -80,10 +85,15 @@ struct FusedDesc {
   const void* w;       // [Cout][taps*Cin]
   const void* w_tiles; // taps == 9, optional: the same weights in the order of launch_pack_conv_w_tiles (what the
                        // specialised-wavefront kernel reads; without it the general kernel runs)
+  const void* w_frags; // taps == 9, optional: the same weights in the order of launch_pack_conv_w_frags, and ...
+  void* xact;          // ... xact_bytes of scratch for activated rows (conv_act_bytes): with both, a bf16 convolution of whole frames
+  size_t xact_bytes;   // runs as an activation pass and launch_conv_dma. src 0 needs no scratch
+  // taps == 9 through launch_conv_dma only: frame f of the launch takes bias + (bias_f0 + f) / bias_div * Cout (bias_div 0: bias)
+  int bias_div, bias_f0;
   const void* w_frag;  // taps == 1: the same matrix in MFMA fragment order (launch_pack_lin_w), or nullptr
   const float* bias;   // [Cout] or nullptr
   int frames, H, W;    // taps == 9
-  int up2;             // taps == 9, src == 1: x is [frames][H / 2][W / 2][Cin] and is upsampled 2x (nearest) on the way in
+  int up2;             // taps == 9, src == 1 (or 0 through launch_conv_dma): x is [frames][H / 2][W / 2][Cin] and is upsampled 2x (nearest) on the way in
   // Spatial window (the spatial block of a feature chunk): only the pixels [win_y0, win_y0 + win_h) x
   // [win_x0, win_x0 + win_w) of every frame are computed, by the tiles they belong to in the whole frame (a
   // window starts on a tile boundary and ends on one or at the frame's edge), with the halo read from the
@@ -155,6 +165,16 @@ hipError_t launch_fused(hipStream_t s, const FusedDesc& d);
 // taps == 9 of a bf16 stage with specialised wavefronts (lc_convws.hip): the same results as the general
 // kernel bit for bit; hipErrorNotSupported for shapes it does not cover. launch_fused tries it first.
 hipError_t launch_conv_ws(hipStream_t s, const FusedDesc& d);
+// taps == 9, src == 0 of a bf16 stage: a convolution over rows that are activated and rounded already (lc_convd.hip). src == 3:
+// x are those of the skip channels, x2 those of the deep ones at half the resolution. The same results as the kernels that
+// activate in their loader bit for bit; hipErrorNotSupported for shapes it does not cover.
+hipError_t launch_conv_dma(hipStream_t s, const FusedDesc& d);
+// src 1..3 with w_frags and xact: activation pass(es) into xact, then launch_conv_dma
+hipError_t launch_conv_act_dma(hipStream_t s, const FusedDesc& d);
+inline size_t conv_act_bytes(const FusedDesc& d) {
+  const size_t px = (size_t)d.frames * d.H * d.W;
+  return d.src == 3 ? px * d.Cs * 2 + px / 4 * (d.Cin - d.Cs) * 2 : (d.up2 ? px / 4 : px) * d.Cin * 2;
+}
 // taps == 1, src == 0 of a bf16 stage (lc_lin2.hip, lc_lin3.hip: operands streamed through a ring of LDS stages);
 // hipErrorNotSupported for widths it does not cover, never because of the rows. launch_fused tries it first.
 hipError_t launch_lin2(hipStream_t s, const FusedDesc& d);
@@ -210,6 +230,8 @@ hipError_t launch_pack_conv_w(hipStream_t s, int dt, const void* w, void* packed
 hipError_t launch_pack_conv_in_w(hipStream_t s, int dt, const void* w, float* packed, int C, int Cl);
 // packed [Cout][9*Cin] -> tiles [Cout/160][9*Cin/64][160][64] (bf16; Cout % 160 == 0, Cin % 64 == 0)
 hipError_t launch_pack_conv_w_tiles(hipStream_t s, int dt, const void* w, void* tiles, int Cout, int Cin);
+// packed [Cout][9*Cin] -> MFMA fragments for launch_conv_dma (bf16; Cout % 32 == 0, Cin % 64 == 0)
+hipError_t launch_pack_conv_w_frags(hipStream_t s, int dt, const void* w, void* frags, int Cout, int Cin);
 // w[Cout][Cin] -> MFMA fragment order for launch_linear
 hipError_t launch_pack_lin_w(hipStream_t s, int dt, const void* w, void* out, int Cout, int Cin);
 // w[Cout][Cin] -> out[Cout][Cin_padded] with zero columns appended

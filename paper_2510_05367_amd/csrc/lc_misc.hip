@@ -132,6 +132,28 @@ hipError_t launch_pack_conv_w_tiles(hipStream_t s, int dt, const void* w, void* 
   return hipGetLastError();
 }
 
+// packed [Cout][9*Cin] -> MFMA fragments [Cin / 64][9][2][2][Cout / 32][64][8]: (slab, tap, k-step, half of the slab, channel tile,
+// lane, element); lane l holds channel l % 32 of the tile and input channels 8 * (l / 32) ..+7 of the 16 of half and k-step
+__global__ void pack_conv_w_frags_kernel(const bf16_t* __restrict__ w, bf16_t* __restrict__ frags, int Cout, int Cin) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i >= (int64_t)Cout * 9 * Cin) return;
+  const int e = (int)(i & 7), l = (int)(i >> 3) & 63;
+  int64_t r = i >> 9;
+  const int ct = Cout / 32, tile = (int)(r % ct);
+  r /= ct;
+  const int half = (int)(r & 1), kk = (int)(r >> 1) & 1;
+  r >>= 2;
+  const int tap = (int)(r % 9), slab = (int)(r / 9);
+  const int co = tile * 32 + (l & 31), ci = slab * 64 + half * 32 + kk * 16 + (l >> 5) * 8 + e;
+  frags[i] = w[(int64_t)co * (9 * Cin) + tap * Cin + ci];
+}
+hipError_t launch_pack_conv_w_frags(hipStream_t s, int dt, const void* w, void* frags, int Cout, int Cin) {
+  if (dt != kBF16 || Cout % 32 != 0 || Cin % 64 != 0) return hipErrorInvalidValue;
+  const int64_t total = (int64_t)Cout * 9 * Cin;
+  pack_conv_w_frags_kernel<<<(unsigned)((total + 255) / 256), 256, 0, s>>>((const bf16_t*)w, (bf16_t*)frags, Cout, Cin);
+  return hipGetLastError();
+}
+
 template <class T>
 __global__ void pack_conv_in_w_kernel(const T* __restrict__ w, float* __restrict__ packed, int C, int Cl) {
   const int total = C * Cl * 9;

@@ -128,7 +128,7 @@ __global__ __launch_bounds__(256) void temb_bias_kernel(const T* __restrict__ te
   if (lane == 0) out[item] = acc + bt[o] + bias[o];
 }
 
-// dst[r][0:Ca] = a[r][:], dst[r][Ca:Ca+Cb] = b[r][:] (fp32, Ca and Cb multiples of 4), fused with what the residual
+// dst[r][0:Ca] = a[r][:], dst[r][Ca:Ca+Cb] = b[r][:] (fp32, Ca and Cb multiples of 4; dst may be nullptr), fused with what the residual
 // block needs of the concatenated rows next: their GroupNorm partial sums (partial[frame][split][Ca + Cb][2], 64-row splits as the statistics kernel writes them, folded in
 // the same fixed order) and, when yb != nullptr, a copy rounded to bf16 (the operand of the 1x1 shortcut). One
 // workgroup = one split of one frame and up to 256 packets of 4 channels (gridDim.z of them side by side).
@@ -155,7 +155,7 @@ __global__ __launch_bounds__(256) void concat_stats_kernel(const float* __restri
     for (int r = r0 + rsub; r < r1; r += R) {
       const f32x4 v = src[(int64_t)r * ld];
       const int64_t o = ((int64_t)frame * rows_per_frame + r) * W4 + c;
-      reinterpret_cast<f32x4*>(dst)[o] = v;
+      if (dst) reinterpret_cast<f32x4*>(dst)[o] = v;
       if (yb) {
         bf16x4 h;
 #pragma unroll
@@ -195,7 +195,7 @@ thread_local std::string g_uerr = "";
 constexpr size_t kAlign = 256;
 inline size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 
-struct ConvP { void *w, *wt; float* b; };            // packed [Cout][9][Cin], the same in tile order (or nullptr), bias
+struct ConvP { void *w, *wf; float* b; };            // packed [Cout][9][Cin], the same in fragment order (or nullptr), bias
 struct LinP { void* w; float* b; };                  // [Cout][Cin] operand type, fp32 bias (or nullptr)
 struct NormP { float *g, *b; };
 struct RbP { int cin, cout; NormP gn1, gn2; ConvP conv1, conv2; float *temb_w, *temb_b; LinP shortcut; };
@@ -212,7 +212,7 @@ struct UPlan {
   size_t map_bytes;  // one map of all frames: the largest tensor that passes between two blocks
   size_t off_map[3], off_s, off_d1, off_slots, slot_bytes;
   size_t off_part, off_parta, off_partb, off_scale, off_shift, off_one, off_zero, off_tb, off_kv, off_vtx;
-  size_t off_xc, off_h, off_sc, off_xb;                           // one chunk inside a residual block
+  size_t off_xc, xc_bytes, off_h, off_sc, off_xb;                           // one chunk inside a residual block
   size_t off_z, off_a, off_qkv, off_vt, off_ao, off_u, off_g;     // one chunk inside a transformer block (same memory)
   size_t total;
 };
@@ -345,7 +345,8 @@ UPlan make_uplan(const lc_unet_config& g, int frame_chunk) {
   // ---- one chunk, residual blocks
   const int64_t cat = std::max(nc0 * P * (g.C + g.C1), nc1 * P1 * (g.C1 + g.C2));
   const int64_t hid = std::max({nc0 * P * g.C, nc1 * P1 * g.C1, nc2 * P2 * g.C2});
-  p.off_xc = take((size_t)cat * 4);
+  p.xc_bytes = (size_t)cat * 4;
+  p.off_xc = take(p.xc_bytes);
   p.off_h = take((size_t)hid * 4);
   p.off_sc = take((size_t)hid * 4);
   p.off_xb = take(g.dtype == kBF16 ? (size_t)cat * es : 0);
@@ -406,14 +407,17 @@ lc_status gn(lc_unet* c, const float* x, int n, int rows, int C, const NormP& w)
 
 // y = [res +] conv3x3(act(x)) over n frames; src 2: SiLU(GroupNorm(x)) with the scale / shift at hand (those of frame
 // `f0` on), src 1: x, at half the resolution, nearest 2x upsampled. planar: y is [n][Cout_store][H][W] of the stage's dtype (the last convolution).
-// stat: where the partial sums of y go ([frame of the launch][conv_stat_splits(H, W)][Cout][2]), or nullptr.
+// stat: where the partial sums of y go ([frame of the launch][conv_stat_splits(H, W)][Cout][2]), or nullptr. act: whether the
+// chunk's buffer `xc` is free for activated rows.
 lc_status conv(lc_unet* c, const ConvP& w, const float* bias, int src, int Cin, int Cout, int n, int f0, int H, int W, const float* x,
-               const float* res, void* y, int planar, int Cout_store, float* stat = nullptr) {
+               const float* res, void* y, int planar, int Cout_store, float* stat = nullptr, bool act = false) {
   const UPlan& p = c->plan;
   FusedDesc f;
   memset(&f, 0, sizeof f);
+  f.w_frags = w.wf;
+  if (act) { f.xact = c->arena + p.off_xc; f.xact_bytes = p.xc_bytes; }
   f.dt = c->cfg.dtype; f.y_f32 = planar ? 0 : 1; f.taps = 9; f.src = src; f.Cin = Cin; f.Cout = Cout; f.Cout_store = Cout_store;
-  f.w = w.w; f.w_tiles = w.wt; f.bias = bias; f.frames = n; f.H = H; f.W = W; f.x = x; f.res = res; f.y = y; f.planar_out = planar;
+  f.w = w.w; f.bias = bias; f.frames = n; f.H = H; f.W = W; f.x = x; f.res = res; f.y = y; f.planar_out = planar;
   f.up2 = src == 1;
   f.scale = (const float*)(c->arena + (src == 2 ? p.off_scale : p.off_one)) + (size_t)f0 * Cin;
   f.shift = (const float*)(c->arena + (src == 2 ? p.off_shift : p.off_zero)) + (size_t)f0 * Cin;
@@ -534,21 +538,35 @@ lc_status res_block(lc_unet* c, const RbP& w, const void* temb, int level, const
     // (a shortcut through the dense-row kernel contracts x rounded to bf16)
     const bool short16 = w.shortcut.w && g.dtype == kBF16 && w.cout % 160 == 0;
     void* xb16 = c->arena + p.off_xb;
+    // The first convolution contracts rows activated in a pass of their own. Of a concatenated input that is all that is
+    // read but the rounded copy, so the pass takes it from the two tensors and the fp32 concatenation exists nowhere.
+    FusedDesc f1;
+    memset(&f1, 0, sizeof f1);
+    f1.dt = g.dtype; f1.y_f32 = 1; f1.taps = 9; f1.Cin = w.cin; f1.Cout = w.cout; f1.Cout_store = w.cout; f1.w_frags = w.conv1.wf;
+    f1.H = H; f1.W = W; f1.x = xc; f1.y = h; f1.stat = part; f1.stat_splits = cs;
+    f1.bias = tb; f1.bias_div = g.F; f1.bias_f0 = n0;  // the time embedding is one vector per batch element: its frames share a bias
+    const bool rows16 = (!Cb || short16) && (size_t)nc * P * w.cin * 2 <= p.xc_bytes && launch_conv_dma(c->cs, f1) == hipSuccess;  // (no frames yet)
     if (Cb) {
-      LCU_TRY(concat_stats(c, x, Ca, xb + (size_t)n0 * P * Cb, Cb, xc, short16 ? xb16 : nullptr, nc, P));
-      x = xc;
+      LCU_TRY(concat_stats(c, x, Ca, xb + (size_t)n0 * P * Cb, Cb, rows16 ? nullptr : xc, short16 ? xb16 : nullptr, nc, P));
+      if (!rows16) x = xc;
       LCU_TRY(gn_fold(c, Stats{part, stat_splits(P)}, nc, P, w.cin, w.gn1));
     } else if (in.part) {
       LCU_TRY(gn_fold(c, Stats{in.part + (size_t)n0 * in.splits * w.cin * 2, in.splits}, nc, P, w.cin, w.gn1));
     } else {
       LCU_TRY(gn(c, x, nc, P, w.cin, w.gn1));
     }
-    // the time embedding is one vector per batch element: its frames share a bias
     // (the scale / shift of x are folded by now: the partial sums of h may take the scratch)
-    LCU_TRY(batch_runs(g, n0, nc, [&](int b, int i0, int n) {
-      return conv(c, w.conv1, tb + (size_t)b * w.cout, 2, w.cin, w.cout, n, i0, H, W, x + (size_t)i0 * P * w.cin, nullptr,
-                  h + (size_t)i0 * P * w.cout, 0, w.cout, part + (size_t)i0 * cs * w.cout * 2);
-    }));
+    if (rows16) {
+      LCU_HIP(c, launch_conv_act(c->cs, kF32, x, Cb ? Ca : w.cin, Cb ? xb + (size_t)n0 * P * Cb : nullptr, Cb,
+                                 (const float*)(c->arena + p.off_scale), (const float*)(c->arena + p.off_shift), w.cin, xc, nc, P));
+      f1.frames = nc;
+      LCU_HIP(c, launch_conv_dma(c->cs, f1));
+    } else {
+      LCU_TRY(batch_runs(g, n0, nc, [&](int b, int i0, int n) {
+        return conv(c, w.conv1, tb + (size_t)b * w.cout, 2, w.cin, w.cout, n, i0, H, W, x + (size_t)i0 * P * w.cin, nullptr,
+                    h + (size_t)i0 * P * w.cout, 0, w.cout, part + (size_t)i0 * cs * w.cout * 2);
+      }));
+    }
     const float* res = x;
     if (w.shortcut.w) {
       const int64_t rows = (int64_t)nc * P;
@@ -566,7 +584,7 @@ lc_status res_block(lc_unet* c, const RbP& w, const void* temb, int level, const
     }
     LCU_TRY(gn_fold(c, Stats{part, cs}, nc, P, w.cout, w.gn2));
     return conv(c, w.conv2, w.conv2.b, 2, w.cout, w.cout, nc, 0, H, W, h, res, y + (size_t)n0 * P * w.cout, 0, w.cout,
-                out ? out + (size_t)n0 * cs * w.cout * 2 : nullptr);
+                out ? out + (size_t)n0 * cs * w.cout * 2 : nullptr, true);
   });
 }
 
@@ -699,7 +717,7 @@ lc_status down_conv(lc_unet* c, const ConvP& w, int C, int level, const float* x
 lc_status up_conv(lc_unet* c, const ConvP& w, int C, int level, const float* x, float* y) {
   const int H = c->cfg.H >> (level + 1), W = c->cfg.W >> (level + 1);
   return frame_chunks(c, level, [&](int n0, int nc) -> lc_status {
-    return conv(c, w, w.b, 1, C, C, nc, 0, 2 * H, 2 * W, x + (size_t)n0 * H * W * C, nullptr, y + (size_t)n0 * 4 * H * W * C, 0, C);
+    return conv(c, w, w.b, 1, C, C, nc, 0, 2 * H, 2 * W, x + (size_t)n0 * H * W * C, nullptr, y + (size_t)n0 * 4 * H * W * C, 0, C, nullptr, true);
   });
 }
 
@@ -929,14 +947,14 @@ lc_status lc_unet_load_weights(lc_unet* c, const lc_unet_weights* w) {
         }
     return q;
   };
-  auto conv3 = [&](const void* wsrc, const void* bsrc, int cout, int cin, int cout_pad, bool tiles) {
+  auto conv3 = [&](const void* wsrc, const void* bsrc, int cout, int cin, int cout_pad, bool frags) {
     ConvP q;
     q.w = take((size_t)cout_pad * 9 * cin * es);
     if (fill) note(launch_pack_conv_w(s, dt, wsrc, q.w, cout, cin, 9, cout_pad));
-    q.wt = nullptr;
-    if (tiles && dt == kBF16 && cout % 160 == 0 && cin % 64 == 0) {
-      q.wt = take((size_t)cout * 9 * cin * es);
-      if (fill) note(launch_pack_conv_w_tiles(s, dt, q.w, q.wt, cout, cin));
+    q.wf = nullptr;
+    if (frags && dt == kBF16) {  // what the kernel over activated rows reads
+      q.wf = take((size_t)cout * 9 * cin * es);
+      if (fill) note(launch_pack_conv_w_frags(s, dt, q.w, q.wf, cout, cin));
     }
     q.b = (float*)take((size_t)cout_pad * 4);
     if (fill) note(launch_to_f32(s, dt, bsrc, q.b, cout, cout_pad));
@@ -1005,8 +1023,8 @@ lc_status lc_unet_load_weights(lc_unet* c, const lc_unet_weights* w) {
       }
     c->down[0] = conv3(w->down[0].w, w->down[0].b, C, C, C, false);
     c->down[1] = conv3(w->down[1].w, w->down[1].b, C1, C1, C1, false);
-    c->up[0] = conv3(w->up[0].w, w->up[0].b, C2, C2, C2, false);
-    c->up[1] = conv3(w->up[1].w, w->up[1].b, C1, C1, C1, false);
+    c->up[0] = conv3(w->up[0].w, w->up[0].b, C2, C2, C2, true);
+    c->up[1] = conv3(w->up[1].w, w->up[1].b, C1, C1, C1, true);
     c->out_gn = norm(w->out_gn_g, w->out_gn_b, C);
     c->out = conv3(w->out.w, w->out.b, g.C_lat, C, 32, false);
   };
