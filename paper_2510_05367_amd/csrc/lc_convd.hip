@@ -16,15 +16,19 @@
 // All widths CO_T and those kernels agree bit for bit, so the width may follow the launch's size.
 //
 // LDS holds 80 KB at most, so that two workgroups share a compute unit and cover each other's waits:
-//  * a ring of four weight sub-steps (16 channels of both halves for one tap: 2 * CO_T fragments of 1 KB in fragment order, as
-//    the weights are laid out at load time; reads are 1 KB in a row);
+//  * a ring of four to eight weight sub-steps (16 channels of both halves for one tap: 2 * CO_T fragments of 1 KB in fragment
+//    order, as the weights are laid out at load time; reads are 1 KB in a row);
 //  * a ring of 16 halo lines of 20 pixels x 64 channels (18 used; 16-byte slots XOR-swizzled by the pixel so that 16
 //    consecutive pixels hit all banks). A slab has 10 lines. Lines 0..5 of the next slab lie in no line of this one, lines 6
 //    and 7 where lines 0 and 1 of this one were, which its taps 6..8 no longer read, lines 8 and 9 where its lines 2 and 3
 //    were: they are requested in the next slab's first sub-step and first read at its tap 3.
 // A sub-step u: its fragments are in registers; those of u + 1 are read from LDS while its MFMAs are issued, the weights of
-// u + 4 are requested into the slot u had, and it ends with a wait for these reads and for the weights of u + 2 (in order:
-// also for every halo line requested up to sub-step u - 2) and the workgroup's barrier.
+// u + ring are requested into the slot u had, and it ends with a wait for these reads and for the weights of u + 2 (and what
+// was requested before them) and the workgroup's barrier.
+// A lone workgroup of 160 channels on an idle chip takes 24 us for 90 sub-steps: 12 of MFMAs, 5 of everything else in the loop,
+// 7 of launch, first loads and epilogue; 256 of them 34, the rest being the residual and the output (42 MB at the rate of a
+// copy), which only a second workgroup per compute unit covers. Eight wavefronts of 32 pixels instead of four of 64 (two per
+// SIMD also where a launch has one workgroup per compute unit) measured the same there and 20-40 % slower in larger launches.
 #include <type_traits>
 
 #include "lc_internal.h"
@@ -33,7 +37,6 @@ namespace lc {
 
 namespace {
 
-constexpr int kdRing = 4;        // weight sub-steps in LDS
 constexpr int kdLines = 16;      // halo lines in LDS
 constexpr int kdLine = 20 * 128; // bytes of a halo line
 constexpr int kdSub = 18;        // sub-steps of a slab: 9 taps x 2
@@ -52,7 +55,11 @@ struct ConvDArgs {
   int stat_splits;
 };
 
-template <int CO_T> constexpr int cd_lds_bytes() { return kdRing * 2 * CO_T * 1024 + kdLines * kdLine; }
+// weight sub-steps in LDS: as many as fit beside the halo lines. Narrow workgroups have short sub-steps and need more of them
+// in flight to cover a request's way from L2 (us; two tiles, 4 frames of 64 x 64, 320 channels: 41.7 with a ring of four, 35.4
+// with eight; three tiles, a frame of 256 x 256, 192 channels: 51.3 with four, 46.9 with six)
+template <int CO_T> constexpr int cd_ring() { return CO_T == 2 ? 8 : CO_T == 3 ? 6 : 4; }
+template <int CO_T> constexpr int cd_lds_bytes() { return cd_ring<CO_T>() * 2 * CO_T * 1024 + kdLines * kdLine; }
 // tiles handed over at a time in the epilogue: their fp32 values of four wavefronts and the four patches must fit
 template <int CO_T> constexpr int cd_give() {
   int g = CO_T;
@@ -60,12 +67,38 @@ template <int CO_T> constexpr int cd_give() {
   return g;
 }
 
-// halo requests every wavefront issues in sub-step t of a slab (a fifth instruction, by one of them, is not counted)
+// Requests that every wavefront has issued (one of them a fifth instruction for a pair of halo lines, some the extra weight
+// fragment of an odd width: these wait for a little more than they need to). Weights of n sub-steps in a row:
+constexpr int cd_weights(int n, int cot) { return n / 2 * cot + n % 2 * (cot / 2); }
+// halo lines in sub-step t of a slab
 constexpr int cd_halo(int t, bool more) { return t == 0 || (more && (t == 2 || t == 4 || t == 6 || t == 12)) ? 1 : 0; }
-// requests that may be in flight at the end of sub-step t: all that are younger than the weights of t + 2
-constexpr int cd_keep(int t, bool more, int cot) {
-  const int w = (more || t + 4 < kdSub) ? cot : (t + 3 < kdSub) ? cot / 2 : 0;
-  return w + (t > 0 ? cd_halo(t - 1, more) : 0) + cd_halo(t, more);
+// Requests that may be in flight at the end of sub-step t: all that are younger than the weights of t + 2, which were requested
+// ring - 2 sub-steps ago (a slab begins with the last halo lines of the one before landed); and at the end of sub-steps 4 and 16 all that are younger than the halo lines requested in 0 and 12,
+// which are read from the next sub-step but one on
+constexpr int cd_keep(int t, bool more, int cot, int ring) {
+  int n = more ? ring - 2 : kdSub - 3 - t < ring - 2 ? kdSub - 3 - t : ring - 2;
+  int k = cd_weights(n > 0 ? n : 0, cot);
+  for (int q = t + 3 - ring > 0 ? t + 3 - ring : 0; q <= t; ++q) k += cd_halo(q, more);
+  if (t == 4 || (t == 16 && more)) {
+    int h = 0, m = 0;
+    for (int q = t - 4; q <= t; ++q) {
+      m += more || q + ring < kdSub;
+      if (q > t - 4) h += cd_halo(q, more);
+    }
+    const int k2 = cd_weights(m, cot) + h;
+    k = k2 < k ? k2 : k;
+  }
+  return k;
+}
+
+// the sum over the eight lanes that are equal modulo 8, in all of them: by lane distances 8, 16, 32, without LDS
+__device__ __forceinline__ float fold8(float x) {
+  const int i = __builtin_bit_cast(int, x);
+  x += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, i, 0x128, 0xf, 0xf, true));  // row_ror:8
+  auto r = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(unsigned, x), __builtin_bit_cast(unsigned, x), false, false);
+  x = __builtin_bit_cast(float, (unsigned)r[0]) + __builtin_bit_cast(float, (unsigned)r[1]);
+  r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, x), __builtin_bit_cast(unsigned, x), false, false);
+  return __builtin_bit_cast(float, (unsigned)r[0]) + __builtin_bit_cast(float, (unsigned)r[1]);
 }
 
 }  // namespace
@@ -74,8 +107,9 @@ template <int CO_T, class OT>
 __global__ __launch_bounds__(256, 2) void conv_dma_kernel(ConvDArgs a) {
   typedef Mma32<bf16_t> M;
   constexpr int kSlot = 2 * CO_T * 1024;
+  constexpr int kRing = cd_ring<CO_T>();
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
-  unsigned char* const hl = smem + kdRing * kSlot;
+  unsigned char* const hl = smem + kRing * kSlot;
 
   const int lane = threadIdx.x & 63, wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lp = lane & 31, hh = lane >> 5;
@@ -118,22 +152,24 @@ __global__ __launch_bounds__(256, 2) void conv_dma_kernel(ConvDArgs a) {
     if (wid == (p & 3)) __builtin_amdgcn_raw_ptr_buffer_load_lds(hsrc, dst + 4096, 16, hofs[1] + adv, 0, 0, 0);
 #endif
   };
-  // ---- requests: weights of sub-step u. Fragment f = kh' * CO_T + i; a wavefront takes every fourth one, and the two left over
+  // ---- requests: weights of sub-step u. Fragment f = kh' * CO_T + i. A wavefront takes every fourth one, and the two left over
   // of an odd CO_T go to two wavefronts in even and to the other two in odd sub-steps: CO_T requests each in any two in a row
-  auto wfrag = [&](int j) { return (CO_T & 1) && j == CO_T / 2 ? (CO_T / 2) * 4 + (wid & 1) : j * 4 + wid; };
+  constexpr bool ODD = CO_T & 1;
+  constexpr int WJ = (CO_T + 1) / 2;  // requests per sub-step; the last one of an odd CO_T not of every wavefront
+  auto wfrag = [&](int j) { return ODD && j + 1 == WJ ? j * 4 + (wid & 1) : j * 4 + wid; };
   const __amdgpu_buffer_rsrc_t wsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(a.w), 0, a.Cin * 9 * a.Cout * 2, kdRawBuffer);
   const unsigned wofs = lane * 16;
-  constexpr int WJ = (CO_T + 1) / 2;  // requests per sub-step; the last one of an odd CO_T only in every other
-  int wsub[WJ];                       // byte offsets in a sub-step's fragments: of the source (all channels) ...
+  int wsub[WJ];  // byte offsets in a sub-step's fragments of all channels
 #pragma unroll
   for (int j = 0; j < WJ; ++j) {
     const int f = wfrag(j);
     wsub[j] = ((f >= CO_T ? ct - CO_T : 0) + cb * CO_T + f) * 1024;
   }
   const int wadv = 2 * ct * 1024;
-  auto wreq = [&](int uofs, int slot, int j, int odd) {  // request j of the sub-step at source offset uofs into ring offset slot
+  // request j of the sub-step at source offset uofs into ring offset slot; odd: of the sub-step's number
+  auto wreq = [&](int uofs, int slot, int j, int odd) {
 #ifdef __HIP_DEVICE_COMPILE__
-    if (!(CO_T & 1) || j + 1 < WJ || (wid >> 1) == odd)
+    if (!ODD || j + 1 < WJ || (wid >> 1) == odd)
       __builtin_amdgcn_raw_ptr_buffer_load_lds(wsrc, smem + slot + wfrag(j) * 1024, 16, wofs, uofs + wsub[j], 0, 0);
 #else
     (void)uofs; (void)slot; (void)j; (void)odd; (void)wofs; (void)wsrc;
@@ -149,8 +185,9 @@ __global__ __launch_bounds__(256, 2) void conv_dma_kernel(ConvDArgs a) {
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
   // Tile column 0 of the accumulators is the one this wavefront finishes after the K halves are folded, column 1 the one
-  // its partner (pxh, kh ^ 1) finishes: which 32 pixels (two image rows) that is depends on kh, the code does not.
-  const int ly[2] = {pxh * 4 + kh * 2 + (lp >> 4), pxh * 4 + (kh ^ 1) * 2 + (lp >> 4)};
+  // its partner of the other half finishes: which 32 pixels (two image rows) that is depends on kh, the code does not.
+  const int quarter = pxh * 2 + kh;  // the 32 pixels of column 0
+  const int ly[2] = {quarter * 2 + (lp >> 4), (quarter ^ 1) * 2 + (lp >> 4)};
   unsigned xofs[3];  // of k-step 0 for dx = 0..2; k-step 1 is 2 packets on: offset ^ 32
 #pragma unroll
   for (int dx = 0; dx < 3; ++dx) {
@@ -172,20 +209,20 @@ __global__ __launch_bounds__(256, 2) void conv_dma_kernel(ConvDArgs a) {
 #pragma unroll
   for (int p = 0; p < 4; ++p) halo(0, p, 0);
 #pragma unroll
-  for (int u = 0; u < 4; ++u)
+  for (int u = 0; u < kRing; ++u)
 #pragma unroll
     for (int j = 0; j < WJ; ++j) wreq(u * wadv, u * kSlot, j, u & 1);
-  barrier_keep<CO_T>();  // the weights of sub-steps 0 and 1 and lines 0..7 have landed
+  barrier_keep<cd_weights(kRing - 2, CO_T)>();  // the weights of sub-steps 0 and 1 and lines 0..7 have landed
   M::Frag w[CO_T], x[2];
 #pragma unroll
   for (int i = 0; i < CO_T; ++i) w[i] = wread(0, i);
   x[0] = xread(0, 0, 0);
   x[1] = xread(0, 0, 1);
-  barrier_keep<CO_T>();
+  barrier_keep<cd_weights(kRing - 2, CO_T)>();
 
   const int nskip = a.Cs >> 6;
-  int slot = 0;          // ring offset of the current sub-step, whose fragments are in registers: the weights of the fourth
-  int uofs = 4 * wadv;   // one from here go there, from this offset of the source
+  int slot = 0;             // ring offset of the current sub-step, whose fragments are in registers: the weights of the kRing-th
+  int uofs = kRing * wadv;  // one from here go there, from this offset of the source
   auto slab_body = [&](int slab, auto more_c) {
     constexpr bool MORE = decltype(more_c)::value;
     auto cofs = [&](int s) { return (s < nskip ? s : s - nskip) * 128; };
@@ -193,7 +230,7 @@ __global__ __launch_bounds__(256, 2) void conv_dma_kernel(ConvDArgs a) {
       constexpr int t = decltype(t_c)::value;
       M::Frag wn[CO_T], xn[2];
       constexpr bool NEXT = MORE || t + 1 < kdSub;
-      const int rd = slot + kSlot == kdRing * kSlot ? 0 : slot + kSlot;  // where the weights of the next sub-step are
+      const int rd = slot + kSlot == kRing * kSlot ? 0 : slot + kSlot;  // where the weights of the next sub-step are
       if (MORE && t == 1)
         if (slab + 1 == nskip) source(a.x2, a.Cin - a.Cs, 1);
       // one request or fragment read behind each MFMA: several in a row hold the next MFMA up
@@ -216,13 +253,13 @@ __global__ __launch_bounds__(256, 2) void conv_dma_kernel(ConvDArgs a) {
         }
 #pragma unroll
         for (int j = 0; j < WJ; ++j)
-          if (g == CO_T + 1 + j && (MORE || t + 4 < kdSub)) wreq(uofs, slot, j, t & 1);
+          if (g == 2 * CO_T - WJ + j && (MORE || t + kRing < kdSub)) wreq(uofs, slot, j, t & 1);
         __builtin_amdgcn_sched_barrier(0);
       }
       uofs += wadv;
       slot = rd;
       if (NEXT) {
-        step_end(std::integral_constant<int, cd_keep(t, MORE, CO_T)>{});
+        step_end(std::integral_constant<int, cd_keep(t, MORE, CO_T, kRing)>{});
 #pragma unroll
         for (int i = 0; i < CO_T; ++i) w[i] = wn[i];
         x[0] = xn[0];
@@ -242,23 +279,30 @@ __global__ __launch_bounds__(256, 2) void conv_dma_kernel(ConvDArgs a) {
   // through a private patch so that eight lanes store 128 contiguous bytes of a pixel; as many tiles at a time as fit
   constexpr int G = cd_give<CO_T>();
   constexpr int kTile = 16 * 64;
-  float* give = reinterpret_cast<float*>(smem) + (pxh * 2 + kh) * (G * kTile);
-  const float* take = reinterpret_cast<const float*>(smem) + (pxh * 2 + (kh ^ 1)) * (G * kTile);
-  float* patch = reinterpret_cast<float*>(smem + 4 * G * kTile * 4) + wid * (32 * 36);
+  float* give = reinterpret_cast<float*>(smem) + quarter * (G * kTile);
+  const float* take = reinterpret_cast<const float*>(smem) + (quarter ^ 1) * (G * kTile);
+  float* patch = reinterpret_cast<float*>(smem + 4 * G * kTile * 4) + quarter * (32 * 36);
   const int prow = lane >> 3, pcol = (lane & 7) * 4;  // patch read-back: rows prow + 8 k, channels pcol..pcol+3
   const int co0 = cb * CO_T * 32;
-  int64_t obase[4];
+  // Output and residual through buffer descriptors over the tile's eight image rows: a pixel beyond the edge has an offset out
+  // of range, whose load gives zero and whose store is dropped, so neither needs a condition per pixel
+  const int64_t row0 = ((int64_t)frame * a.H + ty0) * a.W * a.Cout + co0;
+  const int rows8 = 8 * a.W * a.Cout;
+  const __amdgpu_buffer_rsrc_t ydst = __builtin_amdgcn_make_buffer_rsrc((OT*)a.y + row0, 0, rows8 * (int)sizeof(OT), kdRawBuffer);
+  const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(a.res) + (a.res ? row0 : 0), 0, a.res ? rows8 * 4 : 0, kdRawBuffer);
+  unsigned opix[4];  // element offset of this lane's channels of pixel k
   bool okk[4];
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
-    const int p = pxh * 64 + kh * 32 + prow + 8 * k;
-    const int oy = ty0 + (p >> 4), ox = tx0 + (p & 15);
-    okk[k] = oy < a.H && ox < a.W;
-    obase[k] = okk[k] ? (((int64_t)frame * a.H + oy) * a.W + ox) * a.Cout + co0 + pcol : 0;
+    const int p = quarter * 32 + prow + 8 * k;
+    const int dy = p >> 4, ox = tx0 + (p & 15);
+    okk[k] = ty0 + dy < a.H && ox < a.W;
+    opix[k] = (dy * a.W + ox) * a.Cout + pcol;
   }
-  const float* R = a.res;
   const float* bias = a.bias ? a.bias + (int64_t)((a.bias_f0 + frame) / a.bias_div) * a.Cout : nullptr;
-  OT* Y = (OT*)a.y;
+  typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
+  typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
+  auto far = [&](int k, unsigned bytes) { return okk[k] ? bytes : 0x80000000u; };
   struct Side { f32x4 r[4]; f32x4 b; };
 #pragma unroll
   for (int i0 = 0; i0 < CO_T; i0 += G) {
@@ -274,7 +318,7 @@ __global__ __launch_bounds__(256, 2) void conv_dma_kernel(ConvDArgs a) {
       side[i - i0].b = bias ? *reinterpret_cast<const f32x4*>(bias + co0 + i * 32 + pcol) : f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int k = 0; k < 4; ++k)
-        side[i - i0].r[k] = (R && okk[k]) ? *reinterpret_cast<const f32x4*>(R + obase[k] + i * 32) : f32x4{0.f, 0.f, 0.f, 0.f};
+        side[i - i0].r[k] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, far(k, opix[k] * 4), i * 128, 0));
     }
     barrier_keep<63>();
 #pragma unroll
@@ -296,34 +340,30 @@ __global__ __launch_bounds__(256, 2) void conv_dma_kernel(ConvDArgs a) {
         f32x4 v = *reinterpret_cast<const f32x4*>(patch + (prow + 8 * k) * 36 + pcol);
         v += side[i - i0].b;
         v += side[i - i0].r[k];
-        if (okk[k]) {
-          if constexpr (sizeof(OT) == 4) {
-            *reinterpret_cast<f32x4*>(Y + obase[k] + i * 32) = v;
-          } else {
-            bf16x4 o;
+        if constexpr (sizeof(OT) == 4) {
+          __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), ydst, far(k, opix[k] * 4), i * 128, 0);
+        } else {
+          bf16x4 o;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) o[e] = (bf16_t)v[e];
-            *reinterpret_cast<bf16x4*>(Y + obase[k] + i * 32) = o;
-          }
+          for (int e = 0; e < 4; ++e) o[e] = (bf16_t)v[e];
+          __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, o), ydst, far(k, opix[k] * 2), i * 64, 0);
+        }
 #pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            ssum[e] += v[e];
-            ssq[e] = fmaf(v[e], v[e], ssq[e]);
-          }
+        for (int e = 0; e < 4; ++e) {
+          const float t = okk[k] ? v[e] : 0.f;
+          ssum[e] += t;
+          ssq[e] = fmaf(t, t, ssq[e]);
         }
       }
       if (a.stat) {
         // fold the eight lanes that hold the same channels, in a fixed order; the first writes. One split = these 32 pixels
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-#pragma unroll
-          for (int m = 8; m < 64; m <<= 1) {
-            ssum[e] += __shfl_xor(ssum[e], m, 64);
-            ssq[e] += __shfl_xor(ssq[e], m, 64);
-          }
+          ssum[e] = fold8(ssum[e]);
+          ssq[e] = fold8(ssq[e]);
         }
         if (prow == 0) {
-          const int split = (((ty0 >> 3) * a.tiles_x + (tx0 >> 4)) * 2 + pxh) * 2 + kh;
+          const int split = ((ty0 >> 3) * a.tiles_x + (tx0 >> 4)) * 4 + quarter;
           float* sp = a.stat + (((int64_t)frame * a.stat_splits + split) * a.Cout + co0 + i * 32 + pcol) * 2;
           *reinterpret_cast<f32x4*>(sp) = f32x4{ssum[0], ssq[0], ssum[1], ssq[1]};
           *reinterpret_cast<f32x4*>(sp + 4) = f32x4{ssum[2], ssq[2], ssum[3], ssq[3]};
@@ -354,8 +394,8 @@ static hipError_t run_convd(hipStream_t s, ConvDArgs a) {
 
 // Channel tiles per workgroup. Widest first: a wider workgroup reads less per MFMA, and two share a compute unit. Launches that
 // would not fill the chip with those (up to 512 workgroups of two tiles are resident at once) take two: 320 channels at
-// 3 frames of 36 x 60 33.6 us with five and 23.5 with two, one frame of 64 x 64 27.3 and 17.0; 4 frames of 64 x 64
-// (640 workgroups of two) 36.2 and 42.0.
+// 3 frames of 36 x 60 27.8 us with five and 22.1 with two, one frame of 64 x 64 25.9 and 15.2, two 28.2 and 22.6; 4 frames of
+// 64 x 64 (640 workgroups of two) 33.8 and 35.4, with 960 input channels 82 and 86, 32 frames 227 and 249.
 static int conv_dma_tiles(int64_t ntiles, int ct) {
   if (ct % 2 == 0 && ntiles * (ct / 2) <= 512) return 2;
   for (int w = 5; w >= 2; --w)
@@ -371,7 +411,8 @@ hipError_t launch_conv_dma(hipStream_t s, const FusedDesc& d) {
   if (d.up2 && ((d.H | d.W) & 1)) return hipErrorInvalidValue;
   if (d.stat && (!d.y_f32 || d.stat_splits != conv_stat_splits(d.H, d.W))) return hipErrorInvalidValue;
   if (d.bias_div < 0 || d.bias_f0 < 0) return hipErrorInvalidValue;
-  // 31-bit byte offsets inside a frame and inside the weights
+  // 31-bit byte offsets inside a frame, inside the weights and inside eight image rows of the output
+  if ((int64_t)8 * d.W * d.Cout * 4 >= (int64_t)1 << 31) return hipErrorNotSupported;
   if ((int64_t)d.H * d.W * d.Cin * 2 >= (int64_t)1 << 31 || (int64_t)d.Cout * 9 * d.Cin * 2 >= (int64_t)1 << 31) return hipErrorNotSupported;
   if (d.frames <= 0) return hipSuccess;
   ConvDArgs a;
