@@ -164,8 +164,8 @@ __device__ __forceinline__ float gelu_tanh_f(float x) {
 // the same with the hardware exp2 / reciprocal approximations (about 1 ulp each): x * sigmoid(2 u), two
 // transcendentals and five vector instructions where the form above compiles to an IEEE division
 __device__ __forceinline__ float gelu_tanh_fast(float x) {
-  const float u = 0.7978845608028654f * fmaf(0.044715f * x * x, x, x);
-  return x * __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(-2.8853900817779268f * u));
+  constexpr float k = -2.8853900817779268f * 0.7978845608028654f;  // -2 log2(e) sqrt(2 / pi)
+  return x * __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(x * fmaf(k * 0.044715f, x * x, k)));
 }
 
 __device__ __forceinline__ float wave_sum(float v) {

@@ -139,7 +139,7 @@ __global__ __launch_bounds__(256, 2) void lin2_kernel(Lin2Args a) {
   }
 #pragma unroll
   for (int j = 0; j < MR; ++j)
-    lin_epilogue<OT, NT, MAPPED, false>(a, acc[j], m0 + wid * (32 * MR) + 32 * j + 4 * hh, n0, lane, bias_l, mul_l);
+    lin_epilogue<OT, NT, MAPPED, false>(a, acc[j], m0 + wid * (32 * MR) + 32 * j, n0, lane, bias_l, mul_l);
 }
 
 // taps == 1, src == 0 of a bf16 stage, Cin % 64 == 0 and Cout % 160 == 0 or % 128 == 0 (rows through any row map);
@@ -202,6 +202,8 @@ hipError_t launch_lin2(hipStream_t s, const FusedDesc& d) {
   if (d.gate && (!lin_gate_covers(d.Cin, d.Cout) || !d.y_f32 || !d.res || d.y2 || d.gate_T < 32 || d.gate_n <= 0)) return hipErrorInvalidValue;
   if (d.rows <= 0) return hipSuccess;
   if (d.rows > (int64_t)1 << 30) return hipErrorNotSupported;
+  if (d.yt && d.row0 + d.rows >= (int64_t)1 << 31) return hipErrorInvalidValue;
+  if ((int64_t)d.Cout * 4 * 32 >= (int64_t)1 << 31) return hipErrorNotSupported;  // (32-bit offsets in a block of rows)
   Lin2Args a;
   a.x = (const bf16_t*)d.x; a.w = (const bf16_t*)d.w; a.bias = d.bias; a.res = (const float*)d.res; a.y = d.y;
   a.y2 = (bf16_t*)d.y2;

@@ -1,13 +1,13 @@
 // Linear layers over dense bf16 rows on gfx950: the tiles beside lc_lin2.hip's 128 x 160, wide ones for launches that fill
 // the chip several times and small ones for launches that would leave most of it idle.
 //
-// What loads these kernels most is the LDS: a compute unit reads 64 bytes a clock from it with 16-byte reads (measured with
-// nothing else running), while its four matrix pipes finish a 32x32x16 MFMA each in 32 clocks (counters at 8192 rows of
-// 1024: LDS 55 - 68 % of the cycles, matrix pipe 33 - 37 %). A wavefront that holds
-// MT x NT accumulator tiles reads (MT + NT) / (MT NT) KB per MFMA: 1.2 with lin2's one row tile, 1 at 2 x 2, 0.75 at 2 x 4.
-// Measured, us (lin2's tile -> this file's; rows x N x K): 8192 x 4096 x 1024 with GELU 95 -> 78 and 8192 x 3840 x 1280
-// 97 -> 81 (256 x 256), 8192 x 3072 x 1024 64 -> 56 (256 x 192), 8192 x 1024 x 4096 fp32 75 -> 67 (128 x 128),
-// 3000 x 768 x 3072 fp32 36 -> 27 (64 x 128), 1024 x 1024 x 4096 fp32 43 -> 23, 2048 x 320 x 1280 fp32 18 -> 9 (64 x 64).
+// Where a large launch's time goes (8192 x 4096 x 1024 with GELU, 256 x 256): 49 us per 1024 of K, 1.37 PFLOP/s, as fast as this
+// card runs any long contraction, and 27 us that do not depend on K: first loads, the epilogue and its stores (14 us at the
+// rate of a copy), which one workgroup per compute unit does not cover. In small launches a compute unit has one wavefront per
+// SIMD, and what a stage consists of adds up: requests, fragment reads, MFMAs, barrier.
+// Measured, us (lin2's tile -> this file's; rows x N x K): 8192 x 4096 x 1024 with GELU 95 -> 74 and 8192 x 3840 x 1280
+// 97 -> 81 (256 x 256), 8192 x 3072 x 1024 64 -> 56 (256 x 192), 8192 x 1024 x 4096 fp32 75 -> 68 (128 x 128),
+// 3000 x 768 x 3072 fp32 36 -> 27 (64 x 128), 1024 x 1024 x 4096 fp32 43 -> 21, 2048 x 320 x 1280 fp32 18 -> 8 (64 x 64).
 //
 // The K loop: a ring of S stages of 64 K elements (global -> LDS directly, packet c of row r in slot c ^ ((r >> 1) & 7)).
 // The one barrier of a step stands before its last group of MFMAs, whose operands are in registers by then: behind it the
@@ -36,17 +36,10 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void lin3_kernel(Lin2Args a) {
   const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wid / WN, wn = wid % WN;
   const int lp = lane & 31, hh = lane >> 5;
-  // (row tile, channel tile) of this workgroup: all channel tiles of a row tile on one XCD, where there are row tiles for
-  // all eight of them
-  const int lin = blockIdx.x;
-  int mt, nt;
-  if (a.ntm >= 8) {
-    const int xcd = lin & 7, slot = lin >> 3;
-    mt = xcd + 8 * (slot / a.ntn); nt = slot - (slot / a.ntn) * a.ntn;
-    if (mt >= a.ntm) return;  // the grid is padded to whole rounds of eight row tiles
-  } else {
-    nt = lin / a.ntm; mt = lin - nt * a.ntm;
-  }
+  // (row tile, channel tile) of this workgroup: workgroups go round the eight XCDs, and each XCD has a block of the tiles
+  const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
+  const int mt = xcd % a.xm * a.bm + slot / a.bn, nt = xcd / a.xm * a.bn + slot % a.bn;
+  if (mt >= a.ntm || nt >= a.ntn) return;  // (the blocks at the ends may be smaller)
   const int64_t m0 = (int64_t)mt * kM;
   const int n0 = nt * kN;
 
@@ -95,50 +88,86 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void lin3_kernel(Lin2Args a) {
   // fragment addresses inside a stage: row * 128 + ((slot ^ key) << 4), slot = hh + 2 kk (rows + 32 do not change the key)
   const int key = (lp >> 1) & 7;
   const int xrow0 = wm * (32 * MT) + lp, wrow0 = kM + wn * (32 * NT) + lp;
-  typename M::Frag xf[2][MT], wf[2][NT];
-  auto frags = [&](const unsigned char* st, int kk, int b) {
-    const int so = ((hh + 2 * kk) ^ key) << 4;
-#pragma unroll
-    for (int j = 0; j < MT; ++j) xf[b][j] = M::load((const bf16_t*)(st + (xrow0 + 32 * j) * kKB3 + so));
-#pragma unroll
-    for (int i = 0; i < NT; ++i) wf[b][i] = M::load((const bf16_t*)(st + (wrow0 + 32 * i) * kKB3 + so));
-  };
-  auto mma = [&](int b) {
-#pragma unroll
-    for (int i = 0; i < NT; ++i)
-#pragma unroll
-      for (int j = 0; j < MT; ++j) M::mma(xf[b][j], wf[b][i], acc[j][i]);
-  };
-
   const int nsteps = a.K / 64;
 #pragma unroll
   for (int j = 0; j < S; ++j)
     if (j < nsteps) issue(j, j);
   if (nsteps >= S) barrier_keep<(S - 1) * kPer>();
   else barrier_keep<0>();
-  frags(smem, 0, 0);
+  // this wavefront has read its last fragments of the stage at hand, and its loads of the next one have landed (those of
+  // the S - 2 stages behind it may be on their way; at the end of K there are fewer)
+  auto step_end = [&](int s) __attribute__((always_inline)) {
+    if (s + S - 1 < nsteps) barrier_keep<(S - 2) * kPer>();
+    else barrier_keep<0>();
+  };
   int buf = 0;
-  for (int s = 0; s < nsteps; ++s) {
-    const unsigned char* st = smem + buf * kStage;
-    const int bnext = buf + 1 == S ? 0 : buf + 1;
+  if constexpr (MT * NT <= 2) {
+    // A wavefront with few accumulators has few MFMAs to put between a fragment's request and its use, and one wavefront per
+    // SIMD has nothing else: k-step by k-step an LDS round trip stood in front of each (1024 x 1024 x 4096: 660 clocks a
+    // stage for 4 MFMAs). Here all fragments of a stage are in registers when its first MFMA is issued, and behind the
+    // last MFMA that needs a fragment the same registers are requested for the next stage.
+    typename M::Frag xf[4][MT], wf[4][NT];
+    auto frag = [&](const unsigned char* st, int kk) __attribute__((always_inline)) {
+      const int so = ((hh + 2 * kk) ^ key) << 4;
 #pragma unroll
-    for (int kk = 0; kk < 3; ++kk) {  // the fragments of the next k-step are requested before this one's MFMAs
-      frags(st, kk + 1, (kk + 1) & 1);
+      for (int j = 0; j < MT; ++j) xf[kk][j] = M::load((const bf16_t*)(st + (xrow0 + 32 * j) * kKB3 + so));
+#pragma unroll
+      for (int i = 0; i < NT; ++i) wf[kk][i] = M::load((const bf16_t*)(st + (wrow0 + 32 * i) * kKB3 + so));
+    };
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) frag(smem, kk);
+    for (int s = 0; s < nsteps; ++s) {
+      const int bnext = buf + 1 == S ? 0 : buf + 1;
+      if (s + 1 < nsteps) step_end(s);
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk) {
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < NT; ++i)
+#pragma unroll
+          for (int j = 0; j < MT; ++j) M::mma(xf[kk][j], wf[kk][i], acc[j][i]);
+        __builtin_amdgcn_sched_barrier(0);
+        frag(smem + bnext * kStage, kk);  // (behind the last stage they are of no stage: in bounds, never used)
+      }
       __builtin_amdgcn_sched_barrier(0);
-      mma(kk & 1);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    if (s + 1 < nsteps) {
-      // this wavefront has read its last fragments of this stage, and its loads of the next one have landed (those of
-      // the S - 2 stages behind it may be on their way; at the end of K there are fewer)
-      if (s + S - 1 < nsteps) barrier_keep<(S - 2) * kPer>();
-      else barrier_keep<0>();
       if (s + S < nsteps) issue(s + S, buf);
-      frags(smem + bnext * kStage, 0, 0);
-      __builtin_amdgcn_sched_barrier(0);
+      buf = bnext;
     }
-    mma(1);  // (left in one place: a copy behind the loop costs the compiler a second set of accumulators)
-    buf = bnext;
+  } else {
+    typename M::Frag xf[2][MT], wf[2][NT];
+    auto frags = [&](const unsigned char* st, int kk, int b) __attribute__((always_inline)) {
+      const int so = ((hh + 2 * kk) ^ key) << 4;
+#pragma unroll
+      for (int j = 0; j < MT; ++j) xf[b][j] = M::load((const bf16_t*)(st + (xrow0 + 32 * j) * kKB3 + so));
+#pragma unroll
+      for (int i = 0; i < NT; ++i) wf[b][i] = M::load((const bf16_t*)(st + (wrow0 + 32 * i) * kKB3 + so));
+    };
+    auto mma = [&](int b) __attribute__((always_inline)) {
+#pragma unroll
+      for (int i = 0; i < NT; ++i)
+#pragma unroll
+        for (int j = 0; j < MT; ++j) M::mma(xf[b][j], wf[b][i], acc[j][i]);
+    };
+    frags(smem, 0, 0);
+    for (int s = 0; s < nsteps; ++s) {
+      const unsigned char* st = smem + buf * kStage;
+      const int bnext = buf + 1 == S ? 0 : buf + 1;
+#pragma unroll
+      for (int kk = 0; kk < 3; ++kk) {  // the fragments of the next k-step are requested before this one's MFMAs
+        frags(st, kk + 1, (kk + 1) & 1);
+        __builtin_amdgcn_sched_barrier(0);
+        mma(kk & 1);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      if (s + 1 < nsteps) {
+        step_end(s);
+        if (s + S < nsteps) issue(s + S, buf);
+        frags(smem + bnext * kStage, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      mma(1);  // (left in one place: a copy behind the loop costs the compiler a second set of accumulators)
+      buf = bnext;
+    }
   }
 
   // out, two column tiles at a time (their 64 channels of a row are a whole line, and the registers beside the accumulators
@@ -161,7 +190,7 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void lin3_kernel(Lin2Args a) {
       f32x16 part[SL];
 #pragma unroll
       for (int e = 0; e < SL; ++e) part[e] = acc[j][i + e];
-      lin_epilogue<OT, SL, false, true>(a, part, m0 + wm * (32 * MT) + 32 * j + 4 * hh, ci, lane, bias_l, mul_l);
+      lin_epilogue<OT, SL, false, true>(a, part, m0 + wm * (32 * MT) + 32 * j, ci, lane, bias_l, mul_l);
     }
   }
 }
@@ -180,8 +209,17 @@ static hipError_t run_lin3_k(hipStream_t s, Lin2Args a) {
   if (a.N % kN || (int64_t)(kM > kN ? kM : kN) * a.K * 2 > 0x7fffffff) return hipErrorInvalidValue;  // (32-bit offsets in a tile)
   a.ntn = a.N / kN;
   a.ntm = (int)((a.rows + kM - 1) / kM);
-  const int rounds = a.ntm >= 8 ? (a.ntm + 7) / 8 * 8 : a.ntm;
-  kern<<<(unsigned)(rounds * a.ntn), WM * WN * 64, lds, s>>>(a);
+  // Each XCD fetches what its tiles read into an L2 of its own, and for short contractions and few rows that traffic, from beyond
+  // the L2, is what a launch waits for. Of the four ways to deal the tiles in blocks, the one with the fewest rounds of
+  // workgroups on the fullest XCD, then the fewest rows and channels to fetch.
+  constexpr int kRes = 32 * (2 * lds <= 160 * 1024 ? 2 : 1);  // workgroups resident on an XCD
+  int64_t best = -1;
+  for (int xm = 8; xm >= 1; xm /= 2) {
+    const int bm = (a.ntm + xm - 1) / xm, bn = (a.ntn + 8 / xm - 1) / (8 / xm);
+    const int64_t cost = ((int64_t)((bm * (int64_t)bn + kRes - 1) / kRes) << 40) + (int64_t)bm * kM + (int64_t)bn * kN;
+    if (best < 0 || cost < best) { best = cost; a.xm = xm; a.bm = bm; a.bn = bn; }
+  }
+  kern<<<(unsigned)(8 * a.bm * a.bn), WM * WN * 64, lds, s>>>(a);
   return hipGetLastError();
 }
 

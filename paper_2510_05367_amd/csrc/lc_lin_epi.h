@@ -16,6 +16,7 @@ struct Lin2Args {
   bf16_t* y2;          // fp32 output only: a copy of y rounded to bf16 (the next layer's operand), or nullptr
   int64_t rows;
   int K, N, ntm, ntn;
+  int xm, bm, bn;      // lc_lin3.hip: XCDs along the row tiles, and the tiles of one XCD: bm row tiles x bn channel tiles
   float q_scale;       // channels below q_cols are multiplied by this before they are rounded
   int q_cols;
   int act;             // 0 none, 1 GELU, 2 GEGLU over alternating 32-channel blocks (y is then N / 2 wide)
@@ -38,17 +39,15 @@ struct Lin2Args {
 // lin2_kernel's 128 x 160 is the better one (never with a gate).
 hipError_t launch_lin3(hipStream_t s, const Lin2Args& a, bool y_f32);
 
-// bf16 stores of a 32-row half tile, two channels per lane: lanes l and l ^ 1 hold channels c, c + 1 of the same rows;
+// bf16 stores of a 32-row block, two channels per lane: lanes l and l ^ 1 hold channels c, c + 1 of the same rows;
 // they trade halves so that the even lane holds both channels of the even row of a pair and the odd lane both of the
 // odd row, and each stores 4 bytes: a wavefront instruction then writes 64 consecutive bytes of two rows instead of
-// 64 bytes of one with 2-byte stores. NV: column tiles (32 channels each) in val's second index.
-template <int NV, int NTV, bool MAPPED>
-__device__ __forceinline__ void store_pairs(const float (&val)[16][NTV], bf16_t* __restrict__ Y, int ldy, int c0, int64_t rbase,
-                                            int64_t rows, const RowMap& out_map, int lane, std::integral_constant<bool, MAPPED>) {
-  const int lp = lane & 31;
-  const bool odd = lane & 1;
+// 64 bytes of one with 2-byte stores. NV: column tiles (32 channels each) in val's second index. put(rp, i, v): rows
+// rp and rp + 1 of the accumulator's 16.
+template <int NV, int NTV, class Put>
+__device__ __forceinline__ void store_pairs(const float (&val)[16][NTV], int lane, Put put) {
   // v_perm_b32 selectors (bytes 0-3: own pair, 4-7: the neighbour's): even (own lo, neighbour's lo), odd (neighbour's hi, own hi)
-  const uint32_t sel = odd ? 0x03020706u : 0x05040100u;
+  const uint32_t sel = lane & 1 ? 0x03020706u : 0x05040100u;
 #pragma unroll
   for (int rp = 0; rp < 16; rp += 2) {
     uint32_t out[NV];
@@ -61,38 +60,52 @@ __device__ __forceinline__ void store_pairs(const float (&val)[16][NTV], bf16_t*
       const uint32_t nb = (uint32_t)__builtin_amdgcn_mov_dpp((int)own, 0xB1 /* quad_perm [1,0,3,2] */, 0xF, 0xF, true);
       out[i] = __builtin_amdgcn_perm(nb, own, sel);
     }
-    const int64_t dr = rbase + 8 * (rp >> 2) + (rp & 3) + (odd ? 1 : 0);
-    if (dr >= rows) continue;
-    const int64_t row = MAPPED ? out_map(dr) : dr;
-#pragma unroll
-    for (int i = 0; i < NV; ++i) *reinterpret_cast<uint32_t*>(Y + row * ldy + c0 + 32 * i + (lp & ~1)) = out[i];
+    put(rp, out);
   }
 }
 
-// The epilogue of one 32-row half tile of NT column tiles (32 channels each): the lane holds channel c0 + 32 i + lp of rows
-// rbase + 8 (r / 4) + r % 4, rbase already including 4 hh.
+// The epilogue of one 32-row block of NT column tiles (32 channels each): the lane holds channel c0 + 32 i + lp of rows
+// rblk + 8 (r / 4) + 4 hh + r % 4.
+// Dense rows go through buffer descriptors over the block: row offsets are scalars, and rows beyond the end read as zero and
+// are not stored by the bounds check, where 64-bit addresses and a condition per row took most of a short contraction's time
+// (131072 x 2560, K = 64, GEGLU 215 us with them).
 // GATE: Lin2Args::gate may be set (its own registers: the kernels that never take one stay without them).
 template <class OT, int NT, bool MAPPED, bool GATE>
-__device__ __forceinline__ void lin_epilogue(const Lin2Args& a, const f32x16 (&acc)[NT], int64_t rbase, int c0, int lane,
+__device__ __forceinline__ void lin_epilogue(const Lin2Args& a, const f32x16 (&acc)[NT], int64_t rblk, int c0, int lane,
                                              const float (&bias_l)[NT], const float (&mul_l)[NT]) {
-  const int lp = lane & 31;
+  constexpr int kRaw = 0x00020000;  // descriptor word 3: raw 32-bit data
+  const int lp = lane & 31, hh = lane >> 5;
+  const int64_t rbase = rblk + 4 * hh;
+  const int left = (int)max((int64_t)0, min((int64_t)32, a.rows - rblk));  // existing rows of the block
+  auto rofs = [](int r) { return 8 * (r >> 2) + (r & 3); };
+  // rows of ld elements of es bytes from column c on: the block's descriptor, and the lane's offset in its first row
+  auto block = [&](const void* p, int64_t ld, int es, int c) {
+    return __builtin_amdgcn_make_buffer_rsrc((char*)const_cast<void*>(p) + (rblk * ld + c) * es, 0, (int)max((int64_t)0, (left * ld - c) * es), kRaw);
+  };
   OT* Y = (OT*)a.y;
   const float* R = a.res;
   // The residual (which may be y itself: every element is read and written by the same lane) is fetched for a whole
-  // 32-row half at once, before the first store of that half: a load placed after a store that may alias it cannot
+  // block at once, before the first store of that block: a load placed after a store that may alias it cannot
   // be moved up by the compiler, and one round trip per element would cost more than the whole contraction.
   float rv[16][NT];
   if (R) {
+    if constexpr (MAPPED) {
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      int64_t row = min(rbase + 8 * (r >> 2) + (r & 3), a.rows - 1);
-      if (MAPPED) row = a.out_map(row);
+      for (int r = 0; r < 16; ++r) {
+        const int64_t row = a.out_map(min(rbase + rofs(r), a.rows - 1));
 #pragma unroll
-      for (int i = 0; i < NT; ++i) rv[r][i] = R[row * a.N + c0 + 32 * i + lp];
+        for (int i = 0; i < NT; ++i) rv[r][i] = R[row * a.N + c0 + 32 * i + lp];
+      }
+    } else {
+      const __amdgpu_buffer_rsrc_t rs = block(R, a.N, 4, c0);
+      const int vo = (4 * hh * a.N + lp) * 4;
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+#pragma unroll
+        for (int i = 0; i < NT; ++i) rv[r][i] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, vo + 128 * i, rofs(r) * a.N * 4, 0));
     }
   }
-  // all arithmetic of the half first, so that the stores below depend on no load: a store under a condition
-  // (the ragged last tile) would otherwise be preceded by a wait for everything in flight
+  // all arithmetic of the block first, so that the stores below depend on no load
   float val[16][NT];
   bool gated = false;
   if constexpr (GATE && sizeof(OT) == 4 && !MAPPED) {
@@ -107,7 +120,7 @@ __device__ __forceinline__ void lin_epilogue(const Lin2Args& a, const f32x16 (&a
         const float ga = g0[32 * i], gb = g1[32 * i];
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-          const float g = rbase + 8 * (r >> 2) + (r & 3) >= next ? gb : ga;
+          const float g = rbase + rofs(r) >= next ? gb : ga;
           val[r][i] = fmaf(g, acc[i][r] + bias_l[i], rv[r][i]);
           asm volatile("" : "+v"(val[r][i]));
         }
@@ -118,23 +131,70 @@ __device__ __forceinline__ void lin_epilogue(const Lin2Args& a, const f32x16 (&a
 #pragma unroll
     for (int r = 0; r < 16; ++r)
 #pragma unroll
-      for (int i = 0; i < NT; ++i) {
-        val[r][i] = (acc[i][r] + bias_l[i]) * mul_l[i];
-        if (R) val[r][i] += rv[r][i];
-        if (sizeof(OT) == 2 && a.act == 1) val[r][i] = gelu_tanh_fast(val[r][i]);
-        asm volatile("" : "+v"(val[r][i]));  // computed here: left alone, the compiler sinks it into the store's branch
+      for (int i = 0; i < NT; ++i) val[r][i] = acc[i][r] + bias_l[i];
+    if (a.q_cols) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+#pragma unroll
+        for (int i = 0; i < NT; ++i) val[r][i] *= mul_l[i];
+    }
+    if (R) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+#pragma unroll
+        for (int i = 0; i < NT; ++i) val[r][i] += rv[r][i];
+    }
+    if constexpr (sizeof(OT) == 2) {
+      if (a.act == 1) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+#pragma unroll
+          for (int i = 0; i < NT; ++i) val[r][i] = gelu_tanh_fast(val[r][i]);
       }
+    }
+    if constexpr (MAPPED) {  // computed here: left alone, the compiler sinks it into the stores' branches
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+#pragma unroll
+        for (int i = 0; i < NT; ++i) asm volatile("" : "+v"(val[r][i]));
+    }
   }
+  // NV column tiles of val, rounded, to rows of ld channels from column c on
+  auto put16 = [&](bf16_t* y, int ld, int c, auto nv_c) __attribute__((always_inline)) {
+    constexpr int NV = decltype(nv_c)::value;
+    if constexpr (MAPPED) {
+      store_pairs<NV>(val, lane, [&](int rp, const uint32_t (&out)[NV]) __attribute__((always_inline)) {
+        const int64_t dr = rbase + rofs(rp) + (lane & 1);
+        if (dr >= a.rows) return;
+        const int64_t row = a.out_map(dr);
+#pragma unroll
+        for (int i = 0; i < NV; ++i) *reinterpret_cast<uint32_t*>(y + row * ld + c + 32 * i + (lp & ~1)) = out[i];
+      });
+    } else {
+      const __amdgpu_buffer_rsrc_t ys = block(y, ld, 2, c);
+      const int vo = ((4 * hh + (lane & 1)) * ld + (lp & ~1)) * 2;
+      store_pairs<NV>(val, lane, [&](int rp, const uint32_t (&out)[NV]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < NV; ++i) __builtin_amdgcn_raw_buffer_store_b32(out[i], ys, vo + 64 * i, rofs(rp) * ld * 2, 0);
+      });
+    }
+  };
   if constexpr (sizeof(OT) == 2) {
     if (a.yt && c0 >= a.yt_from) {  // (uniform over the wavefront) a lane holds 4 consecutive rows of a channel: 8 bytes of V^T
       const int Cv = a.N - a.yt_from;
+      const uint32_t g0 = (uint32_t)(a.row0 + rblk), T = (uint32_t)a.yt_T;  // (row0 + rows < 2^31: see launch_lin2)
+      const uint32_t f0 = g0 / T, t0 = g0 - f0 * T;
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
-        const int64_t dr = rbase + 8 * g;
-        if (dr >= a.rows) continue;  // (rows come in fours)
-        const int64_t f = (a.row0 + dr) / a.yt_T;
-        const int t = (int)(a.row0 + dr - f * a.yt_T);
-        bf16_t* dst = a.yt + (f * Cv + (c0 - a.yt_from) + lp) * a.yt_Tp + (t & ~63) + vcol<bf16_t>(t & 63);
+        if (8 * g + 4 * hh >= left) continue;  // (rows come in fours)
+        uint32_t f = f0, t = t0 + 8 * g + 4 * hh;
+        if (T >= 32) {
+          if (t >= T) { t -= T; ++f; }
+        } else {
+          const uint32_t q = t / T;
+          t -= q * T; f += q;
+        }
+        bf16_t* dst = a.yt + ((int64_t)f * Cv + (c0 - a.yt_from) + lp) * a.yt_Tp + (t & ~63u) + vcol<bf16_t>((int)(t & 63));
 #pragma unroll
         for (int i = 0; i < NT; ++i) {
           bf16x4 o;
@@ -151,26 +211,32 @@ __device__ __forceinline__ void lin_epilogue(const Lin2Args& a, const f32x16 (&a
 #pragma unroll
       for (int r = 0; r < 16; ++r)
 #pragma unroll
-        for (int q = 0; q < NT / 2; ++q) {
-          val[r][q] = val[r][2 * q] * gelu_tanh_fast(val[r][2 * q + 1]);
-          asm volatile("" : "+v"(val[r][q]));
-        }
-      store_pairs<NT / 2>(val, (bf16_t*)a.y, a.N / 2, c0 / 2, rbase, a.rows, a.out_map, lane, std::integral_constant<bool, MAPPED>{});
+        for (int q = 0; q < NT / 2; ++q) val[r][q] = val[r][2 * q] * gelu_tanh_fast(val[r][2 * q + 1]);
+      put16((bf16_t*)a.y, a.N / 2, c0 / 2, std::integral_constant<int, NT / 2>{});
       return;
     }
   }
   if constexpr (sizeof(OT) == 2) {
-    store_pairs<NT>(val, (bf16_t*)a.y, a.ldy, c0, rbase, a.rows, a.out_map, lane, std::integral_constant<bool, MAPPED>{});
+    put16((bf16_t*)a.y, a.ldy, c0, std::integral_constant<int, NT>{});
   } else {
+    if constexpr (MAPPED) {
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int64_t dr = rbase + 8 * (r >> 2) + (r & 3);
-      if (dr >= a.rows) continue;
-      const int64_t row = MAPPED ? a.out_map(dr) : dr;
+      for (int r = 0; r < 16; ++r) {
+        const int64_t dr = rbase + rofs(r);
+        if (dr >= a.rows) continue;
+        const int64_t row = a.out_map(dr);
 #pragma unroll
-      for (int i = 0; i < NT; ++i) Y[row * a.N + c0 + 32 * i + lp] = from_f32<OT>(val[r][i]);
+        for (int i = 0; i < NT; ++i) Y[row * a.N + c0 + 32 * i + lp] = from_f32<OT>(val[r][i]);
+      }
+    } else {
+      const __amdgpu_buffer_rsrc_t ys = block(Y, a.N, 4, c0);
+      const int vo = (4 * hh * a.N + lp) * 4;
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+#pragma unroll
+        for (int i = 0; i < NT; ++i) __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, (float)val[r][i]), ys, vo + 128 * i, rofs(r) * a.N * 4, 0);
     }
-    if (a.y2) store_pairs<NT>(val, a.y2, a.N, c0, rbase, a.rows, a.out_map, lane, std::integral_constant<bool, MAPPED>{});
+    if (a.y2) put16(a.y2, a.N, c0, std::integral_constant<int, NT>{});
   }
 }
 
