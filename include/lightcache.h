@@ -378,9 +378,10 @@ lc_status lc_decoder_sync(lc_decoder* dec);
  * One block: h = LN(x) (1 + scale_msa) + shift_msa; x += gate_msa * (Attn(h) Wo^T + bo); h = LN(x) (1 + scale_mlp)
  * + shift_mlp; x += gate_mlp * (W2 gelu_tanh(W1 h + b1) + b2). LN: per token, biased variance, no affine; q,k,v
  * projections with bias; `heads` heads of `head_dim`, scale 1/sqrt(head_dim). The modulation vectors are inputs.
- * Feature chunk ([CHK]): token_chunk of the B*T tokens of a step per pass of LayerNorm / projections / MLP (a pass may
- * run across batch elements: every row looks up its own modulation); the queries of the attention go in one pass. It
- * never changes results. Hidden states and modulation are float at the boundary;
+ * Feature chunk ([CHK]): the workspace has room for token_chunk of the B*T tokens of a step in the MLP beside what is held
+ * for all tokens; a pass of LayerNorm / projections / MLP takes as many rows as fit into the workspace at the time, at
+ * least token_chunk (it may run across batch elements: every row looks up its own modulation), the attention all. The
+ * chunk never changes results. Hidden states and modulation are float at the boundary;
  * weights have cfg dtype (bf16: MFMA operands bf16, accumulation and the residual stream fp32).
  * Requirements (else LC_ERR_SHAPE): sizes > 0; D a multiple of 64, <= 2048; heads * head_dim == D; head_dim in
  * {8, 16, 32, 40, 64}; L <= LC_DIT_MAX_BLOCKS; 0 <= cache_a <= cache_b <= L; mlp_ratio <= 8; 1 <= dev_slots <= 8;

@@ -124,8 +124,8 @@ inline size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 
 struct BlkW { void *wqkv, *wo, *w1, *w2; float *bqkv, *bo, *b1, *b2; };
 struct TPlan {
-  int tc;  // rows per chunk of the per-row layers (LayerNorm, projections, MLP): tokens of the B*T of a step
-  size_t off_x, off_slots, slot_bytes, off_qkv, off_vt, off_ao, off_xn, off_hid, off_t, total;
+  int tc;  // rows of the token chunk, of the B*T of a step
+  size_t off_x, off_slots, slot_bytes, off_qkv, off_vt, off_ao, total;
 };
 
 }  // namespace
@@ -184,14 +184,12 @@ lc_status check_tcfg(lc_dit* c, const lc_dit_config* g) {
 }
 
 // Arena: the fp32 hidden states, dev_slots Delta entries (fp32), q,k,v + V^T + attention output of ALL tokens (a
-// query chunk attends to every key), and what one token chunk works in: its normalised rows, the MLP's hidden
-// rows and a branch output.
+// query chunk attends to every key), and room for the normalised rows, the MLP's hidden rows and a branch output of one
+// token chunk, which together with what is not needed at the time is what a pass works in (see run_block).
 TPlan make_tplan(const lc_dit_config& g, int token_chunk) {
   TPlan p;
   const size_t es = dtype_size(g.dtype);
   const int64_t R = (int64_t)g.B * g.T;
-  // the per-row layers walk the B*T rows of a step in chunks that may run across batch elements (all rows at once
-  // without a chunk)
   p.tc = (token_chunk <= 0 || token_chunk > R) ? (int)R : token_chunk;
   size_t off = 0;
   auto take = [&](size_t bytes) { size_t o = off; off += align_up(bytes); return o; };
@@ -201,9 +199,9 @@ TPlan make_tplan(const lc_dit_config& g, int token_chunk) {
   p.off_qkv = take((size_t)R * 3 * g.D * es);
   p.off_vt = take((size_t)g.B * g.D * attn_tp(g.T) * es);
   p.off_ao = take((size_t)R * g.D * es);
-  p.off_xn = take((size_t)p.tc * g.D * es);
-  p.off_hid = take((size_t)p.tc * g.mlp_ratio * g.D * es);
-  p.off_t = take((size_t)p.tc * g.D * 4);
+  take((size_t)p.tc * g.D * es);
+  take((size_t)p.tc * g.mlp_ratio * g.D * es);
+  take((size_t)p.tc * g.D * 4);
   p.total = off;
   return p;
 }
@@ -277,37 +275,37 @@ lc_status run_block(lc_dit* c, int i, const float* mod, float* x, const float* d
   char* qkv = c->arena + p.off_qkv;
   char* vt = c->arena + p.off_vt;
   char* ao = c->arena + p.off_ao;
-  char* xn = c->arena + p.off_xn;
-  char* hid = c->arena + p.off_hid;
-  float* t = (float*)(c->arena + p.off_t);
   lc_status s;
   // (bf16, widths of the streamed kernels: the gated sum in the projections' epilogues, and V^T from q,k,v's where rows come
   // in fours; the separate passes cost 16 + 16 + 14 us a block at 8192 rows x 1024, 13 % of it)
   const bool gated = g.dtype == kBF16 && lin_gate_covers(D, D) && T >= 32;
-  const bool vt_fused = g.dtype == kBF16 && lin2_covers(D, 3 * D) && 2 * D % (3 * D % 160 == 0 ? 160 : 128) == 0 && T % 4 == 0 &&
-                        (p.tc % 4 == 0 || p.tc >= R);
+  const bool vt_fused = g.dtype == kBF16 && lin2_covers(D, 3 * D) && 2 * D % (3 * D % 160 == 0 ? 160 : 128) == 0 && T % 4 == 0;
   const int ldq = vt_fused ? 2 * D : 3 * D;
+  // The chunk bounds the memory, and a pass takes as many rows as there is memory for: what is held for all tokens is not
+  // needed all the time. The normalised rows of q,k,v lie where the attention output will be, the branch output (where it
+  // exists) where q,k,v were, and the MLP works from q,k,v to the end of the arena, which holds all rows of it in bf16 stages
+  // of mlp_ratio 4. (2 x 3108 tokens of 1024 in chunks of 1024, us a block's linear layers: 403 in launches of 1024 rows, 213.)
   // ---- attention branch: q,k,v of every token first
-  for (int64_t r0 = 0; r0 < R; r0 += p.tc) {
-    const int n = (int)std::min<int64_t>(p.tc, R - r0);
-    if ((s = ln_mod(c, x + r0 * D, delta ? delta + r0 * D : nullptr, m, 0, 1, xn, n, r0)) != LC_OK) return s;
-    if ((s = linear(c, w.wqkv, w.bqkv, D, 3 * D, n, xn, qkv + r0 * ldq * es, 0, 0, D, vt_fused ? vt : nullptr, r0)) != LC_OK) return s;
-  }
+  if ((s = ln_mod(c, x, delta, m, 0, 1, ao, (int)R, 0)) != LC_OK) return s;
+  if ((s = linear(c, w.wqkv, w.bqkv, D, 3 * D, R, ao, qkv, 0, 0, D, vt_fused ? vt : nullptr, 0)) != LC_OK) return s;
   if (!vt_fused) LCT_HIP(c, launch_make_vt(c->cs, g.dtype, qkv + (size_t)2 * D * es, 3 * D, vt, g.B, T, Tp, D));
-  // (all queries at once whatever the token chunk: the kernel keeps nothing per query in memory)
   LCT_HIP(c, launch_spatial_attention(c->cs, g.dtype, qkv, ldq, vt, Tp, ao, g.B, T, g.heads, g.head_dim, 0, T, 1));
-  for (int64_t r0 = 0; r0 < R; r0 += p.tc) {
-    const int n = (int)std::min<int64_t>(p.tc, R - r0);
-    if (gated) {
-      if ((s = linear_gated(c, w.wo, w.bo, D, n, ao + r0 * D * es, dst + r0 * D, m, 2, r0)) != LC_OK) return s;
-      continue;
-    }
-    if ((s = linear(c, w.wo, w.bo, D, D, n, ao + r0 * D * es, t, 1)) != LC_OK) return s;
-    if ((s = gate_add(c, dst + r0 * D, t, m, 2, n, r0)) != LC_OK) return s;
+  if (gated) {
+    if ((s = linear_gated(c, w.wo, w.bo, D, R, ao, dst, m, 2, 0)) != LC_OK) return s;
+  } else {
+    float* t = (float*)qkv;  // (R * D floats: q,k,v take at least 6 R D bytes)
+    if ((s = linear(c, w.wo, w.bo, D, D, R, ao, t, 1)) != LC_OK) return s;
+    if ((s = gate_add(c, dst, t, m, 2, R, 0)) != LC_OK) return s;
   }
-  // ---- MLP branch, chunk by chunk
-  for (int64_t r0 = 0; r0 < R; r0 += p.tc) {
-    const int n = (int)std::min<int64_t>(p.tc, R - r0);
+  // ---- MLP branch, in passes of about the same size: normalised rows, hidden rows and (where it exists) the branch output
+  const size_t per_row = (size_t)(D + H) * es + (gated ? 0 : (size_t)D * 4);
+  const int64_t fit = std::max<int64_t>(p.tc, (int64_t)((p.total - p.off_qkv - 3 * kAlign) / per_row));
+  const int64_t passes = (R + std::min(fit, R) - 1) / std::min(fit, R), step = (R + passes - 1) / passes;
+  char* xn = qkv;
+  char* hid = xn + align_up((size_t)step * D * es);
+  float* t = (float*)(hid + align_up((size_t)step * H * es));
+  for (int64_t r0 = 0; r0 < R; r0 += step) {
+    const int n = (int)std::min<int64_t>(step, R - r0);
     if ((s = ln_mod(c, x + r0 * D, delta ? delta + r0 * D : nullptr, m, 3, 4, xn, n, r0)) != LC_OK) return s;
     // (a bf16 stage whose hidden width the dense-row kernel covers applies the GELU in that kernel's epilogue)
     const bool fused = g.dtype == kBF16 && (H % 160 == 0 || H % 128 == 0);
