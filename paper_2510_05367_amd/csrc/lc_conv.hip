@@ -464,16 +464,17 @@ __global__ __launch_bounds__(256) void conv_in_tile_kernel(const bf16_t* __restr
           s1 += v;
           s2 = fmaf(v, v, s2);
         }
-      } else {
+      } else {  // a descriptor over the pixels that exist: the stores of the others are dropped
+        const __amdgpu_buffer_rsrc_t yd = __builtin_amdgcn_make_buffer_rsrc(yrow, 0, npx * C * 4, 0x00020000);
+        const int vo = (4 * hh * C + ch) * 4;
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
           const float v = acc[r] + bv;
           const int px = 8 * (r >> 2) + 4 * hh + (r & 3);
-          if (px < npx) {
-            yrow[(int64_t)px * C + ch] = v;
-            s1 += v;
-            s2 = fmaf(v, v, s2);
-          }
+          __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), yd, vo, (8 * (r >> 2) + (r & 3)) * C * 4, 0);
+          const float t = px < npx ? v : 0.f;
+          s1 += t;
+          s2 = fmaf(t, t, s2);
         }
       }
       s1 += __shfl_xor(s1, 32, 64);

@@ -73,74 +73,87 @@ hipError_t launch_gn_stats(hipStream_t s, int dt, const void* x, float* partial,
 }
 
 // ---------------------------------------------------------------------------------------------
-// One workgroup folds the partial sums of one group of one frame. The group's (split, channel) cells
-// are dealt to the 256 threads in a fixed pattern, each thread adds its cells in double precision in
-// a fixed order, and the 256 partial results are folded by a fixed tree: the result does not depend
-// on scheduling. The tensor may be the concatenation of two sources (A then B along the channels)
-// with different row counts per frame; `w` weighs a source's rows (the 2x-upsampled deep feature
+// One workgroup folds the partial sums of one group of one frame. The group's (split, channel) cells are dealt to the
+// threads in a fixed pattern, each thread adds its cells in double precision in a fixed order, and the results are folded by
+// a fixed tree: the result does not depend on scheduling. The tensor may be the concatenation of two sources (A then B along
+// the channels) with different row counts per frame; `w` weighs a source's rows (the 2x-upsampled deep feature
 // counts each of its pixels four times).
-// At most 32 vector registers: the 3x3 convolution kernel leaves that many free on every SIMD (two
-// wavefronts of 240), so when a step runs its chunks on two streams this kernel starts beside the other
-// stream's convolution instead of waiting for a compute unit to drain.
-__global__ __launch_bounds__(256) __attribute__((amdgpu_num_vgpr(32))) void gn_finalize_kernel(const float* __restrict__ partA, int CA, int splitsA,
+// What it waits for are its loads: two channels a load where the group lies so (V = 2), kBatch of them in flight, no division
+// per load, and 1024 threads where there are many splits (a 512 x 512 frame has 8192: 48 us with 256 threads, one channel a
+// load and a division for each).
+// At most 32 vector registers: it starts beside what another stream has running instead of waiting for a compute unit to drain.
+template <int V>
+__global__ __launch_bounds__(1024) __attribute__((amdgpu_num_vgpr(32))) void gn_finalize_kernel(const float* __restrict__ partA, int CA, int splitsA,
                                                           int rowsA, float wA, const float* __restrict__ partB,
                                                           int CB, int splitsB, int rowsB, float wB,
                                                           const float* __restrict__ gamma,
                                                           const float* __restrict__ beta, int groups, float eps,
                                                           float* __restrict__ scale, float* __restrict__ shift) {
-  __shared__ double rs[256], rq[256];
+  typedef float __attribute__((ext_vector_type(2 * V))) vec;
+  __shared__ double rs[16], rq[16];
   __shared__ float s_mean, s_rstd;
-  const int g = blockIdx.x, f = blockIdx.y, tid = threadIdx.x;
+  const int g = blockIdx.x, f = blockIdx.y, tid = threadIdx.x, nt = blockDim.x;
   const int Ct = CA + CB, cg = Ct / groups;
   const int c_lo = g * cg;
   // channels of the group that lie in A / in B
   const int nA = max(0, min(c_lo + cg, CA) - c_lo), nB = cg - nA;
-  const int cellsA = nA * splitsA, cellsB = nB * splitsB;
   double ss = 0.0, qq = 0.0;
-  // cells i = tid, tid + 256, ... in batches of kBatch: all loads of a batch are requested before the first
-  // is added (one at a time, every cell paid a trip to L2: that was most of this kernel's time); the order
-  // of the additions is the same either way
+  // cells i = tid, tid + nt, ... in batches of kBatch: all loads of a batch are requested before the first is added
   constexpr int kBatch = 3;
-  auto fold = [&](const float* part, int C, int splits, int n, int c_first, int cells, float w) {
-    for (int i0 = tid; i0 < cells; i0 += 256 * kBatch) {
-      float2 v[kBatch];
+  auto fold = [&](const float* part, int C, int splits, int n, int c_first, float w) {
+    const int per = n / V, cells = per * splits;  // loads per split, in all
+    const float* base = part + ((int64_t)f * splits * C + c_first) * 2;
+    int k = tid / per, j = tid - k * per;
+    const int dk = nt / per, dj = nt - dk * per;
+    for (int i = tid; i < cells; i += nt * kBatch) {
+      vec v[kBatch];
 #pragma unroll
-      for (int j = 0; j < kBatch; ++j) {
-        const int i = min(i0 + 256 * j, cells - 1);  // clamped: a valid cell, not added if beyond the end
-        const int k = i / n, c = c_first + (i - k * n);
-        v[j] = *reinterpret_cast<const float2*>(part + (((int64_t)f * splits + k) * C + c) * 2);
+      for (int b = 0; b < kBatch; ++b) {
+        const int kk = min(k, splits - 1);  // (beyond the end: a valid cell, not added)
+        v[b] = *reinterpret_cast<const vec*>(base + ((int64_t)kk * C + j * V) * 2);
+        k += dk;
+        j += dj;
+        if (j >= per) { j -= per; ++k; }
       }
 #pragma unroll
-      for (int j = 0; j < kBatch; ++j) {
-        if (i0 + 256 * j < cells) {
-          ss += (double)w * (double)v[j].x;
-          qq += (double)w * (double)v[j].y;
+      for (int b = 0; b < kBatch; ++b) {
+        if (i + nt * b < cells) {
+#pragma unroll
+          for (int e = 0; e < V; ++e) {
+            ss += (double)w * (double)v[b][2 * e];
+            qq += (double)w * (double)v[b][2 * e + 1];
+          }
         }
       }
     }
   };
-  if (cellsA > 0) fold(partA, CA, splitsA, nA, c_lo, cellsA, wA);
-  if (cellsB > 0) fold(partB, CB, splitsB, nB, max(c_lo, CA) - CA, cellsB, wB);
-  rs[tid] = ss;
-  rq[tid] = qq;
-  __syncthreads();
-  for (int m = 128; m > 0; m >>= 1) {
-    if (tid < m) {
-      rs[tid] += rs[tid + m];
-      rq[tid] += rq[tid + m];
-    }
-    __syncthreads();
+  if (nA > 0) fold(partA, CA, splitsA, nA, c_lo, wA);
+  if (nB > 0) fold(partB, CB, splitsB, nB, max(c_lo, CA) - CA, wB);
+#pragma unroll
+  for (int m = 32; m > 0; m >>= 1) {
+    ss += __shfl_xor(ss, m, 64);
+    qq += __shfl_xor(qq, m, 64);
   }
+  if ((tid & 63) == 0) {
+    rs[tid >> 6] = ss;
+    rq[tid >> 6] = qq;
+  }
+  __syncthreads();
   if (tid == 0) {
+#pragma unroll 1  // (registers)
+    for (int i = 1; i < nt / 64; ++i) {
+      ss += rs[i];
+      qq += rq[i];
+    }
     const double cnt = (double)nA * rowsA * wA + (double)nB * rowsB * wB;
-    const double mean = rs[0] / cnt;
-    double var = rq[0] / cnt - mean * mean;
+    const double mean = ss / cnt;
+    double var = qq / cnt - mean * mean;
     if (var < 0.0) var = 0.0;
     s_mean = (float)mean;
     s_rstd = (float)(1.0 / sqrt(var + (double)eps));
   }
   __syncthreads();
-  for (int j = tid; j < cg; j += 256) {
+  for (int j = tid; j < cg; j += nt) {
     const int c = c_lo + j;
     const float a = s_rstd * gamma[c];
     scale[(int64_t)f * Ct + c] = a;
@@ -154,9 +167,19 @@ hipError_t launch_gn_finalize(hipStream_t s, const float* partA, int CA, int spl
                               float* shift, int frames) {
   if (frames <= 0) return hipSuccess;
   if (groups <= 0 || (CA + CB) % groups) return hipErrorInvalidValue;
-  dim3 grid(groups, frames);
-  gn_finalize_kernel<<<grid, 256, 0, s>>>(partA, CA, splitsA, rowsA, wA, partB, CB, splitsB, rowsB, wB, gamma, beta,
-                                          groups, eps, scale, shift);
+  const int cg = (CA + CB) / groups;
+  if (cg <= 0) return hipErrorInvalidValue;
+  // two channels a load: every group's channels of A and of B are pairs on 16-byte boundaries
+  const bool pairs = cg % 2 == 0 && CA % 2 == 0 && CB % 2 == 0 && ((uintptr_t)partA | (uintptr_t)partB) % 16 == 0;
+  const int64_t cells = (int64_t)cg * (splitsA > splitsB ? splitsA : splitsB) / (pairs ? 2 : 1);
+  const dim3 grid(groups, frames);
+  // (1024 threads where 256 would take more than two batches; us: 32 x 1 groups, 4 channels: 8192 splits 48 -> 12)
+  const int nt = cells > 1536 ? 1024 : 256;
+#define LC_FIN(V) \
+  gn_finalize_kernel<V><<<grid, nt, 0, s>>>(partA, CA, splitsA, rowsA, wA, partB, CB, splitsB, rowsB, wB, gamma, beta, groups, eps, scale, shift)
+  if (pairs) LC_FIN(2);
+  else LC_FIN(1);
+#undef LC_FIN
   return hipGetLastError();
 }
 
