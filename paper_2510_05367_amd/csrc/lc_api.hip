@@ -614,10 +614,11 @@ lc_status spatial_block(lc_ctx* c, char* hc, char* scr, int nf, StatRef st, floa
     const Win w = bl.w[i];
     if (w.w) {
       LC_LAUNCH(c, LC_K_SATTN, launch_spatial_attention_window(c->cs, g.dtype, qk, 2 * C, vt, Tp, ao, nf, T, g.heads, g.head_dim,
-                                                               w.y0 * g.W + w.x0, w.w * w.h, w.w, g.W, 1));
+                                                               w.y0 * g.W + w.x0, w.w * w.h, w.w, g.W, 1, g.B * g.F));
     } else {
       // (all queries at once whatever the token chunk: the kernel keeps nothing per query in memory)
-      LC_LAUNCH(c, LC_K_SATTN, launch_spatial_attention(c->cs, g.dtype, qk, 2 * C, vt, Tp, ao, nf, T, g.heads, g.head_dim, 0, T, 1));
+      LC_LAUNCH(c, LC_K_SATTN, launch_spatial_attention(c->cs, g.dtype, qk, 2 * C, vt, Tp, ao, nf, T, g.heads, g.head_dim, 0, T, 1,
+                                                        g.B * g.F));
     }
   }
   // the output projection closes the block; its partial sums are those of the next GroupNorm's input
@@ -1535,7 +1536,7 @@ lc_status lc_op_spatial_attention(lc_ctx* c, const void* qkv, void* out, int fra
   LC_LAUNCH(c, LC_K_SATTN, launch_make_vt(c->cs, g.dtype, (const char*)qkv + (size_t)2 * g.C * es, 3 * g.C, vt, frames, T,
                                           Tp, g.C));
   LC_LAUNCH(c, LC_K_SATTN, launch_spatial_attention(c->cs, g.dtype, qkv, 3 * g.C, vt, Tp, out, frames, T, g.heads,
-                                                    g.head_dim, q0, q1, q_prescaled != 0));
+                                                    g.head_dim, q0, q1, q_prescaled != 0, g.B * g.F));
   return LC_OK;
 }
 

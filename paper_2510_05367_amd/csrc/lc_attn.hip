@@ -34,9 +34,14 @@ template <class T> __device__ __forceinline__ int vcol_inv(int c) { return vcol<
 // (a window of rows of qw tokens out of image rows of qstride tokens; a plain range has qw >= nq).
 // PRE: the q columns already hold q * log2(e) / sqrt(d) (the q,k,v projection scales them before it
 // rounds them); `scale_log2e` is then 1.
+// KS: wavefronts that share a block of 32 queries. 1: each wavefront has queries of its own and walks all keys, in stages of
+// 64 that are double buffered. 4: the four wavefronts share their queries and take 32 keys each of stages of 128 (one buffer,
+// the next stage waits in registers); what they summed up is combined through LDS at the end. Either way the fp32 matrix
+// instructions bound it (64 cycles each, 256 FLOP per cycle and compute unit); what KS = 4 shortens is the serial chain of
+// a wavefront, to a quarter, with four times the workgroups.
 // XA (cross-attention): the keys are not the queries' own rows but rows [Tk] of stride ldk at kx, one set (with its
 // V^T) per group of kv_div consecutive frames; T_tok then counts the query tokens of a frame only.
-template <int D, bool PRE, bool XA = false>
+template <int D, bool PRE, int KS, bool XA = false>
 __global__ __launch_bounds__(256, 2) void spatial_attn_kernel(const float* __restrict__ qk, int ldq,
                                                            const float* __restrict__ vt, int Tp, float* __restrict__ out,
                                                            int T_tok, int C, int q0, int nq, int qw, int qstride,
@@ -49,14 +54,20 @@ __global__ __launch_bounds__(256, 2) void spatial_attn_kernel(const float* __res
   constexpr int KSTEPS = DP / M::K;
   constexpr int DM = (D + 31) / 32;                 // 32-row tiles of O^T
   constexpr int KROW = DP * (int)sizeof(T) + 16;    // LDS row stride of the K tile, bytes
-  constexpr int VROW = kKeys * (int)sizeof(T) + 16; // LDS row stride of the V^T tile, bytes
+  static_assert(KS == 1 || KS == 4, "the wavefronts of a workgroup share all their queries or none");
+  constexpr int SK = KS == 1 ? 64 : 128;            // keys per stage
+  constexpr int NB = KS == 1 ? 2 : 1;               // stages in LDS
+  constexpr int VROW = SK * (int)sizeof(T) + 16;    // LDS row stride of the V^T tile, bytes
   constexpr int PSTEPS = 32 / M::K;                 // P^T V instructions per 32-key sub-tile
-  constexpr int KT = kKeys / 32;                    // 32-key sub-tiles per stage
-  constexpr int KBYTES = kKeys * KROW, VBYTES = DM * 32 * VROW;
+  constexpr int KT = SK / KS / 32;                  // 32-key sub-tiles per stage and wavefront
+  constexpr int KBYTES = SK * KROW, VBYTES = DM * 32 * VROW;
   constexpr int PK = D / VEC;                       // 16-byte packets per K / V row
-  constexpr int NP = (kKeys * PK + 255) / 256;      // K (and V) packets per thread per stage
-  __shared__ __attribute__((aligned(16))) unsigned char k_lds[2][KBYTES];
-  __shared__ __attribute__((aligned(16))) unsigned char v_lds[2][VBYTES];
+  constexpr int NP = (SK * PK + 255) / 256;         // K (and V) packets per thread per stage
+  constexpr int RROW = 33;                          // KS == 4: row stride (floats) of the sums handed over at the end
+  static_assert(KS == 1 || NB * (KBYTES + VBYTES) >= 4 * (DM * 32 * RROW + 64) * 4, "the sums of four wavefronts fit");
+  __shared__ __attribute__((aligned(16))) unsigned char smem[NB * (KBYTES + VBYTES)];
+  unsigned char (*const k_lds)[KBYTES] = reinterpret_cast<unsigned char (*)[KBYTES]>(smem);
+  unsigned char (*const v_lds)[VBYTES] = reinterpret_cast<unsigned char (*)[VBYTES]>(smem + NB * KBYTES);
 
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
   const int lq = lane & 31, hh = lane >> 5;
@@ -83,32 +94,32 @@ __global__ __launch_bounds__(256, 2) void spatial_attn_kernel(const float* __res
   const int ldkk = XA ? ldk : ld;
   const T* __restrict__ kb = XA ? kx + (int64_t)kvf * Tk * ldk + head * D : base + C;
   const T* __restrict__ vbase = vt + ((int64_t)kvf * C + head * D) * Tp;
-  const int qblk = qb * (4 * 32) + wid * 32;  // first query number of this wavefront
+  const int qblk = KS == 1 ? qb * (4 * 32) + wid * 32 : qb * 32;  // first query number of this wavefront
+  const int sub0 = KS == 1 ? 0 : wid;                             // its first sub-tile of a stage
   auto token_of = [&](int qi) { const int r = qi / qw; return q0 + r * qstride + (qi - r * qw); };
 
-  // zero both buffers once: K columns beyond D and V^T rows beyond D feed padded MFMA lanes
-  for (int i = tid; i < 2 * KBYTES / 4; i += 256) reinterpret_cast<uint32_t*>(&k_lds[0][0])[i] = 0u;
-  for (int i = tid; i < 2 * VBYTES / 4; i += 256) reinterpret_cast<uint32_t*>(&v_lds[0][0])[i] = 0u;
+  // zero the buffers once: K columns beyond D and V^T rows beyond D feed padded MFMA lanes
+  for (int i = tid; i < NB * (KBYTES + VBYTES) / 4; i += 256) reinterpret_cast<uint32_t*>(smem)[i] = 0u;
   // Softmax denominators for free: when d leaves a spare row in the 32-row tiles of V^T (d = 40:
   // rows 40..63 are padding), row D is set to ones, so O^T[D][q] accumulates the sum over keys of
   // exactly the (rounded) probabilities that multiply V, and is rescaled with the rest of O^T.
   constexpr bool ROWSUM = D % 32 != 0;
   if (ROWSUM) {
     __syncthreads();
-    for (int i = tid; i < 2 * kKeys; i += 256)
-      reinterpret_cast<T*>(&v_lds[i / kKeys][D * VROW])[i % kKeys] = 1.f;
+    for (int i = tid; i < NB * SK; i += 256)
+      reinterpret_cast<T*>(&v_lds[i / SK][D * VROW])[i % SK] = 1.f;
   }
 
   // ---- staging: K packet i = tid + 256 j of a stage is (key i / PK, packet i % PK); V^T packet i is
   //      (dim i / VPK, packet i % VPK) and is already in LDS order
-  constexpr int VPK = kKeys / VEC;              // 16-byte packets per V^T row of a stage
+  constexpr int VPK = SK / VEC;                 // 16-byte packets per V^T row of a stage
   constexpr int NPV = (D * VPK + 255) / 256;
   Vec16<T> kreg[NP], vreg[NPV];
   auto fetch_kv = [&](int k0) {
 #pragma unroll
     for (int j = 0; j < NP; ++j) {
       const int i = tid + 256 * j;
-      const int key = min(i / PK, kKeys - 1), pk = i % PK;
+      const int key = min(i / PK, SK - 1), pk = i % PK;
       const int gk = min(k0 + key, TK - 1);  // clamped: keys beyond the sequence are masked later
       kreg[j] = load16(kb + (int64_t)gk * ldkk + pk * VEC);
     }
@@ -116,16 +127,17 @@ __global__ __launch_bounds__(256, 2) void spatial_attn_kernel(const float* __res
     for (int j = 0; j < NPV; ++j) {
       const int i = tid + 256 * j;
       const int dim = min(i / VPK, D - 1), pk = i % VPK;
-      vreg[j] = load16(vbase + (int64_t)dim * Tp + k0 + pk * VEC);
+      // (a row of V^T is whole stages of 64 keys long: of a stage of 128 the second half may lie behind it)
+      vreg[j] = load16(vbase + (int64_t)dim * Tp + (KS == 1 ? k0 + pk * VEC : min(k0 + pk * VEC, Tp - VEC)));
     }
   };
   auto stash_kv = [&](int buf, int k0) {
 #pragma unroll
     for (int j = 0; j < NP; ++j) {
       const int i = tid + 256 * j;
-      if (i < kKeys * PK) *reinterpret_cast<Vec16<T>*>(&k_lds[buf][(i / PK) * KROW + (i % PK) * 16]) = kreg[j];
+      if (i < SK * PK) *reinterpret_cast<Vec16<T>*>(&k_lds[buf][(i / PK) * KROW + (i % PK) * 16]) = kreg[j];
     }
-    const bool tail = k0 + kKeys > TK;
+    const bool tail = k0 + SK > TK;
 #pragma unroll
     for (int j = 0; j < NPV; ++j) {
       const int i = tid + 256 * j;
@@ -161,11 +173,13 @@ __global__ __launch_bounds__(256, 2) void spatial_attn_kernel(const float* __res
   stash_kv(0, 0);
   __syncthreads();
 
-  const int nstage = (TK + kKeys - 1) / kKeys;
+  const int nstage = (TK + SK - 1) / SK;
   for (int st_i = 0; st_i < nstage; ++st_i) {
-    const int k0 = st_i * kKeys, buf = st_i & 1;
-    const bool tail = k0 + kKeys > TK;  // uniform: some keys of this stage lie beyond the sequence
-    if (st_i + 1 < nstage) fetch_kv(k0 + kKeys);
+    const int k0 = st_i * SK, buf = st_i % NB;
+    const bool tail = k0 + SK > TK;  // uniform: some keys of this stage lie beyond the sequence
+    if (st_i + 1 < nstage) fetch_kv(k0 + SK);
+    // (a wavefront none of whose keys of the stage exist; with KS == 1 there is always one)
+    if (KS == 1 || k0 + sub0 * 32 < TK) {
 
     // ---- S^T sub-tiles [32 keys][32 queries]
     f32x16 sc[KT];
@@ -174,17 +188,17 @@ __global__ __launch_bounds__(256, 2) void spatial_attn_kernel(const float* __res
       typename M::Frag kf[KSTEPS];
 #pragma unroll
       for (int kk = 0; kk < KSTEPS; ++kk)
-        kf[kk] = M::load(reinterpret_cast<const T*>(&k_lds[buf][(kt * 32 + lq) * KROW]) + kk * M::K + hh * M::LK);
+        kf[kk] = M::load(reinterpret_cast<const T*>(&k_lds[buf][((sub0 + kt) * 32 + lq) * KROW]) + kk * M::K + hh * M::LK);
 #pragma unroll
       for (int r = 0; r < 16; ++r) sc[kt][r] = 0.f;
 #pragma unroll
       for (int kk = 0; kk < KSTEPS; ++kk) M::mma(kf[kk], qf[kk], sc[kt]);
     }
-    // lane holds keys  k0 + kt*32 + 8*(r/4) + 4*hh + r%4  of query lq
+    // lane holds keys  k0 + (sub0 + kt)*32 + 8*(r/4) + 4*hh + r%4  of query lq
     if (tail) {
       // (the key indices are built from a value the compiler cannot see through: left alone it hoists
       // these 64 additions out of the branch and every stage pays for them)
-      int kbi = k0 + 4 * hh;
+      int kbi = k0 + sub0 * 32 + 4 * hh;
       asm volatile("" : "+v"(kbi));
 #pragma unroll
       for (int kt = 0; kt < KT; ++kt)
@@ -212,7 +226,8 @@ __global__ __launch_bounds__(256, 2) void spatial_attn_kernel(const float* __res
       mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
       const bool up = st_i == 0 || (mx - m_run) * scale_log2e > kLazy;
       const float m_new = up ? fmaxf(m_run, mx) : m_run;
-      const float alpha = __builtin_amdgcn_exp2f((m_run - m_new) * scale_log2e);
+      // (a sub-tile of scores that are all -inf leaves the maximum there: nothing to rescale, nothing to subtract)
+      const float alpha = KS != 1 && m_new == m_run ? 1.f : __builtin_amdgcn_exp2f((m_run - m_new) * scale_log2e);
       m_run = m_new;
       if (!ROWSUM) l_run *= alpha;
 #pragma unroll
@@ -220,7 +235,7 @@ __global__ __launch_bounds__(256, 2) void spatial_attn_kernel(const float* __res
 #pragma unroll
         for (int r = 0; r < 16; ++r) o[mt][r] *= alpha;
     }
-    const float mc = m_run * scale_log2e;
+    const float mc = KS != 1 && m_run == -INFINITY ? 0.f : m_run * scale_log2e;
     typename M::Frag pf[KT][PSTEPS];
     float ps = 0.f;
 #pragma unroll
@@ -236,15 +251,61 @@ __global__ __launch_bounds__(256, 2) void spatial_attn_kernel(const float* __res
     for (int kt = 0; kt < KT; ++kt)
 #pragma unroll
       for (int st = 0; st < PSTEPS; ++st) {
-        const int col = kt * 32 + 8 * (st >> 2) + 4 * hh + (st & 3);
+        const int col = (sub0 + kt) * 32 + 8 * (st >> 2) + 4 * hh + (st & 3);
 #pragma unroll
         for (int mt = 0; mt < DM; ++mt) {
           const typename M::Frag vf = M::load(reinterpret_cast<const T*>(&v_lds[buf][(mt * 32 + lq) * VROW]) + col);
           M::mma(vf, pf[kt][st], o[mt]);
         }
       }
-    if (st_i + 1 < nstage) stash_kv(buf ^ 1, k0 + kKeys);
+    }
+    if (st_i + 1 < nstage) {
+      if (NB == 1) __syncthreads();  // everybody has read the stage
+      stash_kv(NB == 1 ? 0 : buf ^ 1, k0 + SK);
+    }
     __syncthreads();
+  }
+
+  if constexpr (KS != 1) {
+    // ---- combine: bring the sums of the four wavefronts to the largest of their offsets and add them, in a fixed order
+    float* const red = reinterpret_cast<float*>(smem);  // [wavefront][dim][RROW]: O^T of the 32 queries
+    float* const ml = red + 4 * DM * 32 * RROW;          // [wavefront][offset | denominator][32]
+    if (!ROWSUM) l_run += __shfl_xor(l_run, 32, 64);
+    if (hh == 0) {
+      ml[wid * 64 + lq] = m_run;
+      ml[wid * 64 + 32 + lq] = l_run;
+    }
+    __syncthreads();
+    float m_all = -INFINITY;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) m_all = fmaxf(m_all, ml[w * 64 + lq]);
+    auto factor = [&](float m, float top) { return m == top ? 1.f : __builtin_amdgcn_exp2f((m - top) * scale_log2e); };
+    const float f = factor(m_run, m_all);
+#pragma unroll
+    for (int mt = 0; mt < DM; ++mt)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) red[((wid * DM + mt) * 32 + 8 * (r >> 2) + 4 * hh + (r & 3)) * RROW + lq] = o[mt][r] * f;
+    __syncthreads();
+    const int tq = tid >> 3, td = (tid & 7) * (DM * 4);  // this thread finishes dims td .. td + 4 DM - 1 of query tq
+    float l = 0.f, m_top = -INFINITY;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) m_top = fmaxf(m_top, ml[w * 64 + tq]);
+#pragma unroll
+    for (int w = 0; w < 4; ++w)
+      l += ROWSUM ? red[(w * DM * 32 + D) * RROW + tq] : ml[w * 64 + 32 + tq] * factor(ml[w * 64 + tq], m_top);
+    const float inv = 1.f / l;
+    if (qblk + tq >= nq) return;
+    T* orow = out + ((int64_t)frame * T_tok + token_of(qblk + tq)) * C + head * D;
+#pragma unroll
+    for (int e = 0; e < DM * 4; ++e) {
+      if (td + e < D) {
+        float v = 0.f;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) v += red[(w * DM * 32 + td + e) * RROW + tq];
+        orow[td + e] = v * inv;
+      }
+    }
+    return;
   }
 
   // ---- normalise and store: lane holds O^T[dim = 32*mt + 8*(r/4) + 4*hh + r%4][query lq]
@@ -784,13 +845,28 @@ static hipError_t ring_dispatch(hipStream_t s, const bf16_t* qk, int ldq, const 
 #undef LC_GO
 }
 
+// fp32: whether the wavefronts of a workgroup share their queries and split the keys (KS = 4). Shorter chains and four times
+// the workgroups pay while the chip is idle, the staging that is done once per 32 instead of 128 queries costs where it is not:
+// 2 frames of 1024 tokens, 1 head of 64 (16 workgroups of 128 queries) 79 us without, 32 us with; 8 heads of 40 (128
+// workgroups) 69 and 45 us, 8 frames of 256 (128) 22 and 19 us; 32 frames of 256 (512) 42 and 65 us; 4 frames of 4096 (1024)
+// 878 and 1033 us; up to 64 keys, one stage of either, 10.3 and 11.0 us. The two round differently, and a window of queries or a
+// chunk of frames gives the bits of the whole, so the workgroups counted are those of the whole problem.
+static bool keys_split(int T, int heads, int all_frames) {
+  return all_frames > 0 && T > 64 && (int64_t)((T + 127) / 128) * heads * all_frames <= 128;
+}
+
 template <bool PRE>
 static hipError_t spatial_dispatch(hipStream_t s, const float* qk, int ldq, const float* vt, int Tp, float* out, int frames,
-                                   int T_tok, int heads, int d, int q0, int nq, int qw, int qstride) {
+                                   int T_tok, int heads, int d, int q0, int nq, int qw, int qstride, int all_frames) {
   const int C = heads * d;
   const float sl = PRE ? 1.f : 1.4426950408889634f / sqrtf((float)d);
-  dim3 grid((nq + 127) / 128, heads, frames);
-#define LC_GO(D) spatial_attn_kernel<D, PRE><<<grid, 256, 0, s>>>(qk, ldq, vt, Tp, out, T_tok, C, q0, nq, qw, qstride, sl)
+  const bool split = keys_split(T_tok, heads, all_frames);
+  const int per = split ? 32 : 128;
+  dim3 grid((nq + per - 1) / per, heads, frames);
+#define LC_ARGS qk, ldq, vt, Tp, out, T_tok, C, q0, nq, qw, qstride, sl
+#define LC_GO(D)                                                              \
+  if (split) spatial_attn_kernel<D, PRE, 4><<<grid, 256, 0, s>>>(LC_ARGS);    \
+  else spatial_attn_kernel<D, PRE, 1><<<grid, 256, 0, s>>>(LC_ARGS)
   switch (d) {
     case 8: LC_GO(8); break;
     case 16: LC_GO(16); break;
@@ -800,19 +876,20 @@ static hipError_t spatial_dispatch(hipStream_t s, const float* qk, int ldq, cons
     default: return hipErrorInvalidValue;
   }
 #undef LC_GO
+#undef LC_ARGS
   return hipGetLastError();
 }
 
 hipError_t launch_spatial_attention(hipStream_t s, int dt, const void* qk, int ldq, const void* vt, int Tp, void* out,
-                                    int frames, int T, int heads, int d, int q0, int q1, int q_prescaled) {
+                                    int frames, int T, int heads, int d, int q0, int q1, int q_prescaled, int all_frames) {
   if (q1 <= q0) return hipSuccess;
   return launch_spatial_attention_window(s, dt, qk, ldq, vt, Tp, out, frames, T, heads, d, q0, q1 - q0, q1 - q0, 0,
-                                         q_prescaled);
+                                         q_prescaled, all_frames);
 }
 
 hipError_t launch_spatial_attention_window(hipStream_t s, int dt, const void* qk, int ldq, const void* vt, int Tp, void* out,
                                            int frames, int T, int heads, int d, int q0, int nq, int qw, int qstride,
-                                           int q_prescaled) {
+                                           int q_prescaled, int all_frames) {
   if (frames <= 0 || nq <= 0) return hipSuccess;
   if (Tp % kKeys != 0 || Tp < T || qw <= 0 || q0 < 0) return hipErrorInvalidValue;
   {  // the last query must be a token of the frame
@@ -821,7 +898,7 @@ hipError_t launch_spatial_attention_window(hipStream_t s, int dt, const void* qk
   }
 #define LC_ARGS(TT) s, (const TT*)qk, ldq, (const TT*)vt, Tp, (TT*)out, frames, T, heads, d, q0, nq, qw, qstride
   if (dt == kBF16) return q_prescaled ? ring_dispatch<true, false>(LC_ARGS(bf16_t)) : ring_dispatch<false, false>(LC_ARGS(bf16_t));
-  return q_prescaled ? spatial_dispatch<true>(LC_ARGS(float)) : spatial_dispatch<false>(LC_ARGS(float));
+  return q_prescaled ? spatial_dispatch<true>(LC_ARGS(float), all_frames) : spatial_dispatch<false>(LC_ARGS(float), all_frames);
 #undef LC_ARGS
 }
 
@@ -832,7 +909,7 @@ static hipError_t cross_dispatch(hipStream_t s, const float* q, int ldq, const f
   const int C = heads * d;
   const float sl = 1.f;  // the queries carry the scale
   dim3 grid((Tq + 127) / 128, heads, frames);
-#define LC_GO(D) spatial_attn_kernel<D, true, true><<<grid, 256, 0, s>>>(q, ldq, vt, Tp, out, Tq, C, 0, Tq, Tq, 0, sl, k, ldk, Tk, kv_div)
+#define LC_GO(D) spatial_attn_kernel<D, true, 1, true><<<grid, 256, 0, s>>>(q, ldq, vt, Tp, out, Tq, C, 0, Tq, Tq, 0, sl, k, ldk, Tk, kv_div)
   switch (d) {
     case 8: LC_GO(8); break;
     case 16: LC_GO(16); break;

@@ -244,7 +244,7 @@ lc_status attn_block(lc_decoder* d, const DPlan& p, int n, float* h, Stats* st) 
   f.q_cols = C; f.q_scale = attn_q_scale(g.head_dim);
   f.yt = vt; f.yt_from = 2 * C; f.yt_T = T; f.yt_Tp = Tp;
   LCD_HIP(d, launch_fused(d->s, f));
-  LCD_HIP(d, launch_spatial_attention(d->s, g.dtype, qk, 2 * C, vt, Tp, ao, n, T, g.heads, g.head_dim, 0, T, 1));
+  LCD_HIP(d, launch_spatial_attention(d->s, g.dtype, qk, 2 * C, vt, Tp, ao, n, T, g.heads, g.head_dim, 0, T, 1, 0));
   memset(&f, 0, sizeof f);
   f.dt = g.dtype; f.y_f32 = 1; f.taps = 1; f.src = 0; f.Cin = C; f.Cout = C; f.Cout_store = C; f.w = d->at_wo; f.bias = d->at_bo;
   f.rows = rows; f.in_map = f.out_map = RowMap{0, 0, 1 << 30}; f.x = ao; f.res = h; f.y = h;

@@ -289,7 +289,7 @@ lc_status run_block(lc_dit* c, int i, const float* mod, float* x, const float* d
   if ((s = ln_mod(c, x, delta, m, 0, 1, ao, (int)R, 0)) != LC_OK) return s;
   if ((s = linear(c, w.wqkv, w.bqkv, D, 3 * D, R, ao, qkv, 0, 0, D, vt_fused ? vt : nullptr, 0)) != LC_OK) return s;
   if (!vt_fused) LCT_HIP(c, launch_make_vt(c->cs, g.dtype, qkv + (size_t)2 * D * es, 3 * D, vt, g.B, T, Tp, D));
-  LCT_HIP(c, launch_spatial_attention(c->cs, g.dtype, qkv, ldq, vt, Tp, ao, g.B, T, g.heads, g.head_dim, 0, T, 1));
+  LCT_HIP(c, launch_spatial_attention(c->cs, g.dtype, qkv, ldq, vt, Tp, ao, g.B, T, g.heads, g.head_dim, 0, T, 1, g.B));
   if (gated) {
     if ((s = linear_gated(c, w.wo, w.bo, D, R, ao, dst, m, 2, 0)) != LC_OK) return s;
   } else {

@@ -191,15 +191,16 @@ inline hipError_t launch_linear_any(hipStream_t s, const FusedDesc& d) {
 // Spatial attention core. qk: rows [frames*T] of stride ldq with q at column 0 and k at column C;
 // vt: V transposed [frames][C][Tp], token t at column (t & ~63) + vcol(t & 63), Tp a multiple of 64;
 // out [frames*T][C]; queries [q0,q1) of every frame. q_prescaled: the q columns hold q * log2(e) / sqrt(d)
-// (FusedDesc::q_scale of the projection that wrote them) instead of q.
+// (FusedDesc::q_scale of the projection that wrote them) instead of q. all_frames: the frames of the whole problem that this
+// launch is a chunk of (fp32: chooses how the work is split, which must not depend on the chunk), 0 where that is not fixed.
 inline int attn_tp(int T) { return (T + 63) / 64 * 64; }
 hipError_t launch_spatial_attention(hipStream_t s, int dt, const void* qk, int ldq, const void* vt, int Tp, void* out,
-                                    int frames, int T, int heads, int d, int q0, int q1, int q_prescaled);
+                                    int frames, int T, int heads, int d, int q0, int q1, int q_prescaled, int all_frames);
 // The same for a window of queries: nq queries, number i being token q0 + (i / qw) * qstride + i % qw (rows of qw
 // tokens out of image rows of qstride tokens). Each query's result does not depend on which others share its launch.
 hipError_t launch_spatial_attention_window(hipStream_t s, int dt, const void* qk, int ldq, const void* vt, int Tp, void* out,
                                            int frames, int T, int heads, int d, int q0, int nq, int qw, int qstride,
-                                           int q_prescaled);
+                                           int q_prescaled, int all_frames);
 // Cross-attention core: queries q[frames*Tq] (row stride ldq; head h at column h*d, already multiplied by
 // log2(e) / sqrt(d): FusedDesc::q_scale) against the keys k[(frames /
 // kv_div)*Tk] (row stride ldk) and values vt[(frames / kv_div)][C][Tp] (layout as above) that every kv_div consecutive

@@ -657,7 +657,7 @@ lc_status st_block(lc_unet* c, const TfP& w, const void* cond, int level, float*
   LCU_HIP(c, launch_make_vt(c->cs, g.dtype, kv + (size_t)C * es, 2 * C, vtx, g.B, L, TpL, C));
   return frame_chunks(c, level, [&](int n0, int nc) -> lc_status {
     auto attend = [&]() -> lc_status {
-      LCU_HIP(c, launch_spatial_attention(c->cs, g.dtype, qkv, 2 * C, vt, Tp, ao, nc, P, heads, g.head_dim, 0, P, 1));
+      LCU_HIP(c, launch_spatial_attention(c->cs, g.dtype, qkv, 2 * C, vt, Tp, ao, nc, P, heads, g.head_dim, 0, P, 1, g.B * g.F));
       return LC_OK;
     };
     auto cross = [&]() -> lc_status {
