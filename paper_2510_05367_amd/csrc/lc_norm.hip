@@ -222,17 +222,18 @@ hipError_t launch_gn_apply(hipStream_t s, const float* x, const float* scale, co
 // (ACT) or x, x the channel concatenation of two tensors of rows [frames][rows_per_frame][..] (the second may be missing).
 // The arithmetic of the loaders of the other convolution kernels, so results do not depend on which of them runs. A thread
 // keeps one packet of 8 channels and its scale / shift and takes kActRows rows, all requested before the first is used: bound
-// by memory (fp32, 320 channels: 131072 rows 37 us = 6.8 TB/s, 16384 rows 5.5 us = 5.7 TB/s).
+// by memory (fp32, 320 channels: 131072 rows 37 us = 6.8 TB/s, 16384 rows 5.5 us = 5.7 TB/s). A workgroup has up to 256 packets
+side by side, wider rows (a concatenation) have several workgroups (gridDim.z).
 constexpr int kActRows = 4;
 template <class XT, bool ACT>
 __global__ __launch_bounds__(256) void conv_act_kernel(const XT* __restrict__ xa, const XT* __restrict__ xb,
                                                        const float* __restrict__ scale, const float* __restrict__ shift, int ld,
                                                        bf16_t* __restrict__ y, int rows_per_frame, int Ca8, int Cb8, int R) {
   constexpr int VN = Vec16<XT>::N;
-  const int C8 = Ca8 + Cb8;
-  const int c8 = threadIdx.x % C8, sub = threadIdx.x / C8, f = blockIdx.y;
+  const int C8 = Ca8 + Cb8, W8 = min(C8, 256);
+  const int c8 = threadIdx.x % W8 + blockIdx.z * 256, sub = threadIdx.x / W8, f = blockIdx.y;
   const int r0 = blockIdx.x * (R * kActRows) + sub;
-  if (r0 >= rows_per_frame) return;
+  if (r0 >= rows_per_frame || c8 >= C8) return;
   const bool in_a = c8 < Ca8;
   const int64_t ldx = (in_a ? Ca8 : Cb8) * 8;
   const XT* x = (in_a ? xa + c8 * 8 : xb + (c8 - Ca8) * 8) + (int64_t)f * rows_per_frame * ldx;
@@ -265,11 +266,11 @@ hipError_t launch_conv_act(hipStream_t s, int x_dt, const void* xa, int Ca, cons
                            int ld, void* y, int frames, int rows_per_frame) {
   if (frames <= 0 || rows_per_frame <= 0) return hipSuccess;
   if (Ca <= 0 || Cb < 0 || Ca % 8 || Cb % 8 || (scale && ld % 4) || (scale == nullptr) != (shift == nullptr)) return hipErrorInvalidValue;
-  if (Ca + Cb > 2048 || frames > 65535 || (x_dt == kBF16 && !scale)) return hipErrorNotSupported;
-  const int C8 = (Ca + Cb) / 8, R = 256 / C8;
-  const dim3 grid((unsigned)((rows_per_frame + R * kActRows - 1) / (R * kActRows)), (unsigned)frames);
+  if (frames > 65535 || (x_dt == kBF16 && !scale)) return hipErrorNotSupported;
+  const int C8 = (Ca + Cb) / 8, W8 = C8 < 256 ? C8 : 256, R = 256 / W8;
+  const dim3 grid((unsigned)((rows_per_frame + R * kActRows - 1) / (R * kActRows)), (unsigned)frames, (unsigned)((C8 + 255) / 256));
 #define LC_ACT(XT, A) \
-  conv_act_kernel<XT, A><<<grid, C8 * R, 0, s>>>((const XT*)xa, (const XT*)xb, scale, shift, ld, (bf16_t*)y, rows_per_frame, Ca / 8, Cb / 8, R)
+  conv_act_kernel<XT, A><<<grid, W8 * R, 0, s>>>((const XT*)xa, (const XT*)xb, scale, shift, ld, (bf16_t*)y, rows_per_frame, Ca / 8, Cb / 8, R)
   if (x_dt == kBF16) LC_ACT(bf16_t, true);
   else if (scale) LC_ACT(float, true);
   else LC_ACT(float, false);

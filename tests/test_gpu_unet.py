@@ -21,6 +21,9 @@ SMALL_BF16 = synth.UnetConfig("small_bf16", B=2, F=8, H=24, W=16, C_lat=4, C=64,
 SMALL_F32 = synth.UnetConfig("small_f32", B=2, F=3, H=8, W=12, C_lat=3, C=64, C1=64, C2=128, groups=16, head_dim=16,
                              ctx_len=5, ctx_dim=64, temb_dim=40, dtype="f32", ff_mult=2)
 NARROW_BF16 = SMALL_BF16.with_(name="narrow_bf16", H=32, W=4)     # more splits of the first convolution than other statistics have
+# bf16, concatenations of 2112 and 384 channels: more than one workgroup of the passes over their rows is wide
+WIDE_BF16 = synth.UnetConfig("wide_bf16", B=1, F=2, H=8, W=8, C_lat=4, C=64, C1=320, C2=1792, groups=32, head_dim=32,
+                             ctx_len=5, ctx_dim=64, temb_dim=64, dtype="bf16")
 MID = synth.UNETS["mid"]
 
 
@@ -68,7 +71,7 @@ def run_case(cfg, odtype=np.float64, sharp=4.0, chain=False, frame_chunk=None):
         net.close()
 
 
-@pytest.mark.parametrize("cfg", [TINY, SMALL_F32, SMALL_BF16, NARROW_BF16], ids=lambda c: c.name)
+@pytest.mark.parametrize("cfg", [TINY, SMALL_F32, SMALL_BF16, NARROW_BF16, WIDE_BF16], ids=lambda c: c.name)
 def test_steps_match_oracle(cfg):
     run_case(cfg)
 
