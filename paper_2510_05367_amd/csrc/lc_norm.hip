@@ -223,7 +223,7 @@ hipError_t launch_gn_apply(hipStream_t s, const float* x, const float* scale, co
 // The arithmetic of the loaders of the other convolution kernels, so results do not depend on which of them runs. A thread
 // keeps one packet of 8 channels and its scale / shift and takes kActRows rows, all requested before the first is used: bound
 // by memory (fp32, 320 channels: 131072 rows 37 us = 6.8 TB/s, 16384 rows 5.5 us = 5.7 TB/s). A workgroup has up to 256 packets
-side by side, wider rows (a concatenation) have several workgroups (gridDim.z).
+// side by side, wider rows (a concatenation) have several workgroups (gridDim.z).
 constexpr int kActRows = 4;
 template <class XT, bool ACT>
 __global__ __launch_bounds__(256) void conv_act_kernel(const XT* __restrict__ xa, const XT* __restrict__ xb,
