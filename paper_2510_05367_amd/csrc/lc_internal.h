@@ -163,7 +163,7 @@ inline bool conv_window_tiles(const FusedDesc& d, int* tx0, int* ty0, int* ntx, 
 }
 hipError_t launch_fused(hipStream_t s, const FusedDesc& d);
 // taps == 9 of a bf16 stage with specialised wavefronts (lc_convws.hip): the same results as the general
-// kernel bit for bit; hipErrorNotSupported for shapes it does not cover. launch_fused tries it first.
+// kernel bit for bit; hipErrorNotSupported for shapes it does not cover. launch_fused takes it where the rows below have no room.
 hipError_t launch_conv_ws(hipStream_t s, const FusedDesc& d);
 // taps == 9, src == 0 of a bf16 stage: a convolution over rows that are activated and rounded already (lc_convd.hip). src == 3:
 // x are those of the skip channels, x2 those of the deep ones at half the resolution. The same results as the kernels that
