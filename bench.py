@@ -34,13 +34,13 @@ PEAK_HBM_GBS = 8000.0
 # HBM-side bytes of one launch of a kernel family (animatediff, frame chunk 4) from the rocprofv3 FETCH_SIZE /
 # WRITE_SIZE runs summarised under profiles/ (fetch x 2.0, the factor a plain copy of known size gave). Valid only
 # for the kernel sources the counters were taken with: `sha256_16` covers the listed files, else traffic is null.
-TRAFFIC = {
-    "conv_up": {"sources": ("lc_convws.hip", "lc_common.h", "lc_internal.h"), "sha256_16": "9dd072ac2f610b74",
-                "bytes_per_launch": 83.6e6 + 22.3e6},
-    "sattn": {"sources": ("lc_attn.hip", "lc_common.h", "lc_internal.h"), "sha256_16": "0057d4a2151eab47",
+TRAFFIC = {  # (a convolution is its activation pass(es) and the contraction)
+    "conv_up": {"sources": ("lc_convd.hip", "lc_norm.hip", "lc_common.h", "lc_internal.h"), "sha256_16": "5a1a55f93a6d5690",
+                "bytes_per_launch": 94.1e6 + 38.0e6},
+    "sattn": {"sources": ("lc_attn.hip", "lc_common.h", "lc_internal.h"), "sha256_16": "5c5adb7540d5f45c",
               "bytes_per_launch": 61.0e6 + 12.6e6},
-    "conv_res": {"sources": ("lc_convws.hip", "lc_common.h", "lc_internal.h"), "sha256_16": "9dd072ac2f610b74",
-                 "bytes_per_launch": 54.6e6 + 22.3e6},
+    "conv_res": {"sources": ("lc_convd.hip", "lc_norm.hip", "lc_common.h", "lc_internal.h"), "sha256_16": "5a1a55f93a6d5690",
+                 "bytes_per_launch": 71.1e6 + 32.8e6},
 }
 TRAFFIC_WORKLOAD = ("animatediff", 4)
 
