@@ -66,9 +66,10 @@ __device__ __forceinline__ void store_pairs(const float (&val)[16][NTV], int lan
 
 // The epilogue of one 32-row block of NT column tiles (32 channels each): the lane holds channel c0 + 32 i + lp of rows
 // rblk + 8 (r / 4) + 4 hh + r % 4.
-// Dense rows go through buffer descriptors over the block: row offsets are scalars, and rows beyond the end read as zero and
-// are not stored by the bounds check, where 64-bit addresses and a condition per row took most of a short contraction's time
-// (131072 x 2560, K = 64, GEGLU 215 us with them).
+// Dense rows go through buffer descriptors over the block: rows beyond the end read as zero and are not stored by the bounds
+// check, where 64-bit addresses and a condition per row took most of a short contraction's time (131072 x 2560, K = 64, GEGLU
+// 215 us with them). The row's offset is part of the vector offset, which is what the check compares with the descriptor's size:
+// a scalar offset is taken off that size first, and beyond the end it is the larger of the two.
 // GATE: Lin2Args::gate may be set (its own registers: the kernels that never take one stay without them).
 template <class OT, int NT, bool MAPPED, bool GATE>
 __device__ __forceinline__ void lin_epilogue(const Lin2Args& a, const f32x16 (&acc)[NT], int64_t rblk, int c0, int lane,
@@ -81,6 +82,12 @@ __device__ __forceinline__ void lin_epilogue(const Lin2Args& a, const f32x16 (&a
   // rows of ld elements of es bytes from column c on: the block's descriptor, and the lane's offset in its first row
   auto block = [&](const void* p, int64_t ld, int es, int c) {
     return __builtin_amdgcn_make_buffer_rsrc((char*)const_cast<void*>(p) + (rblk * ld + c) * es, 0, (int)max((int64_t)0, (left * ld - c) * es), kRaw);
+  };
+  // the vector offset of a row; opaque, so that the channel tiles behind it stay immediate offsets (one addition a row)
+  auto row_at = [](int vo, int row) {
+    int v = vo + row;
+    asm("" : "+v"(v));
+    return v;
   };
   OT* Y = (OT*)a.y;
   const float* R = a.res;
@@ -100,9 +107,11 @@ __device__ __forceinline__ void lin_epilogue(const Lin2Args& a, const f32x16 (&a
       const __amdgpu_buffer_rsrc_t rs = block(R, a.N, 4, c0);
       const int vo = (4 * hh * a.N + lp) * 4;
 #pragma unroll
-      for (int r = 0; r < 16; ++r)
+      for (int r = 0; r < 16; ++r) {
+        const int vr = row_at(vo, rofs(r) * a.N * 4);
 #pragma unroll
-        for (int i = 0; i < NT; ++i) rv[r][i] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, vo + 128 * i, rofs(r) * a.N * 4, 0));
+        for (int i = 0; i < NT; ++i) rv[r][i] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, vr + 128 * i, 0, 0));
+      }
     }
   }
   // all arithmetic of the block first, so that the stores below depend on no load
@@ -174,8 +183,9 @@ __device__ __forceinline__ void lin_epilogue(const Lin2Args& a, const f32x16 (&a
       const __amdgpu_buffer_rsrc_t ys = block(y, ld, 2, c);
       const int vo = ((4 * hh + (lane & 1)) * ld + (lp & ~1)) * 2;
       store_pairs<NV>(val, lane, [&](int rp, const uint32_t (&out)[NV]) __attribute__((always_inline)) {
+        const int vr = row_at(vo, rofs(rp) * ld * 2);
 #pragma unroll
-        for (int i = 0; i < NV; ++i) __builtin_amdgcn_raw_buffer_store_b32(out[i], ys, vo + 64 * i, rofs(rp) * ld * 2, 0);
+        for (int i = 0; i < NV; ++i) __builtin_amdgcn_raw_buffer_store_b32(out[i], ys, vr + 64 * i, 0, 0);
       });
     }
   };
@@ -232,9 +242,11 @@ __device__ __forceinline__ void lin_epilogue(const Lin2Args& a, const f32x16 (&a
       const __amdgpu_buffer_rsrc_t ys = block(Y, a.N, 4, c0);
       const int vo = (4 * hh * a.N + lp) * 4;
 #pragma unroll
-      for (int r = 0; r < 16; ++r)
+      for (int r = 0; r < 16; ++r) {
+        const int vr = row_at(vo, rofs(r) * a.N * 4);
 #pragma unroll
-        for (int i = 0; i < NT; ++i) __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, (float)val[r][i]), ys, vo + 128 * i, rofs(r) * a.N * 4, 0);
+        for (int i = 0; i < NT; ++i) __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, (float)val[r][i]), ys, vr + 128 * i, 0, 0);
+      }
     }
     if (a.y2) put16(a.y2, a.N, c0, std::integral_constant<int, NT>{});
   }
