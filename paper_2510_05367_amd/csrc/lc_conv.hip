@@ -471,7 +471,8 @@ __global__ __launch_bounds__(256) void conv_in_tile_kernel(const bf16_t* __restr
         for (int r = 0; r < 16; ++r) {
           const float v = acc[r] + bv;
           const int px = 8 * (r >> 2) + 4 * hh + (r & 3);
-          __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), yd, vo, (8 * (r >> 2) + (r & 3)) * C * 4, 0);
+          // (the pixel in the vector offset: the range check compares that one)
+          __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), yd, vo + (8 * (r >> 2) + (r & 3)) * C * 4, 0, 0);
           const float t = px < npx ? v : 0.f;
           s1 += t;
           s2 = fmaf(t, t, s2);

@@ -1,12 +1,13 @@
-"""Launches whose rows end inside a tile: what the matrix holds behind them is neither written nor read (buffer descriptors over
-the rows that exist drop those stores and give zero for those loads). Known values lie there."""
+"""Launches whose rows (or image rows, whose pixels) end inside a tile: what lies behind them is neither written nor read (buffer
+descriptors over what exists drop those stores and give zero for those loads). Known values lie there."""
 import numpy as np
 import pytest
 import torch
 
+from oracle import lightcache_oracle as lo
 from paper_2510_05367_amd import binding as lcb
 from paper_2510_05367_amd import synth
-from tests.gpu_util import check, dev, dev32, host, make_stage
+from tests.gpu_util import check, dev, dev32, host, make_stage, rows_to_planar
 
 pytestmark = pytest.mark.gpu
 
@@ -53,3 +54,21 @@ def test_gated_sum(B, T, D):
         assert bool(torch.isfinite(out).all()) and torch.equal(dit.dev_entry(0), entry.reshape(dit.dev_entry(0).shape))
     finally:
         dit.close()
+
+
+# image rows that end inside a 32-pixel segment: the last row of a launch's last frame, with another frame behind it
+@pytest.mark.parametrize("C,H,W", [(320, 6, 34), (64, 6, 62), (128, 2, 12)])
+def test_first_convolution(C, H, W):
+    cfg = synth.StageConfig("ends", B=1, F=2, H=H, W=W, C_lat=4, C=C, C_deep=64, groups=32, n_res=0, heads=C // 64, head_dim=64, dtype="bf16")
+    stage, w = make_stage(cfg, seed=7)
+    try:
+        x = synth.make_latents(cfg, 3).reshape(2, 4, H, W)
+        xd = dev(stage, x)
+        h = torch.full((2 * H * W, C), 7.0, dtype=torch.float32, device=stage.device)
+        lcb.lc_op_conv_in(stage.ctx, xd.data_ptr(), h.data_ptr(), 1)
+        stage.sync()
+        assert bool((h[H * W:] == 7.0).all())
+        ref = lo.conv3x3(x[:1].astype(np.float64), w["conv_in.w"].astype(np.float64), w["conv_in.b"].astype(np.float64))
+        check("conv_in", rows_to_planar(host(h[:H * W]), 1, C, H, W), ref, cfg.dtype)
+    finally:
+        stage.close()
