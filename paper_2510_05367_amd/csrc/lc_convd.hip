@@ -285,7 +285,8 @@ __global__ __launch_bounds__(256, 2) void conv_dma_kernel(ConvDArgs a) {
   const int prow = lane >> 3, pcol = (lane & 7) * 4;  // patch read-back: rows prow + 8 k, channels pcol..pcol+3
   const int co0 = cb * CO_T * 32;
   // Output and residual through buffer descriptors over the tile's eight image rows: a pixel beyond the edge has an offset out
-  // of range, whose load gives zero and whose store is dropped, so neither needs a condition per pixel
+  // of range, whose load gives zero and whose store is dropped, so neither needs a condition per pixel. No scalar offsets: the
+  // range check takes them off the size first, and without a residual that is zero
   const int64_t row0 = ((int64_t)frame * a.H + ty0) * a.W * a.Cout + co0;
   const int rows8 = 8 * a.W * a.Cout;
   const __amdgpu_buffer_rsrc_t ydst = __builtin_amdgcn_make_buffer_rsrc((OT*)a.y + row0, 0, rows8 * (int)sizeof(OT), kdRawBuffer);
@@ -318,7 +319,7 @@ __global__ __launch_bounds__(256, 2) void conv_dma_kernel(ConvDArgs a) {
       side[i - i0].b = bias ? *reinterpret_cast<const f32x4*>(bias + co0 + i * 32 + pcol) : f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int k = 0; k < 4; ++k)
-        side[i - i0].r[k] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, far(k, opix[k] * 4), i * 128, 0));
+        side[i - i0].r[k] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, far(k, opix[k] * 4) + i * 128, 0, 0));
     }
     barrier_keep<63>();
 #pragma unroll
@@ -341,12 +342,12 @@ __global__ __launch_bounds__(256, 2) void conv_dma_kernel(ConvDArgs a) {
         v += side[i - i0].b;
         v += side[i - i0].r[k];
         if constexpr (sizeof(OT) == 4) {
-          __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), ydst, far(k, opix[k] * 4), i * 128, 0);
+          __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), ydst, far(k, opix[k] * 4) + i * 128, 0, 0);
         } else {
           bf16x4 o;
 #pragma unroll
           for (int e = 0; e < 4; ++e) o[e] = (bf16_t)v[e];
-          __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, o), ydst, far(k, opix[k] * 2), i * 64, 0);
+          __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, o), ydst, far(k, opix[k] * 2) + i * 64, 0, 0);
         }
 #pragma unroll
         for (int e = 0; e < 4; ++e) {

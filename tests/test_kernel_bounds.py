@@ -13,7 +13,7 @@ from paper_2510_05367_amd import build as lcbuild
 CSRC = Path(lcbuild.__file__).parent / "csrc"
 
 
-@pytest.mark.parametrize("src", ["lc_lin2", "lc_lin3", "lc_conv"])
+@pytest.mark.parametrize("src", ["lc_lin2", "lc_lin3", "lc_conv", "lc_convd"])
 def test_no_scalar_offset_where_the_range_check_decides(src, tmp_path):
     out = tmp_path / f"{src}.s"
     subprocess.run([lcbuild._hipcc(), *lcbuild.FLAGS, "-S", "--cuda-device-only", str(CSRC / f"{src}.hip"), "-o", str(out)], check=True,
