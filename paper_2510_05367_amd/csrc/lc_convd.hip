@@ -436,7 +436,7 @@ hipError_t launch_conv_dma(hipStream_t s, const FusedDesc& d) {
 }
 
 hipError_t launch_conv_act_dma(hipStream_t s, const FusedDesc& d) {
-  if (d.src < 1 || d.src > 3 || !d.xact || d.xact_bytes < conv_act_bytes(d)) return hipErrorNotSupported;
+  if (d.src < 1 || d.src > 3 || (d.src == 1 && !d.unit_scale) || !d.xact || d.xact_bytes < conv_act_bytes(d)) return hipErrorNotSupported;
   FusedDesc c = d;
   c.x = d.xact; c.frames = 0;
   c.src = d.src == 3 ? 3 : 0;
@@ -453,7 +453,7 @@ hipError_t launch_conv_act_dma(hipStream_t s, const FusedDesc& d) {
       e = launch_conv_act(s, kBF16, d.x2, d.Cin - d.Cs, nullptr, 0, d.scale + d.Cs, d.shift + d.Cs, d.Cin, deep, d.frames, T / 4);
   } else if (d.src == 2) {
     e = launch_conv_act(s, kF32, d.x, d.Cin, nullptr, 0, d.scale, d.shift, d.Cin, d.xact, d.frames, T);
-  } else {  // (whoever brings scratch for src 1 has a unit scale: the rows are only rounded)
+  } else {  // (a unit scale: the rows are only rounded)
     e = launch_conv_act(s, kF32, d.x, d.Cin, nullptr, 0, nullptr, nullptr, 0, d.xact, d.frames, d.up2 ? T / 4 : T);
   }
   return e == hipSuccess ? launch_conv_dma(s, c) : e;

@@ -182,6 +182,7 @@ lc_status conv(lc_decoder* d, const DPlan& p, const ConvP& w, int src, int Cin, 
   f.w_frags = w.wf; f.xact = act; f.xact_bytes = act_bytes;
   f.dt = d->cfg.dtype; f.y_f32 = y16 ? 0 : 1; f.taps = 9; f.src = src; f.Cin = Cin; f.Cout = Cout; f.Cout_store = Cout;
   f.w = w.w; f.bias = w.b; f.frames = n; f.H = H; f.W = W; f.x = x; f.res = res; f.y = y; f.up2 = src < 2;
+  f.unit_scale = src == 1;  // (off_one, off_zero)
   f.scale = (const float*)(src == 2 ? d->lane + p.off_scale : d->arena + p.off_one);
   f.shift = (const float*)(src == 2 ? d->lane + p.off_shift : d->arena + p.off_zero);
   f.in_map = f.out_map = RowMap{0, 0, 1 << 30};

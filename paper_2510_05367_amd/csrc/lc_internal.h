@@ -75,7 +75,7 @@ struct FusedDesc {
   int y_f32;     // 1: y is an fp32 stream tensor; 0: y has the operand type
   int taps;      // 9: 3x3 conv over [frames][H][W][Cin]; 1: linear layer over rows
   int src;       // 0: x has the operand type, used as is
-                 // 1: x is fp32, x * scale[f][c] + shift[f][c] (GroupNorm apply; taps == 9: general kernel only)
+                 // 1: x is fp32, x * scale[f][c] + shift[f][c] (GroupNorm apply; taps == 9: see unit_scale)
                  // 2: the same followed by SiLU (taps == 9); taps == 1: x is a planar image
                  //    [frames][Cs][H][W] of the operand type and row r gathers the 3x3 neighbourhood of
                  //    pixel r, k = channel * 9 + tap (a first convolution as a linear layer; Cin = 64 >= 9 Cs)
@@ -90,6 +90,8 @@ struct FusedDesc {
   size_t xact_bytes;   // runs as an activation pass and launch_conv_dma. src 0 needs no scratch
   // taps == 9 through launch_conv_dma only: frame f of the launch takes bias + (bias_f0 + f) / bias_div * Cout (bias_div 0: bias)
   int bias_div, bias_f0;
+  int unit_scale;      // taps == 9, src == 1: scale is all ones and shift all zeros, the rows are only rounded. What the activation pass
+                       // of launch_conv_dma does then; without the flag such a convolution takes the general kernel
   const void* w_frag;  // taps == 1: the same matrix in MFMA fragment order (launch_pack_lin_w), or nullptr
   const float* bias;   // [Cout] or nullptr
   int frames, H, W;    // taps == 9
@@ -169,7 +171,7 @@ hipError_t launch_conv_ws(hipStream_t s, const FusedDesc& d);
 // x are those of the skip channels, x2 those of the deep ones at half the resolution. The same results as the kernels that
 // activate in their loader bit for bit; hipErrorNotSupported for shapes it does not cover.
 hipError_t launch_conv_dma(hipStream_t s, const FusedDesc& d);
-// src 1..3 with w_frags and xact: activation pass(es) into xact, then launch_conv_dma
+// src 1 (with unit_scale) .. 3 with w_frags and xact: activation pass(es) into xact, then launch_conv_dma
 hipError_t launch_conv_act_dma(hipStream_t s, const FusedDesc& d);
 inline size_t conv_act_bytes(const FusedDesc& d) {
   const size_t px = (size_t)d.frames * d.H * d.W;

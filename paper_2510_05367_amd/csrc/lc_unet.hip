@@ -430,6 +430,7 @@ lc_status conv(lc_unet* c, const ConvP& w, const float* bias, int src, int Cin, 
   f.dt = c->cfg.dtype; f.y_f32 = planar ? 0 : 1; f.taps = 9; f.src = src; f.Cin = Cin; f.Cout = Cout; f.Cout_store = Cout_store;
   f.w = w.w; f.bias = bias; f.frames = n; f.H = H; f.W = W; f.x = x; f.res = res; f.y = y; f.planar_out = planar;
   f.up2 = src == 1;
+  f.unit_scale = src == 1;  // (off_one, off_zero)
   f.scale = (const float*)(c->arena + (src == 2 ? p.off_scale : p.off_one)) + (size_t)f0 * Cin;
   f.shift = (const float*)(c->arena + (src == 2 ? p.off_shift : p.off_zero)) + (size_t)f0 * Cin;
   f.in_map = f.out_map = dense_map();
