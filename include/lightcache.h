@@ -190,10 +190,11 @@ lc_status lc_set_lanes(lc_ctx* ctx, int lanes);
 
 /* Kernel choice of the 3x3 convolutions of the shallow branch (residual blocks, up conv; the operations of
  * [FC] and of the residual blocks are the same either way). A bf16 stage activates the rows in a pass of its own and
- * contracts them in a kernel without loaders or, where the scratch has no room for the rows and C % 160 == 0, runs
- * one kernel whose wavefronts are specialised (loaders / contracting); general = 1 forces the general kernel, which
- * fp32 stages use anyway. All accumulate the same products in the same order: results are identical bit for bit
- * (this switch exists so that a test can say so).
+ * contracts them in a kernel without loaders. Under a spatial chunk, and in single-operator calls on more frames than the
+ * chunk scratch has room for, it runs one kernel whose wavefronts are specialised (loaders / contracting) where
+ * C % 160 == 0, else the general kernel; general = 1 forces the general kernel, which fp32 stages use anyway. All
+ * accumulate the same products in the same order: results are identical bit for bit (this switch exists so that a test can
+ * say so).
  * Default 0. LC_ERR_ARG unless general is 0 or 1. */
 lc_status lc_set_conv_general(lc_ctx* ctx, int general);
 

@@ -51,8 +51,7 @@ struct Plan {
 };
 
 struct GnW { float *gamma, *beta; };
-// wt: tile order for the specialised conv kernel, wf: fragment order for the one over activated rows, or nullptr
-struct ConvW { void* w; float* b; void *wt, *wf; };
+struct ConvW { void* w; float* b; };  // w of the 3x3 stride-1 convolutions of a bf16 stage (not `out`): in fragment order
 struct AttnW { GnW gn; void* wqkv; void* wo; float* bo; void* wqkv_f; void* wo_f; };  // *_f: fragment order
 struct Packed {
   float* cin_w; float* cin_b;
@@ -75,7 +74,7 @@ struct lc_ctx {
   hipStream_t cs_main, cs_aux[kMaxLanes - 1];  // the caller's compute stream; the library's own further ones
   hipEvent_t ev_fork, ev_join[kMaxLanes - 1];
   int lanes;                     // 1 or 2: streams a chunked step spreads its chunks over
-  bool conv_general;             // lc_set_conv_general: the specialised-wavefront conv kernel is not used
+  bool conv_general;             // lc_set_conv_general: the 3x3 convolutions take the general kernel
   int lane;                      // the lane in use: selects cs and the per-lane scratch
   bool forked;
   int device;
@@ -395,7 +394,7 @@ FusedDesc fconv_desc(lc_ctx* c, const ConvW& w, int Cin, int Cout, int frames, i
   FusedDesc d;
   memset(&d, 0, sizeof d);
   d.dt = c->cfg.dtype; d.y_f32 = y_f32; d.taps = 9; d.src = 2; d.Cin = Cin; d.Cout = Cout; d.Cout_store = Cout;
-  d.w = w.w; d.w_tiles = c->conv_general ? nullptr : w.wt; d.w_frags = c->conv_general ? nullptr : w.wf; d.bias = w.b; d.frames = frames; d.H = H; d.W = W; d.x = x; d.scale = scale_p(c); d.shift = shift_p(c);
+  d.w = w.w; d.general = c->conv_general; d.bias = w.b; d.frames = frames; d.H = H; d.W = W; d.x = x; d.scale = scale_p(c); d.shift = shift_p(c);
   d.res = res; d.y = y; d.in_map = dense_map(); d.out_map = dense_map();
   return d;
 }
@@ -1025,21 +1024,6 @@ lc_status lc_load_weights(lc_ctx* c, const lc_weights* w) {
     o_res_g[i] = take((size_t)C * 4); o_res_b[i] = take((size_t)C * 4);
     o_res_w[i] = take((size_t)C * 9 * C * es); o_res_bias[i] = take((size_t)C * 4);
   }
-  // a second copy of the big 3x3 weights in the tile order the specialised-wavefront kernel streams
-  const bool tiles = dt == kBF16 && C % 160 == 0 && C % 64 == 0 && (C + Cd) % 64 == 0;
-  size_t o_res_wt[LC_MAX_RES] = {0}, o_up_wt = 0;
-  if (tiles) {
-    for (int i = 0; i < g.n_res; ++i) o_res_wt[i] = take((size_t)C * 9 * C * es);
-    o_up_wt = take((size_t)C * 9 * (C + Cd) * es);
-  }
-  // and one in the fragment order of the kernel that contracts activated rows (the deep stand-in's too)
-  const bool frags = dt == kBF16 && C % 64 == 0 && Cd % 64 == 0;
-  size_t o_res_wf[LC_MAX_RES] = {0}, o_up_wf = 0, o_dres_wf = 0;
-  if (frags) {
-    for (int i = 0; i < g.n_res; ++i) o_res_wf[i] = take((size_t)C * 9 * C * es);
-    o_up_wf = take((size_t)C * 9 * (C + Cd) * es);
-    o_dres_wf = take((size_t)Cd * 9 * Cd * es);
-  }
   size_t o_at[2][7];
   for (int k = 0; k < 2; ++k) {
     o_at[k][0] = take((size_t)C * 4); o_at[k][1] = take((size_t)C * 4);
@@ -1064,6 +1048,9 @@ lc_status lc_load_weights(lc_ctx* c, const lc_weights* w) {
   hipStream_t s = c->cs;
 #define F32(src, dst_off, n, npad) LC_HIP(c, launch_to_f32(s, dt, src, (float*)(b + dst_off), n, npad))
 #define CW(src, dst_off, co, ci, taps, copad) LC_HIP(c, launch_pack_conv_w(s, dt, src, b + dst_off, co, ci, taps, copad))
+  // the 3x3 stride-1 convolutions: bf16 weights in the fragment order that all their kernels read
+#define CF(src, dst_off, co, ci)                                                                  \
+  LC_HIP(c, dt == kBF16 ? launch_pack_conv_w_frags(s, dt, src, b + dst_off, co, ci) : launch_pack_conv_w(s, dt, src, b + dst_off, co, ci, 9, co))
   LC_HIP(c, launch_pack_conv_in_w(s, dt, w->conv_in_w, (float*)(b + o_cin_w), C, Cl));
   F32(w->conv_in_b, o_cin_b, C, C);
   p.cin_w = (float*)(b + o_cin_w); p.cin_b = (float*)(b + o_cin_b);
@@ -1075,17 +1062,9 @@ lc_status lc_load_weights(lc_ctx* c, const lc_weights* w) {
   }
   for (int i = 0; i < g.n_res; ++i) {
     F32(w->res[i].gn_g, o_res_g[i], C, C); F32(w->res[i].gn_b, o_res_b[i], C, C);
-    CW(w->res[i].w, o_res_w[i], C, C, 9, C); F32(w->res[i].b, o_res_bias[i], C, C);
+    CF(w->res[i].w, o_res_w[i], C, C); F32(w->res[i].b, o_res_bias[i], C, C);
     p.res_gn[i] = GnW{(float*)(b + o_res_g[i]), (float*)(b + o_res_b[i])};
-    p.res[i] = ConvW{b + o_res_w[i], (float*)(b + o_res_bias[i]), nullptr, nullptr};
-    if (tiles) {
-      LC_HIP(c, launch_pack_conv_w_tiles(s, dt, b + o_res_w[i], b + o_res_wt[i], C, C));
-      p.res[i].wt = b + o_res_wt[i];
-    }
-    if (frags) {
-      LC_HIP(c, launch_pack_conv_w_frags(s, dt, b + o_res_w[i], b + o_res_wf[i], C, C));
-      p.res[i].wf = b + o_res_wf[i];
-    }
+    p.res[i] = ConvW{b + o_res_w[i], (float*)(b + o_res_bias[i])};
   }
   const lc_attn_w* aw[2] = {&w->sattn, &w->tattn};
   AttnW* ap[2] = {&p.sattn, &p.tattn};
@@ -1103,30 +1082,22 @@ lc_status lc_load_weights(lc_ctx* c, const lc_weights* w) {
                    (float*)(b + o_at[k][4]), b + o_at[k][5], b + o_at[k][6]};
   }
   CW(w->down_w, o_down_w, Cd, C, 9, Cd); F32(w->down_b, o_down_b, Cd, Cd);
-  p.down = ConvW{b + o_down_w, (float*)(b + o_down_b), nullptr, nullptr};
+  p.down = ConvW{b + o_down_w, (float*)(b + o_down_b)};
   F32(w->dres.gn_g, o_dres_g, Cd, Cd); F32(w->dres.gn_b, o_dres_b, Cd, Cd);
-  CW(w->dres.w, o_dres_w, Cd, Cd, 9, Cd); F32(w->dres.b, o_dres_bias, Cd, Cd);
+  CF(w->dres.w, o_dres_w, Cd, Cd); F32(w->dres.b, o_dres_bias, Cd, Cd);
   p.dres_gn = GnW{(float*)(b + o_dres_g), (float*)(b + o_dres_b)};
-  p.dres = ConvW{b + o_dres_w, (float*)(b + o_dres_bias), nullptr, nullptr};
+  p.dres = ConvW{b + o_dres_w, (float*)(b + o_dres_bias)};
   F32(w->up.gn_g, o_up_g, C + Cd, C + Cd); F32(w->up.gn_b, o_up_b, C + Cd, C + Cd);
-  CW(w->up.w, o_up_w, C, C + Cd, 9, C); F32(w->up.b, o_up_bias, C, C);
+  CF(w->up.w, o_up_w, C, C + Cd); F32(w->up.b, o_up_bias, C, C);
   p.up_gn = GnW{(float*)(b + o_up_g), (float*)(b + o_up_b)};
-  p.up = ConvW{b + o_up_w, (float*)(b + o_up_bias), nullptr, nullptr};
-  if (tiles) {
-    LC_HIP(c, launch_pack_conv_w_tiles(s, dt, b + o_up_w, b + o_up_wt, C, C + Cd));
-    p.up.wt = b + o_up_wt;
-  }
-  if (frags) {
-    LC_HIP(c, launch_pack_conv_w_frags(s, dt, b + o_up_w, b + o_up_wf, C, C + Cd));
-    LC_HIP(c, launch_pack_conv_w_frags(s, dt, b + o_dres_w, b + o_dres_wf, Cd, Cd));
-    p.up.wf = b + o_up_wf; p.dres.wf = b + o_dres_wf;
-  }
+  p.up = ConvW{b + o_up_w, (float*)(b + o_up_bias)};
   F32(w->out.gn_g, o_out_g, C, C); F32(w->out.gn_b, o_out_b, C, C);
   CW(w->out.w, o_out_w, Cl, C, 9, 32); F32(w->out.b, o_out_bias, Cl, 32);
   p.out_gn = GnW{(float*)(b + o_out_g), (float*)(b + o_out_b)};
-  p.out = ConvW{b + o_out_w, (float*)(b + o_out_bias), nullptr, nullptr};
+  p.out = ConvW{b + o_out_w, (float*)(b + o_out_bias)};
 #undef F32
 #undef CW
+#undef CF
   LC_HIP(c, hipStreamSynchronize(s));
   c->have_weights = true;
   c->st.weight_bytes = off;

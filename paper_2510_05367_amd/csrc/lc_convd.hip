@@ -405,7 +405,7 @@ static int conv_dma_tiles(int64_t ntiles, int ct) {
 }
 
 hipError_t launch_conv_dma(hipStream_t s, const FusedDesc& d) {
-  if (d.dt != kBF16 || d.taps != 9 || (d.src != 0 && d.src != 3) || d.planar_out || d.yt || d.q_cols || d.win_w || !d.w_frags)
+  if (d.dt != kBF16 || d.taps != 9 || (d.src != 0 && d.src != 3) || d.planar_out || d.yt || d.q_cols || d.win_w || d.general)
     return hipErrorNotSupported;
   if (d.Cin % 64 || d.Cout % 64 || d.Cout_store != d.Cout || d.Cin <= 0 || d.Cout <= 0) return hipErrorNotSupported;
   if (d.src == 3 && (d.up2 || d.Cs % 64 || d.Cs <= 0 || d.Cs >= d.Cin || ((d.H | d.W) & 1))) return hipErrorInvalidValue;
@@ -417,7 +417,7 @@ hipError_t launch_conv_dma(hipStream_t s, const FusedDesc& d) {
   if ((int64_t)d.H * d.W * d.Cin * 2 >= (int64_t)1 << 31 || (int64_t)d.Cout * 9 * d.Cin * 2 >= (int64_t)1 << 31) return hipErrorNotSupported;
   if (d.frames <= 0) return hipSuccess;
   ConvDArgs a;
-  a.x = (const bf16_t*)d.x; a.x2 = (const bf16_t*)d.x2; a.w = (const bf16_t*)d.w_frags; a.bias = d.bias; a.res = (const float*)d.res; a.y = d.y;
+  a.x = (const bf16_t*)d.x; a.x2 = (const bf16_t*)d.x2; a.w = (const bf16_t*)d.w; a.bias = d.bias; a.res = (const float*)d.res; a.y = d.y;
   a.Cin = d.Cin; a.Cs = d.src == 3 ? d.Cs : d.Cin; a.Cout = d.Cout; a.up = d.up2;
   a.bias_div = d.bias_div ? d.bias_div : 1 << 30; a.bias_f0 = d.bias_div ? d.bias_f0 : 0;
   a.H = d.H; a.W = d.W; a.tiles_x = (d.W + 15) / 16; a.tiles_y = (d.H + 7) / 8;

@@ -41,7 +41,7 @@ struct WsArgs {
   const bf16_t* x2;     // concat: cached deep feature [frames][H/2][W/2][Cin - Cs]
   const float* scale;   // [frames][Cin]
   const float* shift;
-  const bf16_t* w;      // tiles [Cout / 160][9 * Cin / 64][160][64]: one step's block is contiguous
+  const bf16_t* w;      // in the order of launch_pack_conv_w_frags
   const float* bias;    // [Cout] or nullptr
   const float* res;     // fp32, indexed like y, or nullptr
   float* y;             // fp32 [frames][H][W][Cout]
@@ -219,31 +219,20 @@ __global__ __launch_bounds__(512) void conv_ws_kernel(WsArgs a) {
   const int xr1 = (p1 >> 4) * kwHaloW + (p1 & 15);
   const int xoff0 = xr0 * kwLds + hh * 16 + kh * (KI / 2) * KB;
   const int xoff1 = xr1 * kwLds + hh * 16 + kh * (KI / 2) * KB;
-  const int wkey = (lp >> 1) & 7;  // slot swizzle of this lane's weight rows (32 i does not change it)
-  int wofs[KI / 2];
-#pragma unroll
-  for (int kk = 0; kk < KI / 2; ++kk) {
-    const int wb = hh * 16 + (kh * (KI / 2) + kk) * KB;
-    wofs[kk] = lp * kwRow + ((((wb >> 4) ^ wkey) << 4) | (wb & 15));
-  }
   // weights: global -> LDS directly, kwAhead steps ahead, requested by the contracting wavefronts themselves
   // (their stream has room between the MFMAs, and the loaders then never wait for memory on the
-  // contracting wavefronts' behalf). A wavefront instruction moves 8 rows x 128 bytes; packet c of row r is
-  // parked in slot c ^ ((r >> 1) & 7) of that row (conflict-free fragment reads without padding).
-  // Instruction i covers rows (4 i + wid) * 8 ..+7 (1 KB of contiguous memory in the tile order of the
-  // weights); the slot key does not depend on i.
-  const int l8 = lane >> 3;
-  const int wr0 = wid * 8 + l8;
-  const int wc = (lane & 7) ^ ((wr0 >> 1) & 7);
-  const bf16_t* __restrict__ wsrc = a.w + ((int64_t)blockIdx.y * (9 * nslab) * BCO + wr0) * 64 + wc * 8;
+  // contracting wavefronts' behalf). A step's tile is 4 CO_T fragments of 1 KB, in LDS as in memory: [k-step][half of the
+  // slab][channel tile]; a wavefront moves those of one k-step and half, and a fragment is read in one piece.
+  const int ct = a.Cout >> 5;  // channel tiles
+  const bf16_t* __restrict__ wsrc = a.w + ((int64_t)wid * ct + blockIdx.y * CO_T) * 512 + lane * 8;
   auto dma_w_one = [&](const bf16_t* src, unsigned char* tile, int i) {  // instruction i of the WP that move one tile
 #ifdef __HIP_DEVICE_COMPILE__  // the host pass only needs the kernel's stub; it does not know this builtin
-    __builtin_amdgcn_global_load_lds(src + i * 32 * 64, tile + (i * 4 + wid) * 1024, 16, 0, 0);
+    __builtin_amdgcn_global_load_lds(src + i * 512, tile + (wid * CO_T + i) * 1024, 16, 0, 0);
 #else
     (void)src; (void)tile;
 #endif
   };
-  auto w_src = [&](int step) { return wsrc + (int64_t)step * (BCO * 64); };
+  auto w_src = [&](int step) { return wsrc + (int64_t)step * (4 * ct * 512); };
   // at most `VM` vector-memory operations outstanding; LDS reads are not waited for
   auto wait_vm = [&](auto vm_c) {
     constexpr int VM = decltype(vm_c)::value;
@@ -263,7 +252,7 @@ __global__ __launch_bounds__(512) void conv_ws_kernel(WsArgs a) {
   };
   auto wload = [&](const unsigned char* wl, int idx) {
     const int kk = idx / CO_T, i = idx - kk * CO_T;
-    return M::load((const bf16_t*)(wl + i * 32 * kwRow + wofs[kk]));
+    return M::load((const bf16_t*)(wl + ((kk * 2 + kh) * CO_T + i) * 1024 + lane * 16));
   };
   // one step: `wl` / `wl_next` the weight tiles of this and the next step, `xbuf_next` / `tap_next` where the
   // next step reads its activations
@@ -460,7 +449,7 @@ static hipError_t run_ws(hipStream_t s, const FusedDesc& d) {
   }
   WsArgs a;
   a.x = (const float*)d.x; a.x2 = (const bf16_t*)d.x2; a.scale = d.scale; a.shift = d.shift;
-  a.w = (const bf16_t*)d.w_tiles; a.bias = d.bias; a.res = (const float*)d.res; a.y = (float*)d.y;
+  a.w = (const bf16_t*)d.w; a.bias = d.bias; a.res = (const float*)d.res; a.y = (float*)d.y;
   a.Cin = d.Cin; a.Cs = d.Cs; a.Cout = d.Cout;
   a.H = d.H; a.W = d.W; a.tiles_x = (d.W + 15) / 16; a.tiles_y = (d.H + 7) / 8;
   a.stat = d.stat; a.stat_splits = d.stat_splits;
@@ -473,7 +462,7 @@ static hipError_t run_ws(hipStream_t s, const FusedDesc& d) {
 // The 3x3 convolutions of a bf16 stage whose widths suit the kernel above (a property of the stage,
 // never of how it is chunked); hipErrorNotSupported otherwise.
 hipError_t launch_conv_ws(hipStream_t s, const FusedDesc& d) {
-  if (d.dt != kBF16 || d.taps != 9 || !d.y_f32 || d.planar_out || d.yt || d.q_cols || !d.w_tiles) return hipErrorNotSupported;
+  if (d.dt != kBF16 || d.taps != 9 || !d.y_f32 || d.planar_out || d.yt || d.q_cols || d.general) return hipErrorNotSupported;
   if (d.src != 2 && d.src != 3) return hipErrorNotSupported;
   if (d.Cout % 160 != 0 || d.Cout_store != d.Cout || d.Cin % 64 != 0) return hipErrorNotSupported;
   if (d.src == 3 && (d.Cs % 64 != 0 || d.Cs <= 0 || d.Cs >= d.Cin || ((d.H | d.W) & 1))) return hipErrorNotSupported;

@@ -24,7 +24,7 @@ constexpr size_t kAlign = 256;
 inline size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 
 struct GnP { float *g, *b; };
-struct ConvP { void* w; float* b; void* wf; };  // wf: fragment order for the kernel over activated rows, or nullptr
+struct ConvP { void* w; float* b; };  // w of a bf16 decoder (not `out`): in fragment order
 
 struct DPlan {
   size_t off_a, off_b, off_part, off_scale, off_shift, off_one, off_zero, off_qkv, off_vt, off_ao, total;
@@ -179,7 +179,7 @@ lc_status conv(lc_decoder* d, const DPlan& p, const ConvP& w, int src, int Cin, 
                const float* res, void* y, Stats* st, void* act = nullptr, size_t act_bytes = 0, bool y16 = false) {
   FusedDesc f;
   memset(&f, 0, sizeof f);
-  f.w_frags = w.wf; f.xact = act; f.xact_bytes = act_bytes;
+  f.xact = act; f.xact_bytes = act_bytes;
   f.dt = d->cfg.dtype; f.y_f32 = y16 ? 0 : 1; f.taps = 9; f.src = src; f.Cin = Cin; f.Cout = Cout; f.Cout_store = Cout;
   f.w = w.w; f.bias = w.b; f.frames = n; f.H = H; f.W = W; f.x = x; f.res = res; f.y = y; f.up2 = src < 2;
   f.unit_scale = src == 1;  // (off_one, off_zero)
@@ -196,7 +196,7 @@ lc_status conv(lc_decoder* d, const DPlan& p, const ConvP& w, int src, int Cin, 
 bool conv_covered(lc_decoder* d, const ConvP& w, int Cin, int Cout, int H, int W, bool up2) {
   FusedDesc f;
   memset(&f, 0, sizeof f);
-  f.dt = d->cfg.dtype; f.taps = 9; f.Cin = Cin; f.Cout = Cout; f.Cout_store = Cout; f.w_frags = w.wf; f.H = H; f.W = W; f.up2 = up2;
+  f.dt = d->cfg.dtype; f.taps = 9; f.Cin = Cin; f.Cout = Cout; f.Cout_store = Cout; f.H = H; f.W = W; f.up2 = up2;
   return launch_conv_dma(d->s, f) == hipSuccess;  // (no frames: nothing is launched)
 }
 
@@ -368,13 +368,6 @@ lc_status lc_decoder_load_weights(lc_decoder* d, const lc_decoder_weights* w) {
     const int C = i < 2 ? C0 : g.widths[i - 2];
     o_rg[i] = take((size_t)C * 4); o_rb[i] = take((size_t)C * 4); o_rw[i] = take((size_t)C * 9 * C * es); o_rbias[i] = take((size_t)C * 4);
   }
-  // the 3x3 weights once more in the fragment order of the kernel that contracts activated rows
-  const bool frags = dt == kBF16;
-  size_t o_rf[2 + LC_DEC_MAX_LEVELS] = {0}, o_uf[LC_DEC_MAX_LEVELS] = {0};
-  if (frags) {
-    for (int i = 0; i < 2 + L; ++i) { const int C = i < 2 ? C0 : g.widths[i - 2]; o_rf[i] = take((size_t)C * 9 * C * es); }
-    for (int l = 0; l < L; ++l) o_uf[l] = take((size_t)g.widths[l + 1] * 9 * g.widths[l] * es);
-  }
   const size_t o_ag = take((size_t)C0 * 4), o_ab = take((size_t)C0 * 4), o_aqkv = take((size_t)3 * C0 * C0 * es),
                o_awo = take((size_t)C0 * C0 * es), o_abo = take((size_t)C0 * 4);
   size_t o_uw[LC_DEC_MAX_LEVELS], o_ub[LC_DEC_MAX_LEVELS];
@@ -389,7 +382,9 @@ lc_status lc_decoder_load_weights(lc_decoder* d, const lc_decoder_weights* w) {
   char* b = (char*)blob;
   hipStream_t s = d->s;
 #define F32(src, dst_off, n, npad) LCD_HIP(d, launch_to_f32(s, dt, src, (float*)(b + dst_off), n, npad))
-#define CW(src, dst_off, co, ci, copad) LCD_HIP(d, launch_pack_conv_w(s, dt, src, b + dst_off, co, ci, 9, copad))
+  // bf16: the fragment order that all kernels of the 3x3 convolutions read
+#define CF(src, dst_off, co, ci)                                                                  \
+  LCD_HIP(d, dt == kBF16 ? launch_pack_conv_w_frags(s, dt, src, b + dst_off, co, ci) : launch_pack_conv_w(s, dt, src, b + dst_off, co, ci, 9, co))
   LCD_HIP(d, launch_pack_conv_in_w(s, dt, w->conv_in_w, (float*)(b + o_cin_w), C0, g.C_lat));
   F32(w->conv_in_b, o_cin_b, C0, C0);
   d->cin_w = (float*)(b + o_cin_w); d->cin_b = (float*)(b + o_cin_b); d->cin_wp = nullptr;
@@ -400,13 +395,9 @@ lc_status lc_decoder_load_weights(lc_decoder* d, const lc_decoder_weights* w) {
   for (int i = 0; i < 2 + L; ++i) {
     const int C = i < 2 ? C0 : g.widths[i - 2];
     const lc_gnconv_w& r = i < 2 ? w->mid_res[i] : w->up_res[i - 2];
-    F32(r.gn_g, o_rg[i], C, C); F32(r.gn_b, o_rb[i], C, C); CW(r.w, o_rw[i], C, C, C); F32(r.b, o_rbias[i], C, C);
+    F32(r.gn_g, o_rg[i], C, C); F32(r.gn_b, o_rb[i], C, C); CF(r.w, o_rw[i], C, C); F32(r.b, o_rbias[i], C, C);
     d->res_gn[i] = GnP{(float*)(b + o_rg[i]), (float*)(b + o_rb[i])};
-    d->res[i] = ConvP{b + o_rw[i], (float*)(b + o_rbias[i]), nullptr};
-    if (frags) {
-      LCD_HIP(d, launch_pack_conv_w_frags(s, dt, b + o_rw[i], b + o_rf[i], C, C));
-      d->res[i].wf = b + o_rf[i];
-    }
+    d->res[i] = ConvP{b + o_rw[i], (float*)(b + o_rbias[i])};
   }
   F32(w->mid_attn.gn_g, o_ag, C0, C0); F32(w->mid_attn.gn_b, o_ab, C0, C0);
   LCD_HIP(d, launch_copy_rows(s, dt, w->mid_attn.wq, b + o_aqkv, (int64_t)C0 * C0));
@@ -417,20 +408,16 @@ lc_status lc_decoder_load_weights(lc_decoder* d, const lc_decoder_weights* w) {
   d->at_gn = GnP{(float*)(b + o_ag), (float*)(b + o_ab)};
   d->at_wqkv = b + o_aqkv; d->at_wo = b + o_awo; d->at_bo = (float*)(b + o_abo);
   for (int l = 0; l < L; ++l) {
-    CW(w->up_conv_w[l], o_uw[l], g.widths[l + 1], g.widths[l], g.widths[l + 1]);
+    CF(w->up_conv_w[l], o_uw[l], g.widths[l + 1], g.widths[l]);
     F32(w->up_conv_b[l], o_ub[l], g.widths[l + 1], g.widths[l + 1]);
-    d->upc[l] = ConvP{b + o_uw[l], (float*)(b + o_ub[l]), nullptr};
-    if (frags) {
-      LCD_HIP(d, launch_pack_conv_w_frags(s, dt, b + o_uw[l], b + o_uf[l], g.widths[l + 1], g.widths[l]));
-      d->upc[l].wf = b + o_uf[l];
-    }
+    d->upc[l] = ConvP{b + o_uw[l], (float*)(b + o_ub[l])};
   }
   F32(w->out.gn_g, o_og, CL, CL); F32(w->out.gn_b, o_ob, CL, CL);
-  CW(w->out.w, o_ow, g.C_img, CL, 32); F32(w->out.b, o_obias, g.C_img, 32);
+  LCD_HIP(d, launch_pack_conv_w(s, dt, w->out.w, b + o_ow, g.C_img, CL, 9, 32)); F32(w->out.b, o_obias, g.C_img, 32);
   d->out_gn = GnP{(float*)(b + o_og), (float*)(b + o_ob)};
-  d->out = ConvP{b + o_ow, (float*)(b + o_obias), nullptr};
+  d->out = ConvP{b + o_ow, (float*)(b + o_obias)};
 #undef F32
-#undef CW
+#undef CF
   LCD_HIP(d, hipStreamSynchronize(s));
   d->have_weights = true;
   return LC_OK;

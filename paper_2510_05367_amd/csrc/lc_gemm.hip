@@ -39,7 +39,7 @@ struct GemmArgs {
   const void* x2;       // CAT: deep, T [frames][H/2][W/2][Cin - Cs]
   const float* scale;   // [frames][Cin]
   const float* shift;
-  const void* w;        // T [Cout][taps * Cin]
+  const void* w;        // T [Cout][taps * Cin]; conv of bf16, not planar: in the order of launch_pack_conv_w_frags
   const float* bias;
   const float* res;     // fp32, indexed like y (may alias y)
   void* y;
@@ -126,17 +126,20 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmArgs a) {
   const int kp = tid & 7, lrow = tid >> 3;  // this thread moves packet kp of rows lrow + 32 * i
 
   // ---------------- weights of a later step ----------------
-  // conv: global -> LDS directly, two steps ahead, into the tile that was read one step ago. A
+  // conv: global -> LDS directly, two steps ahead, into the tile that was read one step ago. Weights in rows: a
   // wavefront instruction moves 8 rows x 128 bytes; the 16-byte packet c of row r is parked in slot
   // c ^ ((r >> 1) & 7) of that row, which makes the MFMA fragment reads (32 consecutive rows, one
-  // slot) conflict-free without padding. linear: global -> registers -> padded LDS tile, one step ahead.
+  // slot) conflict-free without padding. Weights in fragment order: it moves a fragment, 1 KB, which lies in the tile as it
+  // lies in memory and is read in one piece. linear: global -> registers -> padded LDS tile, one step ahead.
   static_assert(TAPS != 9 || (BCO * 8) % 256 == 0, "whole wavefront instructions");
+  constexpr bool FRAGS = TAPS == 9 && sizeof(T) == 2 && !PLANAR;  // the weights lie in fragment order
   auto dma_w_one = [&](int step, int buf, int i) {  // instruction i of the WP that move one tile
     const int slab = step / TAPS, tap = step - slab * TAPS;
-    const int grp = i * 4 + wid;  // 8 rows
+    const int grp = FRAGS ? wid * CO_T + i : i * 4 + wid;  // fragment ([k-step and half][channel tile]), or 8 rows
     const int r = grp * 8 + (lane >> 3);
     const int c = (lane & 7) ^ ((r >> 1) & 7);
-    const T* src = Wt + (int64_t)(co0 + r) * a.ldw + tap * a.Cin + slab * BKC + c * VEC;
+    const T* src = FRAGS ? Wt + (((int64_t)step * 4 + wid) * (a.Cout >> 5) + (co0 >> 5) + i) * 512 + lane * 8
+                         : Wt + (int64_t)(co0 + r) * a.ldw + tap * a.Cin + slab * BKC + c * VEC;
 #ifdef __HIP_DEVICE_COMPILE__  // the host pass only needs the kernel's stub; it does not know this builtin
     __builtin_amdgcn_global_load_lds(src, w_lds(buf) + grp * 1024, 16, 0, 0);
 #else
@@ -281,6 +284,7 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmArgs a) {
     const int wkey = TAPS == 9 ? (lp >> 1) & 7 : 0;  // slot swizzle of this lane's rows (32 i does not change it)
     auto wload = [&](int idx) {
       const int kk = idx / CO_T, i = idx - kk * CO_T;
+      if constexpr (FRAGS) return M::load((const T*)(w_lds(wbuf) + ((kk * 2 + kh) * CO_T + i) * 1024 + lane * 16));
       const int wb = hh * LKB + (kh * (KI / 2) + kk) * KB;  // byte of the fragment inside the row
       const int wofs = (((wb >> 4) ^ wkey) << 4) | (wb & 15);
       return M::load((const T*)(wl + i * 32 * wstride + wofs));
@@ -718,10 +722,10 @@ hipError_t launch_fused(hipStream_t s, const FusedDesc& d) {
   if (d.up2 && (d.taps != 9 || d.src > 1 || ((d.H | d.W) & 1))) return hipErrorInvalidValue;
   if (d.src == 3 && (d.Cs % (kRow / esz) != 0 || d.Cs <= 0 || d.Cs >= d.Cin || (d.H | d.W) & 1)) return hipErrorInvalidValue;
   if (d.taps == 9) {
-    // an activation pass and the kernel without loaders where there is room for the activated rows; else the kernel with
-    // specialised wavefronts where the stage's widths suit it. All agree bit for bit. (at 32 frames of 64 x 64, 320 channels:
-    // residual convolution 343 us with specialised wavefronts, 37 + 225 here; up convolution 848 and 52 + 556)
-    hipError_t e = d.w_frags ? (d.src ? launch_conv_act_dma(s, d) : launch_conv_dma(s, d)) : hipErrorNotSupported;
+    // an activation pass and the kernel without loaders where whole frames are wanted and there is room for the activated rows; else
+    // the kernel with specialised wavefronts where the stage's widths suit it. All agree bit for bit. (at 32 frames of 64 x 64,
+    // 320 channels: residual convolution 343 us with specialised wavefronts, 37 + 225 here; up convolution 848 and 52 + 556)
+    hipError_t e = d.src ? launch_conv_act_dma(s, d) : launch_conv_dma(s, d);
     if (e != hipErrorNotSupported) return e;
     if (d.bias_div || d.src == 0) return hipErrorInvalidValue;  // only that kernel has a bias per frame and takes rows as they are
     e = launch_conv_ws(s, d);

@@ -82,12 +82,10 @@ struct FusedDesc {
                  // 3: channels [0,Cs) from the fp32 skip x, [Cs,Cin) from x2 (operand type, half
                  //    resolution, nearest 2x upsampled), then as 2
   int Cin, Cs, Cout, Cout_store;
-  const void* w;       // [Cout][taps*Cin]
-  const void* w_tiles; // taps == 9, optional: the same weights in the order of launch_pack_conv_w_tiles (what the
-                       // specialised-wavefront kernel reads; without it the general kernel runs)
-  const void* w_frags; // taps == 9, optional: the same weights in the order of launch_pack_conv_w_frags, and ...
-  void* xact;          // ... xact_bytes of scratch for activated rows (conv_act_bytes): with both, a bf16 convolution of whole frames
-  size_t xact_bytes;   // runs as an activation pass and launch_conv_dma. src 0 needs no scratch
+  const void* w;       // [Cout][taps*Cin]; taps == 9 of a bf16 stage, not planar_out: in the order of launch_pack_conv_w_frags
+  int general;         // taps == 9: the general kernel runs, whatever else covers the launch
+  void* xact;          // taps == 9, optional: xact_bytes of scratch for activated rows (conv_act_bytes): with it, a bf16 convolution
+  size_t xact_bytes;   // of whole frames runs as an activation pass and launch_conv_dma. src 0 needs no scratch
   // taps == 9 through launch_conv_dma only: frame f of the launch takes bias + (bias_f0 + f) / bias_div * Cout (bias_div 0: bias)
   int bias_div, bias_f0;
   int unit_scale;      // taps == 9, src == 1: scale is all ones and shift all zeros, the rows are only rounded. What the activation pass
@@ -165,13 +163,14 @@ inline bool conv_window_tiles(const FusedDesc& d, int* tx0, int* ty0, int* ntx, 
 }
 hipError_t launch_fused(hipStream_t s, const FusedDesc& d);
 // taps == 9 of a bf16 stage with specialised wavefronts (lc_convws.hip): the same results as the general
-// kernel bit for bit; hipErrorNotSupported for shapes it does not cover. launch_fused takes it where the rows below have no room.
+// kernel bit for bit; hipErrorNotSupported for shapes it does not cover. launch_fused takes it for spatial windows, and where a
+// launch has no room for the rows below (single operators on more frames than the scratch was made for).
 hipError_t launch_conv_ws(hipStream_t s, const FusedDesc& d);
 // taps == 9, src == 0 of a bf16 stage: a convolution over rows that are activated and rounded already (lc_convd.hip). src == 3:
 // x are those of the skip channels, x2 those of the deep ones at half the resolution. The same results as the kernels that
 // activate in their loader bit for bit; hipErrorNotSupported for shapes it does not cover.
 hipError_t launch_conv_dma(hipStream_t s, const FusedDesc& d);
-// src 1 (with unit_scale) .. 3 with w_frags and xact: activation pass(es) into xact, then launch_conv_dma
+// src 1 (with unit_scale) .. 3 with xact: activation pass(es) into xact, then launch_conv_dma
 hipError_t launch_conv_act_dma(hipStream_t s, const FusedDesc& d);
 inline size_t conv_act_bytes(const FusedDesc& d) {
   const size_t px = (size_t)d.frames * d.H * d.W;
@@ -231,9 +230,7 @@ hipError_t launch_cl_to_planar(hipStream_t s, int dt, const void* src, void* dst
 hipError_t launch_pack_conv_w(hipStream_t s, int dt, const void* w, void* packed, int Cout, int Cin, int taps,
                               int Cout_padded);  // [Cout][Cin][taps] -> [Cout_padded][taps][Cin]
 hipError_t launch_pack_conv_in_w(hipStream_t s, int dt, const void* w, float* packed, int C, int Cl);
-// packed [Cout][9*Cin] -> tiles [Cout/160][9*Cin/64][160][64] (bf16; Cout % 160 == 0, Cin % 64 == 0)
-hipError_t launch_pack_conv_w_tiles(hipStream_t s, int dt, const void* w, void* tiles, int Cout, int Cin);
-// packed [Cout][9*Cin] -> MFMA fragments for launch_conv_dma (bf16; Cout % 32 == 0, Cin % 64 == 0)
+// w[Cout][Cin][3][3] -> MFMA fragments (bf16; Cout % 32 == 0, Cin % 64 == 0): the 3x3 stride-1 weights of a bf16 stage
 hipError_t launch_pack_conv_w_frags(hipStream_t s, int dt, const void* w, void* frags, int Cout, int Cin);
 // w[Cout][Cin] -> MFMA fragment order for launch_linear
 hipError_t launch_pack_lin_w(hipStream_t s, int dt, const void* w, void* out, int Cout, int Cin);

@@ -110,29 +110,7 @@ hipError_t launch_pack_conv_w(hipStream_t s, int dt, const void* w, void* packed
   return hipGetLastError();
 }
 
-// [Cout][9 * Cin] (tap-major rows, as launch_pack_conv_w writes them) -> tiles[Cout / 160][step][160][64],
-// step = slab * 9 + tap: the 160 x 64 block a workgroup of the specialised-wavefront conv kernel moves to LDS
-// in one step is then 20 KB of contiguous memory instead of 160 pieces of 128 bytes a whole row apart.
-__global__ void pack_conv_w_tiles_kernel(const bf16_t* __restrict__ w, bf16_t* __restrict__ tiles, int Cout, int Cin) {
-  const int64_t total = (int64_t)Cout * 9 * Cin;
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= total) return;
-  const int nsteps = 9 * (Cin / 64);
-  const int c = (int)(i % 64);
-  const int r = (int)((i / 64) % 160);
-  const int step = (int)((i / (64 * 160)) % nsteps);
-  const int cb = (int)(i / ((int64_t)64 * 160 * nsteps));
-  const int slab = step / 9, tap = step - slab * 9;
-  tiles[i] = w[(int64_t)(cb * 160 + r) * (9 * Cin) + tap * Cin + slab * 64 + c];
-}
-hipError_t launch_pack_conv_w_tiles(hipStream_t s, int dt, const void* w, void* tiles, int Cout, int Cin) {
-  if (dt != kBF16 || Cout % 160 != 0 || Cin % 64 != 0) return hipErrorInvalidValue;
-  const int64_t total = (int64_t)Cout * 9 * Cin;
-  pack_conv_w_tiles_kernel<<<(unsigned)((total + 255) / 256), 256, 0, s>>>((const bf16_t*)w, (bf16_t*)tiles, Cout, Cin);
-  return hipGetLastError();
-}
-
-// packed [Cout][9*Cin] -> MFMA fragments [Cin / 64][9][2][2][Cout / 32][64][8]: (slab, tap, k-step, half of the slab, channel tile,
+// w[Cout][Cin][3][3] -> MFMA fragments [Cin / 64][9][2][2][Cout / 32][64][8]: (slab, tap, k-step, half of the slab, channel tile,
 // lane, element); lane l holds channel l % 32 of the tile and input channels 8 * (l / 32) ..+7 of the 16 of half and k-step
 __global__ void pack_conv_w_frags_kernel(const bf16_t* __restrict__ w, bf16_t* __restrict__ frags, int Cout, int Cin) {
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
@@ -145,7 +123,7 @@ __global__ void pack_conv_w_frags_kernel(const bf16_t* __restrict__ w, bf16_t* _
   r >>= 2;
   const int tap = (int)(r % 9), slab = (int)(r / 9);
   const int co = tile * 32 + (l & 31), ci = slab * 64 + half * 32 + kk * 16 + (l >> 5) * 8 + e;
-  frags[i] = w[(int64_t)co * (9 * Cin) + tap * Cin + ci];
+  frags[i] = w[((int64_t)co * Cin + ci) * 9 + tap];
 }
 hipError_t launch_pack_conv_w_frags(hipStream_t s, int dt, const void* w, void* frags, int Cout, int Cin) {
   if (dt != kBF16 || Cout % 32 != 0 || Cin % 64 != 0) return hipErrorInvalidValue;

@@ -206,7 +206,7 @@ thread_local std::string g_uerr = "";
 constexpr size_t kAlign = 256;
 inline size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 
-struct ConvP { void *w, *wf; float* b; };            // packed [Cout][9][Cin], the same in fragment order (or nullptr), bias
+struct ConvP { void* w; float* b; };                 // packed [Cout][9][Cin] (stride 1 of a bf16 stage, not `out`: in fragment order), bias
 struct LinP { void* w; float* b; };                  // [Cout][Cin] operand type, fp32 bias (or nullptr)
 struct NormP { float *g, *b; };
 struct RbP { int cin, cout; NormP gn1, gn2; ConvP conv1, conv2; float *temb_w, *temb_b; LinP shortcut; };
@@ -425,7 +425,6 @@ lc_status conv(lc_unet* c, const ConvP& w, const float* bias, int src, int Cin, 
   const UPlan& p = c->plan;
   FusedDesc f;
   memset(&f, 0, sizeof f);
-  f.w_frags = w.wf;
   if (act) { f.xact = c->arena + p.off_xc; f.xact_bytes = p.xc_bytes; }
   f.dt = c->cfg.dtype; f.y_f32 = planar ? 0 : 1; f.taps = 9; f.src = src; f.Cin = Cin; f.Cout = Cout; f.Cout_store = Cout_store;
   f.w = w.w; f.bias = bias; f.frames = n; f.H = H; f.W = W; f.x = x; f.res = res; f.y = y; f.planar_out = planar;
@@ -554,7 +553,7 @@ lc_status res_block(lc_unet* c, const RbP& w, const void* temb, int level, const
     // read but the rounded copy, so the pass takes it from the two tensors and the fp32 concatenation exists nowhere.
     FusedDesc f1;
     memset(&f1, 0, sizeof f1);
-    f1.dt = g.dtype; f1.y_f32 = 1; f1.taps = 9; f1.Cin = w.cin; f1.Cout = w.cout; f1.Cout_store = w.cout; f1.w_frags = w.conv1.wf;
+    f1.dt = g.dtype; f1.y_f32 = 1; f1.taps = 9; f1.Cin = w.cin; f1.Cout = w.cout; f1.Cout_store = w.cout; f1.w = w.conv1.w;
     f1.H = H; f1.W = W; f1.x = xc; f1.y = h; f1.stat = part; f1.stat_splits = cs;
     f1.bias = tb; f1.bias_div = g.F; f1.bias_f0 = n0;  // the time embedding is one vector per batch element: its frames share a bias
     const bool rows16 = (!Cb || short16) && (size_t)nc * P * w.cin * 2 <= p.xc_bytes && launch_conv_dma(c->cs, f1) == hipSuccess;  // (no frames yet)
@@ -962,12 +961,7 @@ lc_status lc_unet_load_weights(lc_unet* c, const lc_unet_weights* w) {
   auto conv3 = [&](const void* wsrc, const void* bsrc, int cout, int cin, int cout_pad, bool frags) {
     ConvP q;
     q.w = take((size_t)cout_pad * 9 * cin * es);
-    if (fill) note(launch_pack_conv_w(s, dt, wsrc, q.w, cout, cin, 9, cout_pad));
-    q.wf = nullptr;
-    if (frags && dt == kBF16) {  // what the kernel over activated rows reads
-      q.wf = take((size_t)cout * 9 * cin * es);
-      if (fill) note(launch_pack_conv_w_frags(s, dt, q.w, q.wf, cout, cin));
-    }
+    if (fill) note(frags && dt == kBF16 ? launch_pack_conv_w_frags(s, dt, wsrc, q.w, cout, cin) : launch_pack_conv_w(s, dt, wsrc, q.w, cout, cin, 9, cout_pad));
     q.b = (float*)take((size_t)cout_pad * 4);
     if (fill) note(launch_to_f32(s, dt, bsrc, q.b, cout, cout_pad));
     return q;

@@ -22,7 +22,7 @@ int main() {
         FusedDesc d;
         memset(&d, 0, sizeof d);
         d.dt = kBF16; d.y_f32 = 1; d.taps = 9; d.src = src; d.Cin = 128; d.Cs = 64; d.Cout = 64; d.Cout_store = 64; d.H = 8; d.W = 16;
-        d.w = d.w_frags = d.x = d.x2 = room; d.y = room; d.scale = d.shift = (const float*)room; d.unit_scale = unit;
+        d.w = d.x = d.x2 = room; d.y = room; d.scale = d.shift = (const float*)room; d.unit_scale = unit;
         if (scratch) { d.xact = room; d.xact_bytes = sizeof room; }
         printf("%d %d %d %d\n", src, unit, scratch, launch_conv_act_dma(nullptr, d) == hipSuccess);
       }

@@ -338,9 +338,10 @@ def test_conv_out(st):
 
 
 def test_specialised_conv_equals_general_bitwise(st):
-    """The 3x3 convolutions of a bf16 stage with C % 160 == 0 run in the kernel with specialised wavefronts;
-    it accumulates the same products in the same order as the general kernel, so the two must agree bit for
-    bit (output and the GroupNorm partial sums it writes, seen through the next operator)."""
+    """The 3x3 convolutions of a bf16 stage run over activated rows where the scratch has room for them, as it has here
+    (the kernel with specialised wavefronts has tests of its own: test_gpu_conv_ws.py); they accumulate the same products in
+    the same order as the general kernel, so the two must agree bit for bit (output and the GroupNorm partial sums, seen
+    through the next operator)."""
     stage, cfg, w = st
     N, C, Cd, H, W = cfg.N, cfg.C, cfg.C_deep, cfg.H, cfg.W
     x = act(cfg, (N, C, H, W), 131, 1.5) + np.float32(0.25)
