@@ -667,8 +667,8 @@ def dit_record(lcb, torch, synth, steps=6):
     w = synth.make_dit_weights(cfg, 0)
     dit = lcb.Dit(cfg, w, host_slots=2, dev_slots=2)
     try:
-        # the record's own figures are taken with all tokens at once (at this size the token chunk saves 18 % of the
-        # workspace for more than twice the time: see the sweep below); the workspace holds any chunk setting
+        # the record's own figures are taken with all tokens at once (of this stack the MLP needs no memory beyond what attention
+        # has released: the token chunk changes neither workspace nor time, see the sweep below)
         dit.set_chunk(0)
         x = dit.to_device(synth.make_dit_hidden(cfg, 1))
         mod = dit.to_device(synth.make_dit_modulation(cfg, 2))
@@ -693,7 +693,7 @@ def dit_record(lcb, torch, synth, steps=6):
                "cache_step_tflops": round(cfg.cached_step_flops() / (ms_cached * 1e-3) / 1e12, 1),
                "entry_mb": round(lcb.lc_dit_entry_bytes(dit.ccfg) / 1e6, 1),
                "workspace_gb": round(lcb.lc_dit_workspace_bytes(dit.ccfg, 0) / 1e9, 4), "schedules": []}
-        # the token chunk trades workspace for launch size (results never change)
+        # where the MLP takes more memory than attention, the token chunk trades it for launch size (results never change)
         rec["token_chunks"] = []
         for chunk in (512, 1024, 2048, 4096, 0):
             dit.set_chunk(chunk)

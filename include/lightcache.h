@@ -380,9 +380,10 @@ lc_status lc_decoder_sync(lc_decoder* dec);
  * One block: h = LN(x) (1 + scale_msa) + shift_msa; x += gate_msa * (Attn(h) Wo^T + bo); h = LN(x) (1 + scale_mlp)
  * + shift_mlp; x += gate_mlp * (W2 gelu_tanh(W1 h + b1) + b2). LN: per token, biased variance, no affine; q,k,v
  * projections with bias; `heads` heads of `head_dim`, scale 1/sqrt(head_dim). The modulation vectors are inputs.
- * Feature chunk ([CHK]): the workspace has room for token_chunk of the B*T tokens of a step in the MLP beside what is held
- * for all tokens; a pass of LayerNorm / projections / MLP takes as many rows as fit into the workspace at the time, at
- * least token_chunk (it may run across batch elements: every row looks up its own modulation), the attention all. The
+ * Feature chunk ([CHK]): attention, its projections and the LayerNorm in front of them take all B*T tokens of a step at
+ * once. The MLP works in the memory that these then no longer need; what a pass over all rows would take beyond that, the
+ * workspace has in full without a chunk and by the share of token_chunk in the B*T tokens with one. A pass of the MLP takes
+ * as many rows as fit, at least token_chunk (it may run across batch elements: every row looks up its own modulation). The
  * chunk never changes results. Hidden states and modulation are float at the boundary;
  * weights have cfg dtype (bf16: MFMA operands bf16, accumulation and the residual stream fp32).
  * Requirements (else LC_ERR_SHAPE): sizes > 0; D a multiple of 64, <= 2048; heads * head_dim == D; head_dim in

@@ -126,6 +126,7 @@ struct BlkW { void *wqkv, *wo, *w1, *w2; float *bqkv, *bo, *b1, *b2; };
 struct TPlan {
   int tc;  // rows of the token chunk, of the B*T of a step
   size_t off_x, off_slots, slot_bytes, off_qkv, off_vt, off_ao, total;
+  int64_t step;  // rows of a pass of the MLP
 };
 
 }  // namespace
@@ -183,9 +184,19 @@ lc_status check_tcfg(lc_dit* c, const lc_dit_config* g) {
   return LC_OK;
 }
 
+// (bf16, widths of the streamed kernels: the gated sum in the projections' epilogues, and V^T from q,k,v's where rows come
+// in fours; the separate passes cost 16 + 16 + 14 us a block at 8192 rows x 1024, 13 % of it)
+inline bool gate_fused(const lc_dit_config& g) { return g.dtype == kBF16 && lin_gate_covers(g.D, g.D) && g.T >= 32; }
+// bytes of a row of the MLP: normalised, hidden, and the branch output where it exists
+inline size_t mlp_row_bytes(const lc_dit_config& g) {
+  return (size_t)(1 + g.mlp_ratio) * g.D * dtype_size(g.dtype) + (gate_fused(g) ? 0 : (size_t)g.D * 4);
+}
+
 // Arena: the fp32 hidden states, dev_slots Delta entries (fp32), q,k,v + V^T + attention output of ALL tokens (a
-// query chunk attends to every key), and room for the normalised rows, the MLP's hidden rows and a branch output of one
-// token chunk, which together with what is not needed at the time is what a pass works in (see run_block).
+// query chunk attends to every key). The MLP runs when none of the latter is needed any more, and works there (see
+// run_block): with all tokens at once the arena is as much longer as a pass over all rows needs, with a token chunk by the
+// chunk's share of that. A pass then has room for the chunk in any case: what is held for all tokens covers at least its share
+// of the rest.
 TPlan make_tplan(const lc_dit_config& g, int token_chunk) {
   TPlan p;
   const size_t es = dtype_size(g.dtype);
@@ -199,10 +210,13 @@ TPlan make_tplan(const lc_dit_config& g, int token_chunk) {
   p.off_qkv = take((size_t)R * 3 * g.D * es);
   p.off_vt = take((size_t)g.B * g.D * attn_tp(g.T) * es);
   p.off_ao = take((size_t)R * g.D * es);
-  take((size_t)p.tc * g.D * es);
-  take((size_t)p.tc * g.mlp_ratio * g.D * es);
-  take((size_t)p.tc * g.D * 4);
+  const size_t held = off - p.off_qkv, whole = (size_t)R * mlp_row_bytes(g);
+  if (whole > held) take((size_t)(((unsigned __int128)(whole - held) * p.tc + R - 1) / R));
   p.total = off;
+  // passes of about the same size
+  const int64_t fit = std::min<int64_t>(R, (int64_t)((p.total - p.off_qkv) / mlp_row_bytes(g)));
+  const int64_t passes = (R + fit - 1) / fit;
+  p.step = (R + passes - 1) / passes;
   return p;
 }
 
@@ -276,15 +290,15 @@ lc_status run_block(lc_dit* c, int i, const float* mod, float* x, const float* d
   char* vt = c->arena + p.off_vt;
   char* ao = c->arena + p.off_ao;
   lc_status s;
-  // (bf16, widths of the streamed kernels: the gated sum in the projections' epilogues, and V^T from q,k,v's where rows come
-  // in fours; the separate passes cost 16 + 16 + 14 us a block at 8192 rows x 1024, 13 % of it)
-  const bool gated = g.dtype == kBF16 && lin_gate_covers(D, D) && T >= 32;
+  const bool gated = gate_fused(g);
   const bool vt_fused = g.dtype == kBF16 && lin2_covers(D, 3 * D) && 2 * D % (3 * D % 160 == 0 ? 160 : 128) == 0 && T % 4 == 0;
   const int ldq = vt_fused ? 2 * D : 3 * D;
   // The chunk bounds the memory, and a pass takes as many rows as there is memory for: what is held for all tokens is not
   // needed all the time. The normalised rows of q,k,v lie where the attention output will be, the branch output (where it
-  // exists) where q,k,v were, and the MLP works from q,k,v to the end of the arena, which holds all rows of it in bf16 stages
-  // of mlp_ratio 4. (2 x 3108 tokens of 1024 in chunks of 1024, us a block's linear layers: 403 in launches of 1024 rows, 213.)
+  // exists) where q,k,v were, and the MLP works from q,k,v to the end of the arena, which holds all rows of it whatever the chunk
+  // in bf16 stages with fused gated sums and mlp_ratio up to 4: 10 D bytes a row, of which q,k,v, V^T and attention output have
+  // that much; without the fusion it takes 14 D. (2 x 3108 tokens of 1024 in chunks of 1024, us a block's linear layers: 403 in
+  // launches of 1024 rows, 213.)
   // ---- attention branch: q,k,v of every token first
   if ((s = ln_mod(c, x, delta, m, 0, 1, ao, (int)R, 0)) != LC_OK) return s;
   if ((s = linear(c, w.wqkv, w.bqkv, D, 3 * D, R, ao, qkv, 0, 0, D, vt_fused ? vt : nullptr, 0)) != LC_OK) return s;
@@ -298,12 +312,10 @@ lc_status run_block(lc_dit* c, int i, const float* mod, float* x, const float* d
     if ((s = gate_add(c, dst, t, m, 2, R, 0)) != LC_OK) return s;
   }
   // ---- MLP branch, in passes of about the same size: normalised rows, hidden rows and (where it exists) the branch output
-  const size_t per_row = (size_t)(D + H) * es + (gated ? 0 : (size_t)D * 4);
-  const int64_t fit = std::max<int64_t>(p.tc, (int64_t)((p.total - p.off_qkv - 3 * kAlign) / per_row));
-  const int64_t passes = (R + std::min(fit, R) - 1) / std::min(fit, R), step = (R + passes - 1) / passes;
+  const int64_t step = p.step;
   char* xn = qkv;
-  char* hid = xn + align_up((size_t)step * D * es);
-  float* t = (float*)(hid + align_up((size_t)step * H * es));
+  char* hid = xn + (size_t)step * D * es;  // (rows are multiples of 128 bytes)
+  float* t = (float*)(hid + (size_t)step * H * es);
   for (int64_t r0 = 0; r0 < R; r0 += step) {
     const int n = (int)std::min<int64_t>(step, R - r0);
     if ((s = ln_mod(c, x + r0 * D, delta ? delta + r0 * D : nullptr, m, 3, 4, xn, n, r0)) != LC_OK) return s;

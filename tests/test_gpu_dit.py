@@ -75,7 +75,7 @@ def test_invariants_bitwise(cfg):
         dit.sync()
         assert torch.equal(dit.dev_entry(1), d0) and torch.equal(swapped, full)
         assert lcb.lc_dit_get_counts(dit.ctx) == (1, 2, 1, 1)
-        for chunk in (1, 37, 64, cfg.T - 1, cfg.T + 5):  # token chunks never change a bit
+        for chunk in (1, 37, 64, cfg.T - 1, cfg.T + 5):  # token chunks never change a bit (one or two passes of the MLP)
             print(f"[chunk] {cfg.name} {chunk}", flush=True)
             dit.set_chunk(chunk)
             a, b = dit.empty(cfg.B, cfg.T, cfg.D), dit.empty(cfg.B, cfg.T, cfg.D)
@@ -84,6 +84,54 @@ def test_invariants_bitwise(cfg):
             dit.sync()
             assert torch.equal(a, full) and torch.equal(b, full), chunk
             assert torch.equal(dit.dev_entry(0), d0), chunk
+    finally:
+        dit.close()
+
+
+def mlp_passes(cfg, chunk):
+    """(passes, rows of a pass) of the MLP under a token chunk, from the footprint the library states: what lies behind hidden
+    states and cache entries, over the bytes of a row - normalised, hidden and, unless the gated sum is fused into the
+    projections, the branch output."""
+    es, R = (2 if cfg.dtype == "bf16" else 4), cfg.B * cfg.T
+    fused = cfg.dtype == "bf16" and cfg.D % 128 == 0 and cfg.T >= 32
+    row = (1 + cfg.mlp_ratio) * cfg.D * es + (0 if fused else 4 * cfg.D)
+    states = (R * cfg.D * 4 + 255) // 256 * 256
+    room = lcb.lc_dit_workspace_bytes(lcb.make_dit_config(cfg, 0, 1), chunk) - 2 * states
+    passes = -(-R // min(R, room // row))
+    return passes, -(-R // passes)
+
+
+# Stacks whose MLP takes more memory than attention held, so that a chunk leaves it two passes, of an odd number of rows that ends
+# inside a batch element: the gated sum in the projections' epilogues (rows 0..74 and 75..149 of 3 x 50), and in a pass of its
+# own (101 and 100 of 3 x 67; fp32: 225 and 225 of 3 x 150)
+TWO_GATED = synth.DitConfig("two_gated", B=3, T=50, D=256, heads=4, head_dim=64, L=2, cache_a=1, cache_b=2, dtype="bf16", mlp_ratio=8)
+TWO_APART = synth.DitConfig("two_apart", B=3, T=67, D=320, heads=8, head_dim=40, L=2, cache_a=1, cache_b=2, dtype="bf16")
+TWO_F32 = synth.DitConfig("two_f32", B=3, T=150, D=128, heads=2, head_dim=64, L=2, cache_a=1, cache_b=2, dtype="f32")
+
+
+@pytest.mark.parametrize("cfg", [TWO_GATED, TWO_APART, TWO_F32], ids=lambda c: c.name)
+def test_two_passes_that_straddle_batch_elements(cfg):
+    passes, rows = mlp_passes(cfg, 1)
+    assert passes == 2 and rows % 2 == 1 and rows % cfg.T and cfg.T % rows, (passes, rows)
+    assert mlp_passes(cfg, 0)[0] == 1
+    w = synth.make_dit_weights(cfg, 0)
+    dit = lcb.Dit(cfg, w, host_slots=0, dev_slots=1, token_chunk=0)
+    try:
+        x, mod = synth.make_dit_hidden(cfg, 1), synth.make_dit_modulation(cfg, 2)
+        xd, md = dit.to_device(x), dit.to_device(mod)
+        outs = []
+        for chunk in (0, 1):
+            dit.set_chunk(chunk)
+            full, cached = dit.empty(*x.shape), dit.empty(*x.shape)
+            dit.full_step(xd, md, full, 0)
+            dit.cached_step(xd, md, cached, 0)
+            dit.sync()
+            outs.append((full, cached, dit.dev_entry(0).clone()))
+        orc = dito.DitOracle(cfg, w64_of(w))
+        check("normal step in two passes", host(outs[1][0]), orc.full_step(x, mod, 0), cfg.dtype, wide_range=True)
+        check("Delta", host(outs[1][2]), orc.dev[0], cfg.dtype)
+        for a, b in zip(*outs):
+            assert torch.equal(a, b)
     finally:
         dit.close()
 
