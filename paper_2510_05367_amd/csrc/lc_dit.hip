@@ -227,15 +227,15 @@ inline const float* mod_blk(const lc_dit* c, const float* mod, int blk) { return
 
 // y[rows][Cout] = x[rows][Cin] W^T + bias; x of the operand type, y fp32 (y32) or of the operand type
 // q_cols: the first channels, multiplied by the softmax scale before they are rounded (the form attention takes)
-// vt: the channels from 2 Cin on go there transposed instead (rows of y have 2 Cin channels); r0: the rows' place in the step
+// vt: the channels from 2 Cin on go there transposed instead (all rows of the step; those of y have 2 Cin channels)
 lc_status linear(lc_dit* c, const void* w, const float* bias, int Cin, int Cout, int64_t rows, const void* x, void* y, int y32,
-                 int act = 0, int q_cols = 0, void* vt = nullptr, int64_t r0 = 0) {
+                 int act = 0, int q_cols = 0, void* vt = nullptr) {
   FusedDesc f;
   memset(&f, 0, sizeof f);
   f.dt = c->cfg.dtype; f.y_f32 = y32; f.taps = 1; f.src = 0; f.Cin = Cin; f.Cout = Cout; f.Cout_store = Cout; f.w = w; f.bias = bias;
   f.rows = rows; f.in_map = f.out_map = RowMap{0, 0, 1 << 30}; f.x = x; f.y = y; f.act = act;
   if (q_cols) { f.q_cols = q_cols; f.q_scale = attn_q_scale(c->cfg.head_dim); }
-  if (vt) { f.yt = vt; f.yt_from = 2 * Cin; f.yt_T = c->cfg.T; f.yt_Tp = attn_tp(c->cfg.T); f.row0 = r0; }
+  if (vt) { f.yt = vt; f.yt_from = 2 * Cin; f.yt_T = c->cfg.T; f.yt_Tp = attn_tp(c->cfg.T); }
   LCT_HIP(c, launch_fused(c->cs, f));
   return LC_OK;
 }
@@ -301,7 +301,7 @@ lc_status run_block(lc_dit* c, int i, const float* mod, float* x, const float* d
   // launches of 1024 rows, 213.)
   // ---- attention branch: q,k,v of every token first
   if ((s = ln_mod(c, x, delta, m, 0, 1, ao, (int)R, 0)) != LC_OK) return s;
-  if ((s = linear(c, w.wqkv, w.bqkv, D, 3 * D, R, ao, qkv, 0, 0, D, vt_fused ? vt : nullptr, 0)) != LC_OK) return s;
+  if ((s = linear(c, w.wqkv, w.bqkv, D, 3 * D, R, ao, qkv, 0, 0, D, vt_fused ? vt : nullptr)) != LC_OK) return s;
   if (!vt_fused) LCT_HIP(c, launch_make_vt(c->cs, g.dtype, qkv + (size_t)2 * D * es, 3 * D, vt, g.B, T, Tp, D));
   LCT_HIP(c, launch_spatial_attention(c->cs, g.dtype, qkv, ldq, vt, Tp, ao, g.B, T, g.heads, g.head_dim, 0, T, 1, g.B));
   if (gated) {

@@ -127,7 +127,6 @@ struct FusedDesc {
   int yt_from, yt_T, yt_Tp;
   // taps == 1, src == 0, fp32 y with `res` of a bf16 stage over dense rows, widths of lin_gate_covers only, optional:
   // y = res + gate[(row0 + r) / gate_T][:] * (x W^T + bias), gate_n vectors gate_ld floats apart, gate_T >= 32.
-  // row0 (a multiple of 4) also counts in yt's frames: frame = (row0 + r) / yt_T.
   const float* gate;
   int gate_T, gate_n;
   int64_t gate_ld, row0;

@@ -196,13 +196,12 @@ hipError_t launch_lin2(hipStream_t s, const FusedDesc& d) {
   if (d.yt) {  // the transposed tail: whole channel tiles of a bf16 output, rows in fours
     const int tile = d.Cout % 160 == 0 ? 160 : 128;
     if (d.y_f32 || d.res || d.act || d.y2) return hipErrorInvalidValue;
-    if (d.yt_from <= 0 || d.yt_from >= d.Cout || d.yt_from % tile || d.yt_T <= 0 || d.yt_T % 4 || d.rows % 4 || d.row0 % 4 || d.yt_Tp % 64 || d.yt_Tp < d.yt_T)
+    if (d.yt_from <= 0 || d.yt_from >= d.Cout || d.yt_from % tile || d.yt_T <= 0 || d.yt_T % 4 || d.rows % 4 || d.yt_Tp % 64 || d.yt_Tp < d.yt_T)
       return hipErrorNotSupported;
   }
   if (d.gate && (!lin_gate_covers(d.Cin, d.Cout) || !d.y_f32 || !d.res || d.y2 || d.gate_T < 32 || d.gate_n <= 0)) return hipErrorInvalidValue;
   if (d.rows <= 0) return hipSuccess;
   if (d.rows > (int64_t)1 << 30) return hipErrorNotSupported;
-  if (d.yt && d.row0 + d.rows >= (int64_t)1 << 31) return hipErrorInvalidValue;
   if ((int64_t)d.Cout * 4 * 32 >= (int64_t)1 << 31) return hipErrorNotSupported;  // (32-bit offsets in a block of rows)
   Lin2Args a;
   a.x = (const bf16_t*)d.x; a.w = (const bf16_t*)d.w; a.bias = d.bias; a.res = (const float*)d.res; a.y = d.y;

@@ -22,7 +22,7 @@ struct Lin2Args {
   int act;             // 0 none, 1 GELU, 2 GEGLU over alternating 32-channel blocks (y is then N / 2 wide)
   RowMap in_map, out_map;  // dense row r is row in_map(r) of x and row out_map(r) of y / res / y2
   // bf16 output over dense rows only: channels >= yt_from are not stored in y (whose rows then have yt_from channels)
-  // but transposed into yt[g / yt_T][N - yt_from][yt_Tp] at column (t & ~63) + vcol(t & 63), g = row0 + r, t = g % yt_T:
+  // but transposed into yt[g / yt_T][N - yt_from][yt_Tp] at column (t & ~63) + vcol(t & 63), g the launch's row, t = g % yt_T:
   // the V^T layout of the spatial attention kernel. nullptr: off. yt_from a multiple of a wavefront's channels, yt_T of 4.
   bf16_t* yt;
   int yt_from, yt_T, yt_Tp;
@@ -31,7 +31,7 @@ struct Lin2Args {
   const float* gate;
   int gate_T, gate_n;
   int64_t gate_ld;
-  int64_t row0;  // gate, yt: the launch's first row within the whole matrix
+  int64_t row0;  // gate: the launch's first row within the whole matrix
   int ldy;  // channels per row of y (yt_from with yt, else N; N / 2 after a GEGLU)
 };
 
@@ -192,7 +192,7 @@ __device__ __forceinline__ void lin_epilogue(const Lin2Args& a, const f32x16 (&a
   if constexpr (sizeof(OT) == 2) {
     if (a.yt && c0 >= a.yt_from) {  // (uniform over the wavefront) a lane holds 4 consecutive rows of a channel: 8 bytes of V^T
       const int Cv = a.N - a.yt_from;
-      const uint32_t g0 = (uint32_t)(a.row0 + rblk), T = (uint32_t)a.yt_T;  // (row0 + rows < 2^31: see launch_lin2)
+      const uint32_t g0 = (uint32_t)rblk, T = (uint32_t)a.yt_T;  // (rows <= 2^30: see launch_lin2)
       const uint32_t f0 = g0 / T, t0 = g0 - f0 * T;
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
