@@ -223,9 +223,9 @@ static hipError_t run_lin3_k(hipStream_t s, Lin2Args a) {
   return hipGetLastError();
 }
 
-// The tile of a dense launch; hipErrorNotSupported where lin2's 128 x 160 is the better one. 256 compute units: a launch
-// wants at least about that many workgroups, and the large tiles pay only where their last round is nearly full.
-hipError_t launch_lin3(hipStream_t s, const Lin2Args& a, bool y_f32) {
+// The tile of a dense launch. 256 compute units: a launch wants at least about that many workgroups, and the large tiles pay only
+// where their last round is nearly full.
+LinTile lin3_tile(const Lin2Args& a, bool y_f32) {
   auto tiles = [&](int m, int n) { return (a.rows + m - 1) / m * (a.N / n); };
   auto fills = [&](int64_t t) { return t >= 256 && t * 10 >= (t + 255) / 256 * 256 * 9; };
   if (a.N % 160 == 0 && a.act != 2 && !a.gate) {
@@ -233,32 +233,41 @@ hipError_t launch_lin3(hipStream_t s, const Lin2Args& a, bool y_f32) {
     // 11.6, 16384 (256) 12.6 against 15.8; K = 1280: 2048 rows (32) 18 -> 9, 16384 (256) 26 against 30. At 128 tiles the two are
     // close one launch after the other (8192 rows of 320, K = 320 9.5 and 9.4, K = 1280 21.1 and 19.2; 4096 of 640 13.1 and
     // 12.3) but not among other kernels: the cache step of the U-Net at 256 x 256, which has them, 1454 and 1477 us
-    if (a.N % 64 == 0 && tiles(128, 160) < 128)
-      return y_f32 ? run_lin3_k<float, 2, 2, 1, 1, 4>(s, a) : run_lin3_k<bf16_t, 2, 2, 1, 1, 4>(s, a);
+    if (a.N % 64 == 0 && tiles(128, 160) < 128) return LinTile::k64x64;
     // (fp32 outputs stay: 32768 x 640 x 640 47 against 51 with 128 x 128, 32768 x 640 x 2560 150 against 162)
-    if (y_f32) return hipErrorNotSupported;
+    if (y_f32) return LinTile::k128x160;
     // 8192 x 3840 x 1280 97 -> 81
-    if (a.N % 256 == 0 && fills(tiles(256, 256))) return run_lin3_k<bf16_t, 4, 2, 2, 4, 2>(s, a);
+    if (a.N % 256 == 0 && fills(tiles(256, 256))) return LinTile::k256x256;
     // 32768 x 1920 x 640 110 -> 103, but 131072 x 960 x 320 166 against 183: the larger tile's epilogue is not covered
-    if (a.N % 192 == 0 && a.K >= 640 && fills(tiles(256, 192))) return run_lin3_k<bf16_t, 4, 2, 2, 3, 2>(s, a);
-    return hipErrorNotSupported;
+    if (a.N % 192 == 0 && a.K >= 640 && fills(tiles(256, 192))) return LinTile::k256x192;
+    return LinTile::k128x160;
   }
   if (!y_f32) {
     // 8192 x 4096 x 1024 88 with 128 x 128, 78 with 256 x 256; 8192 x 3072 x 1024 (384 tiles, the second round half empty)
     // 59 against 64, and 56 with 256 x 192. Short contractions too: 131072 x 1280 x 320 238 with 128 x 128, 210 with 256 x 256,
     // and with GEGLU 131072 x 2560 x 320 415 and 408, 65536 x 2560 x 320 197 and 190, 32768 x 5120 x 640 346 and 307, 8192 x 10240
     // x 1280 291 and 250 (their epilogue, two transcendentals for each value that leaves, is uncovered in either)
-    if (a.N % 256 == 0 && fills(tiles(256, 256))) return run_lin3_k<bf16_t, 4, 2, 2, 4, 2>(s, a);
-    if (a.N % 192 == 0 && a.K >= 640 && a.act != 2 && fills(tiles(256, 192))) return run_lin3_k<bf16_t, 4, 2, 2, 3, 2>(s, a);
+    if (a.N % 256 == 0 && fills(tiles(256, 256))) return LinTile::k256x256;
+    if (a.N % 192 == 0 && a.K >= 640 && a.act != 2 && fills(tiles(256, 192))) return LinTile::k256x192;
   }
   // 128 x 128 and 64 x 128 (tiles of the former): 1024 x 3072 x 1024 (192) 15.8 and 14.4, 1024 x 4096 x 1024 (256) 17.8 and 17.9,
   // 2048 x 2048 x 512 (256) 11.1 and 9.8, 4096 x 1024 x 1024 fp32 (256) 19.3 and 15.7, 1536 x 3072 x 768 (288) 18.6 and 18.8,
   // 3108 x 3072 x 1024 (600) 31.8 and 38.2. GEGLU: 4096 x 2560 x 320 16.2 and 16.3, 2048 x 5120 x 640 25.7 and 30.8
-  if (tiles(128, 128) > 256 || a.act == 2)
-    return y_f32 ? run_lin3_k<float, 2, 2, 2, 2, 2>(s, a) : run_lin3_k<bf16_t, 2, 2, 2, 2, 2>(s, a);
+  if (tiles(128, 128) > 256 || a.act == 2) return LinTile::k128x128;
   // 512 x 3072 x 1024 (192 tiles of 64 x 128) 11.0 against 11.7 with 64 x 64; 1024 x 1024 x 1024 (128) 10.0 against 8.5
-  if (tiles(64, 128) >= 192) return y_f32 ? run_lin3_k<float, 2, 2, 1, 2, 3>(s, a) : run_lin3_k<bf16_t, 2, 2, 1, 2, 3>(s, a);
-  return y_f32 ? run_lin3_k<float, 2, 2, 1, 1, 4>(s, a) : run_lin3_k<bf16_t, 2, 2, 1, 1, 4>(s, a);
+  return tiles(64, 128) >= 192 ? LinTile::k64x128 : LinTile::k64x64;
+}
+
+hipError_t launch_lin3(hipStream_t s, const Lin2Args& a, bool y_f32) {
+  switch (lin3_tile(a, y_f32)) {
+    case LinTile::k256x256: return run_lin3_k<bf16_t, 4, 2, 2, 4, 2>(s, a);  // (bf16 outputs only)
+    case LinTile::k256x192: return run_lin3_k<bf16_t, 4, 2, 2, 3, 2>(s, a);
+    case LinTile::k128x128: return y_f32 ? run_lin3_k<float, 2, 2, 2, 2, 2>(s, a) : run_lin3_k<bf16_t, 2, 2, 2, 2, 2>(s, a);
+    case LinTile::k64x128: return y_f32 ? run_lin3_k<float, 2, 2, 1, 2, 3>(s, a) : run_lin3_k<bf16_t, 2, 2, 1, 2, 3>(s, a);
+    case LinTile::k64x64: return y_f32 ? run_lin3_k<float, 2, 2, 1, 1, 4>(s, a) : run_lin3_k<bf16_t, 2, 2, 1, 1, 4>(s, a);
+    case LinTile::k128x160: break;
+  }
+  return hipErrorNotSupported;
 }
 
 }  // namespace lc

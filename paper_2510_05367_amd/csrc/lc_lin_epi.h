@@ -35,8 +35,10 @@ struct Lin2Args {
   int ldy;  // channels per row of y (yt_from with yt, else N; N / 2 after a GEGLU)
 };
 
-// A dense launch (N % 128 == 0 or % 160 == 0; yt_from % 64 == 0) on one of lc_lin3.hip's tiles; hipErrorNotSupported where
-// lin2_kernel's 128 x 160 is the better one (never with a gate).
+// The tile of a dense launch by its size: lc_lin3.hip's, or lin2_kernel's 128 x 160 (never with a gate)
+enum class LinTile { k64x64, k64x128, k128x128, k256x192, k256x256, k128x160 };
+LinTile lin3_tile(const Lin2Args& a, bool y_f32);
+// A dense launch (N % 128 == 0 or % 160 == 0; yt_from % 64 == 0) on one of lc_lin3.hip's tiles; hipErrorNotSupported for 128 x 160
 hipError_t launch_lin3(hipStream_t s, const Lin2Args& a, bool y_f32);
 
 // bf16 stores of a 32-row block, two channels per lane: lanes l and l ^ 1 hold channels c, c + 1 of the same rows;

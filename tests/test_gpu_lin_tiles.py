@@ -1,7 +1,9 @@
 """The tiles a dense linear layer may take by its number of rows (lc_lin3.hip): every output element is contracted in the
-same order by all of them, so a transformer step in chunks, which takes the small tiles, has to give the bits of the step on
-all rows at once, which takes the large ones; with the gated sum in the projections' epilogues over rows of several batch
-elements, V^T from the projection's epilogue (rows in fours) and from its own pass (odd token counts)."""
+same order by all of them, so a transformer step on a few batch elements, which takes the small tiles, has to give the bits
+of the step on all of them at once, which takes the large ones (which tiles these are: test_lin_dispatch.py); with the gated
+sum in the projections' epilogues over rows of several batch elements, V^T from the projection's epilogue (rows in fours) and
+from its own pass (odd token counts). A token chunk does not reach other tiles, since the MLP of these stacks has room for
+all rows whatever the chunk; it must not change a bit either."""
 import numpy as np
 import pytest
 import torch
@@ -24,7 +26,35 @@ def steps(cfg, dit, xd, md):
     return full, cached, dit.dev_entry(0).clone()
 
 
-# rows x width: 256 x 256, 256 x 192 and 128 x 128 tiles without a chunk; a remainder of rows in every tile; an odd token
+# B, T, D, heads, batch elements at a time: all at once 256 x 256 (MLP, 4092 rows of 1024), 256 x 192 (q,k,v) and 64 x 128 tiles, four
+# at a time 64 x 128 and 64 x 64, one 64 x 64; 128 x 128 with an odd token count (no fused V^T) against small tiles; widths of
+# 160 channels: 128 x 160 (q,k,v, MLP) against 64 x 64. Every one with a remainder of rows
+SPLITS = [(33, 124, 1024, 16, (4, 1)), (24, 129, 1024, 16, (5, 1)), (33, 124, 640, 10, (8, 1))]
+
+
+@pytest.mark.parametrize("B,T,D,heads,groups", SPLITS)
+def test_batch_elements_alone_give_the_bits_of_all(B, T, D, heads, groups):
+    cfg = BASE.with_(B=B, T=T, D=D, heads=heads, L=2, cache_a=1, cache_b=2, token_chunk=0)
+    w = synth.make_dit_weights(cfg, 0)
+    x, mod = synth.make_dit_hidden(cfg, 1), synth.make_dit_modulation(cfg, 2)
+
+    def run(c, xs, ms):
+        dit = lcb.Dit(c, w, host_slots=0, dev_slots=1, token_chunk=0)
+        try:
+            return steps(c, dit, dit.to_device(np.ascontiguousarray(xs)), dit.to_device(np.ascontiguousarray(ms)))
+        finally:
+            dit.close()
+    ref = run(cfg, x, mod)
+    assert bool(torch.isfinite(ref[0]).all()) and torch.equal(ref[0], ref[1])
+    for n in groups:
+        for b in sorted({0, (B // n) // 2 * n, B - n}):  # the first ones, some in the middle and the last, whose rows end the matrix
+            print(f"[case] {B} x {T} x {D}: batch elements {b}..{b + n - 1}", flush=True)
+            got = run(cfg.with_(B=n), x[b:b + n], mod[:, b:b + n])
+            for name, g, r in zip(("normal step", "cache step", "Delta"), got, ref):
+                assert torch.equal(g.reshape(n, T, D), r.reshape(B, T, D)[b:b + n]), (name, n, b)
+
+
+# rows x width: 256 x 256, 256 x 192 and 128 x 128 tiles; a remainder of rows in every tile; an odd token
 # count (no fused V^T); widths that the 192-channel tile does not divide
 @pytest.mark.parametrize("B,T,D,chunks", [(2, 2048, 1024, (1024, 388)), (1, 8190, 512, (2000, 61)), (3, 1363, 768, (640, 1000)), (2, 129, 1024, (64, 7))])
 def test_tiles_agree_bitwise(B, T, D, chunks):
