@@ -849,10 +849,16 @@ static hipError_t ring_dispatch(hipStream_t s, const bf16_t* qk, int ldq, const 
 // the workgroups pay while the chip is idle, the staging that is done once per 32 instead of 128 queries costs where it is not:
 // 2 frames of 1024 tokens, 1 head of 64 (16 workgroups of 128 queries) 79 us without, 32 us with; 8 heads of 40 (128
 // workgroups) 69 and 45 us, 8 frames of 256 (128) 22 and 19 us; 32 frames of 256 (512) 42 and 65 us; 4 frames of 4096 (1024)
-// 878 and 1033 us; up to 64 keys, one stage of either, 10.3 and 11.0 us. The two round differently, and a window of queries or a
-// chunk of frames gives the bits of the whole, so the workgroups counted are those of the whole problem.
+// 878 and 1033 us; up to 64 keys, one stage of either, 10.3 and 11.0 us. Beyond one workgroup of 32 queries per compute unit short
+// sequences gain little (8 heads of 40, 128 workgroups: 128 tokens 18.5 and 17.2, 192 tokens 21.9 and 21.3), and they lose where
+// the problems are no multiple of eight, so that the workgroups of one fetch its keys into several XCDs' L2 (5 heads of 64,
+// 128 tokens: 16 frames 21.5 and 19.8, 25 frames 22.9 and 25.4; 192 tokens, 12 frames 27.5 and 29.8; 256 tokens 33.4 and 31.3). The
+// two round differently, and a window of queries or a chunk of frames gives the bits of the whole, so the workgroups counted
+// are those of the whole problem.
 static bool keys_split(int T, int heads, int all_frames) {
-  return all_frames > 0 && T > 64 && (int64_t)((T + 127) / 128) * heads * all_frames <= 128;
+  const int64_t problems = (int64_t)heads * all_frames;
+  return all_frames > 0 && T > 64 && (T + 127) / 128 * problems <= 128 &&
+         ((T + 31) / 32 * problems <= 256 || T > 192 || problems % 8 == 0);
 }
 
 template <bool PRE>

@@ -53,6 +53,30 @@ def test_spatial_attention(heads, d, F, H, W, kind):
         stage.close()
 
 
+# the split where its workgroups of 32 queries are at most one per compute unit, or the sequence is long, or the problems (heads x
+# frames) are a multiple of eight: on either side of each. A stage of 200 frames never splits; its operator on the first F of
+# them gives the bits of a stage of F that does not, and others (of the same result) than one that does
+@pytest.mark.parametrize("heads,d,F,H,W,split", [(5, 64, 25, 8, 16, False), (5, 64, 12, 8, 16, True), (5, 64, 16, 8, 16, True), (5, 64, 9, 12, 16, False),
+                                                 (5, 64, 9, 14, 16, True), (8, 40, 15, 8, 16, True), (3, 64, 22, 8, 16, False)])
+def test_split_keys_where_they_pay(heads, d, F, H, W, split):
+    cfg = config(F, H, W, heads, d)
+    few, many = make_stage(cfg, seed=6)[0], make_stage(cfg.with_(F=200), seed=6)[0]
+    try:
+        rng = np.random.default_rng(7)
+        qd = dev(few, rng.standard_normal((F * cfg.T, 3 * cfg.C)).astype(np.float32))
+        outs = []
+        for st in (few, many):
+            outs.append(st.empty(F * cfg.T, cfg.C))
+            torch.cuda.synchronize()
+            lcb.lc_op_spatial_attention(st.ctx, qd.data_ptr(), outs[-1].data_ptr(), F, 0, cfg.T, 0)
+            st.sync()
+        assert torch.equal(*outs) == (not split)
+        assert float((outs[0] - outs[1]).norm() / outs[1].norm()) < 1e-5
+    finally:
+        few.close()
+        many.close()
+
+
 @pytest.mark.parametrize("heads,d,F", [(1, 64, 70), (8, 40, 40)])
 def test_narrow_convolutions_give_the_bits_of_wide_ones(heads, d, F):
     """16 x 16 images are two tiles a frame: all frames fill more than 128 workgroups, one frame does not."""
