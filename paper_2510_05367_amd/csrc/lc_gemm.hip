@@ -675,7 +675,9 @@ template <class T, class OT, int TAPS, int SRC>
 static hipError_t by_width(hipStream_t s, const FusedDesc& d) {
   // fp32 convolutions that leave half of the 256 compute units idle: 32 channels a workgroup. A step of 64 channels x 128 pixels
   // is 2048 cycles of matrix instructions on each wavefront's SIMD, so idle units are idle rate; the order of every sum is the
-  // same. (2 frames of 32 x 32, 64 channels, 16 workgroups: from 192 channels 76 -> 55 us, from 64 30 -> 20 us)
+  // same. (2 frames of 32 x 32, 64 channels, 16 workgroups: from 192 channels 76 -> 55 us, from 64 30 -> 20 us. Residual block with its
+  // statistics at 8, 64 and 128 workgroups: 64 channels 34.3 -> 24.6, 35 -> 26 and 36 -> 27; 320 channels, where 160 become five of
+  // 32 and halo and activations are done five times, 249 -> 83, 257 -> 138 and 259 -> 205; 640 492 -> 165, 503 -> 268 and 504 -> 397)
   if constexpr (TAPS == 9 && sizeof(T) == 4) {
     const int64_t wgs = (int64_t)((d.W + 15) / 16) * ((d.H + 7) / 8) * d.frames * (d.Cout % 160 == 0 ? d.Cout / 160 : d.Cout / 64);
     if ((d.Cout % 160 == 0 || d.Cout % 64 == 0) && wgs <= 128) return run_gemm<T, OT, TAPS, 1, SRC, false>(s, d);
