@@ -11,7 +11,7 @@ from paper_2510_05367_amd import synth
 
 pytestmark = pytest.mark.gpu
 
-SLACK = 6 << 20  # padding of the 256-byte pieces, biases and norms held in fp32, the allocator's granularity
+SLACK = 6 << 20  # padding of the 256-byte pieces, biases and norms held in fp32, the allocator's granularity (2 MiB a piece)
 
 
 def held(monkeypatch, name, make):
@@ -56,5 +56,7 @@ def test_one_copy_of_the_convolutions(path, monkeypatch):
     name, make, (conv, rest) = case(path)
     n = held(monkeypatch, name, make)
     print(f"\n[{path}] 3x3 weights {conv / 2**20:.1f} MiB, others {rest / 2**20:.1f} MiB, held {n / 2**20:.1f} MiB", flush=True)
-    assert n >= conv + rest  # (the measurement sees the memory)
+    # the measurement sees the memory, less what the runtime had left over of earlier holders' or gives back meanwhile, in pieces
+    # of 2 MiB: 172 MiB for the U-Net's 171.0 alone, 170 behind the other tests of a process
+    assert n >= conv + rest - SLACK
     assert n <= conv + 2 * rest + SLACK
