@@ -2,12 +2,14 @@
 // the chip several times and small ones for launches that would leave most of it idle.
 //
 // Where a large launch's time goes (8192 x 4096 x 1024 with GELU, 256 x 256): 49 us per 1024 of K, 1.37 PFLOP/s, as fast as this
-// card runs any long contraction, and 27 us that do not depend on K: first loads, the epilogue and its stores (14 us at the
-// rate of a copy), which one workgroup per compute unit does not cover. In small launches a compute unit has one wavefront per
+// card runs any long contraction, and about 25 us that do not depend on K: first loads, the epilogue and its stores (14 us at
+// the rate of a copy), which one workgroup per compute unit does not cover. In small launches a compute unit has one wavefront per
 // SIMD, and what a stage consists of adds up: requests, fragment reads, MFMAs, barrier.
-// Measured, us (lin2's tile -> this file's; rows x N x K): 8192 x 4096 x 1024 with GELU 95 -> 74 and 8192 x 3840 x 1280
-// 97 -> 81 (256 x 256), 8192 x 3072 x 1024 64 -> 56 (256 x 192), 8192 x 1024 x 4096 fp32 75 -> 68 (128 x 128),
-// 3000 x 768 x 3072 fp32 36 -> 27 (64 x 128), 1024 x 1024 x 4096 fp32 43 -> 21, 2048 x 320 x 1280 fp32 18 -> 8 (64 x 64).
+// Measured, us (rows x N x K; fp32 outputs with their residual; in all figures of this file each launch behind one of the same shape
+// on other buffers, so that short ones are close to what they are in a step and large ones a few percent more): lin2's 128 x 160
+// -> this file's, 8192 x 3840 x 1280 86 -> 75 (256 x 256), 2048 x 320 x 1280 fp32 18 -> 8 (64 x 64); 128 x 128 -> the other
+// tiles, 8192 x 4096 x 1024 with GELU 76 -> 73 (256 x 256), 3000 x 768 x 3072 fp32 36 -> 23 (64 x 128), 1024 x 1024 x 4096 fp32
+// 39 -> 19 (64 x 64).
 //
 // The K loop: a ring of S stages of 64 K elements (global -> LDS directly, packet c of row r in slot c ^ ((r >> 1) & 7)).
 // The one barrier of a step stands before its last group of MFMAs, whose operands are in registers by then: behind it the
@@ -229,32 +231,39 @@ LinTile lin3_tile(const Lin2Args& a, bool y_f32) {
   auto tiles = [&](int m, int n) { return (a.rows + m - 1) / m * (a.N / n); };
   auto fills = [&](int64_t t) { return t >= 256 && t * 10 >= (t + 255) / 256 * 256 * 9; };
   if (a.N % 160 == 0 && a.act != 2 && !a.gate) {
-    // 128 x 160 -> 64 x 64 (tiles of the former). 320 channels, K = 320: 4096 rows (64) 8.4 -> 5.9, 12288 (192) 10.8 against
-    // 11.6, 16384 (256) 12.6 against 15.8; K = 1280: 2048 rows (32) 18 -> 9, 16384 (256) 26 against 30. At 128 tiles the two are
-    // close one launch after the other (8192 rows of 320, K = 320 9.5 and 9.4, K = 1280 21.1 and 19.2; 4096 of 640 13.1 and
-    // 12.3) but not among other kernels: the cache step of the U-Net at 256 x 256, which has them, 1454 and 1477 us
+    // 128 x 160 and 64 x 64, fp32 (tiles of the former). 320 channels, K = 320: 4096 rows (64) 8.1 and 5.6, 12288 (192) 12.0 and
+    // 11.4, 16384 (256) 13.5 and 15.1; K = 1280: 2048 rows (32) 18 and 8, 16384 (256) 25 and 28. At 128 tiles the small ones are
+    // level or ahead one launch after the other (8192 rows of 320, K = 320 9.7 and 9.7, K = 1280 21 and 18; 4096 of 640 13.3 and
+    // 12.1) and nothing is gained among other kernels: the cache step of the U-Net at 256 x 256, which has them, 1329 and 1330
+    // us, its normal step at 512 x 512 15.83 and 15.77 ms
     if (a.N % 64 == 0 && tiles(128, 160) < 128) return LinTile::k64x64;
-    // (fp32 outputs stay: 32768 x 640 x 640 47 against 51 with 128 x 128, 32768 x 640 x 2560 150 against 162)
+    // (fp32 outputs stay: 32768 x 640 x 640 58 against 62 with 128 x 128, 32768 x 640 x 2560 131 against 143, 8192 x 1280 x 1280
+    // 36 against 43, 131072 x 320 x 320 85 against 119 with 64 x 64)
     if (y_f32) return LinTile::k128x160;
-    // 8192 x 3840 x 1280 97 -> 81
+    // 8192 x 3840 x 1280 86 with 128 x 160, 75 with 256 x 256; 131072 x 1280 x 320 207 and 172
     if (a.N % 256 == 0 && fills(tiles(256, 256))) return LinTile::k256x256;
-    // 32768 x 1920 x 640 110 -> 103, but 131072 x 960 x 320 166 against 183: the larger tile's epilogue is not covered
+    // 131072 x 960 x 320 136 with 128 x 160 against 166: the larger tile's epilogue is not covered. At K = 640 it still costs more
+    // than it saves (32768 x 1920 x 640 107 against 118; with an epilogue of a condition per row, when the line was
+    // drawn, it was 110 against 103)
     if (a.N % 192 == 0 && a.K >= 640 && fills(tiles(256, 192))) return LinTile::k256x192;
     return LinTile::k128x160;
   }
   if (!y_f32) {
-    // 8192 x 4096 x 1024 88 with 128 x 128, 78 with 256 x 256; 8192 x 3072 x 1024 (384 tiles, the second round half empty)
-    // 59 against 64, and 56 with 256 x 192. Short contractions too: 131072 x 1280 x 320 238 with 128 x 128, 210 with 256 x 256,
-    // and with GEGLU 131072 x 2560 x 320 415 and 408, 65536 x 2560 x 320 197 and 190, 32768 x 5120 x 640 346 and 307, 8192 x 10240
-    // x 1280 291 and 250 (their epilogue, two transcendentals for each value that leaves, is uncovered in either)
+    // 8192 x 4096 x 1024 with GELU 76 with 128 x 128, 73 with 256 x 256; 8192 x 3072 x 1024 (384 tiles, the second round half empty)
+    // 52 against 58, and 52 with 256 x 192. Short contractions too: with GEGLU 131072 x 2560 x 320 315 and 289, 65536 x 2560 x 320 158
+    // and 151, 32768 x 5120 x 640 270 and 240, 8192 x 10240 x 1280 208 and 192 (their epilogue, two transcendentals for each value
+    // that leaves, is uncovered in either)
     if (a.N % 256 == 0 && fills(tiles(256, 256))) return LinTile::k256x256;
     if (a.N % 192 == 0 && a.K >= 640 && a.act != 2 && fills(tiles(256, 192))) return LinTile::k256x192;
   }
-  // 128 x 128 and 64 x 128 (tiles of the former): 1024 x 3072 x 1024 (192) 15.8 and 14.4, 1024 x 4096 x 1024 (256) 17.8 and 17.9,
-  // 2048 x 2048 x 512 (256) 11.1 and 9.8, 4096 x 1024 x 1024 fp32 (256) 19.3 and 15.7, 1536 x 3072 x 768 (288) 18.6 and 18.8,
-  // 3108 x 3072 x 1024 (600) 31.8 and 38.2. GEGLU: 4096 x 2560 x 320 16.2 and 16.3, 2048 x 5120 x 640 25.7 and 30.8
+  // 128 x 128 and 64 x 128 (tiles of the former): 1024 x 3072 x 1024 (192) 12.9 and 11.8, 1024 x 4096 x 1024 (256) 15.2 and 13.8,
+  // 2048 x 2048 x 512 (256) 9.0 and 8.4, 4096 x 1024 x 1024 fp32 (256) 17.6 and 15.4, 1536 x 3072 x 768 (288) 14.5 and 15.3,
+  // 3108 x 3072 x 1024 (600) 28.2 and 28.3, 6216 x 3072 x 1024 (1176) 45 and 53. GEGLU: 4096 x 2560 x 320 13.2 and 13.9, 2048 x
+  // 5120 x 640 19.5 and 20.4
   if (tiles(128, 128) > 256 || a.act == 2) return LinTile::k128x128;
-  // 512 x 3072 x 1024 (192 tiles of 64 x 128) 11.0 against 11.7 with 64 x 64; 1024 x 1024 x 1024 (128) 10.0 against 8.5
+  // 64 x 128 and 64 x 64 (tiles of the former): 1024 x 4096 x 1024 (512) 13.8 and 16.6, 2048 x 2048 x 512 (512) 8.4 and 10.2, 1024 x
+  // 3072 x 1024 (384) 11.8 and 13.2; 512 x 3072 x 1024 (192) 9.0 and 7.8, so the line is a little low for bf16; 1024 x 1024 x 1024
+  // fp32 (128) 9.0 and 7.5
   return tiles(64, 128) >= 192 ? LinTile::k64x128 : LinTile::k64x64;
 }
 

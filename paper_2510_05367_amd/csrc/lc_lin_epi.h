@@ -70,7 +70,7 @@ __device__ __forceinline__ void store_pairs(const float (&val)[16][NTV], int lan
 // rblk + 8 (r / 4) + 4 hh + r % 4.
 // Dense rows go through buffer descriptors over the block: rows beyond the end read as zero and are not stored by the bounds
 // check, where 64-bit addresses and a condition per row took most of a short contraction's time (131072 x 2560, K = 64, GEGLU
-// 215 us with them). The row's offset is part of the vector offset, which is what the check compares with the descriptor's size:
+// 215 us with them, 160 now). The row's offset is part of the vector offset, which is what the check compares with the descriptor's size:
 // a scalar offset is taken off that size first, and beyond the end it is the larger of the two.
 // GATE: Lin2Args::gate may be set (its own registers: the kernels that never take one stay without them).
 template <class OT, int NT, bool MAPPED, bool GATE>
