@@ -35,11 +35,11 @@ PEAK_HBM_GBS = 8000.0
 # WRITE_SIZE runs summarised under profiles/ (fetch x 2.0, the factor a plain copy of known size gave). Valid only
 # for the kernel sources the counters were taken with: `sha256_16` covers the listed files, else traffic is null.
 TRAFFIC = {  # (a convolution is its activation pass(es) and the contraction)
-    "conv_up": {"sources": ("lc_convd.hip", "lc_norm.hip", "lc_common.h", "lc_internal.h"), "sha256_16": "5a1a55f93a6d5690",
+    "conv_up": {"sources": ("lc_convd.hip", "lc_norm.hip", "lc_common.h", "lc_internal.h"), "sha256_16": "47f20bf91a99fae7",
                 "bytes_per_launch": 94.1e6 + 38.0e6},
-    "sattn": {"sources": ("lc_attn.hip", "lc_common.h", "lc_internal.h"), "sha256_16": "5c5adb7540d5f45c",
+    "sattn": {"sources": ("lc_attn.hip", "lc_common.h", "lc_internal.h"), "sha256_16": "7d49ccc9d041693e",
               "bytes_per_launch": 61.0e6 + 12.6e6},
-    "conv_res": {"sources": ("lc_convd.hip", "lc_norm.hip", "lc_common.h", "lc_internal.h"), "sha256_16": "5a1a55f93a6d5690",
+    "conv_res": {"sources": ("lc_convd.hip", "lc_norm.hip", "lc_common.h", "lc_internal.h"), "sha256_16": "47f20bf91a99fae7",
                  "bytes_per_launch": 71.1e6 + 32.8e6},
 }
 TRAFFIC_WORKLOAD = ("animatediff", 4)
