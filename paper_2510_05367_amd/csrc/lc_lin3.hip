@@ -242,9 +242,9 @@ LinTile lin3_tile(const Lin2Args& a, bool y_f32) {
     if (y_f32) return LinTile::k128x160;
     // 8192 x 3840 x 1280 86 with 128 x 160, 75 with 256 x 256; 131072 x 1280 x 320 207 and 172
     if (a.N % 256 == 0 && fills(tiles(256, 256))) return LinTile::k256x256;
-    // 131072 x 960 x 320 136 with 128 x 160 against 166: the larger tile's epilogue is not covered. At K = 640 it still costs more
-    // than it saves (32768 x 1920 x 640 107 against 118; with an epilogue of a condition per row, when the line was
-    // drawn, it was 110 against 103)
+    // 128 x 160 and 256 x 192: 131072 x 960 x 320 136 and 166, the larger tile's epilogue is not covered; 8192 x 2880 x 960 57 and 50,
+    // 32768 x 2880 x 960 218 and 210, 65536 x 960 x 1280 189 and 189, 32768 x 1920 x 1280 184 and 188. At the line itself the smaller
+    // one has come ahead since its epilogue has no condition per row (32768 x 1920 x 640 110 and 103 before, 109 and 118 now)
     if (a.N % 192 == 0 && a.K >= 640 && fills(tiles(256, 192))) return LinTile::k256x192;
     return LinTile::k128x160;
   }
@@ -262,8 +262,9 @@ LinTile lin3_tile(const Lin2Args& a, bool y_f32) {
   // 5120 x 640 19.5 and 20.4
   if (tiles(128, 128) > 256 || a.act == 2) return LinTile::k128x128;
   // 64 x 128 and 64 x 64 (tiles of the former): 1024 x 4096 x 1024 (512) 13.8 and 16.6, 2048 x 2048 x 512 (512) 8.4 and 10.2, 1024 x
-  // 3072 x 1024 (384) 11.8 and 13.2; 512 x 3072 x 1024 (192) 9.0 and 7.8, so the line is a little low for bf16; 1024 x 1024 x 1024
-  // fp32 (128) 9.0 and 7.5
+  // 3072 x 1024 (384) 11.8 and 13.2; 1024 x 1024 x 1024 fp32 (128) 9.0 and 7.5. Between the two the small ones are ahead by less since
+  // they hold a stage in registers: 512 x 3072 x 1024 (192) 9.2 and 8.1, 640 x 3072 x 1024 (240) 9.2 and 8.4, 1024 x 2048 x 512 (256)
+  // 6.5 and 5.9; fp32 1536 x 1024 x 1024 (192) 9.6 and 9.1, 1600 x 1024 x 4096 (200) 27 and 26
   return tiles(64, 128) >= 192 ? LinTile::k64x128 : LinTile::k64x64;
 }
 
